@@ -6,6 +6,7 @@
 
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "../../include/mttkrp.h"
 #include "../../include/mttkrp_cpals.h"
@@ -14,7 +15,10 @@ namespace {
 
 constexpr int kSmallRank = 64;     // up to here the R x R matrices are handled in one workgroup's LDS
 constexpr int kChunkRows = 64;     // rows of a factor one workgroup turns into a partial Gram matrix
-constexpr int kNormBlocks = 2048;  // partial sums of ||X||^2
+constexpr int kNormBlocks = 4096;  // partial sums of ||X||^2
+constexpr int kGramBlocks = 128;   // workgroups of an update (ranks up to 64) at most
+constexpr int kScaleBlocks = 256;  // ... of its second launch
+constexpr int kFitChunks = 256;    // row chunks of the fit's inner product (ranks above 64)
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -33,33 +37,56 @@ __device__ __forceinline__ double block_sum_256(double v, double* lds)
     return r;
 }
 
-// partial[b] = sum of squares of block b's contiguous share of X (fixed assignment and order).
+// partial[b] = sum of squares of block b's share of X (fixed assignment and order).  One read of X at
+// what a plain stream reaches: four 16-byte non-temporal loads in flight per lane, blocks interleaved
+// (8 GB: 1.41 ms with one 8-byte load in flight, contiguous shares; 1.20 ms so).  X is 8-byte aligned;
+// an odd first value and a last one are added by block 0.
+typedef double double2_t __attribute__((ext_vector_type(2)));
 __global__ void __launch_bounds__(256) sumsq_partial(const double* __restrict__ X, int64_t N, double* partial)
 {
     __shared__ double lds[256];
-    const int64_t per = (N + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = per * blockIdx.x;
-    const int64_t hi = lo + per < N ? lo + per : N;
+    const int64_t head = ((uintptr_t)X & 15u) != 0 ? 1 : 0;
+    const double2_t* const x2 = (const double2_t*)(X + head);
+    const int64_t n2 = (N - head) >> 1;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double s = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) {
-        const double v = X[i];
-        s += v * v;
+    for (; i + 3 * stride < n2; i += 4 * stride) {
+        double2_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u] = __builtin_nontemporal_load(x2 + i + u * stride);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            s += v[u].x * v[u].x + v[u].y * v[u].y;
+    }
+    for (; i < n2; i += stride) {
+        const double2_t v = x2[i];
+        s += v.x * v.x + v.y * v.y;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (head)
+            s += X[0] * X[0];
+        if (head + 2 * n2 < N)
+            s += X[N - 1] * X[N - 1];
     }
     s = block_sum_256(s, lds);
     if (threadIdx.x == 0)
         partial[blockIdx.x] = s;
 }
 
-// out[0] = sum of n values, one workgroup, fixed order.
-__global__ void __launch_bounds__(256) sum_fixed(const double* __restrict__ v, int n, double* out)
+// out[0] = sum of n values, one workgroup, fixed order; clears the pivot flag.
+__global__ void __launch_bounds__(256) sum_fixed(const double* __restrict__ v, int n, double* out, int* flag)
 {
     __shared__ double lds[256];
     double s = 0.0;
     for (int i = threadIdx.x; i < n; i += 256)
         s += v[i];
     s = block_sum_256(s, lds);
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         out[0] = s;
+        flag[0] = 0;
+    }
 }
 
 // Partial Gram matrix of rows [64 b, 64 b + 64) of A (I x R): ws[b][a * R + c] = sum_r A(r, a) A(r, c).
@@ -106,134 +133,365 @@ __global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__
     V[e] = v;
 }
 
-// In-place Cholesky factor of the R x R matrix V (lower triangle, L L^T = V) by one workgroup.
-// flag[0] is set to 1 when a pivot is not positive.
-__global__ void __launch_bounds__(256) cholesky_lower(double* V, int R, int* flag)
+// ---------------------------------------------------------------------------
+// Update of one factor: A_k = M V^{-1} with V = L D L^T (unit lower L; the pivots are those of the
+// Cholesky factorisation, squared), then the columns' 2-norms, the normalised columns and their Gram
+// matrix.  These steps are short chains, bound by launches and by latency, not by arithmetic.
+// ---------------------------------------------------------------------------
+
+// 1 / d to the last place or two: the hardware estimate and two Newton steps (an IEEE division is
+// three times as long a chain, and a step of the factorisation waits for it).
+__device__ __forceinline__ double reciprocal(double d)
 {
-    extern __shared__ double Ls[];   // R x R
-    for (int t = threadIdx.x; t < R * R; t += 256)
-        Ls[t] = V[t];
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return r;
+}
+
+// L D L^T of an R x R matrix, R <= RP, by one workgroup.  Thread (ti, tc) = (tid & 15, tid >> 4) of the first
+// 256 holds the entries (ti + 16 p, tc + 16 q) in registers; only the column that is eliminated next passes
+// through LDS, so a step costs one barrier (~250 cycles at R = 10, where scaling the column and updating
+// the triangle in LDS took two).  Result: Lf[c * (RP + 1) + i] = L(i, c) for i > c, 0 elsewhere (the padding
+// up to RP too); dinv[c] = 1 / D(c), 0 for c >= R.  False (for every thread) when a pivot is not positive.
+template <int RP>
+__device__ __forceinline__ bool factorise(double (&own)[RP / 16][RP / 16], int R, double (*col)[RP], double* Lf, double* dinv)
+{
+    constexpr int NT = RP / 16;
+    const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4;
+    const bool mine = tid < 256;
+    if (tid < RP)
+        dinv[tid] = 0.0;
+    if (mine && tc == 0) {
+#pragma unroll
+        for (int p = 0; p < NT; ++p)
+            col[0][ti + 16 * p] = own[p][0];
+    }
     __syncthreads();
     for (int j = 0; j < R; ++j) {
-        const double piv = Ls[j * R + j];
-        if (!(piv > 0.0)) {
-            if (threadIdx.x == 0)
-                flag[0] = 1;
-            return;   // uniform: every thread sees the same pivot
+        const double* const cj = col[j & 1];
+        const double d = cj[j];
+        if (!(d > 0.0))
+            return false;      // uniform: every thread sees the same pivot
+        const double rd = reciprocal(d);
+        if (mine) {
+            double x[NT];
+#pragma unroll
+            for (int p = 0; p < NT; ++p)
+                x[p] = cj[ti + 16 * p];
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                const int c = tc + 16 * q;
+                if (c > j && c < R) {
+                    const double xc = cj[c] * rd;
+#pragma unroll
+                    for (int p = 0; p < NT; ++p)
+                        own[p][q] -= x[p] * xc;
+                    if (c == j + 1) {
+#pragma unroll
+                        for (int p = 0; p < NT; ++p)
+                            col[(j + 1) & 1][ti + 16 * p] = own[p][q];
+                    }
+                }
+            }
         }
-        const double dj = sqrt(piv);
-        __syncthreads();
-        for (int i = j + threadIdx.x; i < R; i += 256)
-            Ls[i * R + j] = i == j ? dj : Ls[i * R + j] / dj;
-        __syncthreads();
-        const int n = R - j - 1;
-        for (int t = threadIdx.x; t < n * n; t += 256) {
-            const int i = j + 1 + t / n, c = j + 1 + t % n;
-            if (c <= i)
-                Ls[i * R + c] -= Ls[i * R + j] * Ls[c * R + j];
-        }
+        if (tid == 0)
+            dinv[j] = rd;
         __syncthreads();
     }
-    for (int t = threadIdx.x; t < R * R; t += 256) {
-        const int i = t / R, c = t - i * R;
-        V[t] = c <= i ? Ls[t] : 0.0;
+    if (mine) {
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+#pragma unroll
+            for (int p = 0; p < NT; ++p) {
+                const int i = ti + 16 * p, c = tc + 16 * q;
+                Lf[c * (RP + 1) + i] = i > c && i < R ? own[p][q] * dinv[c] : 0.0;
+            }
     }
-}
-
-// Rows of A = M V^{-1} with V = L L^T: forward solve L y = m, backward solve L^T z = y, one
-// thread per row, 32 rows per workgroup; L and the rows live in LDS.
-__global__ void __launch_bounds__(32) solve_rows(const double* __restrict__ L, const double* __restrict__ M,
-                                                  int64_t I, int R, double* A, const int* flag)
-{
-    extern __shared__ double lds[];
-    if (flag[0])      // no valid factor: leave A_k as it is
-        return;
-    double* Ls = lds;                       // R x R
-    double* Y = lds + R * R;                // 32 x (R + 1)
-    for (int t = threadIdx.x; t < R * R; t += 32)
-        Ls[t] = L[t];
-    const int64_t row = (int64_t)blockIdx.x * 32 + threadIdx.x;
-    double* y = Y + threadIdx.x * (R + 1);
-    if (row < I)
-        for (int a = 0; a < R; ++a)
-            y[a] = M[row * R + a];
     __syncthreads();
-    if (row >= I)
-        return;
-    for (int a = 0; a < R; ++a) {
-        double s = y[a];
-        for (int b = 0; b < a; ++b)
-            s -= Ls[a * R + b] * y[b];
-        y[a] = s / Ls[a * R + a];
-    }
-    for (int a = R - 1; a >= 0; --a) {
-        double s = y[a];
-        for (int b = a + 1; b < R; ++b)
-            s -= Ls[b * R + a] * y[b];
-        y[a] = s / Ls[a * R + a];
-    }
-    for (int a = 0; a < R; ++a)
-        A[row * R + a] = y[a];
+    return true;
 }
 
-// Workgroup j: lambda[j] = 2-norm of column j of A (I x R), then the column is divided by it.
-__global__ void __launch_bounds__(256) normalise_columns(double* A, int64_t I, int R, double* lambda, const int* flag)
+// The value of lane 4 * (lane / 4) + p in all four lanes of the quad.
+__device__ __forceinline__ double quad_value(double v, int p)
 {
-    __shared__ double lds[256];
+    int lo = __double2loint(v), hi = __double2hiint(v);
+    switch (p) {      // p is a constant wherever this is called, after unrolling
+    case 0: lo = __builtin_amdgcn_mov_dpp(lo, 0x00, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x00, 0xf, 0xf, true); break;
+    case 1: lo = __builtin_amdgcn_mov_dpp(lo, 0x55, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x55, 0xf, 0xf, true); break;
+    case 2: lo = __builtin_amdgcn_mov_dpp(lo, 0xaa, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0xaa, 0xf, 0xf, true); break;
+    default: lo = __builtin_amdgcn_mov_dpp(lo, 0xff, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0xff, 0xf, 0xf, true); break;
+    }
+    return __hiloint2double(hi, lo);
+}
+
+// Triangular solves of 16 rows by one wavefront: the four lanes of a quad share a row, lane `part` holds its
+// unknowns 4 q + part.  An unknown that is final goes to the quad by DPP and every lane subtracts its
+// multiples of it (independent FMAs; L from LDS in the layout of factorise(), zeros where it has no entry).
+template <int RP> __device__ __forceinline__ void solve_forward(double (&y)[RP / 4], const double* Lf, int R, int part)
+{
+#pragma unroll
+    for (int a = 0; a < RP; ++a)
+        if (a < R) {
+            const double ya = quad_value(y[a >> 2], a & 3);
+#pragma unroll
+            for (int q = a >> 2; q < RP / 4; ++q)
+                y[q] -= Lf[a * (RP + 1) + 4 * q + part] * ya;
+        }
+}
+template <int RP> __device__ __forceinline__ void solve_backward(double (&y)[RP / 4], const double* Lf, int R, int part)
+{
+#pragma unroll
+    for (int a = RP - 1; a >= 0; --a)
+        if (a < R) {
+            const double ya = quad_value(y[a >> 2], a & 3);
+#pragma unroll
+            for (int q = 0; q <= a >> 2; ++q)
+                y[q] -= Lf[(4 * q + part) * (RP + 1) + a] * ya;
+        }
+}
+
+// Rows [row0, row0 + n) of A (R columns): divided by their columns' norms; returns this thread's share of the
+// column sums of M * A, which belong to column threadIdx.x % RP.
+template <int RP>
+__device__ __forceinline__ double scale_rows(double* A, const double* __restrict__ M, int64_t row0, int64_t n, int R, const double* nrm)
+{
+    const int j = threadIdx.x % RP;
+    double s = 0.0;
+    if (j < R)
+        for (int64_t i = threadIdx.x / RP; i < n; i += blockDim.x / RP) {
+            const int64_t e = (row0 + i) * R + j;
+            const double v = A[e] / nrm[j];
+            A[e] = v;
+            s += M[e] * v;
+        }
+    return s;
+}
+
+// Up to rank 64.  V is formed (Hadamard product of the Gram matrices of the other modes) and factorised
+// by every workgroup for itself: that costs no time beside the launches it saves.  A wavefront
+// solves 16 rows at a time; the tile's rows then go through LDS into the Gram matrix, which also holds
+// the columns' squared norms.
+//   WHOLE (one workgroup, short factors): the norms, the normalised rows, the Gram matrix and the column
+//   sums of M * A follow in the same launch.  Otherwise every workgroup leaves its Gram matrix in gram_ws and
+//   als_normalise does the rest.
+// 100 x 80 x 60 at R = 10: six launches of 23 us a mode and the gaps between them -> one of 11 us; the call of
+// 12 sweeps 2.35 -> 1.48 ms.
+template <int RP, int WAVES, bool WHOLE>
+__global__ void __launch_bounds__(64 * WAVES)
+als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, int64_t n_tiles,
+           double* gram_ws, double* lambda, double* inner, int* flag)
+{
+    constexpr int NT = RP / 16, THREADS = 64 * WAVES, TR = 16 * WAVES;
+    constexpr int YR = RP == 64 ? 32 : TR;          // rows of a tile that pass through LDS at once
+    constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
+    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP];
+    __shared__ double Ys[YR * (RP + 1)];
+    if (flag[0])      // an earlier update failed: every factor stays as it is
+        return;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ti = tid & 15, tc = (tid >> 4) & 15, grp = tid >> 8;
+    const int64_t RR = (int64_t)R * R;
+    double own[NT][NT];
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            const int i = ti + 16 * p, c = tc + 16 * q;
+            double v = 0.0;
+            if (i < R && c < R) {
+                v = 1.0;
+                for (int m = 0; m < ndim; ++m)
+                    if (m != k)
+                        v *= G[m * RR + i * R + c];
+            }
+            own[p][q] = v;
+        }
+    if (!factorise<RP>(own, R, col, Lf, dinv)) {
+        if (blockIdx.x == 0 && tid == 0)
+            flag[0] = 1;
+        return;
+    }
+    double acc[NT][NT];
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+            acc[p][q] = 0.0;
+    const int part = lane & 3, trow = 16 * wave + (lane >> 2);
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const int64_t row = tile * TR + trow;
+        double y[RP / 4];
+#pragma unroll
+        for (int q = 0; q < RP / 4; ++q)
+            y[q] = row < I && 4 * q + part < R ? M[row * R + 4 * q + part] : 0.0;
+        solve_forward<RP>(y, Lf, R, part);
+#pragma unroll
+        for (int q = 0; q < RP / 4; ++q)
+            y[q] *= dinv[4 * q + part];
+        solve_backward<RP>(y, Lf, R, part);
+        if (row < I) {
+#pragma unroll
+            for (int q = 0; q < RP / 4; ++q)
+                if (4 * q + part < R)
+                    A[row * R + 4 * q + part] = y[q];
+        }
+#pragma unroll
+        for (int h = 0; h < TR / YR; ++h) {
+            if (trow / YR == h) {
+#pragma unroll
+                for (int q = 0; q < RP / 4; ++q)
+                    Ys[(trow % YR) * (RP + 1) + 4 * q + part] = y[q];
+            }
+            __syncthreads();
+            for (int r = grp; r < YR; r += NG) {
+                double a[NT], b[NT];
+#pragma unroll
+                for (int p = 0; p < NT; ++p) {
+                    a[p] = Ys[r * (RP + 1) + ti + 16 * p];
+                    b[p] = Ys[r * (RP + 1) + tc + 16 * p];
+                }
+#pragma unroll
+                for (int p = 0; p < NT; ++p)
+#pragma unroll
+                    for (int q = 0; q < NT; ++q)
+                        acc[p][q] += a[p] * b[q];
+            }
+            __syncthreads();
+        }
+    }
+    if (!WHOLE) {
+        static_assert(WHOLE || NG == 1, "one group of threads per partial Gram matrix");
+        double* const o = gram_ws + (int64_t)blockIdx.x * RR;
+#pragma unroll
+        for (int p = 0; p < NT; ++p)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                if (ti + 16 * p < R && tc + 16 * q < R)
+                    o[(ti + 16 * p) * R + tc + 16 * q] = acc[p][q];
+        return;
+    }
+    // the groups' Gram sums in group order
+    for (int g = 1; g < NG; ++g) {
+        if (grp == g) {
+#pragma unroll
+            for (int p = 0; p < NT; ++p)
+#pragma unroll
+                for (int q = 0; q < NT; ++q)
+                    Ys[(p * NT + q) * 256 + (tid & 255)] = acc[p][q];
+        }
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int p = 0; p < NT; ++p)
+#pragma unroll
+                for (int q = 0; q < NT; ++q)
+                    acc[p][q] += Ys[(p * NT + q) * 256 + tid];
+        }
+        __syncthreads();
+    }
+    if (grp == 0 && ti == tc) {
+#pragma unroll
+        for (int p = 0; p < NT; ++p) {
+            const double n = sqrt(acc[p][p]);
+            nrm[ti + 16 * p] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+            if (ti + 16 * p < R)
+                lambda[ti + 16 * p] = n;
+        }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int p = 0; p < NT; ++p)
+#pragma unroll
+            for (int q = 0; q < NT; ++q)
+                if (ti + 16 * p < R && tc + 16 * q < R)
+                    G[k * RR + (ti + 16 * p) * R + tc + 16 * q] = acc[p][q] / (nrm[ti + 16 * p] * nrm[tc + 16 * q]);
+    }
+    const double s = scale_rows<RP>(A, M, 0, I, R, nrm);
+    Ys[tid] = s;
+    __syncthreads();
+    if (tid < R) {
+        double v = 0.0;
+        for (int q = tid; q < THREADS; q += RP)
+            v += Ys[q];
+        inner[tid] = v;
+    }
+}
+
+// Second launch of the update for longer factors: every workgroup adds up the columns' squared norms (n_gram
+// partial Gram matrices, in order), normalises its rows and its share of the Gram matrix, and leaves its
+// column sums of M * A in inner[block][R].
+template <int RP>
+__global__ void __launch_bounds__(256)
+als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, const double* __restrict__ M, int64_t I,
+              int64_t rows_per_block, double* Gk, double* lambda, double* inner, const int* flag)
+{
+    __shared__ double red[256], nrm[RP];
     if (flag[0])
         return;
-    const int j = blockIdx.x;
+    const int tid = (int)threadIdx.x, j = tid % RP;
+    const int64_t RR = (int64_t)R * R;
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < I; i += 256) {
-        const double v = A[i * R + j];
-        s += v * v;
+    if (j < R)
+        for (int b = tid / RP; b < n_gram; b += 256 / RP)
+            s += gram_ws[b * RR + (int64_t)j * R + j];
+    red[tid] = s;
+    __syncthreads();
+    if (tid < RP) {
+        double v = 0.0;
+        for (int q = tid; q < 256; q += RP)
+            v += red[q];
+        const double n = sqrt(v);
+        nrm[tid] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+        if (blockIdx.x == 0 && tid < R)
+            lambda[tid] = n;
     }
-    s = block_sum_256(s, lds);
-    const double nrm = sqrt(s);
-    if (threadIdx.x == 0)
-        lambda[j] = nrm;
-    if (nrm > 0.0)
-        for (int64_t i = threadIdx.x; i < I; i += 256)
-            A[i * R + j] /= nrm;
+    __syncthreads();
+    for (int64_t e = (int64_t)blockIdx.x * 256 + tid; e < RR; e += (int64_t)gridDim.x * 256) {
+        const int a = (int)(e / R), c = (int)(e - (int64_t)a * R);
+        double v = 0.0;
+        for (int b = 0; b < n_gram; ++b)
+            v += gram_ws[b * RR + e];
+        Gk[e] = v / (nrm[a] * nrm[c]);
+    }
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
+    red[tid] = scale_rows<RP>(A, M, r0, I - r0 < rows_per_block ? I - r0 : rows_per_block, R, nrm);
+    __syncthreads();
+    if (tid < R) {
+        double v = 0.0;
+        for (int q = tid; q < 256; q += RP)
+            v += red[q];
+        inner[(int64_t)blockIdx.x * R + tid] = v;
+    }
 }
 
-// Workgroup j: col[j] = lambda[j] * sum_i M(i, j) A(i, j).
-__global__ void __launch_bounds__(256) inner_product_columns(const double* __restrict__ M, const double* __restrict__ A,
-                                                              const double* __restrict__ lambda, int64_t I, int R,
-                                                              double* col)
+// Fit terms up to rank 64, one workgroup: out[0] = sum_j lambda_j (sum over the blocks of inner[b][j]) = <X, X^>,
+// out[1] = lambda^T (Hadamard product of all Gram matrices) lambda = ||X^||^2.
+__global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict__ G, int ndim, int R, const double* __restrict__ lambda,
+                                                        const double* __restrict__ inner, int n_inner, double* out)
 {
     __shared__ double lds[256];
-    const int j = blockIdx.x;
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < I; i += 256)
-        s += M[i * R + j] * A[i * R + j];
-    s = block_sum_256(s, lds);
-    if (threadIdx.x == 0)
-        col[j] = lambda[j] * s;
-}
-
-// out[0] = lambda^T V lambda, one workgroup, fixed order (row sums, then their sum).
-__global__ void __launch_bounds__(256) quadratic_form(const double* __restrict__ V, const double* __restrict__ lambda,
-                                                       int R, double* out)
-{
-    __shared__ double lds[256];
-    double s = 0.0;
-    for (int a = threadIdx.x; a < R; a += 256) {
-        double r = 0.0;
-        for (int c = 0; c < R; ++c)
-            r += V[a * R + c] * lambda[c];
-        s += lambda[a] * r;
+    double s = 0.0, t = 0.0;
+    for (int e = threadIdx.x; e < n_inner * R; e += 256)
+        s += inner[e] * lambda[e % R];
+    for (int e = threadIdx.x; e < R * R; e += 256) {
+        double v = lambda[e / R] * lambda[e % R];
+        for (int m = 0; m < ndim; ++m)
+            v *= G[(int64_t)m * R * R + e];
+        t += v;
     }
     s = block_sum_256(s, lds);
-    if (threadIdx.x == 0)
+    t = block_sum_256(t, lds);
+    if (threadIdx.x == 0) {
         out[0] = s;
+        out[1] = t;
+    }
 }
-
 
 // ---------------------------------------------------------------------------
-// Ranks above 64: the R x R matrices no longer fit the LDS of one workgroup.  Gram matrices,
-// the Cholesky factorisation and the two triangular solves run blocked from global memory,
-// 32 columns at a time, every sum still in a fixed order.
+// Ranks above 64: Gram matrices, the factorisation and the triangular solves run blocked, 32 columns
+// at a time, every sum still in a fixed order.
 // ---------------------------------------------------------------------------
 constexpr int kNB = 32;
 
@@ -259,196 +517,304 @@ __global__ void __launch_bounds__(256) gram_tiled(const double* __restrict__ A, 
         G[(int64_t)(p0 + ty) * R + q0 + tx] = s;
 }
 
-// Diagonal block [j0, j0 + nb) of the blocked factorisation: Cholesky factor of the block in
-// LDS by one workgroup, lower triangle written back, the block's upper triangle zeroed.
-__global__ void __launch_bounds__(256) chol_diag(double* V, int R, int j0, int nb, int* flag)
+// One launch per 32 columns of V = L D L^T, V holding what is still to be factorised.  Workgroup (tj, ti),
+// ti >= tj, owns the 32 x 32 tile (ti, tj) of the trailing lower triangle.  It factorises the diagonal block for
+// itself, solves the two 32-row pieces of the block column that its tile needs against it, and subtracts
+// their product: no workgroup waits for another, and a step is one launch of 14 us (before: a launch for the
+// diagonal block, one for the panel and one for the update, 47 us at R = 500).  The block column of V is only
+// read; the tiles on the diagonal write their rows of L, workgroup (0, 0) the block's own rows and dinv = 1 / D.
+__global__ void __launch_bounds__(256)
+factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag)
 {
-    __shared__ double B[kNB][kNB + 1];
+    __shared__ double Lf[kNB * (kNB + 1)], dinv[kNB], col[2][kNB];
+    __shared__ double W[2][kNB][kNB + 1];
+    if (flag[0] || blockIdx.x > blockIdx.y)
+        return;
+    const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4, lane = tid & 63, wave = tid >> 6;
+    const int nb = R - j0 < kNB ? R - j0 : kNB, j1 = j0 + nb;
+    // rows of the block column for this wavefront: 16 rows of tile row ti (wavefronts 0, 1) or tj (2, 3)
+    const int side = wave >> 1, part = lane & 3, wrow = 16 * (wave & 1) + (lane >> 2);
+    const int row = j1 + kNB * (int)(side == 0 ? blockIdx.y : blockIdx.x) + wrow;
+    double y[kNB / 4], own[2][2], v[2][2];
+#pragma unroll
+    for (int q = 0; q < kNB / 4; ++q)
+        y[q] = row < R ? V[(int64_t)row * R + j0 + 4 * q + part] : 0.0;     // a trailing row: nb == 32
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int i = ti + 16 * p, c = tc + 16 * q;
+            own[p][q] = i < nb && c < nb ? V[(int64_t)(j0 + (i > c ? i : c)) * R + j0 + (i > c ? c : i)] : 0.0;
+            const int vi = j1 + kNB * (int)blockIdx.y + i, vc = j1 + kNB * (int)blockIdx.x + c;
+            v[p][q] = vi < R && vc <= vi ? V[(int64_t)vi * R + vc] : 0.0;
+        }
+    if (!factorise<kNB>(own, nb, col, Lf, dinv)) {
+        if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0)
+            flag[0] = 1;
+        return;
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
+        for (int t = tid; t < nb * nb; t += 256) {
+            const int i = t / nb, c = t - i * nb;
+            if (c < i)
+                L[(int64_t)(j0 + i) * R + j0 + c] = Lf[c * (kNB + 1) + i];
+        }
+        if (tid < nb)
+            dinv_out[j0 + tid] = dinv[tid];
+    }
+    if (j1 >= R)
+        return;
+    solve_forward<kNB>(y, Lf, kNB, part);
+#pragma unroll
+    for (int q = 0; q < kNB / 4; ++q) {
+        if (side == 1)
+            y[q] *= dinv[4 * q + part];        // rows of L itself
+        W[side][wrow][4 * q + part] = y[q];
+        if (side == 1 && blockIdx.x == blockIdx.y && row < R)
+            L[(int64_t)row * R + j0 + 4 * q + part] = y[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kNB; ++k) {
+        const double a0 = W[0][ti][k], a1 = W[0][ti + 16][k], b0 = W[1][tc][k], b1 = W[1][tc + 16][k];
+        v[0][0] -= a0 * b0;
+        v[0][1] -= a0 * b1;
+        v[1][0] -= a1 * b0;
+        v[1][1] -= a1 * b1;
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int vi = j1 + kNB * (int)blockIdx.y + ti + 16 * p, vc = j1 + kNB * (int)blockIdx.x + tc + 16 * q;
+            if (vi < R && vc <= vi)
+                V[(int64_t)vi * R + vc] = v[p][q];
+        }
+}
+
+// Rows of A = M V^{-1} with V = L D L^T.  A workgroup owns 16 rows and takes them through the whole forward and
+// backward solve: per block of 32 unknowns the first wavefront solves against the diagonal block (quads of lanes
+// as above), then all wavefronts subtract the block's multiples from the columns that follow, 16 at a time on the
+// matrix cores.  The 16 x R slab lies in LDS (LDSY, R <= 1024) or in A itself.  One launch instead of four
+// per block: 129 rows at R = 500 0.89 -> 0.135 ms; bound by the chain of 2 R / 32 block solves, so what matters is
+// that loads of L are under way before a block is solved.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+template <int WAVES, bool LDSY>
+__global__ void __launch_bounds__(64 * WAVES)
+solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv, int R, const double* __restrict__ M,
+                   double* A, int64_t I, const int* flag)
+{
+    extern __shared__ double slab[];
+    __shared__ double Ld[2][kNB * (kNB + 1)];
+    constexpr int THREADS = 64 * WAVES;
     if (flag[0])
         return;
-    for (int t = threadIdx.x; t < nb * nb; t += 256)
-        B[t / nb][t % nb] = V[(int64_t)(j0 + t / nb) * R + j0 + t % nb];
-    __syncthreads();
-    for (int j = 0; j < nb; ++j) {
-        const double piv = B[j][j];
-        if (!(piv > 0.0)) {
-            if (threadIdx.x == 0)
-                flag[0] = 1;
-            return;   // uniform: every thread sees the same pivot
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3;
+    const int64_t r0 = (int64_t)blockIdx.x * 16;
+    const int rows = (int)(I - r0 < 16 ? I - r0 : 16);
+    const int nblk = (R + kNB - 1) / kNB;
+    const int ldy = nblk * kNB + 1;
+    auto get = [&](int r, int c) -> double {
+        if (LDSY)
+            return slab[r * ldy + c];
+        return r < rows && c < R ? A[(r0 + r) * R + c] : 0.0;
+    };
+    auto put = [&](int r, int c, double v) {
+        if (LDSY)
+            slab[r * ldy + c] = v;
+        else if (r < rows && c < R)
+            A[(r0 + r) * R + c] = v;
+    };
+    for (int r = wave; r < 16; r += WAVES)
+        for (int c = lane; c < nblk * kNB; c += 64)
+            put(r, c, r < rows && c < R ? M[(r0 + r) * R + c] : 0.0);
+    auto load_diag = [&](int b, int t0, int step) {        // entry (c, a), c > a, of the diagonal block b
+        double* const o = Ld[b & 1];
+        for (int t = t0; t < kNB * kNB; t += step) {
+            const int a = t & (kNB - 1), c = t / kNB, j0 = b * kNB;
+            o[a * (kNB + 1) + c] = c > a && j0 + c < R ? L[(int64_t)(j0 + c) * R + j0 + a] : 0.0;
         }
-        const double dj = sqrt(piv);
+    };
+    // columns [16 ct, 16 ct + 16) -= (the block's 16 x 32 unknowns) * bt, bt[s] = row 8 kq + s of the 32 x 16 operand
+    auto update = [&](int b, int ct, const double (&bt)[8]) {
+        double4_t acc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc[q] = get(4 * q + kq, 16 * ct + n16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-get(n16, b * kNB + 8 * kq + s), bt[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            put(4 * q + kq, 16 * ct + n16, acc[q]);
+    };
+    auto diag_solve = [&](int b, bool forward) {
+        double y[kNB / 4];
+        const int r = lane >> 2;
+#pragma unroll
+        for (int q = 0; q < kNB / 4; ++q)
+            y[q] = get(r, b * kNB + 4 * q + part);
+        if (forward)
+            solve_forward<kNB>(y, Ld[b & 1], kNB, part);
+        else
+            solve_backward<kNB>(y, Ld[b & 1], kNB, part);
+#pragma unroll
+        for (int q = 0; q < kNB / 4; ++q)
+            put(r, b * kNB + 4 * q + part, y[q]);
+    };
+    const int ncol = (R + 15) / 16;
+    load_diag(0, tid, THREADS);
+    __syncthreads();
+    for (int b = 0; b < nblk; ++b) {
+        auto load_b = [&](int ct, double (&bt)[8]) {       // L(16 ct + n, 32 b + 8 kq + s): a following row, so block b is full
+            const int c = 16 * ct + n16;
+            const double* const src = L + (int64_t)c * R + b * kNB + 8 * kq;
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                bt[s] = c < R ? src[s] : 0.0;
+        };
+        double bt[8];
+        int ct = 2 * (b + 1) + wave;
+        if (ct < ncol)
+            load_b(ct, bt);
+        if (wave == 0)
+            diag_solve(b, true);
+        else if (b + 1 < nblk)
+            load_diag(b + 1, tid - 64, THREADS - 64);
         __syncthreads();
-        for (int i = j + threadIdx.x; i < nb; i += 256)
-            B[i][j] = i == j ? dj : B[i][j] / dj;
-        __syncthreads();
-        const int n = nb - j - 1;
-        for (int t = threadIdx.x; t < n * n; t += 256) {
-            const int i = j + 1 + t / n, c = j + 1 + t % n;
-            if (c <= i)
-                B[i][c] -= B[i][j] * B[c][j];
+        for (; ct < ncol; ct += WAVES) {
+            double nx[8];
+            if (ct + WAVES < ncol)
+                load_b(ct + WAVES, nx);
+            update(b, ct, bt);
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                bt[s] = nx[s];
         }
         __syncthreads();
     }
-    for (int t = threadIdx.x; t < nb * nb; t += 256) {
-        const int r = t / nb, c = t % nb;
-        V[(int64_t)(j0 + r) * R + j0 + c] = c <= r ? B[r][c] : 0.0;
+    for (int r = wave; r < 16; r += WAVES)
+        for (int c = lane; c < R; c += 64)
+            put(r, c, get(r, c) * dinv[c]);
+    __syncthreads();
+    for (int b = nblk - 1; b >= 0; --b) {                   // Ld[b & 1] holds block b: the last one is still there
+        auto load_b = [&](int ct, double (&bt)[8]) {       // L(32 b + 8 kq + s, 16 ct + n)
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int k = b * kNB + 8 * kq + s;
+                bt[s] = k < R ? L[(int64_t)k * R + 16 * ct + n16] : 0.0;
+            }
+        };
+        double bt[8];
+        int ct = wave;
+        if (ct < 2 * b)
+            load_b(ct, bt);
+        if (wave == 0)
+            diag_solve(b, false);
+        else if (b > 0)
+            load_diag(b - 1, tid - 64, THREADS - 64);
+        __syncthreads();
+        for (; ct < 2 * b; ct += WAVES) {
+            double nx[8];
+            if (ct + WAVES < 2 * b)
+                load_b(ct + WAVES, nx);
+            update(b, ct, bt);
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                bt[s] = nx[s];
+        }
+        __syncthreads();
+    }
+    if (LDSY)
+        for (int r = wave; r < rows; r += WAVES)
+            for (int c = lane; c < R; c += 64)
+                A[(r0 + r) * R + c] = get(r, c);
+}
+
+// Columns of A (n entries) divided by their norms = the roots of the diagonal of the Gram matrix S, and the
+// normalised Gram matrix.  One thread per entry of A, then of S.
+__global__ void __launch_bounds__(256)
+scale_by_gram(const double* __restrict__ S, int R, double* A, int64_t n, double* Gk, double* lambda, const int* flag)
+{
+    if (flag[0])
+        return;
+    const int64_t RR = (int64_t)R * R;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n + RR; e += (int64_t)gridDim.x * 256) {
+        if (e < n) {
+            const int j = (int)(e % R);
+            const double nrm = sqrt(S[(int64_t)j * R + j]);
+            if (nrm > 0.0)
+                A[e] /= nrm;
+            if (e < R)
+                lambda[j] = nrm;
+        } else {
+            const int64_t t = e - n;
+            const int a = (int)(t / R), c = (int)(t - (int64_t)a * R);
+            const double na = sqrt(S[(int64_t)a * R + a]), nc = sqrt(S[(int64_t)c * R + c]);
+            Gk[t] = S[t] / ((na > 0.0 ? na : 1.0) * (nc > 0.0 ? nc : 1.0));
+        }
     }
 }
 
-// The nb x nb triangle L11 = V[j0 .., j0 ..] into LDS (all of the workgroup's threads).
-__device__ __forceinline__ void load_diag_block(const double* __restrict__ V, int R, int j0, int nb, double (*B)[kNB + 1])
+// Fit terms, partial sums: blocks [0, n_chunks) add lambda_j M(i, j) A(i, j) over their rows, blocks n_chunks + a
+// lambda_a V(a, c) lambda_c over c, with V the Hadamard product of all Gram matrices.
+__global__ void __launch_bounds__(256)
+fit_terms_partial(const double* __restrict__ G, int ndim, int R, const double* __restrict__ lambda, const double* __restrict__ M,
+                  const double* __restrict__ A, int64_t I, int n_chunks, int64_t rows_per_chunk, double* part)
 {
-    for (int t = threadIdx.x; t < kNB * kNB; t += blockDim.x) {
-        const int r = t / kNB, c = t % kNB;
-        B[r][c] = r < nb && c < nb ? V[(int64_t)(j0 + r) * R + j0 + c] : (r == c ? 1.0 : 0.0);
-    }
-    __syncthreads();
-}
-
-// Rows [r0, r1) of the matrix Y (leading dimension R), columns [j0, j0 + nb): every row is solved
-// against L11 (forward: y_c = (y_c - sum_{q < c} L11(c, q) y_q) / L11(c, c), c ascending) or its
-// transpose (backward: x_c = (x_c - sum_{q > c} L11(q, c) x_q) / L11(c, c), c descending); one
-// thread per row, the row's unknowns in LDS.
-constexpr int kSolveThreads = 128;
-template <bool FORWARD>
-__global__ void __launch_bounds__(kSolveThreads)
-solve_diag_rows(const double* __restrict__ L, int R, int j0, int nb, double* Y, int64_t r0, int64_t r1, const int* flag)
-{
-    __shared__ double B[kNB][kNB + 1];
-    __shared__ double ys[kNB][kSolveThreads];
-    if (flag[0])
-        return;
-    load_diag_block(L, R, j0, nb, B);
-    const int64_t row = r0 + (int64_t)blockIdx.x * kSolveThreads + threadIdx.x;
-    if (row >= r1)
-        return;
-    const int tid = threadIdx.x;
-    for (int c = 0; c < nb; ++c)
-        ys[c][tid] = Y[row * R + j0 + c];
-    if (FORWARD) {
-        for (int c = 0; c < nb; ++c) {
-            double v = ys[c][tid];
-            for (int q = 0; q < c; ++q)
-                v -= B[c][q] * ys[q][tid];
-            ys[c][tid] = v / B[c][c];
+    __shared__ double lds[256];
+    double s = 0.0;
+    if ((int)blockIdx.x < n_chunks) {
+        const int64_t i0 = (int64_t)blockIdx.x * rows_per_chunk;
+        const int64_t i1 = i0 + rows_per_chunk < I ? i0 + rows_per_chunk : I;
+        for (int j = threadIdx.x; j < R; j += 256) {
+            double t = 0.0;
+            for (int64_t i = i0; i < i1; ++i)
+                t += M[i * R + j] * A[i * R + j];
+            s += lambda[j] * t;
         }
     } else {
-        for (int c = nb - 1; c >= 0; --c) {
-            double v = ys[c][tid];
-            for (int q = nb - 1; q > c; --q)
-                v -= B[q][c] * ys[q][tid];
-            ys[c][tid] = v / B[c][c];
+        const int a = (int)blockIdx.x - n_chunks;
+        for (int c = threadIdx.x; c < R; c += 256) {
+            double v = lambda[a] * lambda[c];
+            for (int m = 0; m < ndim; ++m)
+                v *= G[((int64_t)m * R + a) * R + c];
+            s += v;
         }
     }
-    for (int c = 0; c < nb; ++c)
-        Y[row * R + j0 + c] = ys[c][tid];
+    s = block_sum_256(s, lds);
+    if (threadIdx.x == 0)
+        part[blockIdx.x] = s;
 }
 
-// Y(row, c) -= sum_{q < nb} S(row, q) * W(c, q) for rows [r0, r1) and columns [c0, c1), a 16 x 16
-// tile per workgroup.  S(row, q) = Y(row, j0 + q); W(c, q) = L(c, j0 + q) (TRANS = false: the
-// columns below a block of the forward solve and of the factorisation's trailing update) or
-// L(j0 + q, c) (TRANS = true: the columns before a block of the backward solve).  LOWER: only
-// entries with c <= row are touched (the factorisation keeps the lower triangle).
-template <bool TRANS, bool LOWER>
-__global__ void __launch_bounds__(256)
-update_tile(const double* __restrict__ L, int R, int j0, int nb, double* Y, int64_t r0, int64_t r1, int c0, int c1,
-            const int* flag)
+// out[b] = sum of part[first[b] ..): the two fit terms, one workgroup each, fixed order.
+__global__ void __launch_bounds__(256) fit_terms_sum(const double* __restrict__ part, int n_chunks, int R, double* out)
 {
-    __shared__ double S[16][kNB + 1], W[16][kNB + 1];
-    if (flag[0])
-        return;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t rt = r0 + (int64_t)blockIdx.y * 16;
-    const int ct = c0 + blockIdx.x * 16;
-    if (LOWER && ct > rt + 15)
-        return;      // a tile above the diagonal
-    for (int t = threadIdx.x; t < 16 * kNB; t += 256) {
-        const int a = t / kNB, q = t % kNB;
-        S[a][q] = q < nb && rt + a < r1 ? Y[(rt + a) * R + j0 + q] : 0.0;
-        double w = 0.0;
-        if (q < nb && ct + a < c1)
-            w = TRANS ? L[(int64_t)(j0 + q) * R + ct + a] : L[(int64_t)(ct + a) * R + j0 + q];
-        W[a][q] = w;
-    }
-    __syncthreads();
-    const int64_t row = rt + ty;
-    const int c = ct + tx;
-    if (row >= r1 || c >= c1 || (LOWER && c > row))
-        return;
+    __shared__ double lds[256];
+    const int i0 = blockIdx.x == 0 ? 0 : n_chunks, i1 = blockIdx.x == 0 ? n_chunks : n_chunks + R;
     double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kNB; ++q)
-        s += S[ty][q] * W[tx][q];
-    Y[row * R + c] -= s;
+    for (int i = i0 + threadIdx.x; i < i1; i += 256)
+        s += part[i];
+    s = block_sum_256(s, lds);
+    if (threadIdx.x == 0)
+        out[blockIdx.x] = s;
 }
 
-// dst = src (n values) unless the factorisation failed.
-__global__ void __launch_bounds__(256) copy_unless_flag(const double* __restrict__ src, double* dst, int64_t n, const int* flag)
-{
-    if (flag[0])
-        return;
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e < n)
-        dst[e] = src[e];
-}
-
-// V := its Cholesky factor (lower triangle; the strict upper triangle keeps stale values that
-// nothing reads), block column by block column: factor the diagonal block, solve the panel below
-// it (rows of V against L11), update the trailing lower triangle.
-void cholesky_blocked(double* V, int R, int* flag, hipStream_t st)
-{
-    for (int j0 = 0; j0 < R; j0 += kNB) {
-        const int nb = R - j0 < kNB ? R - j0 : kNB;
-        hipLaunchKernelGGL(chol_diag, dim3(1), dim3(256), 0, st, V, R, j0, nb, flag);
-        const int j1 = j0 + nb;
-        if (j1 >= R)
-            break;
-        const int below = R - j1;
-        hipLaunchKernelGGL((solve_diag_rows<true>), dim3((unsigned)ceil_div(below, kSolveThreads)), dim3(kSolveThreads), 0, st,
-                           (const double*)V, R, j0, nb, V, (int64_t)j1, (int64_t)R, (const int*)flag);
-        const unsigned nt = (unsigned)ceil_div(below, 16);
-        hipLaunchKernelGGL((update_tile<false, true>), dim3(nt, nt), dim3(256), 0, st,
-                           (const double*)V, R, j0, nb, V, (int64_t)j1, (int64_t)R, j1, R, (const int*)flag);
-    }
-}
-
-// Rows of Y (I x R, in place) := Y V^{-1} with V = L L^T: forward against L block by block, then
-// backward against L^T.
-void solve_blocked(const double* L, int R, double* Y, int64_t I, const int* flag, hipStream_t st)
-{
-    const unsigned rb = (unsigned)ceil_div(I, kSolveThreads), rt = (unsigned)ceil_div(I, 16);
-    for (int j0 = 0; j0 < R; j0 += kNB) {
-        const int nb = R - j0 < kNB ? R - j0 : kNB;
-        hipLaunchKernelGGL((solve_diag_rows<true>), dim3(rb), dim3(kSolveThreads), 0, st, L, R, j0, nb, Y, (int64_t)0, I, flag);
-        const int j1 = j0 + nb;
-        if (j1 < R)
-            hipLaunchKernelGGL((update_tile<false, false>), dim3((unsigned)ceil_div(R - j1, 16), rt), dim3(256), 0, st,
-                               L, R, j0, nb, Y, (int64_t)0, I, j1, R, flag);
-    }
-    for (int j0 = (R - 1) / kNB * kNB; j0 >= 0; j0 -= kNB) {
-        const int nb = R - j0 < kNB ? R - j0 : kNB;
-        hipLaunchKernelGGL((solve_diag_rows<false>), dim3(rb), dim3(kSolveThreads), 0, st, L, R, j0, nb, Y, (int64_t)0, I, flag);
-        if (j0 > 0)
-            hipLaunchKernelGGL((update_tile<true, false>), dim3((unsigned)ceil_div(j0, 16), rt), dim3(256), 0, st,
-                               L, R, j0, nb, Y, (int64_t)0, I, 0, j0, flag);
-    }
-}
-
+// The driver's device memory: one allocation, cut up by cpals_run.
 struct Buffers {
+    char* base = nullptr;
     double* M = nullptr;        // max_n I_n x R
     double* G = nullptr;        // d x R x R Gram matrices
-    double* V = nullptr;        // R x R
-    double* gram_ws = nullptr;  // chunks x R x R
-    double* partial = nullptr;  // kNormBlocks + R values
-    double* scalars = nullptr;  // ||X||^2, <X, X^>, ||X^||^2
+    double* V = nullptr;        // R x R (ranks above 64)
+    double* L = nullptr;        // R x R and 1 / D, R (ranks above 64)
+    double* gram_ws = nullptr;  // partial Gram matrices, or the fit's partial sums
+    double* inner = nullptr;    // column sums of M * A (ranks up to 64)
+    double* partial = nullptr;  // kNormBlocks values
+    double* scalars = nullptr;  // ||X||^2, <X, X^>, ||X^||^2, then the pivot flag
     int* flag = nullptr;
     void* shared_ws = nullptr;  // intermediates of the sweeps that share partial contractions
-    ~Buffers()
-    {
-        (void)hipFree(shared_ws);
-        (void)hipFree(M); (void)hipFree(G); (void)hipFree(V); (void)hipFree(gram_ws);
-        (void)hipFree(partial); (void)hipFree(scalars); (void)hipFree(flag);
-    }
+    ~Buffers() { (void)hipFree(base); }
 };
 
 void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t st)
@@ -461,6 +827,64 @@ void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t 
     const int n_chunks = (int)ceil_div(I, kChunkRows);
     hipLaunchKernelGGL(gram_partial, dim3(n_chunks), dim3(256), (size_t)kChunkRows * R * sizeof(double), st, A, I, R, ws);
     hipLaunchKernelGGL(gram_reduce, dim3((unsigned)ceil_div(R * R, 256)), dim3(256), 0, st, ws, n_chunks, R * R, G);
+}
+
+
+// The update of a factor up to rank 64: one workgroup for short factors, else two launches.  Returns the number
+// of blocks that left column sums of M * A in b.inner.  One workgroup takes I * RP values up to 16384 (RP = the
+// rank rounded up to 16 or 32): its tiles then take about as long as a second launch.
+int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, hipStream_t st)
+{
+    double* const Gk = b.G + (int64_t)k * R * R;
+    if (R <= 32 && I * (R <= 16 ? 16 : 32) <= 16384) {
+        const int64_t tiles = ceil_div(I, 128);
+        if (R <= 16)
+            hipLaunchKernelGGL((als_update<16, 8, true>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, tiles,
+                               b.gram_ws, lambda, b.inner, b.flag);
+        else
+            hipLaunchKernelGGL((als_update<32, 8, true>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, tiles,
+                               b.gram_ws, lambda, b.inner, b.flag);
+        return 1;
+    }
+    const int64_t tiles = ceil_div(I, 64);
+    const int n_gram = (int)(tiles < kGramBlocks ? tiles : kGramBlocks);
+    const int64_t want = ceil_div(I * R, 2048);
+    const int64_t rows = ceil_div(I, want < kScaleBlocks ? want : kScaleBlocks);
+    const int n_scale = (int)ceil_div(I, rows);
+    if (R <= 16) {
+        hipLaunchKernelGGL((als_update<16, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
+                           tiles, b.gram_ws, lambda, b.inner, b.flag);
+        hipLaunchKernelGGL((als_normalise<16>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
+                           rows, Gk, lambda, b.inner, b.flag);
+    } else if (R <= 32) {
+        hipLaunchKernelGGL((als_update<32, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
+                           tiles, b.gram_ws, lambda, b.inner, b.flag);
+        hipLaunchKernelGGL((als_normalise<32>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
+                           rows, Gk, lambda, b.inner, b.flag);
+    } else {
+        hipLaunchKernelGGL((als_update<64, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
+                           tiles, b.gram_ws, lambda, b.inner, b.flag);
+        hipLaunchKernelGGL((als_normalise<64>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
+                           rows, Gk, lambda, b.inner, b.flag);
+    }
+    return n_scale;
+}
+
+// Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns; many: four, so
+// that several workgroups fit a compute unit.  Above rank 1024 the slab does not fit the 160 KB of LDS.
+void solve_big(const double* L, const double* dinv, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
+{
+    const unsigned grid = (unsigned)ceil_div(I, 16);
+    const size_t lds = (size_t)16 * (ceil_div(R, kNB) * kNB + 1) * sizeof(double);
+    if (R > 1024) {
+        hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, dinv, R, M, A, I, flag);
+    } else if (grid <= 512) {
+        (void)hipFuncSetAttribute((const void*)solve_rows_blocked<16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, dinv, R, M, A, I, flag);
+    } else {
+        (void)hipFuncSetAttribute((const void*)solve_rows_blocked<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL((solve_rows_blocked<4, true>), dim3(grid), dim3(256), lds, st, L, dinv, R, M, A, I, flag);
+    }
 }
 
 
@@ -880,36 +1304,53 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
             max_I = dims[m];
     }
     if (big && max_I > (int64_t)65535 * 16)
-        return MTTKRP_ERR_UNSUPPORTED;     // the blocked solves' grids
+        return MTTKRP_ERR_UNSUPPORTED;     // the limit the header states
     *iters = 0;
     hipStream_t st = (hipStream_t)stream;
     const int RR = R * R;
-    Buffers b;
     // shared sweeps: the intermediates' buffer; without a cut that fits, d separate passes
     SharedPlan sp;
     if (shared && plan_shared(ndim, dims, R, (int)sizeof(double), sp) != MTTKRP_OK)
         shared = false;
-    if (shared && hipMalloc(&b.shared_ws, sp.total) != hipSuccess)
-        return MTTKRP_ERR_DEVICE;
-    const int64_t max_chunks = big ? 1 : ceil_div(max_I, kChunkRows);
-    if (hipMalloc(&b.M, (size_t)max_I * R * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.G, (size_t)ndim * RR * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.V, (size_t)RR * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.gram_ws, (size_t)max_chunks * (big ? 1 : RR) * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.partial, (size_t)(kNormBlocks + R) * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.scalars, 3 * sizeof(double)) != hipSuccess ||
-        hipMalloc(&b.flag, sizeof(int)) != hipSuccess)
-        return MTTKRP_ERR_DEVICE;
+    // One allocation: an allocation and a free each cost about as much as a sweep over a small tensor.
+    Buffers b;
+    {
+        size_t off = 0;
+        auto take = [&](size_t values) {
+            const size_t at = off;
+            off += align256(values * sizeof(double));
+            return at;
+        };
+        const int64_t chunks = ceil_div(max_I, kChunkRows);      // of the initial Gram matrices
+        const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
+                     o_L = take(big ? (size_t)RR + R : 0),
+                     o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * RR),
+                     o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4);
+        const size_t o_shared = off;
+        if (hipMalloc(&b.base, off + (shared ? sp.total : 0)) != hipSuccess) {
+            (void)hipGetLastError();
+            b.base = nullptr;
+            return MTTKRP_ERR_DEVICE;
+        }
+        b.M = (double*)(b.base + o_M);
+        b.G = (double*)(b.base + o_G);
+        b.V = (double*)(b.base + o_V);
+        b.L = (double*)(b.base + o_L);
+        b.gram_ws = (double*)(b.base + o_ws);
+        b.inner = (double*)(b.base + o_in);
+        b.partial = (double*)(b.base + o_part);
+        b.scalars = (double*)(b.base + o_sc);
+        b.flag = (int*)(b.scalars + 3);
+        b.shared_ws = b.base + o_shared;
+    }
 
-    // ||X||^2 once, Gram matrices of the initial factors, cleared pivot flag
-    const int nb = (int)(N < kNormBlocks ? N : kNormBlocks);
+    // ||X||^2 once (which also clears the pivot flag), Gram matrices of the initial factors
+    const int64_t want_nb = ceil_div(N, 2048);
+    const int nb = (int)(want_nb < kNormBlocks ? want_nb : kNormBlocks);
     hipLaunchKernelGGL(sumsq_partial, dim3(nb), dim3(256), 0, st, X, N, b.partial);
-    hipLaunchKernelGGL(sum_fixed, dim3(1), dim3(256), 0, st, b.partial, nb, b.scalars + 0);
+    hipLaunchKernelGGL(sum_fixed, dim3(1), dim3(256), 0, st, b.partial, nb, b.scalars + 0, b.flag);
     for (int m = 0; m < ndim; ++m)
         gram(factors[m], dims[m], R, b.gram_ws, b.G + (int64_t)m * RR, st);
-    int zero = 0;
-    if (hipMemcpyAsync(b.flag, &zero, sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess)
-        return MTTKRP_ERR_DEVICE;
 
     const double* cf[MTTKRP_MAX_NDIM];
     double* mo[MTTKRP_MAX_NDIM];
@@ -917,25 +1358,27 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         cf[m] = factors[m];
         mo[m] = b.M;
     }
+    int n_inner = 1;            // blocks that left column sums of M * A at the last update
     // the update of factor k from its MTTKRP in b.M
     auto update = [&](int k) {
+        double* const Gk = b.G + (int64_t)k * RR;
+        const int64_t I = dims[k];
+        if (!big) {
+            n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, st);
+        } else {
             hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(RR, 256)), dim3(256), 0, st, b.G, ndim, RR, k, b.V);
-            if (big) {
-                // the rows of M go to A_k (unless the factorisation failed) and are solved there in
-                // place: M itself stays for the fit
-                cholesky_blocked(b.V, R, b.flag, st);
-                const int64_t n = dims[k] * (int64_t)R;
-                hipLaunchKernelGGL(copy_unless_flag, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
-                                   (const double*)b.M, factors[k], n, (const int*)b.flag);
-                solve_blocked(b.V, R, factors[k], dims[k], b.flag, st);
-            } else {
-                hipLaunchKernelGGL(cholesky_lower, dim3(1), dim3(256), (size_t)RR * sizeof(double), st, b.V, R, b.flag);
-                hipLaunchKernelGGL(solve_rows, dim3((unsigned)ceil_div(dims[k], 32)), dim3(32),
-                                   (size_t)(RR + 32 * (R + 1)) * sizeof(double), st, b.V, b.M, dims[k], R, factors[k], b.flag);
+            double* const dinv = b.L + RR;
+            for (int j0 = 0; j0 < R; j0 += kNB) {
+                const unsigned nt = R - j0 > kNB ? (unsigned)ceil_div(R - j0 - kNB, kNB) : 1u;
+                hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(256), 0, st, b.V, R, j0, b.L, dinv, b.flag);
             }
-            hipLaunchKernelGGL(normalise_columns, dim3(R), dim3(256), 0, st, factors[k], dims[k], R, lambda, b.flag);
-            gram(factors[k], dims[k], R, b.gram_ws, b.G + (int64_t)k * RR, st);
-            return (int)MTTKRP_OK;
+            solve_big(b.L, dinv, R, b.M, factors[k], I, b.flag, st);
+            gram(factors[k], I, R, b.gram_ws, b.V, st);
+            const int64_t want = ceil_div(I * R + RR, 1024);
+            hipLaunchKernelGGL(scale_by_gram, dim3((unsigned)(want < 4096 ? want : 4096)), dim3(256), 0, st, b.V, R, factors[k],
+                               I * (int64_t)R, Gk, lambda, b.flag);
+        }
+        return (int)MTTKRP_OK;
     };
     double fit_prev = 0.0;
     for (int sweep = 0; sweep < max_iters; ++sweep) {
@@ -952,17 +1395,22 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
             }
         }
         // fit terms: b.M still holds the last mode's MTTKRP
-        hipLaunchKernelGGL(inner_product_columns, dim3(R), dim3(256), 0, st, b.M, factors[ndim - 1], lambda,
-                           dims[ndim - 1], R, b.partial + kNormBlocks);
-        hipLaunchKernelGGL(sum_fixed, dim3(1), dim3(256), 0, st, b.partial + kNormBlocks, R, b.scalars + 1);
-        hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(RR, 256)), dim3(256), 0, st, b.G, ndim, RR, -1, b.V);
-        hipLaunchKernelGGL(quadratic_form, dim3(1), dim3(256), 0, st, b.V, lambda, R, b.scalars + 2);
-        double h[3];
-        int flag = 0;
-        if (hipMemcpyAsync(h, b.scalars, 3 * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipMemcpyAsync(&flag, b.flag, sizeof(int), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        if (big) {
+            const int64_t I = dims[ndim - 1];
+            const int64_t per = ceil_div(I, kFitChunks) > 16 ? ceil_div(I, kFitChunks) : 16;
+            const int chunks = (int)ceil_div(I, per);
+            hipLaunchKernelGGL(fit_terms_partial, dim3((unsigned)(chunks + R)), dim3(256), 0, st, b.G, ndim, R, lambda, b.M,
+                               factors[ndim - 1], I, chunks, per, b.gram_ws);
+            hipLaunchKernelGGL(fit_terms_sum, dim3(2), dim3(256), 0, st, b.gram_ws, chunks, R, b.scalars + 1);
+        } else {
+            hipLaunchKernelGGL(fit_terms_small, dim3(1), dim3(256), 0, st, b.G, ndim, R, lambda, b.inner, n_inner, b.scalars + 1);
+        }
+        double h[4];
+        if (hipMemcpyAsync(h, b.scalars, 4 * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return MTTKRP_ERR_DEVICE;
+        int flag = 0;
+        memcpy(&flag, h + 3, sizeof(int));
         if (flag)
             return MTTKRP_ERR_NUMERICAL;   // a Gram Hadamard product was not positive definite
         const double normX = sqrt(h[0]);

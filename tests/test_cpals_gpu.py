@@ -168,3 +168,46 @@ def test_cpals_errors(mt):
     assert e.value.status == mt.MTTKRP_ERR_NUMERICAL
     torch.cuda.synchronize()
     assert torch.equal(Ad[0], before)                           # the failed update left A_0 as it was
+
+
+# The dense steps of an update where their launches change shape: one workgroup or several (1024 rows at
+# R <= 16, 512 at R <= 32; tiles of 128 and 64 rows), ranks at the register tiles' edges (16 / 17, 32 / 33, 48, 64),
+# more tiles than workgroups, above rank 64 full and partial blocks of 32, factors of more than 8192 rows (four
+# wavefronts a workgroup) and ranks above 1024 (the rows no longer in LDS).  Rounding differences between two
+# orders of the sums grow with the condition of V (1e2 to 1e5 here) and over the sweeps: 1e-16 * 1e5 * a few
+# hundred terms stays below 1e-8.
+UPDATE_SHAPES = [((1024, 9, 7), 16, 2), ((1025, 9, 7), 16, 2), ((127, 129, 3), 15, 2), ((512, 20, 11), 17, 2),
+                 ((513, 20, 11), 32, 2), ((65, 64, 63), 33, 2), ((130, 20, 31), 48, 2), ((9000, 30, 10), 64, 2),
+                 ((70, 64, 60), 64, 2), ((8300, 30, 26), 70, 2), ((40, 39, 38), 97, 2), ((24, 23, 22, 21), 1030, 1)]
+
+
+@pytest.mark.parametrize("dims,R,sweeps", UPDATE_SHAPES)
+def test_cpals_update_launch_shapes(mt, dims, R, sweeps):
+    from oracle import cp_als_oracle, mttkrp_oracle
+    mttkrp_oracle.build()
+    X, A0 = problem(dims, R, 60 + R)
+    A_ref, lam_ref, fits_ref = cp_als_oracle.cp_als(inputs.as_ndarray_view(X, dims), [a.numpy() for a in A0], sweeps, 0.0)
+    Ad = [a.clone().cuda() for a in A0]
+    print("cp-als update dims=%s R=%d" % (dims, R), flush=True)
+    lam, fits = mt.mttkrp_cpals(X.cuda(), dims, Ad, sweeps, 0.0)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(fits, fits_ref, rtol=0, atol=1e-8)
+    np.testing.assert_allclose(lam.cpu().numpy(), lam_ref, rtol=1e-7)
+    for m in range(len(dims)):
+        got = Ad[m].cpu().numpy()
+        err = np.linalg.norm(got - A_ref[m]) / np.linalg.norm(A_ref[m])
+        assert err <= 1e-8, (m, err)
+
+
+def test_cpals_norm_of_an_unaligned_tensor(mt):
+    # X that starts 8 bytes off a 16-byte boundary, odd and even length: ||X|| enters every fit
+    from oracle import cp_als_oracle, mttkrp_oracle
+    mttkrp_oracle.build()
+    for dims in ((33, 7, 5), (40, 30, 20)):
+        X, A0 = problem(dims, 3, 90)
+        buf = torch.zeros(X.numel() + 1, dtype=torch.float64, device="cuda")
+        buf[1:] = X.cuda()
+        Ad = [a.clone().cuda() for a in A0]
+        _, _, fits_ref = cp_als_oracle.cp_als(inputs.as_ndarray_view(X, dims), [a.numpy() for a in A0], 2, 0.0)
+        _, fits = mt.mttkrp_cpals(buf[1:], dims, Ad, 2, 0.0)
+        np.testing.assert_allclose(fits, fits_ref, rtol=0, atol=1e-10)
