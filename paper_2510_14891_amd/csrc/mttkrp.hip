@@ -2222,14 +2222,19 @@ struct OwnedWorkspace {
     bool used = false;           // stream is meaningful
     void* ws = nullptr;
     size_t ws_bytes = 0;
-    hipEvent_t done = nullptr;   // recorded after the last kernel that uses ws
+    hipEvent_t done = nullptr;   // recorded after the last kernel that uses ws (see DeviceState::record)
     bool pending = false;        // done has been recorded at least once
+    bool unmarked = false;       // calls have used ws since, with no event behind them
     uint64_t last_use = 0;
 };
 
 struct DeviceState {
     OwnedWorkspace own[kOwnedSlots];
     uint64_t use_counter = 0;
+    // Whether calls record an event behind their last kernel.  A workspace only changes hands when a ninth
+    // stream comes along, and the event costs the GPU about 5 us a call (64^3: 20.5 -> 15.7 us), so none is
+    // recorded until then; the first hand-over waits for the whole device once.
+    bool record = false;
     TimedCall* calls = nullptr;  // kTimingSlots entries once timing has been used
     int64_t n_timed = 0;         // calls recorded since timing was last enabled
     const void* zeros = nullptr; // this device's address of zero_pad
@@ -2252,13 +2257,20 @@ OwnedWorkspace* owned_workspace(DeviceState& ds, hipStream_t st, size_t bytes)
             if (!slot || (!c.used && slot->used) || (c.used == slot->used && c.last_use < slot->last_use))
                 slot = &c;
         }
+        if (slot->used && !ds.record) {
+            if (hipDeviceSynchronize() != hipSuccess)
+                return nullptr;
+            for (int i = 0; i < kOwnedSlots; ++i)
+                ds.own[i].unmarked = false;
+            ds.record = true;
+        }
         if (slot->pending && hipEventSynchronize(slot->done) != hipSuccess)
             return nullptr;
         slot->pending = false;
         slot->used = true;
         slot->stream = st;
     }
-    if (!slot->done && hipEventCreateWithFlags(&slot->done, hipEventDisableTiming) != hipSuccess) {
+    if (ds.record && !slot->done && hipEventCreateWithFlags(&slot->done, hipEventDisableTiming) != hipSuccess) {
         slot->done = nullptr;
         return nullptr;
     }
@@ -2266,7 +2278,10 @@ OwnedWorkspace* owned_workspace(DeviceState& ds, hipStream_t st, size_t bytes)
         if (slot->ws) {
             if (slot->pending && hipEventSynchronize(slot->done) != hipSuccess)
                 return nullptr;
+            if (slot->unmarked && hipStreamSynchronize(st) != hipSuccess)     // the slot's stream is the caller's
+                return nullptr;
             slot->pending = false;
+            slot->unmarked = false;
             (void)hipFree(slot->ws);
             slot->ws = nullptr;
             slot->ws_bytes = 0;
@@ -2424,8 +2439,12 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     }
     // behind the call's last kernel: marks when its owned workspace may change hands or be freed
     auto finish = [&]() {
-        if (owned && hipEventRecord(owned->done, st) == hipSuccess)
+        if (!owned)
+            return;
+        if (ds.record && hipEventRecord(owned->done, st) == hipSuccess)
             owned->pending = true;
+        else
+            owned->unmarked = true;
     };
     const bool timing = g_timing && allow_timing;    // timing creates events on first use
     TimedCall* tc = nullptr;
@@ -2840,6 +2859,7 @@ void mttkrp_release(void)
         }
         ds.calls = nullptr;
         ds.n_timed = 0;
+        ds.record = false;
     }
     (void)hipSetDevice(cur);
 }
