@@ -811,29 +811,41 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
     }
 }
 
-// Zero fill of n_words 32-bit words (grid-stride).
-__global__ void __launch_bounds__(256)
-mttkrp_zero_kernel(uint32_t* __restrict__ dst, int64_t n_words)
-{
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n_words; e += (int64_t)gridDim.x * 256)
-        dst[e] = 0u;
-}
-
-// Product matrix of two fused modes: F(i_a + I_a i_b, j) = A_a(i_a, j) A_b(i_b, j), row-major with
-// leading dimension R.  One thread per entry.
+// What a streaming launch needs beforehand, in one launch (three separate ones cost about 4 us each):
+//   the product matrices of up to two fused pairs of modes, F(i_a + I_a i_b, j) = A_a(i_a, j) A_b(i_b, j),
+//   row-major with leading dimension R, one thread per entry;
+//   zeros in n_words 32-bit words of the partial sums (grid-stride over the remaining blocks).
+template <typename T> struct PrepareArgs {
+    const T* Aa[2];
+    const T* Ab[2];
+    T* F[2];
+    int64_t lda[2], ldb[2];
+    uint32_t Ia[2], n_entries[2], blocks[2];     // n_entries < 2^31: product matrices are at most 32 MiB
+    uint32_t* zero;
+    int64_t n_words;
+    uint32_t zero_blocks;
+    int32_t R;
+};
 template <typename T>
 __global__ void __launch_bounds__(256)
-mttkrp_fuse_kernel(const T* __restrict__ Aa, int64_t lda, int64_t Ia, const T* __restrict__ Ab, int64_t ldb,
-                   int64_t n_entries, int R, T* __restrict__ F)
+mttkrp_prepare_kernel(const PrepareArgs<T> p)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= n_entries)
-        return;
-    const int64_t row = e / R;
-    const int j = (int)(e - row * R);
-    const int64_t ib = row / Ia;
-    const int64_t ia = row - ib * Ia;
-    F[e] = Aa[ia * lda + j] * Ab[ib * ldb + j];
+    uint32_t b = blockIdx.x;
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        if (b < p.blocks[f]) {
+            const uint32_t e = b * 256 + threadIdx.x;
+            if (e < p.n_entries[f]) {
+                const uint32_t row = e / (uint32_t)p.R, j = e - row * (uint32_t)p.R;
+                const uint32_t ib = row / p.Ia[f], ia = row - ib * p.Ia[f];
+                p.F[f][e] = p.Aa[f][ia * p.lda[f] + j] * p.Ab[f][ib * p.ldb[f] + j];
+            }
+            return;
+        }
+        b -= p.blocks[f];
+    }
+    for (int64_t e = (int64_t)b * 256 + threadIdx.x; e < p.n_words; e += (int64_t)p.zero_blocks * 256)
+        p.zero[e] = 0u;
 }
 
 // M(n, j) = sum of the partial sums of all slots, in fp64 and in a fixed order:
@@ -1244,9 +1256,9 @@ mttkrp_rowsum_kernel(const RowSumArgs<T> p)
 // W(c, j) = prod over the column modes of A_m(c_m, j), c decomposed with the lowest
 // mode fastest; row-major with leading dimension R.  One thread per entry.
 template <typename T> struct ColWeightArgs {
-    const T* A[kMaxOuter];
-    int64_t ld[kMaxOuter];
-    int32_t dim[kMaxOuter];
+    const T* A[MTTKRP_MAX_NDIM - 1];
+    int64_t ld[MTTKRP_MAX_NDIM - 1];
+    int32_t dim[MTTKRP_MAX_NDIM - 1];
     int32_t n;                   // column modes (0: W is all ones)
 };
 template <typename T>
@@ -1605,7 +1617,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
     {
         const int64_t cap = tn.fuse_bytes > 0 ? tn.fuse_bytes : (int64_t)8 << 20;
         auto small_enough = [&](int64_t a, int64_t b) {
-            return a > 1 && b > 1 && a * b < ((int64_t)1 << 31) && a * b * (int64_t)R * sbytes <= cap;
+            return a > 1 && b > 1 && a * b < ((int64_t)1 << 31) / R && a * b * (int64_t)R * sbytes <= cap;
         };
         // the column pair of a problem (nd, d, kk): index of its first mode, or -1
         auto column_pair = [&](int nd, const int64_t* d, int kk) {
@@ -1653,7 +1665,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
         // (the rows' product matrix is only read in the epilogue, one row per accumulator entry:
         // it may be four times as large as one that is read in the streaming loop)
         auto small_rows = [&](int64_t a, int64_t b) {
-            return a > 1 && b > 1 && a * b < ((int64_t)1 << 31) && a * b * (int64_t)R * sbytes <= 4 * cap;
+            return a > 1 && b > 1 && a * b < ((int64_t)1 << 31) / R && a * b * (int64_t)R * sbytes <= 4 * cap;
         };
         // What the choice of row blocks below makes of a row extent: blocks per wavefront, and the
         // share of the tiles' rows that are rows of the tensor.
@@ -2060,7 +2072,7 @@ void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, P
     out.n_slots = lp.n_rsplit;
     out.steps_per_item = lp.rows_per_split / 16;
     out.part_bytes = lp.ws_bytes;
-    out.fused_bytes = ndim == 2 ? 0 : (ndim == 3 ? kbytes : 2 * kbytes);   // K, and a second buffer for the chain of products
+    out.fused_bytes = ndim == 2 ? 0 : kbytes;   // K
     out.ws_bytes = (out.part_bytes + 255) / 256 * 256 + out.fused_bytes;
     pl = out;
 }
@@ -2465,25 +2477,27 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     }
 
     if (pl.lead_route) {
-        // K = Khatri-Rao product of the factors of modes 0 .. d-2 (mode 0 fastest), by a chain of
-        // pairwise products that alternates between two buffers behind the partial sums
-        char* const kbase = (char*)ws + (pl.part_bytes + 255) / 256 * 256;
-        const size_t kbytes = ((size_t)pl.lead_P * (size_t)R * sizeof(T) + 255) / 256 * 256;
+        // K = Khatri-Rao product of the factors of modes 0 .. d-2 (mode 0 fastest), behind the partial sums
         const T* K = factors[0];
         int64_t ldK = ld[0];
-        int64_t rows = pl.dims[0];
         (void)hipGetLastError();
         if (timing)
             (void)hipEventRecord(tc->ev[0], st);
-        for (int m = 1; m < ndim - 1; ++m) {
-            // the last product lands in the first buffer
-            T* const dst = (T*)(kbase + (((ndim - 2 - m) & 1) ? kbytes : 0));
-            const int64_t n_entries = rows * pl.dims[m] * (int64_t)R;
-            hipLaunchKernelGGL((mttkrp_fuse_kernel<T>), dim3((unsigned)ceil_div(n_entries, 256)), dim3(256), 0, st,
-                               K, ldK, rows, factors[m], ld[m], n_entries, R, dst);
+        if (ndim > 2) {
+            ColWeightArgs<T> cw;
+            memset(&cw, 0, sizeof(cw));
+            for (int m = 0; m < ndim - 1; ++m) {
+                cw.A[m] = factors[m];
+                cw.ld[m] = ld[m];
+                cw.dim[m] = (int32_t)pl.dims[m];
+            }
+            cw.n = ndim - 1;
+            T* const dst = (T*)((char*)ws + (pl.part_bytes + 255) / 256 * 256);
+            const int64_t n_entries = pl.lead_P * (int64_t)R;
+            hipLaunchKernelGGL((mttkrp_colweights_kernel<T>), dim3((unsigned)ceil_div(n_entries, 256)), dim3(256), 0, st,
+                               cw, n_entries, R, dst);
             K = dst;
             ldK = R;
-            rows *= pl.dims[m];
         }
         const int lrc = launch_leading<T>(pl.lead, pl.lead_P, pl.lead_Q, X, K, ldK, R, M, ldM, ws, lambda, beta, st);
         if (timing) {
@@ -2628,17 +2642,34 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     (void)hipGetLastError();
     if (timing)
         (void)hipEventRecord(tc->ev[0], st);
-    for (int f = 0; f < pl.n_fuse; ++f) {
-        const Plan::Fusion& fu = pl.fus[f];
-        const int64_t n_entries = fu.Ia * fu.Ib * (int64_t)R;
-        hipLaunchKernelGGL((mttkrp_fuse_kernel<T>), dim3((unsigned)ceil_div(n_entries, 256)), dim3(256), 0, st,
-                           factors[fu.a], ld[fu.a], fu.Ia, factors[fu.a + 1], ld[fu.a + 1],
-                           n_entries, R, (T*)(fused + fu.offset));
-    }
-    if (pl.seg > 0 && !pl.seg_first) {        // not every slot of every output row is written: the others must read as zero
-        const int64_t n_words = (int64_t)(pl.part_bytes / 4);
-        const int64_t zblocks = ceil_div(n_words, 4 * 256) < 4096 ? ceil_div(n_words, 4 * 256) : 4096;
-        hipLaunchKernelGGL(mttkrp_zero_kernel, dim3((unsigned)zblocks), dim3(256), 0, st, (uint32_t*)ws, n_words);
+    // not every slot of every output row is written with paired rows in the second mode: the others must read as zero
+    const bool clear_slots = pl.seg > 0 && !pl.seg_first;
+    if (pl.n_fuse > 0 || clear_slots) {
+        PrepareArgs<T> pa;
+        memset(&pa, 0, sizeof(pa));
+        pa.R = R;
+        int64_t pblocks = 0;
+        for (int f = 0; f < pl.n_fuse; ++f) {
+            const Plan::Fusion& fu = pl.fus[f];
+            const int64_t n_entries = fu.Ia * fu.Ib * (int64_t)R;
+            pa.Aa[f] = factors[fu.a];
+            pa.Ab[f] = factors[fu.a + 1];
+            pa.lda[f] = ld[fu.a];
+            pa.ldb[f] = ld[fu.a + 1];
+            pa.F[f] = (T*)(fused + fu.offset);
+            pa.Ia[f] = (uint32_t)fu.Ia;
+            pa.n_entries[f] = (uint32_t)n_entries;
+            pa.blocks[f] = (uint32_t)ceil_div(n_entries, 256);
+            pblocks += pa.blocks[f];
+        }
+        if (clear_slots) {
+            pa.zero = (uint32_t*)ws;
+            pa.n_words = (int64_t)(pl.part_bytes / 4);
+            const int64_t zblocks = ceil_div(pa.n_words, 4 * 256);
+            pa.zero_blocks = (uint32_t)(zblocks < 4096 ? zblocks : 4096);
+            pblocks += pa.zero_blocks;
+        }
+        hipLaunchKernelGGL((mttkrp_prepare_kernel<T>), dim3((unsigned)pblocks), dim3(256), 0, st, pa);
     }
     launch_stream_rb<T>(pl.RB, pl.JB, a, dim3((unsigned)blocks), st, pl.wave_cap, pl.nt_off, pl.deep);
     if (timing) {
