@@ -297,6 +297,11 @@ int mttkrp_timing_last(float* stream_ms, float* combine_ms);
  *                   0 = chosen by the planner
  *   "deep"          1 = always the kernel build with the software-pipelined run,
  *                   2 = always the build with batches only, 0 = by item length
+ *   "small_route"   1 = the kernel for small tensors wherever its 32-bit offsets allow (a workgroup per
+ *                   output row, or per 16 rows of the first mode: one launch), 2 = never, 0 = chosen by
+ *                   estimated times, and never while another key is set
+ *   "small_groups"  that route only: workgroups that share an output row's columns (1..1024; from 2 on
+ *                   their sums are added by a second launch), 0 = chosen by the planner
  *   "linear"        1 = the column space is split into balanced ranges of steps that may
  *                   begin and end inside a sweep, 2 = only whole sweeps and equal pieces
  *                   of sweeps, 0 = chosen by the planner (ranges for the first mode when
@@ -308,7 +313,9 @@ int mttkrp_tune_set(const char* key, int64_t value);
 /*
  * Writes a one-line description of the decomposition the library would use
  * (row blocks, column blocks, work items, steps per item, partial slots,
- * workspace bytes) into buf (always NUL-terminated when buflen > 0).
+ * workspace bytes) into buf (always NUL-terminated when buflen > 0).  For a small tensor
+ * that runs on the kernel for small tensors the line begins with "small_route=1" and that
+ * kernel's figures; the decomposition after the bar is what "small_route" = 2 would run.
  */
 int mttkrp_plan_describe(int ndim, const int64_t* dims, int R, int k,
                          int dtype_bytes, char* buf, size_t buflen);

@@ -10,6 +10,8 @@ SRC = os.path.join(HERE, "csrc", "mttkrp.hip")
 SRC_ABLATION = os.path.join(HERE, "csrc", "ablation.hip")
 SRC_CPALS = os.path.join(HERE, "csrc", "cpals.hip")
 SRC_CALIBRATE = os.path.join(HERE, "csrc", "calibrate.hip")
+SRC_SMALL = os.path.join(HERE, "csrc", "small.hip")
+HEADER_SMALL = os.path.join(HERE, "csrc", "mttkrp_small.h")
 HEADER = os.path.join(os.path.dirname(HERE), "include", "mttkrp.h")
 HEADER_ABLATION = os.path.join(os.path.dirname(HERE), "include", "mttkrp_ablation.h")
 LIB = os.path.join(HERE, "libmttkrp_hip.so")
@@ -28,6 +30,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
             and os.path.getmtime(LIB) >= max(os.path.getmtime(SRC), os.path.getmtime(HEADER),
                                              os.path.getmtime(SRC_ABLATION), os.path.getmtime(HEADER_ABLATION),
                                              os.path.getmtime(SRC_CPALS), os.path.getmtime(SRC_CALIBRATE),
+                                             os.path.getmtime(SRC_SMALL), os.path.getmtime(HEADER_SMALL),
                                              os.path.getmtime(os.path.join(HERE, "csrc", "gen_pipe.py")),
                                              os.path.getmtime(os.path.join(HERE, "csrc", "gen_rows_pipe.py")))):
         return LIB
@@ -35,7 +38,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     for gen in ("gen_pipe.py", "gen_rows_pipe.py"):
         subprocess.run([sys.executable, os.path.join(HERE, "csrc", gen)], check=True, stdout=subprocess.DEVNULL)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB, SRC, SRC_ABLATION, SRC_CPALS, SRC_CALIBRATE]
+    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB, SRC, SRC_ABLATION, SRC_CPALS, SRC_CALIBRATE, SRC_SMALL]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

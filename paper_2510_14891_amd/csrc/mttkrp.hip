@@ -32,6 +32,7 @@
 #include <new>
 
 #include "../../include/mttkrp.h"
+#include "mttkrp_small.h"
 
 // Scratch memory of mttkrp_dense_f64_noalloc, the entry point for callers that cannot allocate:
 // a fixed array in the library's code object, so each GPU the library runs on holds one copy at
@@ -1302,6 +1303,8 @@ struct Tuning {
     int64_t pair_rows = 0;
     int64_t fuse_rows = 0;
     int64_t lead_last = 0;
+    int64_t small_route = 0;
+    int64_t small_groups = 0;
 };
 Tuning g_tune;
 std::mutex g_mutex;
@@ -1357,6 +1360,11 @@ struct Plan {
     int64_t seg = 0, out_rows = 0;
     bool seg_first = false;    // the output mode is mode 0 (else mode 1)
     bool seg_store = false;    // ... and the weighted tiles are stored whole (I_0 > 32)
+    // The call runs on the small kernel instead (small.hip); everything else here still describes the general
+    // decomposition, whose workspace a caller provides in any case.
+    bool small = false;
+    SmallPlan sp;
+    size_t small_bytes = 0;    // its partial sums
     int seg_nblk = 0;
 };
 
@@ -2090,7 +2098,7 @@ double plan_cost(const Plan& pl)
            (1.0 + 2.0 * (double)pl.part_bytes / ((double)pl.N * pl.sbytes));
 }
 
-int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 {
     int rc = make_plan_for(ndim, dims, R, k, sbytes, pl, false);
     if (rc == MTTKRP_OK && pl.seg_store) {
@@ -2118,6 +2126,101 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
     Plan alt;
     if (make_plan_for(ndim, dims, R, k, sbytes, alt, true) == MTTKRP_OK && alt.contract_rows && alt.ws_bytes < pl.ws_bytes)
         pl = alt;
+    return MTTKRP_OK;
+}
+
+// One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times in us, fitted
+// to 2600 calls (fp64 and fp32, two to eight modes, 2^7 to 2^27 values, R = 1 to 147; median error 14 and 9 %).
+// A launch costs 2.3 to 3.6 us, whatever it does, on top of the first.  The small kernel is bound by the
+// instructions of the few compute units it runs on (MFMAs and the address arithmetic of its columns), the general
+// one by its launches and the length of its items.  Taken when its estimate is below 0.8 of the other: over those
+// calls 1.20 times faster in the mean (1.5 times below 2^13 values, 1.2 at 2^18, 1.05 at 2^21, none from 2^24 on), 2 %
+// of the calls more than 10 % slower.
+double small_cost(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
+{
+    const double steps = (double)sp.n_tiles * sp.n_ranges * (sp.cols_per_range / 4);       // of one workgroup
+    const double cycles = sbytes == 8 ? 64.0 : 32.0;
+    const double mfma = steps * sp.RB * sp.JB * cycles / 4.0 / 2200.0;
+    const double instr = steps * (12 + 6 * n_modes + 3 * sp.RB + 3 * sp.JB * n_modes) / 2200.0;
+    const double sweeps = (double)ceil_div((int64_t)sp.n_tiles * sp.n_ranges, sp.waves);
+    const double groups = (double)sp.blocks * sp.n_jchunk * sp.n_groups;
+    const double resident = 256.0 * (16 / sp.waves);
+    const double rounds = groups > resident ? groups / resident : 1.0;
+    return 3.6 + rounds * (1.2 * mfma + 1.38 * instr + 2.3 * sweeps) + (sp.n_groups > 1 ? 3.55 : 0.0) +
+           0.027e-6 * (double)N * sbytes;
+}
+
+double general_cost(const Plan& pl)
+{
+    const bool paired_second = pl.seg > 0 && !pl.seg_first;
+    const bool prepare = pl.fused_bytes > 0 || paired_second || pl.contract_rows;
+    const bool combine = pl.n_slots > 1 || pl.seg > 0;
+    const bool rows = pl.contract_rows || pl.lead_route;      // (their tiles count as one row block of the fit)
+    const double cycles = (pl.sbytes == 8 ? 64.0 : 32.0) * (rows ? 1 : pl.RB) * (pl.lead_route ? pl.lead.JB : pl.JB);
+    const double items = (double)pl.n_items, rounds = items > 3072.0 ? items / 3072.0 : 1.0;
+    const double steps = (double)pl.steps_per_item * rounds;
+    return 5.5 + (prepare ? 2.6 : 0.0) + (combine ? 2.3 : 0.0) + (pl.seg > 0 ? 1.8 : 0.0) + 0.0455 * steps +
+           1.96 * cycles * steps / 2200.0 + 0.107e-6 * (double)pl.N * pl.sbytes + 1.1e-3 * items;
+}
+
+int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+{
+    const int rc = make_general_plan(ndim, dims, R, k, sbytes, pl);
+    if (rc != MTTKRP_OK)
+        return rc;
+    Tuning tn;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        tn = g_tune;
+    }
+    if (tn.small_route == 2)
+        return rc;
+    if (tn.small_route == 0) {
+        // the other keys choose among the decompositions of the general plans
+        const Tuning none;
+        if (memcmp(&tn, &none, sizeof(tn)) != 0)
+            return rc;
+    }
+    // 32-bit offsets in the kernel, and a bounded grid
+    int64_t N = 1, C = 1;
+    for (int m = 0; m < ndim; ++m) {
+        N *= dims[m];
+        if (m > 0 && m != k)
+            C *= dims[m];
+        if (dims[m] >= ((int64_t)1 << 24) || dims[m] * (int64_t)R >= ((int64_t)1 << 30))
+            return rc;
+    }
+    if (N * sbytes >= ((int64_t)1 << 31) || R > 4096)
+        return rc;
+    const int n_modes = k == 0 ? ndim - 1 : ndim - 2;
+    SmallPlan best;
+    double best_cost = tn.small_route == 1 ? 1e300 : 0.8 * general_cost(pl);
+    bool take = false;
+    for (int groups = 1; groups <= 64; groups = groups == 1 ? 4 : 2 * groups) {
+        if (tn.small_groups > 0)
+            groups = (int)tn.small_groups;
+        if (groups > 1 && C < 16 * (int64_t)groups && tn.small_groups == 0)
+            break;
+        const SmallPlan sp = mttkrp_small_plan(ndim, dims, R, k, sbytes, groups);
+        // fp32: accumulation chains as short as the streaming kernel's
+        if (sbytes == 8 || sp.cols_per_range <= 4096) {
+            const double cost = small_cost(sp, sbytes, n_modes, N);
+            if (cost < best_cost) {
+                best = sp;
+                best_cost = cost;
+                take = true;
+            }
+        }
+        if (tn.small_groups > 0)
+            break;
+    }
+    if (!take)
+        return rc;
+    pl.small = true;
+    pl.sp = best;
+    pl.small_bytes = best.n_groups > 1 ? (size_t)best.n_groups * (size_t)dims[k] * (size_t)R * (size_t)sbytes : 0;
+    if (pl.ws_bytes < (pl.small_bytes + 255) / 256 * 256)
+        pl.ws_bytes = (pl.small_bytes + 255) / 256 * 256;
     return MTTKRP_OK;
 }
 
@@ -2398,7 +2501,8 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     const bool scaled = lambda != nullptr || beta != 0.0;
     if (scaled && pl.part_bytes == 0) {
         pl.part_bytes = (size_t)dims[k] * (size_t)R * sizeof(T);
-        pl.ws_bytes = (pl.part_bytes + 255) / 256 * 256 + pl.fused_bytes;
+        const size_t bytes = (pl.part_bytes + 255) / 256 * 256 + pl.fused_bytes;
+        pl.ws_bytes = pl.ws_bytes > bytes ? pl.ws_bytes : bytes;
     }
     for (int m = 0; m < ndim; ++m)
         if (m != k && !factors[m])
@@ -2411,6 +2515,7 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
         fac[m] = factors[pl.orig[m]];
         fld[m] = ld[pl.orig[m]];
     }
+    const int k_call = k;
     k = pl.k;
 
     int dev = 0;
@@ -2434,10 +2539,11 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     OwnedWorkspace* owned = nullptr;
     if (pl.ws_bytes > 0) {
         if (own_ws) {
-            owned = owned_workspace(ds, st, pl.ws_bytes);
-            if (!owned)
+            const size_t bytes = pl.small ? pl.small_bytes : pl.ws_bytes;
+            owned = bytes > 0 ? owned_workspace(ds, st, bytes) : nullptr;
+            if (bytes > 0 && !owned)
                 return MTTKRP_ERR_DEVICE;
-            ws = (T*)owned->ws;
+            ws = owned ? (T*)owned->ws : nullptr;
         } else {
             if (!workspace || workspace_bytes < pl.ws_bytes || ((uintptr_t)workspace & 255u))
                 return MTTKRP_ERR_WORKSPACE;
@@ -2476,6 +2582,71 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
         tc = &ds.calls[ds.n_timed % kTimingSlots];
     }
 
+    if (pl.small) {
+        k = k_call;
+        SmallArgs<T> sa;
+        memset(&sa, 0, sizeof(sa));
+        sa.X = X;
+        sa.A0 = k == 0 ? nullptr : factors[0];
+        sa.out = pl.small_bytes > 0 ? ws : M;
+        sa.lambda = lambda;
+        sa.beta = beta;
+        int64_t C = 1, stride = 1;
+        for (int m = 0; m < ndim; ++m) {
+            if (m == k)
+                sa.sx_batch = k == 0 ? 0 : (int32_t)stride;
+            else if (m > 0) {
+                sa.A[sa.n] = factors[m];
+                sa.dim[sa.n] = (int32_t)dims[m];
+                sa.ld[sa.n] = (int32_t)ld[m];
+                sa.sx[sa.n] = (int32_t)stride;
+                if (dims[m] > 1)
+                    mttkrp_small_divisor((uint32_t)dims[m], sa.magic[sa.n], sa.shift[sa.n]);
+                sa.n += 1;
+                C *= dims[m];
+            }
+            stride *= dims[m];
+        }
+        sa.I0 = (int32_t)dims[0];
+        sa.R = R;
+        sa.C = (int32_t)C;
+        sa.ld0 = k == 0 ? 0 : (int32_t)ld[0];
+        sa.ld_out = (int32_t)ldM;
+        sa.group_stride = dims[k] * (int64_t)R;
+        sa.row_stride = R;
+        sa.n_tiles = pl.sp.n_tiles;
+        sa.n_ranges = pl.sp.n_ranges;
+        sa.cols_per_range = pl.sp.cols_per_range;
+        sa.cols_per_group = pl.sp.cols_per_group;
+        (void)hipGetLastError();
+        if (timing)
+            (void)hipEventRecord(tc->ev[0], st);
+        const int src = mttkrp_small_launch<T>(pl.sp, sa, k == 0, st);
+        if (timing) {
+            (void)hipEventRecord(tc->ev[1], st);
+            tc->combine = false;
+        }
+        if (src != MTTKRP_OK) {
+            finish();
+            return src;
+        }
+        if (pl.small_bytes > 0) {
+            launch_combine<T>(ws, M, dims[k] * (int64_t)R, R, pl.sp.n_groups, (int64_t)R, dims[k] * (int64_t)R, lambda,
+                              beta, ldM, st);
+            if (timing) {
+                (void)hipEventRecord(tc->ev[2], st);
+                tc->combine = true;
+            }
+            if (hipGetLastError() != hipSuccess) {
+                finish();
+                return MTTKRP_ERR_DEVICE;
+            }
+        }
+        if (timing)
+            ds.n_timed += 1;
+        finish();
+        return MTTKRP_OK;
+    }
     if (pl.lead_route) {
         // K = Khatri-Rao product of the factors of modes 0 .. d-2 (mode 0 fastest), behind the partial sums
         const T* K = factors[0];
@@ -2783,7 +2954,8 @@ size_t mttkrp_dense_ex_workspace_bytes(int ndim, const int64_t* dims, int R, int
     if (make_plan(ndim, dims, R, k, dtype_bytes, pl) != MTTKRP_OK)
         return (size_t)-1;
     const size_t part = pl.part_bytes > 0 ? pl.part_bytes : (size_t)pl.dims[pl.k] * (size_t)R * (size_t)dtype_bytes;
-    return (part + 255) / 256 * 256 + pl.fused_bytes;
+    const size_t bytes = (part + 255) / 256 * 256 + pl.fused_bytes;
+    return bytes > pl.ws_bytes ? bytes : pl.ws_bytes;
 }
 
 int mttkrp_dense_f64_ex(int ndim, const int64_t* dims, const double* X,
@@ -2967,6 +3139,12 @@ int mttkrp_tune_set(const char* key, int64_t value)
     } else if (!strcmp(key, "waves_per_simd")) {
         if (value > 8) return MTTKRP_ERR_INVALID_ARG;
         g_tune.waves_per_simd = value;
+    } else if (!strcmp(key, "small_route")) {
+        if (value > 2) return MTTKRP_ERR_INVALID_ARG;
+        g_tune.small_route = value;
+    } else if (!strcmp(key, "small_groups")) {
+        if (value > 1024) return MTTKRP_ERR_INVALID_ARG;
+        g_tune.small_groups = value;
     } else if (!strcmp(key, "lead_last")) {
         if (value > 2) return MTTKRP_ERR_INVALID_ARG;
         g_tune.lead_last = value;
@@ -3015,6 +3193,15 @@ int mttkrp_plan_describe(int ndim, const int64_t* dims, int R, int k, int dtype_
     int rc = make_plan(ndim, dims, R, k, dtype_bytes, pl);
     if (rc != MTTKRP_OK)
         return rc;
+    // small tensors: the line of the general decomposition, then what runs instead of it
+    if (pl.small) {
+        const int used = snprintf(buf, buflen, "small_route=1 small_rows=%d small_groups=%d small_waves=%d small_steps=%d | ",
+                                  16 * pl.sp.RB, pl.sp.n_groups, pl.sp.waves, pl.sp.cols_per_range / 4);
+        if (used < 0 || (size_t)used >= buflen)
+            return MTTKRP_OK;
+        buf += used;
+        buflen -= (size_t)used;
+    }
     if (pl.lead_route) {
         snprintf(buf, buflen,
                  "shape=leading P=%lld Q=%lld cols_per_wave=%d col_blocks=%d j_chunks=%d row_splits=%d "
