@@ -12,6 +12,8 @@ SRC_CPALS = os.path.join(HERE, "csrc", "cpals.hip")
 SRC_CALIBRATE = os.path.join(HERE, "csrc", "calibrate.hip")
 SRC_SMALL = os.path.join(HERE, "csrc", "small.hip")
 HEADER_SMALL = os.path.join(HERE, "csrc", "mttkrp_small.h")
+SRC_CONTRACT = os.path.join(HERE, "csrc", "contract.hip")
+HEADER_CONTRACT = os.path.join(HERE, "csrc", "mttkrp_contract.h")
 HEADER = os.path.join(os.path.dirname(HERE), "include", "mttkrp.h")
 HEADER_ABLATION = os.path.join(os.path.dirname(HERE), "include", "mttkrp_ablation.h")
 LIB = os.path.join(HERE, "libmttkrp_hip.so")
@@ -31,6 +33,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
                                              os.path.getmtime(SRC_ABLATION), os.path.getmtime(HEADER_ABLATION),
                                              os.path.getmtime(SRC_CPALS), os.path.getmtime(SRC_CALIBRATE),
                                              os.path.getmtime(SRC_SMALL), os.path.getmtime(HEADER_SMALL),
+                                             os.path.getmtime(SRC_CONTRACT), os.path.getmtime(HEADER_CONTRACT),
                                              os.path.getmtime(os.path.join(HERE, "csrc", "gen_pipe.py")),
                                              os.path.getmtime(os.path.join(HERE, "csrc", "gen_rows_pipe.py")))):
         return LIB
@@ -38,7 +41,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     for gen in ("gen_pipe.py", "gen_rows_pipe.py"):
         subprocess.run([sys.executable, os.path.join(HERE, "csrc", gen)], check=True, stdout=subprocess.DEVNULL)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB, SRC, SRC_ABLATION, SRC_CPALS, SRC_CALIBRATE, SRC_SMALL]
+    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB, SRC, SRC_ABLATION, SRC_CPALS, SRC_CALIBRATE, SRC_SMALL, SRC_CONTRACT]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

@@ -10,6 +10,7 @@
 
 #include "../../include/mttkrp.h"
 #include "../../include/mttkrp_cpals.h"
+#include "mttkrp_contract.h"
 
 namespace {
 
@@ -917,56 +918,6 @@ __global__ void __launch_bounds__(256) khatri_rao_rows(const ModeSet<T> p, int64
     K[e] = v;
 }
 
-// One mode's MTTKRP from a partial contraction.  Tp (P x R, row-major, leading dimension R)
-// holds, for every multi-index i of the modes in `p` (lowest fastest, P entries) and every
-// column j, the sum of Eq. (elem) over the modes that are not in `p`, without the factors of
-// the modes in `p`.  Mode t of the set then gets
-//     M(i_t, j) = sum over the other indices of Tp(i, j) * prod_{m in p, m != t} A_m(i_m, j).
-// A workgroup owns (i_t, a segment of the other indices, TJ columns): thread (tj, to) adds
-// the entries o = to, to + TO, ... of its segment in fp64, the TO subtotals are added in
-// order, and the segment totals go to part[i_t][segment][R] for sum_segments.
-template <typename T, int TJ>
-__global__ void __launch_bounds__(256)
-partial_mode_kernel(const ModeSet<T> p, const T* __restrict__ Tp, int t, int R, int64_t n_others,
-                    int64_t others_per_seg, int n_seg, double* __restrict__ part)
-{
-    constexpr int TO = 256 / TJ;
-    __shared__ double red[TO][TJ + 1];
-    const int tj = threadIdx.x % TJ, to = threadIdx.x / TJ;
-    const int64_t it = blockIdx.x;
-    const int seg = blockIdx.y;
-    const int j = blockIdx.z * TJ + tj;
-    const int jj = j < R ? j : R - 1;
-    const int64_t o_begin = (int64_t)seg * others_per_seg;
-    const int64_t o_end = o_begin + others_per_seg < n_others ? o_begin + others_per_seg : n_others;
-    double acc = 0.0;
-    for (int64_t o = o_begin + to; o < o_end; o += TO) {
-        int64_t rem = o, row = 0, stride = 1;
-        double w = 1.0;
-        for (int m = 0; m < p.n; ++m) {
-            if (m == t) {
-                row += it * stride;
-            } else {
-                const int64_t q = rem / p.dim[m];
-                const int64_t im = rem - q * p.dim[m];
-                rem = q;
-                row += im * stride;
-                w *= (double)p.A[m][im * p.ld[m] + jj];
-            }
-            stride *= p.dim[m];
-        }
-        acc += (double)Tp[row * R + jj] * w;
-    }
-    red[to][tj] = acc;
-    __syncthreads();
-    if (to == 0 && j < R) {
-        double v = 0.0;
-        for (int q = 0; q < TO; ++q)
-            v += red[q][tj];
-        part[(it * n_seg + seg) * R + j] = v;
-    }
-}
-
 // M(i, j) = sum over the segments, in order.  One thread per entry.
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -1110,8 +1061,17 @@ template <typename T>
 int mode_from_partial(const T* Tp, int n, const int64_t* dims, const T* const* factors, int t, int R, T* M,
                       double* part, hipStream_t st)
 {
-    ModeSet<T> ms;
+    // Tp (P x R, row-major, leading dimension R) holds, for every multi-index of the set's modes (lowest fastest), the sum
+    // of Eq. (elem) over the other modes; mode t gets the sum over its own set's other indices, weighted with their factors
+    ModeSumArgs<T, double> ms;
+    memset(&ms, 0, sizeof(ms));
+    ms.S = Tp;
+    ms.part = part;
     ms.n = n;
+    ms.t = t;
+    ms.R = R;
+    ms.ld_part = R;
+    ms.n_split = 1;
     int64_t P = 1;
     for (int m = 0; m < n; ++m) {
         ms.A[m] = m == t ? nullptr : factors[m];
@@ -1121,22 +1081,13 @@ int mode_from_partial(const T* Tp, int n, const int64_t* dims, const T* const* f
     }
     const int64_t n_others = P / dims[t];
     const int n_seg = segments(dims[t], n_others);
-    const int64_t per_seg = ceil_div(n_others, n_seg);
-    if (dims[t] >= ((int64_t)1 << 31) || n_seg > 65535)
+    if (dims[t] >= ((int64_t)1 << 31) || P >= ((int64_t)1 << 31) || n_seg > 65535 || ceil_div(R, 32) > 65535)
         return MTTKRP_ERR_UNSUPPORTED;
-    if (R >= 32) {
-        const int64_t jt = ceil_div(R, 32);
-        if (jt > 65535)
-            return MTTKRP_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL((partial_mode_kernel<T, 32>), dim3((unsigned)dims[t], (unsigned)n_seg, (unsigned)jt), dim3(256), 0, st,
-                           ms, Tp, t, R, n_others, per_seg, n_seg, part);
-    } else if (R > 8) {
-        hipLaunchKernelGGL((partial_mode_kernel<T, 16>), dim3((unsigned)dims[t], (unsigned)n_seg, (unsigned)ceil_div(R, 16)), dim3(256), 0, st,
-                           ms, Tp, t, R, n_others, per_seg, n_seg, part);
-    } else {
-        hipLaunchKernelGGL((partial_mode_kernel<T, 8>), dim3((unsigned)dims[t], (unsigned)n_seg, 1), dim3(256), 0, st,
-                           ms, Tp, t, R, n_others, per_seg, n_seg, part);
-    }
+    ms.n_pairs = (uint32_t)n_others;
+    ms.per_seg = (uint32_t)ceil_div(n_others, n_seg);
+    const int rc = mttkrp_modesum_launch<T, double>(ms, dims[t], n_seg, st);
+    if (rc != MTTKRP_OK)
+        return rc;
     const int64_t n_entries = dims[t] * (int64_t)R;
     hipLaunchKernelGGL((sum_segments<T>), dim3((unsigned)ceil_div(n_entries, 256)), dim3(256), 0, st,
                        part, n_entries, R, n_seg, M, (int64_t)R);

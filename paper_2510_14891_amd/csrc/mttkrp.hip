@@ -32,6 +32,7 @@
 #include <new>
 
 #include "../../include/mttkrp.h"
+#include "mttkrp_contract.h"
 #include "mttkrp_small.h"
 
 // Scratch memory of mttkrp_dense_f64_noalloc, the entry point for callers that cannot allocate:
@@ -1305,6 +1306,7 @@ struct Tuning {
     int64_t lead_last = 0;
     int64_t small_route = 0;
     int64_t small_groups = 0;
+    int64_t lds_contract = 0;
 };
 Tuning g_tune;
 std::mutex g_mutex;
@@ -1313,6 +1315,8 @@ struct LeadingPlan {
     int JB = 1, n_jchunk = 1, CB = 1, n_cchunk = 1, n_rsplit = 1, rows_per_split = 16;
     int64_t n_items = 0;
     size_t ws_bytes = 0;        // partial sums of the row splits (0: the kernel writes T itself)
+    int plain_rsplit = 1;       // row splits of mttkrp_rowsum_kernel
+    ContractPlan cp;            // ok: the kernel through LDS (contract.hip) runs, with its own row splits (copied above)
 };
 
 struct Plan {
@@ -1345,6 +1349,9 @@ struct Plan {
     bool contract_rows = false;
     int CB = 1, n_cchunk = 1, n_rsplit = 1, rows_per_split = 16;
     int64_t C = 1, C_lo = 1;
+    // ... or, for k != 0 as well, S(q, j) for every combination q of the modes above 0 (contract.hip), then a weighted sum
+    ContractPlan cp;
+    int cp_segs = 1;           // workgroups per output row of that sum
     bool xcd_remap = true;
     int group = 4;             // first mode: wavefronts per partial tile
     int wave_cap = 0;          // > 0: resident wavefronts per SIMD are capped (by reserving LDS)
@@ -1412,7 +1419,17 @@ int plan_leading(int64_t P, int64_t Q, int R, int sbytes, LeadingPlan& pl)
     if (pl.n_items >= ((int64_t)1 << 31) - 64 || n_cchunk >= ((int64_t)1 << 31) || n_rsplit >= (1 << 20))
         return MTTKRP_ERR_UNSUPPORTED;
     pl.n_cchunk = (int)n_cchunk;
-    pl.n_rsplit = (int)n_rsplit;
+    pl.n_rsplit = pl.plain_rsplit = (int)n_rsplit;
+    // The kernel through LDS wherever it takes the shape (its tiles are not the ones the two keys choose among)
+    if (tn.rows_col_blocks == 0 && tn.max_col_blocks == 0 && tn.lds_contract != 2)
+        pl.cp = mttkrp_contract_plan(P, Q, R, sbytes, n_rsplit, tn.target_items, 16 * tn.max_steps);
+    if (pl.cp.ok) {
+        pl.n_rsplit = pl.cp.n_rsplit;
+        pl.rows_per_split = (int)pl.cp.rows_per_split;
+        pl.n_items = pl.cp.n_items * pl.cp.CW;
+        pl.ws_bytes = pl.n_rsplit > 1 ? (size_t)Q * (size_t)pl.n_rsplit * (size_t)R * (size_t)sbytes : 0;
+        return MTTKRP_OK;
+    }
     pl.ws_bytes = n_rsplit > 1 ? (size_t)Q * (size_t)n_rsplit * (size_t)R * (size_t)sbytes : 0;
     return MTTKRP_OK;
 }
@@ -1619,6 +1636,39 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
             pl.fused_bytes = ((size_t)C * (size_t)R * (size_t)sbytes + 255) / 256 * 256;     // W
             pl.ws_bytes = (pl.part_bytes + 255) / 256 * 256 + pl.fused_bytes;
             pl.xcd_remap = false;
+            // All column indices at once, whatever mode they belong to: no tile is padded at the end of a batch (20 column
+            // entries in tiles of 32: 10^6 x 20 x 20, fp32, R = 32 0.50 -> 0.40 ms), and the kernel through LDS can run.
+            // Its intermediate is written and read once: taken while that stays below 2 % of the tensor's bytes.
+            const Tuning none;
+            Tuning rest = tn;
+            rest.small_route = rest.small_groups = rest.lds_contract = 0;
+            const int64_t Q = pl.N / dims[0];
+            if (tn.lds_contract != 2 && memcmp(&rest, &none, sizeof(rest)) == 0 && dims[0] < ((int64_t)1 << 31) && Q < ((int64_t)1 << 31) - 256) {
+                // (fp32: accumulation chains no longer than the other kernel's)
+                const ContractPlan cp = mttkrp_contract_plan(dims[0], Q, R, sbytes, 4096, 0, sbytes == 4 ? pl.rows_per_split : 0);
+                const double s_bytes = (double)Q * cp.n_rsplit * R * sbytes;
+                if (cp.ok && s_bytes <= 0.02 * (double)pl.N * sbytes && C * (int64_t)cp.n_rsplit < ((int64_t)1 << 31)) {
+                    pl.cp = cp;
+                    const int64_t pairs = C * cp.n_rsplit;
+                    int64_t segs = ceil_div(2048, dims[k] * ceil_div(R, 32));
+                    if (segs > ceil_div(pairs, 64))
+                        segs = ceil_div(pairs, 64);
+                    pl.cp_segs = (int)(segs < 1 ? 1 : segs);
+                    pl.n_rsplit = cp.n_rsplit;
+                    pl.n_splits = cp.n_rsplit;
+                    pl.n_items = cp.n_items * cp.CW;
+                    pl.rows_per_split = (int)(cp.rows_per_split < ((int64_t)1 << 30) ? cp.rows_per_split : (int64_t)1 << 30);
+                    pl.steps_per_item = cp.rows_per_split / 16;
+                    pl.CB = 1;
+                    pl.JB = cp.JB;
+                    pl.n_jchunk = 1;
+                    pl.n_cchunk = (int)cp.n_ctile;
+                    pl.n_slots = pl.cp_segs;
+                    pl.part_bytes = pl.cp_segs > 1 ? (size_t)dims[k] * (size_t)pl.cp_segs * (size_t)R * (size_t)sbytes : 0;
+                    pl.fused_bytes = ((size_t)s_bytes + 255) / 256 * 256;       // S
+                    pl.ws_bytes = (pl.part_bytes + 255) / 256 * 256 + pl.fused_bytes;
+                }
+            }
             return MTTKRP_OK;
         }
     }
@@ -2059,7 +2109,7 @@ void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, P
         return;
     // few output rows leave few work items, or need row splits with partial sums: not then
     // (16 x 16 x 16 x 50000 at R = 8 with six row splits: 0.34 ms against 0.30 ms on the streaming kernel)
-    if (tn.lead_last != 1 && (Q < 256 || lp.n_rsplit > 1))
+    if (tn.lead_last != 1 && (Q < 256 || lp.plain_rsplit > 1))
         return;
     const size_t kbytes = ((size_t)P * (size_t)R * (size_t)sbytes + 255) / 256 * 256;
     Plan out;
@@ -2424,6 +2474,30 @@ int launch_leading(const LeadingPlan& pl, int64_t P, int64_t Q, const T* X, cons
         return MTTKRP_ERR_UNSUPPORTED;
     const bool scaled = lambda != nullptr || beta != 0.0;
     const bool via_ws = pl.ws_bytes > 0 || scaled;
+    if (pl.cp.ok) {
+        ContractArgs<T> ca;
+        memset(&ca, 0, sizeof(ca));
+        ca.X = X;
+        ca.K = K;
+        ca.out = via_ws ? (T*)workspace : out;
+        ca.P = P;
+        ca.Q = Q;
+        ca.ldK = ldK;
+        ca.ld_out = via_ws ? R : ld_out;
+        ca.rows_per_split = pl.cp.rows_per_split;
+        ca.n_items = pl.cp.n_items;
+        ca.R = R;
+        ca.n_rsplit = pl.cp.n_rsplit;
+        ca.n_ctile = (int32_t)pl.cp.n_ctile;
+        (void)hipGetLastError();
+        const int rc = mttkrp_contract_launch<T>(pl.cp, ca, st);
+        if (rc != MTTKRP_OK)
+            return rc;
+        if (via_ws)
+            launch_combine<T>((T*)workspace, out, Q * (int64_t)R, R, pl.n_rsplit, pl.n_rsplit * (int64_t)R,
+                              (int64_t)R, lambda, beta, ld_out, st);
+        return hipGetLastError() == hipSuccess ? MTTKRP_OK : MTTKRP_ERR_DEVICE;
+    }
     RowSumArgs<T> ra;
     memset(&ra, 0, sizeof(ra));
     ra.X = X;
@@ -2679,6 +2753,68 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
         }
         finish();
         return lrc;
+    }
+    if (pl.contract_rows && pl.cp.ok) {
+        T* const S = (T*)((char*)ws + (pl.part_bytes + 255) / 256 * 256);
+        ContractArgs<T> ca;
+        memset(&ca, 0, sizeof(ca));
+        ca.X = X;
+        ca.K = factors[0];
+        ca.out = S;
+        ca.P = pl.dims[0];
+        ca.Q = pl.N / pl.dims[0];
+        ca.ldK = ld[0];
+        ca.ld_out = R;
+        ca.rows_per_split = pl.cp.rows_per_split;
+        ca.n_items = pl.cp.n_items;
+        ca.R = R;
+        ca.n_rsplit = pl.cp.n_rsplit;
+        ca.n_ctile = (int32_t)pl.cp.n_ctile;
+        ModeSumArgs<T, T> ms;
+        memset(&ms, 0, sizeof(ms));
+        ms.S = S;
+        ms.part = pl.part_bytes > 0 ? ws : M;
+        ms.ld_part = pl.part_bytes > 0 ? R : ldM;
+        for (int m = 1; m < pl.ndim; ++m) {
+            ms.A[m - 1] = m == k ? nullptr : factors[m];
+            ms.ld[m - 1] = m == k ? 0 : ld[m];
+            ms.dim[m - 1] = (int32_t)pl.dims[m];
+        }
+        ms.n = pl.ndim - 1;
+        ms.t = k - 1;
+        ms.R = R;
+        ms.n_split = (uint32_t)pl.cp.n_rsplit;
+        ms.n_pairs = (uint32_t)(pl.C * pl.cp.n_rsplit);
+        ms.per_seg = (uint32_t)ceil_div(pl.C * (int64_t)pl.cp.n_rsplit, pl.cp_segs);
+        (void)hipGetLastError();
+        if (timing)
+            (void)hipEventRecord(tc->ev[0], st);
+        int crc = mttkrp_contract_launch<T>(pl.cp, ca, st);
+        if (crc == MTTKRP_OK)
+            crc = mttkrp_modesum_launch<T, T>(ms, pl.dims[k], pl.cp_segs, st);
+        if (timing) {
+            (void)hipEventRecord(tc->ev[1], st);
+            tc->combine = false;
+        }
+        if (crc != MTTKRP_OK) {
+            finish();
+            return crc;
+        }
+        if (pl.part_bytes > 0) {
+            launch_combine<T>((T*)ws, M, pl.dims[k] * (int64_t)R, R, pl.cp_segs, pl.cp_segs * (int64_t)R, (int64_t)R, lambda, beta, ldM, st);
+            if (timing) {
+                (void)hipEventRecord(tc->ev[2], st);
+                tc->combine = true;
+            }
+            if (hipGetLastError() != hipSuccess) {
+                finish();
+                return MTTKRP_ERR_DEVICE;
+            }
+        }
+        if (timing)
+            ds.n_timed += 1;
+        finish();
+        return MTTKRP_OK;
     }
     if (pl.contract_rows) {
         if (pl.CB * pl.JB > 8 || pl.CB < 1 || pl.CB > 4 || pl.JB < 1 || pl.JB > 8)
@@ -3142,6 +3278,9 @@ int mttkrp_tune_set(const char* key, int64_t value)
     } else if (!strcmp(key, "small_route")) {
         if (value > 2) return MTTKRP_ERR_INVALID_ARG;
         g_tune.small_route = value;
+    } else if (!strcmp(key, "lds_contract")) {
+        if (value > 2) return MTTKRP_ERR_INVALID_ARG;
+        g_tune.lds_contract = value;
     } else if (!strcmp(key, "small_groups")) {
         if (value > 1024) return MTTKRP_ERR_INVALID_ARG;
         g_tune.small_groups = value;

@@ -1,0 +1,55 @@
+// Contraction over the leading index through LDS (see contract.hip).  Internal to the library.
+#ifndef MTTKRP_CONTRACT_H
+#define MTTKRP_CONTRACT_H
+
+#include <hip/hip_runtime.h>
+
+#include <stdint.h>
+
+#include "../../include/mttkrp.h"
+
+#define MTTKRP_INTERNAL __attribute__((visibility("hidden")))
+
+struct ContractPlan {
+    bool ok = false;             // the kernel takes this shape
+    int JB = 1;                  // 16-column blocks of the output
+    int CW = 4;                  // wavefronts along the tensor columns, 16 each
+    int64_t n_ctile = 1;         // tiles of 16 CW tensor columns
+    int n_rsplit = 1;
+    int64_t rows_per_split = 0;  // multiple of a stage's rows (the last split takes what is left)
+    int64_t n_items = 1;
+    int grid = 1;                // persistent workgroups
+};
+
+template <typename T> struct ContractArgs {
+    const T* X;                  // P x Q, first index fastest
+    const T* K;                  // P x R, row-major, leading dimension ldK
+    T* out;                      // row c, split s at out + (c n_rsplit + s) ld_out
+    int64_t P, Q, ldK, ld_out;
+    int64_t rows_per_split, n_items;
+    int32_t R, n_rsplit, n_ctile;
+};
+
+// max_splits: row splits at most; target_items > 0: row splits until that many work items exist; max_rows > 0: rows per
+// split at most
+MTTKRP_INTERNAL ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64_t max_splits, int64_t target_items,
+                                                  int64_t max_rows);
+template <typename T>
+MTTKRP_INTERNAL int mttkrp_contract_launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st);
+
+
+// A mode's result from the contraction over mode 0, S(q, s, j) (see mttkrp_modesum_kernel).
+template <typename T, typename TP> struct ModeSumArgs {
+    const T* S;                  // [q][n_split][R]
+    TP* part;                    // [i_t][segment][R]
+    const T* A[MTTKRP_MAX_NDIM]; // factors of the modes of q (entry t is not read)
+    int64_t ld[MTTKRP_MAX_NDIM];
+    int32_t dim[MTTKRP_MAX_NDIM];
+    int64_t ld_part;             // row stride of part
+    int32_t n, t, R;
+    uint32_t n_split, n_pairs, per_seg;      // pairs (o, s) in all, and per segment
+};
+template <typename T, typename TP>
+MTTKRP_INTERNAL int mttkrp_modesum_launch(const ModeSumArgs<T, TP>& a, int64_t I_t, int n_seg, hipStream_t st);
+
+#endif

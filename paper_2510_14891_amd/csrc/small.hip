@@ -12,7 +12,7 @@
 // Columns are decoded by every lane for itself (a multiply-high per mode above the lowest): that hides
 // behind the loads, and short modes need no fused product matrices.  With few output rows several workgroups share
 // a row's columns and the combine kernel adds their sums (two launches instead of three).  fp64, us a call, before and
-// now: 64^3 at R = 16 15.7 / 8.4 / 8.4 -> 11 / 6 / 6, 40 x 66 x 17 at R = 36 second mode 14.7 -> 6.7; 100 x 80 x 60 at
+// now: 64^3 at R = 16 15.7 / 8.4 / 8.4 -> 8.3 / 5.1 / 5.0, 40 x 66 x 17 at R = 36 second mode 14.7 -> 6.7; 100 x 80 x 60 at
 // R = 10, CP-ALS, 12 sweeps 1482 -> 1214.  mttkrp.hip says where the line between the two paths lies.
 #include "mttkrp_small.h"
 
