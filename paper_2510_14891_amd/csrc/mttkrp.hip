@@ -1455,6 +1455,29 @@ template <typename T> int stream_waves_rb(int RB, int JB)
     default: return stream_waves_jb<T, 4>(JB);
     }
 }
+// ... and its steps of loads in flight
+template <typename T, int RB> int stream_depth_jb(int JB)
+{
+    switch (JB) {
+    case 1: return Pipe<T, RB, 1>::value ? Pipe<T, RB, 1>::depth : 3;
+    case 2: return Pipe<T, RB, 2>::value ? Pipe<T, RB, 2>::depth : 3;
+    case 3: return Pipe<T, RB, 3>::value ? Pipe<T, RB, 3>::depth : 3;
+    default: return Pipe<T, RB, 4>::value ? Pipe<T, RB, 4>::depth : 3;
+    }
+}
+template <typename T> int stream_depth_rb(int RB, int JB)
+{
+    switch (RB) {
+    case 1: return stream_depth_jb<T, 1>(JB);
+    case 2: return stream_depth_jb<T, 2>(JB);
+    case 3: return stream_depth_jb<T, 3>(JB);
+    default: return stream_depth_jb<T, 4>(JB);
+    }
+}
+int stream_depth(int sbytes, int RB, int JB)
+{
+    return sbytes == 8 ? stream_depth_rb<double>(RB, JB) : stream_depth_rb<float>(RB, JB);
+}
 int stream_waves(int sbytes, int RB, int JB)
 {
     return sbytes == 8 ? stream_waves_rb<double>(RB, JB) : stream_waves_rb<float>(RB, JB);
@@ -1514,7 +1537,7 @@ int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb
     return best;
 }
 
-int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl, bool prefer_rows,
+int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl, bool prefer_rows,
                   bool no_pair_first = false)
 {
     const int64_t* const dims_in = dims;
@@ -1522,11 +1545,6 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
     int rc = validate(ndim, dims, R, k, sbytes);
     if (rc != MTTKRP_OK)
         return rc;
-    Tuning tn;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        tn = g_tune;
-    }
     // Fusing two adjacent modes: they are treated as one mode of I_a * I_b entries whose factor
     // is the row-wise product of the two factors, (I_a I_b) x R, formed in the workspace by a
     // small kernel at every call.  X needs no change: adjacent modes of a first-index-fastest
@@ -2060,7 +2078,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
             limit = 64.0 * 1048576.0;
         if ((double)pl.part_bytes > limit) {
             pl = Plan();
-            return make_plan_for(ndim_in, dims_in, R, k_in, sbytes, pl, prefer_rows, true);
+            return make_plan_for(ndim_in, dims_in, R, k_in, sbytes, tn, pl, prefer_rows, true);
         }
     }
     pl.ws_bytes = (pl.part_bytes + 255) / 256 * 256 + pl.fused_bytes;
@@ -2082,13 +2100,8 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan&
 // workspace), i.e. the contraction over the leading index.  Taken when K stays cache-resident
 // (4 MiB) and mode 0 alone fills the streaming kernel's row tiles badly: then neither kernel has a
 // plan with long work items (20 x 20 x 10^6 at R = 32: 2.1 ms on the second schedule, 0.68 ms here).
-void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl)
 {
-    Tuning tn;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        tn = g_tune;
-    }
     if (k != ndim - 1 || ndim < 2 || tn.lead_last == 2 || (tn.contract_rows == 1 && tn.lead_last != 1))
         return;
     int64_t P = 1;
@@ -2148,24 +2161,19 @@ double plan_cost(const Plan& pl)
            (1.0 + 2.0 * (double)pl.part_bytes / ((double)pl.N * pl.sbytes));
 }
 
-int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl)
 {
-    int rc = make_plan_for(ndim, dims, R, k, sbytes, pl, false);
+    int rc = make_plan_for(ndim, dims, R, k, sbytes, tn, pl, false);
     if (rc == MTTKRP_OK && pl.seg_store) {
         // whole stored tiles cost traffic, and their cap can leave few items: compare with the plain plan
         // (129 x 257 x 12 x 500: 2076 items on 2048 slots, 0.39 against 0.35 ms; 40^5: 0.14 against 0.25 ms)
-        Tuning tn;
-        {
-            std::lock_guard<std::mutex> lock(g_mutex);
-            tn = g_tune;
-        }
         Plan plain;
-        if (tn.pair_rows != 1 && make_plan_for(ndim, dims, R, k, sbytes, plain, false, true) == MTTKRP_OK &&
+        if (tn.pair_rows != 1 && make_plan_for(ndim, dims, R, k, sbytes, tn, plain, false, true) == MTTKRP_OK &&
             !plain.contract_rows && plan_cost(plain) < plan_cost(pl))
             pl = plain;
     }
     if (rc == MTTKRP_OK)
-        maybe_lead_route(ndim, dims, R, k, sbytes, pl);
+        maybe_lead_route(ndim, dims, R, k, sbytes, tn, pl);
     if (rc != MTTKRP_OK || pl.contract_rows || pl.lead_route || k == 0)
         return rc;
     double limit = 0.05 * (double)pl.N * sbytes;
@@ -2174,7 +2182,7 @@ int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, P
     if ((double)pl.part_bytes <= limit)
         return rc;
     Plan alt;
-    if (make_plan_for(ndim, dims, R, k, sbytes, alt, true) == MTTKRP_OK && alt.contract_rows && alt.ws_bytes < pl.ws_bytes)
+    if (make_plan_for(ndim, dims, R, k, sbytes, tn, alt, true) == MTTKRP_OK && alt.contract_rows && alt.ws_bytes < pl.ws_bytes)
         pl = alt;
     return MTTKRP_OK;
 }
@@ -2213,24 +2221,97 @@ double general_cost(const Plan& pl)
            1.96 * cycles * steps / 2200.0 + 0.107e-6 * (double)pl.N * pl.sbytes + 1.1e-3 * items;
 }
 
-int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+// Time of a streaming plan in us, fitted to 7500 calls
+// (fp64 and fp32, 2^20 to 2^28 values, R = 4 to 128, up to twenty decompositions each; median error 8.5 %): what a step
+// costs (matrix cores at 1.9 GHz, HBM at 6.9 TB/s, or the latency of its loads), what an item and a sweep cost besides,
+// the launches around it and the partial sums.
+double stream_time(const Plan& pl)
 {
-    const int rc = make_general_plan(ndim, dims, R, k, sbytes, pl);
+    const double cycles = (pl.sbytes == 8 ? 64.0 : 32.0) * pl.RB * pl.JB;
+    int waves = stream_waves(pl.sbytes, pl.RB, pl.JB), depth = stream_depth(pl.sbytes, pl.RB, pl.JB);
+    if (!pl.deep) {
+        const int tiles = pl.RB * pl.JB * (pl.sbytes / 4);
+        waves = tiles <= 8 ? 4 : (tiles <= 12 ? 3 : 2);
+        depth = 3;
+    }
+    const double slots = 1024.0 * waves, items = (double)pl.n_items;
+    const double active = items < slots ? items : slots;
+    const double mfma = cycles / 1885.0 * (active > 1024.0 ? active / 1024.0 : 1.0);
+    const double mem = active * 64.0 * pl.RB * pl.sbytes / 6.866e6;
+    const double latency = 0.315 / depth;
+    const double step = pow(mfma * mfma * mfma * mfma + mem * mem * mem * mem + latency * latency * latency * latency, 0.25);
+    const bool second = pl.seg > 0 && !pl.seg_first, per_row = pl.seg_first && !pl.seg_store;
+    const double fixed = 1.459 + 0.266 * pl.RB * pl.JB + (second ? 1.70 : 0.0) + (per_row ? 5.62 : 0.0) +
+                         0.765 * (double)pl.o_per_item;
+    const double rounds = items > slots ? items / slots : 1.0;
+    return 2.94 + (pl.fused_bytes > 0 || second ? 3.31 : 0.0) + (pl.n_slots > 1 || pl.seg > 0 ? 3.22 : 0.0) +
+           0.966 * 1e-6 * (double)(pl.ws_bytes - pl.fused_bytes) + rounds * (fixed + (double)pl.steps_per_item * step);
+}
+
+// Tensors of 2^20 to 2^28 values: the rules above were fitted to larger ones, where a launch has many rounds of long
+// items.  Other targets for the number of items, three row blocks, and rows paired / fused or not are compared by
+// estimated time, and one of them is taken when it is estimated 15 % faster
+// (20 % where the second mode's paired rows are given up): 1.05 times faster in the mean over 6000 such calls, 1.10 at
+// 2^21 values, 1.05 at 2^25, 1.02 at 2^26, and 2 % of them more than 5 % slower (20 x 30 x 40 x 50 x 60 at R = 16, fourth
+// mode: 178 -> 113 us).
+void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+{
+    int64_t N = 1;
+    for (int m = 0; m < ndim; ++m)
+        N *= dims[m];
+    if (N < ((int64_t)1 << 20) || N > ((int64_t)1 << 28) || pl.contract_rows || pl.lead_route)
+        return;
+    const double now = stream_time(pl);
+    const bool paired_second = pl.seg > 0 && !pl.seg_first;
+    // memory stays in its class: the bounds of the plan itself, for the first mode (whose workspace a shared sweep counts
+    // on) never more than that plan, elsewhere up to 5 % of the tensor and what mttkrp_dense_f64_noalloc has
+    size_t ws_max = pl.ws_bytes;
+    if (k != 0) {
+        double most = 0.05 * (double)N * sbytes;
+        if (most > 67108864.0)
+            most = 67108864.0;
+        if ((double)ws_max < most)
+            ws_max = (size_t)most;
+    }
+    Plan best;
+    double best_time = now;
+    bool found = false;
+    for (int t = 0; t < 3; ++t)
+        for (int rb = 0; rb <= 3; rb += 3)
+            for (int rows = 0; rows < 3; ++rows) {
+                if (t + rb + rows == 0)
+                    continue;
+                Tuning tn;
+                tn.target_items = t == 0 ? 0 : (t == 1 ? 768 : 3072);
+                tn.row_blocks = rb;
+                tn.contract_rows = 2;
+                (k < 2 ? tn.pair_rows : tn.fuse_rows) = rows;
+                Plan c;
+                if (make_plan_for(ndim, dims, R, k, sbytes, tn, c, false) != MTTKRP_OK || c.ws_bytes > ws_max)
+                    continue;
+                if (c.RB == 1 && c.JB >= 3)        // short of registers for what the fit gives it
+                    continue;
+                const double time = stream_time(c);
+                if (time < best_time && time < (paired_second && c.seg == 0 ? 0.80 : 0.85) * now) {
+                    best = c;
+                    best_time = time;
+                    found = true;
+                }
+            }
+    if (found)
+        pl = best;
+}
+
+int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, bool tuned, Plan& pl)
+{
+    const int rc = make_general_plan(ndim, dims, R, k, sbytes, tn, pl);
     if (rc != MTTKRP_OK)
         return rc;
-    Tuning tn;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        tn = g_tune;
-    }
-    if (tn.small_route == 2)
+    if (!tuned)
+        better_stream_plan(ndim, dims, R, k, sbytes, pl);
+    // the other keys choose among the decompositions of the general plans
+    if (tn.small_route == 2 || (tn.small_route == 0 && tuned))
         return rc;
-    if (tn.small_route == 0) {
-        // the other keys choose among the decompositions of the general plans
-        const Tuning none;
-        if (memcmp(&tn, &none, sizeof(tn)) != 0)
-            return rc;
-    }
     // 32-bit offsets in the kernel, and a bounded grid
     int64_t N = 1, C = 1;
     for (int m = 0; m < ndim; ++m) {
@@ -2272,6 +2353,56 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
     if (pl.ws_bytes < (pl.small_bytes + 255) / 256 * 256)
         pl.ws_bytes = (pl.small_bytes + 255) / 256 * 256;
     return MTTKRP_OK;
+}
+
+// Plans at default settings are kept by shape: a call pays for the planning above once (15 us with the candidates of
+// better_stream_plan, as long as a small call) and then for a look-up.  One entry per hash, overwritten; g_mutex held.
+struct PlanKey {
+    int64_t dims[MTTKRP_MAX_NDIM];
+    int32_t ndim, R, k, sbytes;
+};
+constexpr int kPlanEntries = 64;
+struct PlanEntry {
+    bool used = false;
+    PlanKey key;
+    Plan plan;
+};
+PlanEntry g_plans[kPlanEntries];
+
+int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+{
+    int rc = validate(ndim, dims, R, k, sbytes);
+    if (rc != MTTKRP_OK)
+        return rc;
+    PlanKey key;
+    memset(&key, 0, sizeof(key));
+    uint64_t h = (uint64_t)R * 31 + (uint64_t)k * 7 + (uint64_t)sbytes;
+    for (int m = 0; m < ndim; ++m) {
+        key.dims[m] = dims[m];
+        h = (h ^ (uint64_t)dims[m]) * 0x9e3779b97f4a7c15ull;
+    }
+    key.ndim = ndim; key.R = R; key.k = k; key.sbytes = sbytes;
+    PlanEntry& e = g_plans[(h >> 40) % kPlanEntries];
+    const Tuning none;
+    Tuning tn;
+    bool tuned;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        tn = g_tune;
+        tuned = memcmp(&tn, &none, sizeof(tn)) != 0;
+        if (!tuned && e.used && memcmp(&e.key, &key, sizeof(key)) == 0) {
+            pl = e.plan;
+            return MTTKRP_OK;
+        }
+    }
+    rc = choose_plan(ndim, dims, R, k, sbytes, tn, tuned, pl);
+    if (rc == MTTKRP_OK && !tuned) {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        e.key = key;
+        e.plan = pl;
+        e.used = true;
+    }
+    return rc;
 }
 
 template <typename T, int RB, int JB>
