@@ -1515,7 +1515,12 @@ int validate(int ndim, const int64_t* dims, int R, int k, int sbytes)
 // rows 0.92 / 0.80 / 0.78 / 0.70; 129 rows (7.7 GB) 2.50 / 2.00 / 1.61 / 2.23.  eff[rb] receives
 // the share of the tiles' rows that are rows of the tensor.
 const double per_row[5] = {0.0, 1.5, 1.2, 1.06, 1.0};
-int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb_max)
+// With four blocks of output columns in fp64 a wavefront is bound by its MFMAs and two row blocks are nearly as good as
+// three: 3 to 5 % a row in the first mode, 5 to 6 % elsewhere (eleven shapes at R = 64 to 1000: 245 rows at R = 208
+// 1.81 -> 1.69 ms, 401 rows at R = 1000, first mode, 17.2 -> 16.1).
+const double per_row_wide[4] = {0.0, 1.31, 1.12, 1.06};
+const double per_row_wide_first[4] = {0.0, 1.31, 1.095, 1.06};
+int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb_max, bool first = false)
 {
     // fp64 accumulators of more than 12 MFMA tiles do not fit the register file next to the operands
     const int jb_all = (int)ceil_div(ceil_div(R, 16), ceil_div(ceil_div(R, 16), 4));
@@ -1528,7 +1533,7 @@ int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb
     for (int rb = 1; rb <= rb_max; ++rb) {
         const double tiles = (double)(ceil_div(rows, 16 * rb) * 16 * rb);
         eff[rb] = (double)rows / tiles;
-        const double cost = tiles * per_row[rb];
+        const double cost = tiles * (rb_cap == 4 ? per_row : (first ? per_row_wide_first : per_row_wide))[rb];
         if (rb == 1 || cost < best_cost - 1e-9) {     // equal cost: the fewer rows
             best = rb;
             best_cost = cost;
@@ -1832,7 +1837,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     {
         double eff[5];
         int rb_max = 1;
-        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max);
+        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max, k == 0);
         double best_eff = 0.0;
         for (int rb = 1; rb <= rb_max; ++rb)
             if (eff[rb] > best_eff)
