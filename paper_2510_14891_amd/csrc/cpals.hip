@@ -630,24 +630,13 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
     for (int r = wave; r < 16; r += WAVES)
         for (int c = lane; c < nblk * kNB; c += 64)
             put(r, c, r < rows && c < R ? M[(r0 + r) * R + c] : 0.0);
-    // Diagonal block b, entries (c, a), c > a: requested into registers one block before it is written to LDS, two before it
-    // is used (written as soon as it is loaded, every block waited for a load from another die's cache).
-    constexpr int KD = kNB * kNB / THREADS;
-    auto load_diag = [&](int b, double (&d)[KD]) {
-#pragma unroll
-        for (int i = 0; i < KD; ++i) {
-            const int t = tid + i * THREADS, a = t & (kNB - 1), c = t / kNB, j0 = b * kNB;
-            d[i] = b >= 0 && c > a && j0 + c < R ? L[(int64_t)(j0 + c) * R + j0 + a] : 0.0;
+    auto load_diag = [&](int b, int t0, int step) {        // entry (c, a), c > a, of the diagonal block b
+        double* const o = Ld[b & 1];
+        for (int t = t0; t < kNB * kNB; t += step) {
+            const int a = t & (kNB - 1), c = t / kNB, j0 = b * kNB;
+            o[a * (kNB + 1) + c] = c > a && j0 + c < R ? L[(int64_t)(j0 + c) * R + j0 + a] : 0.0;
         }
     };
-    auto write_diag = [&](int b, const double (&d)[KD]) {
-#pragma unroll
-        for (int i = 0; i < KD; ++i) {
-            const int t = tid + i * THREADS, a = t & (kNB - 1), c = t / kNB;
-            Ld[b & 1][a * (kNB + 1) + c] = d[i];
-        }
-    };
-    double dn[KD];
     // columns [16 ct, 16 ct + 16) -= (the block's 16 x 32 unknowns) * bt, bt[s] = row 8 kq + s of the 32 x 16 operand
     auto update = [&](int b, int ct, const double (&bt)[8]) {
         double4_t acc;
@@ -676,9 +665,7 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
             put(r, b * kNB + 4 * q + part, y[q]);
     };
     const int ncol = (R + 15) / 16;
-    load_diag(0, dn);
-    write_diag(0, dn);
-    load_diag(1, dn);
+    load_diag(0, tid, THREADS);
     __syncthreads();
     for (int b = 0; b < nblk; ++b) {
         auto load_b = [&](int ct, double (&bt)[8]) {       // L(16 ct + n, 32 b + 8 kq + s): a following row, so block b is full
@@ -692,12 +679,10 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
         int ct = 2 * (b + 1) + wave;
         if (ct < ncol)
             load_b(ct, bt);
-        if (b + 1 < nblk) {
-            write_diag(b + 1, dn);
-            load_diag(b + 2, dn);
-        }
         if (wave == 0)
             diag_solve(b, true);
+        else if (b + 1 < nblk)
+            load_diag(b + 1, tid - 64, THREADS - 64);
         __syncthreads();
         for (; ct < ncol; ct += WAVES) {
             double nx[8];
@@ -710,7 +695,6 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
         }
         __syncthreads();
     }
-    load_diag(nblk - 2, dn);
     for (int r = wave; r < 16; r += WAVES)
         for (int c = lane; c < R; c += 64)
             put(r, c, get(r, c) * dinv[c]);
@@ -727,12 +711,10 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
         int ct = wave;
         if (ct < 2 * b)
             load_b(ct, bt);
-        if (b > 0) {
-            write_diag(b - 1, dn);
-            load_diag(b - 2, dn);
-        }
         if (wave == 0)
             diag_solve(b, false);
+        else if (b > 0)
+            load_diag(b - 1, tid - 64, THREADS - 64);
         __syncthreads();
         for (; ct < 2 * b; ct += WAVES) {
             double nx[8];
