@@ -2258,7 +2258,9 @@ double stream_time(const Plan& pl)
 // estimated time, and one of them is taken when it is estimated 15 % faster
 // (20 % where the second mode's paired rows are given up): 1.05 times faster in the mean over 6000 such calls, 1.10 at
 // 2^21 values, 1.05 at 2^25, 1.02 at 2^26, and 2 % of them more than 5 % slower (20 x 30 x 40 x 50 x 60 at R = 16, fourth
-// mode: 178 -> 113 us).
+// mode: 178 -> 113 us). In fp32 a plan with longer chains of sums in an item than before is not taken
+// (12 % of the fp32 calls keep their plan for it): such chains, up to 4 times as long, gave up to twice the error against
+// fp64 (4112 x 359 x 25 at R = 32, first mode: 3.3e-8 -> 6.7e-8 rms).
 void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 {
     int64_t N = 1;
@@ -2295,6 +2297,8 @@ void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes,
                 if (make_plan_for(ndim, dims, R, k, sbytes, tn, c, false) != MTTKRP_OK || c.ws_bytes > ws_max)
                     continue;
                 if (c.RB == 1 && c.JB >= 3)        // short of registers for what the fit gives it
+                    continue;
+                if (sbytes == 4 && c.steps_per_item > pl.steps_per_item)   // fp32: no longer chain of sums than before
                     continue;
                 const double time = stream_time(c);
                 if (time < best_time && time < (paired_second && c.seg == 0 ? 0.80 : 0.85) * now) {
@@ -2338,8 +2342,8 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         if (groups > 1 && C < 16 * (int64_t)groups && tn.small_groups == 0)
             break;
         const SmallPlan sp = mttkrp_small_plan(ndim, dims, R, k, sbytes, groups);
-        // fp32: accumulation chains as short as the streaming kernel's
-        if (sbytes == 8 || sp.cols_per_range <= 4096) {
+        // fp32: no longer chain of sums than the general plan's (beyond it the sums are fp64 in both)
+        if (sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) {
             const double cost = small_cost(sp, sbytes, n_modes, N);
             if (cost < best_cost) {
                 best = sp;

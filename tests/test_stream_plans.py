@@ -1,0 +1,119 @@
+"""Streaming plans that are chosen by estimated time (2^20 to 2^28 values) and the row blocks of wide fp64 tiles: what
+every choice keeps of the plan it replaces (scratch, length of fp32 sums, validity after tuning), and calls whose plan
+changes against the CPU oracle: each mode, both types, rows paired or fused and not, 16 to 64 rows per wavefront, odd
+extents.  Tolerances are those of every parity test: 1e-12 (fp64) and 1e-5 (fp32), normwise."""
+import math
+import random
+import re
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2510_14891_amd import inputs
+
+TOL = {torch.float64: 1e-12, torch.float32: 1e-5}
+DTYPE = {8: torch.float64, 4: torch.float32}
+
+# (value bytes, extents, R, mode): the chosen plan differs from the rule-based one in rows per wavefront, pairing,
+# fusing or the number of items
+CHANGED = [(4, (82, 129, 157), 5, 0), (4, (13, 11, 53, 146), 16, 0), (4, (59, 235, 139), 17, 0), (4, (104, 5, 276, 8), 64, 1),
+           (4, (51, 75, 10, 66), 64, 1), (4, (370, 37, 109), 17, 1), (4, (110, 2, 127, 61), 17, 2),
+           (4, (49, 6, 17, 12, 22), 33, 2), (4, (165, 21, 5, 84), 5, 2), (8, (7, 6, 29, 24, 41), 16, 0), (8, (129, 1508, 9), 5, 0),
+           (8, (544, 699, 7), 17, 0), (8, (26, 425, 242), 17, 0), (8, (306, 82, 98), 5, 0), (8, (1603, 34, 38), 16, 1),
+           (8, (18, 160, 620), 17, 1), (8, (187, 61, 257), 33, 1), (8, (6, 465, 898), 17, 2), (8, (65, 4, 73, 85), 17, 2),
+           (8, (26, 33, 40, 61), 17, 2), (8, (113, 14, 47, 26), 33, 3)]
+# rows around the lines between one, two and three row blocks with four blocks of columns
+WIDE = [(15, 64), (33, 64), (49, 50), (65, 64), (97, 200), (129, 128), (161, 64), (245, 208)]
+
+
+@pytest.fixture(scope="module")
+def mt():
+    from paper_2510_14891_amd import binding
+    if not binding.os.path.exists(binding.LIB_PATH):
+        pytest.skip("library not built")
+    binding.lib()
+    yield binding
+    binding.mttkrp_tune_set("small_route", 0)
+
+
+def plans(mt, dims, R, k, b):
+    """The rule-based plan (any key away from its default) and the chosen one, as dictionaries."""
+    mt.mttkrp_tune_set("small_route", 2)
+    base = mt.mttkrp_plan_describe(dims, R, k, b)
+    mt.mttkrp_tune_set("small_route", 0)
+    now = mt.mttkrp_plan_describe(dims, R, k, b)
+    return [dict(re.findall(r"(\w+)=(-?\w+)", p.split("| ")[-1])) for p in (base, now)], now
+
+
+def test_chosen_plans_keep_their_bounds(mt):
+    rng = random.Random(17)
+    changed = 0
+    for _ in range(400):
+        nd = rng.randint(2, 6)
+        w = [rng.random() + 0.2 for _ in range(nd)]
+        N = 2.0 ** rng.uniform(18.0, 29.0)
+        dims = [max(2, int(N ** (x / sum(w)))) for x in w]
+        R, k, b = rng.choice([4, 16, 17, 33, 64, 100, 128]), rng.randrange(nd), rng.choice([4, 8])
+        (base, now), text = plans(mt, dims, R, k, b)
+        assert text == mt.mttkrp_plan_describe(dims, R, k, b)              # kept plan = planned one
+        assert mt.mttkrp_dense_workspace_bytes(dims, R, k, b) >= int(now["ws_bytes"])
+        if base == now or "small_route" in text:
+            continue
+        changed += 1
+        n = math.prod(dims)
+        assert 2 ** 20 <= n <= 2 ** 28, dims
+        limit = int(base["ws_bytes"])
+        if k != 0:
+            limit = max(limit, min(0.05 * n * b, 2 ** 26))
+        assert int(now["ws_bytes"]) <= limit, (dims, R, k, b)
+        if b == 4:
+            assert int(now["steps_per_item"]) <= int(base["steps_per_item"]), (dims, R, k)
+    assert changed > 50
+
+
+@pytest.mark.parametrize("b,dims,R,k", CHANGED)
+def test_listed_plans_differ(mt, b, dims, R, k):
+    (base, now), text = plans(mt, dims, R, k, b)
+    assert base != now and "small_route" not in text
+
+
+def check(mt, oracle, dims, R, k, dtype, seed):
+    X = inputs.uniform(seed, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
+    A = [inputs.uniform(seed + 100 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
+    Xd, f = X.cuda(), [a.cuda() for a in A]
+    f[k] = None
+    ref = oracle.mttkrp(inputs.as_ndarray_view(X, dims), [a.numpy() for a in A], k)
+    print("stream plan dims=%s R=%d k=%d" % (dims, R, k), flush=True)
+    got = mt.mttkrp_dense(Xd, dims, f, k)
+    assert oracle.normwise_rel_err(got.cpu().numpy(), ref) <= TOL[dtype]
+    assert torch.equal(got, mt.mttkrp_dense(Xd, dims, f, k))               # fixed order
+    lam = inputs.uniform(seed + 1, R, 0.5, 2.0, dtype=dtype)
+    M = inputs.uniform(seed + 2, (dims[k], R), -1.0, 1.0, dtype=dtype)
+    want = 0.5 * M.numpy().astype(np.float64) + ref * lam.numpy()
+    acc = mt.mttkrp_dense(Xd, dims, f, k, M=M.cuda(), lam=lam.cuda(), beta=0.5)
+    assert oracle.normwise_rel_err(acc.cpu().numpy(), want) <= TOL[dtype]
+    wide = [torch.zeros((I, R + 3), dtype=dtype, device="cuda") for I in dims]
+    for w, a in zip(wide, A):
+        w[:, :R] = a.cuda()
+    Mw = torch.full((dims[k], R + 5), 7.0, dtype=dtype, device="cuda")
+    mt.mttkrp_dense_ld(Xd, dims, wide, k, Mw, R)
+    assert torch.equal(Mw[:, :R], got) and bool((Mw[:, R:] == 7.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("b,dims,R,k", CHANGED)
+def test_changed_plans_match_the_oracle(mt, oracle, b, dims, R, k):
+    check(mt, oracle, dims, R, k, DTYPE[b], 31)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,R", WIDE)
+def test_wide_tiles_match_the_oracle(mt, oracle, rows, R):
+    mt.mttkrp_tune_set("small_route", 2)
+    try:
+        for k in range(3):
+            check(mt, oracle, (rows, 37, 19), R, k, torch.float64, 41)
+    finally:
+        mt.mttkrp_tune_set("small_route", 0)
