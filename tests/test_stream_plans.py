@@ -50,7 +50,7 @@ def plans(mt, dims, R, k, b):
 def test_chosen_plans_keep_their_bounds(mt):
     rng = random.Random(17)
     changed = 0
-    for _ in range(400):
+    for _ in range(1500):
         nd = rng.randint(2, 6)
         w = [rng.random() + 0.2 for _ in range(nd)]
         N = 2.0 ** rng.uniform(18.0, 29.0)
