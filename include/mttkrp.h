@@ -89,8 +89,10 @@ typedef enum {
  * calls allocate; they then wait on the host for the last call that used it.
  * A device keeps the workspaces of the eight most recently used streams; a
  * ninth stream takes over the least recently used one after waiting for that
- * stream's last call.  Not for use under stream capture (the calls record an
- * event they may later wait on): capture the *_ws calls instead.
+ * stream's last call: the first time for the whole device, from then on for an
+ * event that every call records (with eight streams or fewer none does).  Not
+ * for use under stream capture (the calls may allocate, wait and record
+ * events): capture the *_ws calls instead.
  *   ndim     number of modes d, 2 <= d <= MTTKRP_MAX_NDIM
  *   dims     host array of d extents I_0..I_{d-1}, each >= 1
  *   X        device, prod(dims) values

@@ -19,9 +19,10 @@
  *   stop when |fit - previous fit| < tol, or after max_iters sweeps.
  *
  * The paper's CP-ALS experiment (Sec. IV-C) runs ranks 10, 500, 1000 and 2000; up to rank
- * 64 the R x R work (Gram matrices, Cholesky factor, row solves) runs in one workgroup's
- * LDS, above that blocked from global memory, 32 columns at a time (then also every
- * I_n <= 1048560).
+ * 64 the R x R work (Hadamard product of the Gram matrices, its L D L^T factor, row solves) runs
+ * in registers of one workgroup per block of rows, in one or two launches per mode; above that blocked
+ * from global memory, 32 columns a launch of the factor and one launch for the solves (then also
+ * every I_n <= 1048560).
  *
  * Everything runs on the GPU in fp64 with fixed-order reductions (reruns are
  * bit-identical); the host only reads three scalars per sweep to evaluate the

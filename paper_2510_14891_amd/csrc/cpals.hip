@@ -1018,7 +1018,7 @@ int plan_shared(int ndim, const int64_t* dims, int R, int sbytes, SharedPlan& sp
     if (ndim - sp.s > 1) {
         sp.off_TL = off;  off += align256((size_t)sp.PR * row);
     }
-    // segment totals of partial_mode_kernel (fp64), the largest over the modes that use it
+    // segment totals of mttkrp_modesum_kernel (fp64), the largest over the modes that use it
     size_t part = 0;
     sp.max_seg = 1;
     for (int k = 0; k < ndim; ++k) {
