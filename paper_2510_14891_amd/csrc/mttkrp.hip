@@ -1285,6 +1285,10 @@ mttkrp_colweights_kernel(const ColWeightArgs<T> p, int64_t n_entries, int R, T* 
 // Host side: plan, launch, C ABI
 // ---------------------------------------------------------------------------
 
+// What a plan may take beyond the one it replaces: the array of mttkrp_dense_f64_noalloc, so that no call is refused there
+// for a faster plan.
+constexpr double kNoallocBytes = 67108864.0;
+
 struct Tuning {
     int64_t row_blocks = 0;
     int64_t target_items = 0;
@@ -1307,6 +1311,7 @@ struct Tuning {
     int64_t small_route = 0;
     int64_t small_groups = 0;
     int64_t lds_contract = 0;
+    int64_t plain_rows = 0;     // no key of its own: row blocks of wide fp64 tiles by the general costs (choose_plan)
 };
 Tuning g_tune;
 std::mutex g_mutex;
@@ -1520,7 +1525,7 @@ const double per_row[5] = {0.0, 1.5, 1.2, 1.06, 1.0};
 // 1.81 -> 1.69 ms, 401 rows at R = 1000, first mode, 17.2 -> 16.1).
 const double per_row_wide[4] = {0.0, 1.31, 1.12, 1.06};
 const double per_row_wide_first[4] = {0.0, 1.31, 1.095, 1.06};
-int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb_max, bool first = false)
+int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb_max, bool plain, bool first = false)
 {
     // fp64 accumulators of more than 12 MFMA tiles do not fit the register file next to the operands
     const int jb_all = (int)ceil_div(ceil_div(R, 16), ceil_div(ceil_div(R, 16), 4));
@@ -1533,7 +1538,7 @@ int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb
     for (int rb = 1; rb <= rb_max; ++rb) {
         const double tiles = (double)(ceil_div(rows, 16 * rb) * 16 * rb);
         eff[rb] = (double)rows / tiles;
-        const double cost = tiles * (rb_cap == 4 ? per_row : (first ? per_row_wide_first : per_row_wide))[rb];
+        const double cost = tiles * (rb_cap == 4 || plain ? per_row : (first ? per_row_wide_first : per_row_wide))[rb];
         if (rb == 1 || cost < best_cost - 1e-9) {     // equal cost: the fewer rows
             best = rb;
             best_cost = cost;
@@ -1664,19 +1669,24 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             // Its intermediate is written and read once: taken while that stays below 2 % of the tensor's bytes.
             const Tuning none;
             Tuning rest = tn;
-            rest.small_route = rest.small_groups = rest.lds_contract = 0;
+            rest.small_route = rest.small_groups = rest.lds_contract = rest.plain_rows = 0;
             const int64_t Q = pl.N / dims[0];
             if (tn.lds_contract != 2 && memcmp(&rest, &none, sizeof(rest)) == 0 && dims[0] < ((int64_t)1 << 31) && Q < ((int64_t)1 << 31) - 256) {
                 // (fp32: accumulation chains no longer than the other kernel's)
                 const ContractPlan cp = mttkrp_contract_plan(dims[0], Q, R, sbytes, 4096, 0, sbytes == 4 ? pl.rows_per_split : 0);
                 const double s_bytes = (double)Q * cp.n_rsplit * R * sbytes;
-                if (cp.ok && s_bytes <= 0.02 * (double)pl.N * sbytes && C * (int64_t)cp.n_rsplit < ((int64_t)1 << 31)) {
+                const int64_t pairs = C * cp.n_rsplit;
+                int64_t segs = ceil_div(2048, dims[k] * ceil_div(R, 32));
+                if (segs > ceil_div(pairs, 64))
+                    segs = ceil_div(pairs, 64);
+                if (segs < 1)
+                    segs = 1;
+                const double bytes = s_bytes + 512.0 + (segs > 1 ? (double)dims[k] * (double)segs * R * sbytes : 0.0);
+                // (and never beyond what mttkrp_dense_f64_noalloc has)
+                if (cp.ok && s_bytes <= 0.02 * (double)pl.N * sbytes && pairs < ((int64_t)1 << 31) &&
+                    (bytes <= kNoallocBytes || bytes <= (double)pl.ws_bytes)) {
                     pl.cp = cp;
-                    const int64_t pairs = C * cp.n_rsplit;
-                    int64_t segs = ceil_div(2048, dims[k] * ceil_div(R, 32));
-                    if (segs > ceil_div(pairs, 64))
-                        segs = ceil_div(pairs, 64);
-                    pl.cp_segs = (int)(segs < 1 ? 1 : segs);
+                    pl.cp_segs = (int)segs;
                     pl.n_rsplit = cp.n_rsplit;
                     pl.n_splits = cp.n_rsplit;
                     pl.n_items = cp.n_items * cp.CW;
@@ -1753,7 +1763,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
         auto tile_rows = [&](int64_t rows, int& rb_out) {
             double eff[5];
             int rb_max = 1;
-            rb_out = choose_row_blocks(rows, R, sbytes, eff, rb_max);
+            rb_out = choose_row_blocks(rows, R, sbytes, eff, rb_max, tn.plain_rows != 0);
             if (tn.row_blocks >= 1 && tn.row_blocks <= rb_max)
                 rb_out = (int)tn.row_blocks;
             return eff[rb_out];
@@ -1837,7 +1847,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     {
         double eff[5];
         int rb_max = 1;
-        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max, k == 0);
+        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max, tn.plain_rows != 0, k == 0);
         double best_eff = 0.0;
         for (int rb = 1; rb <= rb_max; ++rb)
             if (eff[rb] > best_eff)
@@ -2118,7 +2128,7 @@ void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, c
     if (tn.lead_last != 1) {
         double eff[5];
         int rb_max = 1;
-        const int rb = choose_row_blocks(dims[0], R, sbytes, eff, rb_max);
+        const int rb = choose_row_blocks(dims[0], R, sbytes, eff, rb_max, tn.plain_rows != 0);
         if (eff[rb] >= 0.9 && rb > 2)
             return;
     }
@@ -2275,8 +2285,8 @@ void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes,
     size_t ws_max = pl.ws_bytes;
     if (k != 0) {
         double most = 0.05 * (double)N * sbytes;
-        if (most > 67108864.0)
-            most = 67108864.0;
+        if (most > kNoallocBytes)
+            most = kNoallocBytes;
         if ((double)ws_max < most)
             ws_max = (size_t)most;
     }
@@ -2316,6 +2326,19 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
     const int rc = make_general_plan(ndim, dims, R, k, sbytes, tn, pl);
     if (rc != MTTKRP_OK)
         return rc;
+    if (tn.row_blocks == 0 && sbytes == 8 && R > 48) {
+        // Fewer row blocks a wavefront can mean more partial rows (446 x 118 x 9560 at R = 64, third mode: 49 -> 69 MB): the
+        // costs of wide tiles choose only within min(5 % of the tensor, 64 MiB) or the memory of the other plan.
+        Tuning general = tn;
+        general.plain_rows = 1;
+        Plan c;
+        double most = 0.05 * (double)pl.N * sbytes;
+        if (most > kNoallocBytes)
+            most = kNoallocBytes;
+        if ((double)pl.ws_bytes > most && make_general_plan(ndim, dims, R, k, sbytes, general, c) == MTTKRP_OK &&
+            c.ws_bytes < pl.ws_bytes)
+            pl = c;
+    }
     if (!tuned)
         better_stream_plan(ndim, dims, R, k, sbytes, pl);
     // the other keys choose among the decompositions of the general plans
@@ -2343,7 +2366,10 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
             break;
         const SmallPlan sp = mttkrp_small_plan(ndim, dims, R, k, sbytes, groups);
         // fp32: no longer chain of sums than the general plan's (beyond it the sums are fp64 in both)
-        if (sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) {
+        // partial sums of the groups: 16 MiB, or what the general plan has (tall outputs of a high rank)
+        const double bytes = groups > 1 ? (double)sp.n_groups * (double)dims[k] * R * sbytes : 0.0;
+        if ((sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) &&
+            (bytes <= 16777216.0 || bytes <= (double)pl.ws_bytes)) {
             const double cost = small_cost(sp, sbytes, n_modes, N);
             if (cost < best_cost) {
                 best = sp;

@@ -73,6 +73,15 @@ def test_chosen_plans_keep_their_bounds(mt):
     assert changed > 50
 
 
+# Calls whose faster routes would take more scratch than the 64 MiB of mttkrp_dense_f64_noalloc where the general plan does
+# not: the contraction over a long mode 0 beside many columns, wide row blocks, workgroups that share a small tensor's rows.
+@pytest.mark.parametrize("b,dims,R,k", [(8, (60975, 1773, 19), 32, 1), (8, (22763, 3, 22943), 32, 2), (8, (2360, 870332), 32, 1),
+                                        (4, (13350, 98910), 16, 1), (4, (80643, 161, 100), 64, 1), (8, (446, 118, 9560), 64, 2),
+                                        (8, (198, 32, 222, 43, 6), 128, 0), (8, (129408, 64), 1000, 0)])
+def test_no_plan_takes_more_than_the_fixed_array(mt, b, dims, R, k):
+    assert mt.mttkrp_dense_workspace_bytes(dims, R, k, b) <= 1 << 26
+
+
 @pytest.mark.parametrize("b,dims,R,k", CHANGED)
 def test_listed_plans_differ(mt, b, dims, R, k):
     (base, now), text = plans(mt, dims, R, k, b)
