@@ -2737,6 +2737,11 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     int rc = make_plan(ndim, dims, R, k, (int)sizeof(T), pl);
     if (rc != MTTKRP_OK)
         return rc;
+    // The kernel for small tensors addresses a factor's rows in 32 bits: blocks of arrays of 2^32 values and more run on
+    // the general decomposition, which the plan holds besides and whose workspace it counts.
+    for (int m = 0; m < ndim; ++m)
+        if (m != k && dims[m] * ld[m] >= ((int64_t)1 << 32))
+            pl.small = false;
     // Weights and accumulation are applied by the combine kernel, which then always runs.
     const bool scaled = lambda != nullptr || beta != 0.0;
     if (scaled && pl.part_bytes == 0) {

@@ -91,6 +91,30 @@ def test_small_route_non_finite_values(mt, oracle, dtype):
                 assert oracle.normwise_rel_err(np.where(fin, got, 0.0), np.where(fin, ref, 0.0)) <= TOL[dtype]
 
 
+@pytest.mark.gpu
+def test_factors_inside_arrays_beyond_32_bit_offsets(mt, oracle):
+    """34 rows that lie 2^27 - 1 values apart (18 GB of single precision): a row offset formed in 32 bits wraps and reads
+    another place of the same array."""
+    dims, R, ld = (34, 34, 34), 16, 2 ** 27 - 1
+    X, A = make(dims, R, torch.float32, 61)
+    big = torch.full((34 * ld,), float("nan"), dtype=torch.float32, device="cuda")
+    wide = [big.as_strided((34, R), (ld, 1), 64 * m) for m in range(2)] + [A[2].cuda()]
+    for w, a in zip(wide, A[:2]):
+        w.copy_(a)
+    lam = inputs.uniform(62, R, 0.5, 2.0, dtype=torch.float32)
+    for k in range(3):
+        assert "small_route=1" in mt.mttkrp_plan_describe(dims, R, k, 4)
+        ref = oracle.mttkrp(inputs.as_ndarray_view(X, dims), [a.numpy() for a in A], k)
+        print("wide leading dimensions k=%d" % k, flush=True)
+        M = torch.full((dims[k], R), 1.0, dtype=torch.float32, device="cuda")
+        mt.mttkrp_dense_ld(X.cuda(), dims, wide, k, M, R)
+        assert oracle.normwise_rel_err(M.cpu().numpy(), ref) <= TOL[torch.float32], k
+        M = torch.full((dims[k], R), 1.0, dtype=torch.float32, device="cuda")
+        mt.mttkrp_dense_ld(X.cuda(), dims, wide, k, M, R, lam=lam.cuda(), beta=0.5)
+        want = ref * lam.numpy() + 0.5
+        assert oracle.normwise_rel_err(M.cpu().numpy(), want) <= TOL[torch.float32], k
+
+
 def test_small_route_is_for_small_tensors():
     from paper_2510_14891_amd import binding
     for dims, R, k, sb in (((64, 64, 64), 16, 0, 8), ((100, 80, 60), 10, 1, 8), ((20, 10, 5), 4, 2, 4)):
