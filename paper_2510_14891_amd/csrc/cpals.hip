@@ -140,6 +140,11 @@ __global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__
 // matrix.  These steps are short chains, bound by launches and by latency, not by arithmetic.
 // ---------------------------------------------------------------------------
 
+// The failure flag, read once for a whole workgroup.  In the kernels that factorise V, workgroup 0 may set it while others
+// are still starting: read by each wavefront for itself, some of a workgroup could leave and the rest go on with
+// columns in LDS that nobody wrote.  (Every workgroup finds the same bad pivot, so it does not matter which value it sees.)
+__device__ __forceinline__ bool failed_before(const int* flag) { return __syncthreads_or(flag[0]) != 0; }
+
 // 1 / d to the last place or two: the hardware estimate and two Newton steps (an IEEE division is
 // three times as long a chain, and a step of the factorisation waits for it).
 __device__ __forceinline__ double reciprocal(double d)
@@ -288,7 +293,7 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
     __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP];
     __shared__ double Ys[YR * (RP + 1)];
-    if (flag[0])      // an earlier update failed: every factor stays as it is
+    if (failed_before(flag))      // an earlier update failed: every factor stays as it is
         return;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ti = tid & 15, tc = (tid >> 4) & 15, grp = tid >> 8;
@@ -529,7 +534,7 @@ factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag
 {
     __shared__ double Lf[kNB * (kNB + 1)], dinv[kNB], col[2][kNB];
     __shared__ double W[2][kNB][kNB + 1];
-    if (flag[0] || blockIdx.x > blockIdx.y)
+    if (blockIdx.x > blockIdx.y || failed_before(flag))
         return;
     const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4, lane = tid & 63, wave = tid >> 6;
     const int nb = R - j0 < kNB ? R - j0 : kNB, j1 = j0 + nb;

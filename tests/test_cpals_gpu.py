@@ -106,6 +106,27 @@ def test_cpals_large_rank_singular_gram_is_reported(mt):
     assert torch.equal(Ad[0], before)
 
 
+# Updates of several workgroups, which all read the flag that the first of them sets: a zero column in the first or the last
+# place (the first pivot is bad, or only the last), 32 to 1094 tiles, ranks of every register tile, one panel and
+# several above rank 64.  No factor may change.
+@pytest.mark.parametrize("dims,R", [((2000, 9, 7), 8), ((70000, 6, 5), 20), ((9000, 30, 10), 64), ((70000, 9, 9), 33),
+                                    ((300, 80, 75), 72), ((400, 40, 150), 130)])
+@pytest.mark.parametrize("column", [0, -1])
+def test_cpals_failed_update_of_several_workgroups_changes_no_factor(mt, dims, R, column):
+    X, A0 = problem(dims, R, 37)
+    Ad = [a.clone().cuda() for a in A0]
+    Ad[1][:, column] = 0.0
+    before = [a.clone() for a in Ad]
+    for shared in (False, True):
+        print("cp-als failed update dims=%s R=%d column=%d" % (dims, R, column), flush=True)
+        with pytest.raises(mt.MttkrpError) as e:
+            mt.mttkrp_cpals(X.cuda(), dims, Ad, 2, 0.0, shared=shared)
+        assert e.value.status == mt.MTTKRP_ERR_NUMERICAL
+        torch.cuda.synchronize()
+        for a, b in zip(Ad, before):
+            assert torch.equal(a, b)
+
+
 def test_cpals_tolerance_stop_and_reproducibility(mt):
     from oracle import cp_als_oracle, mttkrp_oracle
     mttkrp_oracle.build()
