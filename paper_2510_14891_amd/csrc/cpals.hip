@@ -121,17 +121,29 @@ __global__ void __launch_bounds__(256) gram_reduce(const double* __restrict__ ws
     G[e] = s;
 }
 
-// V = Hadamard product of the Gram matrices of all modes but `skip` (skip < 0: of all modes).
-__global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__ G, int ndim, int RR, int skip, double* V)
+// The power of two whose square brings a diagonal entry of V to [1, 4).  V is factorised as S V S and the rows of M and A
+// are multiplied by S: products with powers of two are exact, and the pivots and their reciprocals stay normal
+// numbers for start factors of any scale.
+__device__ __forceinline__ double unit_scale(double d) { return d > 0.0 && d < INFINITY ? ldexp(1.0, -(ilogb(d) >> 1)) : 1.0; }
+
+// S V S with V = Hadamard product of the Gram matrices of all modes but `skip`, and the diagonal of S.
+__global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__ G, int ndim, int R, int skip, double* V, double* S)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
+    const int e = blockIdx.x * 256 + threadIdx.x, RR = R * R;
     if (e >= RR)
         return;
-    double v = 1.0;
+    const int a = e / R, c = e - a * R;
+    double v = 1.0, da = 1.0, dc = 1.0;
     for (int m = 0; m < ndim; ++m)
-        if (m != skip)
+        if (m != skip) {
             v *= G[(int64_t)m * RR + e];
-    V[e] = v;
+            da *= G[(int64_t)m * RR + (int64_t)a * R + a];
+            dc *= G[(int64_t)m * RR + (int64_t)c * R + c];
+        }
+    da = unit_scale(da);
+    V[e] = v * da * unit_scale(dc);
+    if (a == c)
+        S[a] = da;
 }
 
 // ---------------------------------------------------------------------------
@@ -145,8 +157,9 @@ __global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__
 // columns in LDS that nobody wrote.  (Every workgroup finds the same bad pivot, so it does not matter which value it sees.)
 __device__ __forceinline__ bool failed_before(const int* flag) { return __syncthreads_or(flag[0]) != 0; }
 
-// 1 / d to the last place or two: the hardware estimate and two Newton steps (an IEEE division is
-// three times as long a chain, and a step of the factorisation waits for it).
+// 1 / d for a pivot of the scaled V: the hardware estimate and two Newton steps (an IEEE division is
+// three times as long a chain, and a step of the factorisation waits for it).  Against a Cholesky factor with
+// divisions and square roots the factors of one sweep are 0.95 times as far from extended precision (384 calls, R = 3 to 97).
 __device__ __forceinline__ double reciprocal(double d)
 {
     double r = __builtin_amdgcn_rcp(d);
@@ -291,7 +304,7 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     constexpr int NT = RP / 16, THREADS = 64 * WAVES, TR = 16 * WAVES;
     constexpr int YR = RP == 64 ? 32 : TR;          // rows of a tile that pass through LDS at once
     constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
-    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP];
+    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP], scale[RP];
     __shared__ double Ys[YR * (RP + 1)];
     if (failed_before(flag))      // an earlier update failed: every factor stays as it is
         return;
@@ -313,6 +326,17 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
             }
             own[p][q] = v;
         }
+    if (tid < 256 && ti == tc) {
+#pragma unroll
+        for (int p = 0; p < NT; ++p)
+            scale[ti + 16 * p] = unit_scale(own[p][p]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+        for (int q = 0; q < NT; ++q)
+            own[p][q] = own[p][q] * scale[ti + 16 * p] * scale[tc + 16 * q];
     if (!factorise<RP>(own, R, col, Lf, dinv)) {
         if (blockIdx.x == 0 && tid == 0)
             flag[0] = 1;
@@ -330,12 +354,15 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
         double y[RP / 4];
 #pragma unroll
         for (int q = 0; q < RP / 4; ++q)
-            y[q] = row < I && 4 * q + part < R ? M[row * R + 4 * q + part] : 0.0;
+            y[q] = row < I && 4 * q + part < R ? M[row * R + 4 * q + part] * scale[4 * q + part] : 0.0;
         solve_forward<RP>(y, Lf, R, part);
 #pragma unroll
         for (int q = 0; q < RP / 4; ++q)
             y[q] *= dinv[4 * q + part];
         solve_backward<RP>(y, Lf, R, part);
+#pragma unroll
+        for (int q = 0; q < RP / 4; ++q)
+            y[q] *= scale[4 * q + part];
         if (row < I) {
 #pragma unroll
             for (int q = 0; q < RP / 4; ++q)
@@ -534,7 +561,7 @@ factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag
 {
     __shared__ double Lf[kNB * (kNB + 1)], dinv[kNB], col[2][kNB];
     __shared__ double W[2][kNB][kNB + 1];
-    if (blockIdx.x > blockIdx.y || failed_before(flag))
+    if (blockIdx.x > blockIdx.y)
         return;
     const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4, lane = tid & 63, wave = tid >> 6;
     const int nb = R - j0 < kNB ? R - j0 : kNB, j1 = j0 + nb;
@@ -554,6 +581,8 @@ factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag
             const int vi = j1 + kNB * (int)blockIdx.y + i, vc = j1 + kNB * (int)blockIdx.x + c;
             v[p][q] = vi < R && vc <= vi ? V[(int64_t)vi * R + vc] : 0.0;
         }
+    if (failed_before(flag))      // (behind the loads, so that it does not delay them)
+        return;
     if (!factorise<kNB>(own, nb, col, Lf, dinv)) {
         if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0)
             flag[0] = 1;
@@ -598,7 +627,7 @@ factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag
         }
 }
 
-// Rows of A = M V^{-1} with V = L D L^T.  A workgroup owns 16 rows and takes them through the whole forward and
+// Rows of A = M V^{-1} = M S (L D L^T)^{-1} S.  A workgroup owns 16 rows and takes them through the whole forward and
 // backward solve: per block of 32 unknowns the first wavefront solves against the diagonal block (quads of lanes
 // as above), then all wavefronts subtract the block's multiples from the columns that follow, 16 at a time on the
 // matrix cores.  The 16 x R slab lies in LDS (LDSY, R <= 1024) or in A itself.  One launch instead of four
@@ -607,8 +636,8 @@ factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag
 typedef double double4_t __attribute__((ext_vector_type(4)));
 template <int WAVES, bool LDSY>
 __global__ void __launch_bounds__(64 * WAVES)
-solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv, int R, const double* __restrict__ M,
-                   double* A, int64_t I, const int* flag)
+solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv, const double* __restrict__ S, int R,
+                   const double* __restrict__ M, double* A, int64_t I, const int* flag)
 {
     extern __shared__ double slab[];
     __shared__ double Ld[2][kNB * (kNB + 1)];
@@ -634,7 +663,7 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
     };
     for (int r = wave; r < 16; r += WAVES)
         for (int c = lane; c < nblk * kNB; c += 64)
-            put(r, c, r < rows && c < R ? M[(r0 + r) * R + c] : 0.0);
+            put(r, c, r < rows && c < R ? M[(r0 + r) * R + c] * S[c] : 0.0);
     auto load_diag = [&](int b, int t0, int step) {        // entry (c, a), c > a, of the diagonal block b
         double* const o = Ld[b & 1];
         for (int t = t0; t < kNB * kNB; t += step) {
@@ -732,10 +761,9 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
         }
         __syncthreads();
     }
-    if (LDSY)
-        for (int r = wave; r < rows; r += WAVES)
-            for (int c = lane; c < R; c += 64)
-                A[(r0 + r) * R + c] = get(r, c);
+    for (int r = wave; r < rows; r += WAVES)
+        for (int c = lane; c < R; c += 64)
+            A[(r0 + r) * R + c] = get(r, c) * S[c];
 }
 
 // Columns of A (n entries) divided by their norms = the roots of the diagonal of the Gram matrix S, and the
@@ -813,7 +841,7 @@ struct Buffers {
     double* M = nullptr;        // max_n I_n x R
     double* G = nullptr;        // d x R x R Gram matrices
     double* V = nullptr;        // R x R (ranks above 64)
-    double* L = nullptr;        // R x R and 1 / D, R (ranks above 64)
+    double* L = nullptr;        // R x R, then R values 1 / D and the R scales (ranks above 64)
     double* gram_ws = nullptr;  // partial Gram matrices, or the fit's partial sums
     double* inner = nullptr;    // column sums of M * A (ranks up to 64)
     double* partial = nullptr;  // kNormBlocks values
@@ -878,18 +906,18 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
 
 // Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns; many: four, so
 // that several workgroups fit a compute unit.  Above rank 1024 the slab does not fit the 160 KB of LDS.
-void solve_big(const double* L, const double* dinv, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
+void solve_big(const double* L, const double* dinv, const double* S, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
 {
     const unsigned grid = (unsigned)ceil_div(I, 16);
     const size_t lds = (size_t)16 * (ceil_div(R, kNB) * kNB + 1) * sizeof(double);
     if (R > 1024) {
-        hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, dinv, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, dinv, S, R, M, A, I, flag);
     } else if (grid <= 512) {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, dinv, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, dinv, S, R, M, A, I, flag);
     } else {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((solve_rows_blocked<4, true>), dim3(grid), dim3(256), lds, st, L, dinv, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<4, true>), dim3(grid), dim3(256), lds, st, L, dinv, S, R, M, A, I, flag);
     }
 }
 
@@ -1279,7 +1307,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         };
         const int64_t chunks = ceil_div(max_I, kChunkRows);      // of the initial Gram matrices
         const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
-                     o_L = take(big ? (size_t)RR + R : 0),
+                     o_L = take(big ? (size_t)RR + 2 * R : 0),
                      o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * RR),
                      o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4);
         const size_t o_shared = off;
@@ -1322,13 +1350,14 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         if (!big) {
             n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, st);
         } else {
-            hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(RR, 256)), dim3(256), 0, st, b.G, ndim, RR, k, b.V);
+            hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(RR, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V,
+                               b.L + RR + R);
             double* const dinv = b.L + RR;
             for (int j0 = 0; j0 < R; j0 += kNB) {
                 const unsigned nt = R - j0 > kNB ? (unsigned)ceil_div(R - j0 - kNB, kNB) : 1u;
                 hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(256), 0, st, b.V, R, j0, b.L, dinv, b.flag);
             }
-            solve_big(b.L, dinv, R, b.M, factors[k], I, b.flag, st);
+            solve_big(b.L, dinv, dinv + R, R, b.M, factors[k], I, b.flag, st);
             gram(factors[k], I, R, b.gram_ws, b.V, st);
             const int64_t want = ceil_div(I * R + RR, 1024);
             hipLaunchKernelGGL(scale_by_gram, dim3((unsigned)(want < 4096 ? want : 4096)), dim3(256), 0, st, b.V, R, factors[k],

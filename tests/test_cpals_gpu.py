@@ -220,6 +220,33 @@ def test_cpals_update_launch_shapes(mt, dims, R, sweeps):
         assert err <= 1e-8, (m, err)
 
 
+# Start factors whose Gram products lie near the ends of the exponents: pivots below 2^-1024, whose reciprocal is infinite, and
+# above 2^1022, whose reciprocal is subnormal.  Values at 1e-310 carry about 45 bits, times the condition of V (11 to 450):
+# below 1e-11 in a factor, 1e-9 leaves room for the second sweep.
+@pytest.mark.parametrize("dims,R,low,high", [((40, 30, 20), 5, -258, 254.0), ((1100, 9, 7), 8, -258, 255.0),
+                                             ((65, 64, 63), 33, -259, 253.5), ((72, 66, 70), 70, -259, 253.14)])
+@pytest.mark.parametrize("end", ["low", "high"])
+def test_cpals_pivots_near_the_ends_of_the_exponents(mt, dims, R, low, high, end):
+    from oracle import cp_als_oracle, mttkrp_oracle
+    mttkrp_oracle.build()
+    X, A0 = problem(dims, R, 5)
+    X = X * (2.0 ** -400 if end == "low" else 2.0 ** 300)
+    A0 = [a * 2.0 ** (low if end == "low" else high) for a in A0]
+    V = (A0[1].t() @ A0[1]) * (A0[2].t() @ A0[2])
+    assert 1e-311 < float(V.diagonal().min()) and float(V.max()) < 1.7e308
+    assert float(V.diagonal().min()) < 2.0 ** -1024 if end == "low" else float(V.diagonal().max()) > 2.0 ** 1022
+    A_ref, lam_ref, fits_ref = cp_als_oracle.cp_als(inputs.as_ndarray_view(X, dims), [a.numpy() for a in A0], 2, 0.0)
+    for shared in (False, True):
+        Ad = [a.clone().cuda() for a in A0]
+        print("cp-als exponents dims=%s R=%d %s" % (dims, R, end), flush=True)
+        lam, fits = mt.mttkrp_cpals(X.cuda(), dims, Ad, 2, 0.0, shared=shared)
+        np.testing.assert_allclose(fits, fits_ref, rtol=0, atol=1e-9)
+        np.testing.assert_allclose(lam.cpu().numpy(), lam_ref, rtol=1e-9)
+        for m in range(len(dims)):
+            err = np.linalg.norm(Ad[m].cpu().numpy() - A_ref[m]) / np.linalg.norm(A_ref[m])
+            assert err <= 1e-9, (m, err)
+
+
 def test_cpals_norm_of_an_unaligned_tensor(mt):
     # X that starts 8 bytes off a 16-byte boundary, odd and even length: ||X|| enters every fit
     from oracle import cp_als_oracle, mttkrp_oracle
