@@ -45,7 +45,7 @@ template <typename T> __device__ __forceinline__ typename Types<T>::piece_t load
     return v;
 }
 
-template <typename T, int JB, int CW>
+template <typename T, int JB, int CW, bool CHAINS>
 __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_contract_kernel(const ContractArgs<T> p)
 {
     typedef Types<T> TT;
@@ -133,10 +133,35 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
 
     // --- consumer
     acc_t acc[JB];
-    auto clear = [&]() {
+    // CHAINS (fp32): after p.chain stages the accumulators go into fp64 sums, so that no chain of fp32 sums is longer than
+    // the row splits of the kernel this one replaces, however few its own are
+    double sum[CHAINS ? JB : 1][4];
+    int chain = p.chain;
+    auto clear_acc = [&]() {
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb)
             acc[jb] = (acc_t)(0);
+        chain = p.chain;
+    };
+    auto clear = [&]() {
+        clear_acc();
+        if constexpr (CHAINS) {
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    sum[jb][q] = 0.0;
+        }
+    };
+    auto end_chain = [&]() {
+        if constexpr (CHAINS) {
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    sum[jb][q] += (double)acc[jb][q];
+            clear_acc();
+        }
     };
     // natural output column (inside the workgroup's NC) of block jb in this lane: chunks of G blocks, consecutive
     // columns per lane inside a chunk, so that one LDS read fetches a chunk's entries
@@ -190,6 +215,12 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
         }
     };
     auto store = [&](const Item& o) {
+        auto value = [&](int jb, int q) {
+            if constexpr (CHAINS)
+                return (T)(sum[jb][q] + (double)acc[jb][q]);
+            else
+                return acc[jb][q];
+        };
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int64_t c = o.c0 + 16 * cw + TT::row(lane, q);
@@ -200,7 +231,7 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
                     const int nat = natural(jb), first = nat / G * G;                   // of its piece
                     const int j = (first + G <= p.R ? first : p.R - G) + nat % G;
                     if (j >= first)                                                     // else it belongs to another piece
-                        dst[j] = acc[jb][q];
+                        dst[j] = value(jb, q);
                 }
             }
         }
@@ -236,6 +267,8 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
                 cur = item_of(c_item);
                 c_row = cur.r0;
             }
+        } else if (CHAINS && --chain == 0) {
+            end_chain();
         }
         stash(xr[par ^ 1], kr[par ^ 1], par ^ 1);
         __syncthreads();
@@ -299,20 +332,33 @@ __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T
     }
 }
 
+// The fp64 sums spill where three workgroups of four wavefronts share a compute unit at two blocks of output columns (10^6 x
+// 400 at R = 32: 0.356 -> 0.428 ms): more row splits keep the chains short there.
+constexpr bool has_chains(int JB, int CW) { return !(JB == 2 && CW == 4); }
+
 int lds_bytes(int JB, int CW) { return 2 * (16 * CW * kPieces * 16 + 4096 * JB); }
 
-template <typename T, int JB, int CW>
-void launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st)
+template <typename T, int JB, int CW, bool CHAINS>
+void launch_kernel(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st)
 {
     const size_t lds = (size_t)lds_bytes(JB, CW);
     if (lds > 65536)
-        (void)hipFuncSetAttribute((const void*)mttkrp_contract_kernel<T, JB, CW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((mttkrp_contract_kernel<T, JB, CW>), dim3((unsigned)pl.grid), dim3(64 * CW), lds, st, a);
+        (void)hipFuncSetAttribute((const void*)mttkrp_contract_kernel<T, JB, CW, CHAINS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((mttkrp_contract_kernel<T, JB, CW, CHAINS>), dim3((unsigned)pl.grid), dim3(64 * CW), lds, st, a);
+}
+template <typename T, int JB, int CW>
+void launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 4 && has_chains(JB, CW))
+        if (pl.chain > 0)
+            return launch_kernel<T, JB, CW, true>(pl, a, st);
+    launch_kernel<T, JB, CW, false>(pl, a, st);
 }
 
 }  // namespace
 
-ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64_t max_splits, int64_t target_items, int64_t max_rows)
+ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64_t max_splits, int64_t target_items, int64_t max_rows,
+                                  int64_t max_chain)
 {
     ContractPlan pl;
     const int G = 16 / sbytes, SR = kPieces * G;
@@ -338,7 +384,11 @@ ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64
     if (max_rows <= 0 || max_rows > ((int64_t)1 << 40))
         max_rows = (int64_t)1 << 40;
     if (sbytes == 4 && max_rows > 4096)
-        max_rows = 4096;               // fp32: accumulation chains of at most 4096 terms
+        max_rows = 4096;
+    if (sbytes == 8 || max_chain <= 0)
+        max_chain = max_rows;
+    if (!has_chains(pl.JB, pl.CW) && max_rows > max_chain)
+        max_rows = max_chain;
     int64_t best = 1;
     if (target_items > 0) {
         best = (target_items + pl.n_ctile - 1) / pl.n_ctile;
@@ -357,10 +407,15 @@ ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64
             }
         }
     }
-    int64_t per = (stages + best - 1) / best;
-    if (per * SR > max_rows)
-        per = max_rows / SR > 0 ? max_rows / SR : 1;
-    pl.rows_per_split = per * SR;
+    pl.rows_per_split = (stages + best - 1) / best * SR;
+    if (pl.rows_per_split > max_rows) {
+        // whole stages, unless that makes more splits (partial sums) than asked for; one stage at least
+        pl.rows_per_split = max_rows / SR * SR;
+        if (pl.rows_per_split < SR || (P + pl.rows_per_split - 1) / pl.rows_per_split > max_splits)
+            pl.rows_per_split = max_rows > SR ? max_rows : SR;
+    }
+    if (pl.rows_per_split > max_chain && P > max_chain)
+        pl.chain = max_chain / SR > 0 ? (int)(max_chain / SR) : 1;
     const int64_t n = (P + pl.rows_per_split - 1) / pl.rows_per_split;
     if (n >= (1 << 20) || pl.n_ctile >= ((int64_t)1 << 31) || pl.n_ctile * n >= ((int64_t)1 << 40))
         return pl;

@@ -1427,7 +1427,8 @@ int plan_leading(int64_t P, int64_t Q, int R, int sbytes, LeadingPlan& pl)
     pl.n_rsplit = pl.plain_rsplit = (int)n_rsplit;
     // The kernel through LDS wherever it takes the shape (its tiles are not the ones the two keys choose among)
     if (tn.rows_col_blocks == 0 && tn.max_col_blocks == 0 && tn.lds_contract != 2)
-        pl.cp = mttkrp_contract_plan(P, Q, R, sbytes, n_rsplit, tn.target_items, 16 * tn.max_steps);
+        // (fp32: chains of fp32 sums no longer than the other kernel's, whose row splits are added in fp64)
+        pl.cp = mttkrp_contract_plan(P, Q, R, sbytes, n_rsplit, tn.target_items, 16 * tn.max_steps, rows);
     if (pl.cp.ok) {
         pl.n_rsplit = pl.cp.n_rsplit;
         pl.rows_per_split = (int)pl.cp.rows_per_split;
@@ -1673,7 +1674,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             const int64_t Q = pl.N / dims[0];
             if (tn.lds_contract != 2 && memcmp(&rest, &none, sizeof(rest)) == 0 && dims[0] < ((int64_t)1 << 31) && Q < ((int64_t)1 << 31) - 256) {
                 // (fp32: accumulation chains no longer than the other kernel's)
-                const ContractPlan cp = mttkrp_contract_plan(dims[0], Q, R, sbytes, 4096, 0, sbytes == 4 ? pl.rows_per_split : 0);
+                const ContractPlan cp = mttkrp_contract_plan(dims[0], Q, R, sbytes, 4096, 0, sbytes == 4 ? pl.rows_per_split : 0, 0);
                 const double s_bytes = (double)Q * cp.n_rsplit * R * sbytes;
                 const int64_t pairs = C * cp.n_rsplit;
                 int64_t segs = ceil_div(2048, dims[k] * ceil_div(R, 32));
@@ -2655,6 +2656,7 @@ int launch_leading(const LeadingPlan& pl, int64_t P, int64_t Q, const T* X, cons
         ca.R = R;
         ca.n_rsplit = pl.cp.n_rsplit;
         ca.n_ctile = (int32_t)pl.cp.n_ctile;
+        ca.chain = pl.cp.chain;
         (void)hipGetLastError();
         const int rc = mttkrp_contract_launch<T>(pl.cp, ca, st);
         if (rc != MTTKRP_OK)
@@ -2941,6 +2943,7 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
         ca.R = R;
         ca.n_rsplit = pl.cp.n_rsplit;
         ca.n_ctile = (int32_t)pl.cp.n_ctile;
+        ca.chain = pl.cp.chain;
         ModeSumArgs<T, T> ms;
         memset(&ms, 0, sizeof(ms));
         ms.S = S;

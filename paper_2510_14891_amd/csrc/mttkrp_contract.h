@@ -16,7 +16,8 @@ struct ContractPlan {
     int CW = 4;                  // wavefronts along the tensor columns, 16 each
     int64_t n_ctile = 1;         // tiles of 16 CW tensor columns
     int n_rsplit = 1;
-    int64_t rows_per_split = 0;  // multiple of a stage's rows (the last split takes what is left)
+    int64_t rows_per_split = 0;  // a stage's rows at least (the last split takes what is left)
+    int chain = 0;               // fp32: stages that are added in fp32 before they go into fp64 sums (0: all of a split)
     int64_t n_items = 1;
     int grid = 1;                // persistent workgroups
 };
@@ -27,13 +28,13 @@ template <typename T> struct ContractArgs {
     T* out;                      // row c, split s at out + (c n_rsplit + s) ld_out
     int64_t P, Q, ldK, ld_out;
     int64_t rows_per_split, n_items;
-    int32_t R, n_rsplit, n_ctile;
+    int32_t R, n_rsplit, n_ctile, chain;
 };
 
 // max_splits: row splits at most; target_items > 0: row splits until that many work items exist; max_rows > 0: rows per
-// split at most
+// split at most; fp32: max_chain > 0: rows that are added in fp32 at most (else those of a split, at most 4096)
 MTTKRP_INTERNAL ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64_t max_splits, int64_t target_items,
-                                                  int64_t max_rows);
+                                                  int64_t max_rows, int64_t max_chain);
 template <typename T>
 MTTKRP_INTERNAL int mttkrp_contract_launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st);
 

@@ -97,3 +97,26 @@ def test_contraction_non_finite_rows_beside_masked_ones(mt, dtype):
     want[3, :] = float("inf")
     want[:, 2] = float("inf")
     assert torch.equal(T, want)
+
+
+# Calls whose own row splits are longer than the chains of the kernel that "lds_contract" = 2 selects: both add the same number
+# of products in single precision and the rest in double precision, so their errors agree up to the scatter of
+# tens of thousands of outputs (1.25) and the rounding of a result (2e-8).  One to four blocks of output columns, tiles of 64 and
+# 128 columns, splits of whole stages and not.
+@pytest.mark.parametrize("P,Q,R", [(3978, 2857, 17), (4096, 2000, 32), (5000, 9000, 10), (16641, 500, 4), (20000, 130, 10),
+                                   (8000, 3000, 40), (8000, 3000, 64), (30000, 130, 20), (300000, 300, 32), (1300, 20000, 24)])
+def test_single_precision_chains_are_no_longer_than_the_other_kernels(mt, P, Q, R):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(P)
+    for signed in (False, True):
+        X = torch.rand((Q, P), dtype=torch.float32, device="cuda", generator=g) - 0.5 * signed
+        K = torch.rand((P, R), dtype=torch.float32, device="cuda", generator=g) - 0.5 * signed
+        W = torch.cat([X[q:q + 512].double() @ K.double() for q in range(0, Q, 512)])
+        err = []
+        for v in (0, 2):
+            mt.mttkrp_tune_set("lds_contract", v)
+            print("contract chains P=%d Q=%d R=%d lds_contract=%d" % (P, Q, R, v), flush=True)
+            T = mt.mttkrp_contract_leading(X.view(-1), P, Q, K)
+            mt.mttkrp_tune_set("lds_contract", 0)
+            err.append(float((T.double() - W).norm() / W.norm()))
+        assert err[0] <= 1.25 * err[1] + 2e-8, err
