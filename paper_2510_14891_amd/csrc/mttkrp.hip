@@ -1316,6 +1316,13 @@ struct Tuning {
 Tuning g_tune;
 std::mutex g_mutex;
 
+// The keys as they are now.  Taken once per call: what is planned in pieces is planned with the same keys throughout.
+Tuning tuning()
+{
+    std::lock_guard<std::mutex> lock(g_mutex);
+    return g_tune;
+}
+
 struct LeadingPlan {
     int JB = 1, n_jchunk = 1, CB = 1, n_cchunk = 1, n_rsplit = 1, rows_per_split = 16;
     int64_t n_items = 0;
@@ -1382,7 +1389,7 @@ struct Plan {
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-int plan_leading(int64_t P, int64_t Q, int R, int sbytes, LeadingPlan& pl)
+int plan_leading(int64_t P, int64_t Q, int R, int sbytes, const Tuning& tn, LeadingPlan& pl)
 {
     if (P < 1 || Q < 1 || R < 1 || (sbytes != 4 && sbytes != 8))
         return MTTKRP_ERR_INVALID_ARG;
@@ -1390,11 +1397,6 @@ int plan_leading(int64_t P, int64_t Q, int R, int sbytes, LeadingPlan& pl)
         return MTTKRP_ERR_INVALID_ARG;
     if (P >= ((int64_t)1 << 31) - 64 || Q >= ((int64_t)1 << 31) - 64 || R >= (1 << 27))
         return MTTKRP_ERR_UNSUPPORTED;
-    Tuning tn;
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        tn = g_tune;
-    }
     // tiles as in the second schedule: at most eight accumulator tiles per wavefront
     const int jb_total = (int)ceil_div(R, 16);
     const int jb_max = tn.max_col_blocks >= 1 && tn.max_col_blocks <= 8 ? (int)tn.max_col_blocks
@@ -2134,7 +2136,7 @@ void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, c
             return;
     }
     LeadingPlan lp;
-    if (plan_leading(P, Q, R, sbytes, lp) != MTTKRP_OK)
+    if (plan_leading(P, Q, R, sbytes, tn, lp) != MTTKRP_OK)
         return;
     // few output rows leave few work items, or need row splits with partial sums: not then
     // (16 x 16 x 16 x 50000 at R = 8 with six row splits: 0.34 ms against 0.30 ms on the streaming kernel)
@@ -2705,7 +2707,7 @@ int run_leading(int64_t P, int64_t Q, const T* X, const T* K, int64_t ldK, int R
     if (!X || !K || !out)
         return MTTKRP_ERR_INVALID_ARG;
     LeadingPlan pl;
-    const int rc = plan_leading(P, Q, R, (int)sizeof(T), pl);
+    const int rc = plan_leading(P, Q, R, (int)sizeof(T), tuning(), pl);
     if (rc != MTTKRP_OK)
         return rc;
     if (ldK < R || ldK >= ((int64_t)1 << 27) || ld_out < R || ld_out >= ((int64_t)1 << 27))
@@ -3308,7 +3310,7 @@ int mttkrp_dense_f32_ld(int ndim, const int64_t* dims, const float* X, const flo
 size_t mttkrp_contract_leading_workspace_bytes(int64_t P, int64_t Q, int R, int dtype_bytes)
 {
     LeadingPlan pl;
-    if (plan_leading(P, Q, R, dtype_bytes, pl) != MTTKRP_OK)
+    if (plan_leading(P, Q, R, dtype_bytes, tuning(), pl) != MTTKRP_OK)
         return (size_t)-1;
     return pl.ws_bytes;
 }

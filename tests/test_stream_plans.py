@@ -2,9 +2,11 @@
 every choice keeps of the plan it replaces (scratch, length of fp32 sums, validity after tuning), and calls whose plan
 changes against the CPU oracle: each mode, both types, rows paired or fused and not, 16 to 64 rows per wavefront, odd
 extents.  Tolerances are those of every parity test: 1e-12 (fp64) and 1e-5 (fp32), normwise."""
+import ctypes
 import math
 import random
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -71,6 +73,40 @@ def test_chosen_plans_keep_their_bounds(mt):
         if b == 4:
             assert int(now["steps_per_item"]) <= int(base["steps_per_item"]), (dims, R, k)
     assert changed > 50
+
+
+TUNER = """
+#include <pthread.h>
+#include <stdint.h>
+static volatile int stop;
+static pthread_t thread;
+typedef int (*set_fn)(const char*, int64_t);
+static void* work(void* f)
+{
+    while (!stop) { ((set_fn)f)("rows_col_blocks", 1); ((set_fn)f)("rows_col_blocks", 0); }
+    return 0;
+}
+int tuner_start(void* f) { stop = 0; return pthread_create(&thread, 0, work, f); }
+void tuner_stop(void) { stop = 1; pthread_join(thread, 0); }
+"""
+
+
+def test_a_plan_is_made_with_one_set_of_keys(mt, tmp_path):
+    """Last modes that run as a contraction over all the others, planned while another thread sets and clears a key that only
+    this contraction reads (16 columns a wavefront).  With the key set the kernel for small tensors is off: a line with both
+    comes from a plan made half with the key, and would be kept as the plan at default settings."""
+    src, so = tmp_path / "tuner.c", tmp_path / "tuner.so"
+    src.write_text(TUNER)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-pthread", "-o", str(so), str(src)], check=True)
+    tuner = ctypes.CDLL(str(so))
+    assert tuner.tuner_start(ctypes.cast(mt.lib().mttkrp_tune_set, ctypes.c_void_p)) == 0
+    try:
+        lines = [mt.mttkrp_plan_describe((7, 3, 3, 3000 + i), 32, 3, 8) for i in range(20000)]
+    finally:
+        tuner.tuner_stop()
+        mt.mttkrp_tune_set("rows_col_blocks", 0)
+    assert all("shape=leading" in line for line in lines)
+    assert not any("small_route=1" in line and "cols_per_wave=16" in line for line in lines)
 
 
 # Calls whose faster routes would take more scratch than the 64 MiB of mttkrp_dense_f64_noalloc where the general plan does
