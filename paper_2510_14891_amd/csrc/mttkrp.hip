@@ -2394,18 +2394,48 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
 }
 
 // Plans at default settings are kept by shape: a call pays for the planning above once (15 us with the candidates of
-// better_stream_plan, as long as a small call) and then for a look-up.  One entry per hash, overwritten; g_mutex held.
+// better_stream_plan, as long as a small call) and then for a look-up.  Sixteen sets of eight plans, the least recently used
+// one of a set makes room: a tensor has at most eight modes, so no two of them can drive each other out (with one entry per
+// hash 4 % of the three-way and 21 % of the six-way shapes planned two of their modes anew at every call, 5 to 21 us).
+// g_mutex held.
 struct PlanKey {
     int64_t dims[MTTKRP_MAX_NDIM];
     int32_t ndim, R, k, sbytes;
 };
-constexpr int kPlanEntries = 64;
+constexpr int kPlanSets = 16, kPlanWays = 8;
+static_assert(kPlanWays >= MTTKRP_MAX_NDIM, "the modes of a tensor fit in one set");
 struct PlanEntry {
-    bool used = false;
+    uint64_t last_use = 0;       // 0: empty
+    uint64_t hash = 0;
     PlanKey key;
     Plan plan;
 };
-PlanEntry g_plans[kPlanEntries];
+PlanEntry g_plans[kPlanSets][kPlanWays];
+uint64_t g_plan_clock = 0;
+
+PlanEntry* kept_plan(uint64_t hash, const PlanKey& key)
+{
+    for (PlanEntry& e : g_plans[(hash >> 40) % kPlanSets])
+        if (e.last_use && e.hash == hash && memcmp(&e.key, &key, sizeof(key)) == 0) {
+            e.last_use = ++g_plan_clock;
+            return &e;
+        }
+    return nullptr;
+}
+
+void keep_plan(uint64_t hash, const PlanKey& key, const Plan& pl)
+{
+    PlanEntry* oldest = &g_plans[(hash >> 40) % kPlanSets][0];
+    if (kept_plan(hash, key))    // another thread was faster
+        return;
+    for (PlanEntry& e : g_plans[(hash >> 40) % kPlanSets])
+        if (e.last_use < oldest->last_use)
+            oldest = &e;
+    oldest->last_use = ++g_plan_clock;
+    oldest->hash = hash;
+    oldest->key = key;
+    oldest->plan = pl;
+}
 
 int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 {
@@ -2420,7 +2450,6 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
         h = (h ^ (uint64_t)dims[m]) * 0x9e3779b97f4a7c15ull;
     }
     key.ndim = ndim; key.R = R; key.k = k; key.sbytes = sbytes;
-    PlanEntry& e = g_plans[(h >> 40) % kPlanEntries];
     const Tuning none;
     Tuning tn;
     bool tuned;
@@ -2428,17 +2457,16 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
         std::lock_guard<std::mutex> lock(g_mutex);
         tn = g_tune;
         tuned = memcmp(&tn, &none, sizeof(tn)) != 0;
-        if (!tuned && e.used && memcmp(&e.key, &key, sizeof(key)) == 0) {
-            pl = e.plan;
-            return MTTKRP_OK;
-        }
+        if (!tuned)
+            if (const PlanEntry* e = kept_plan(h, key)) {
+                pl = e->plan;
+                return MTTKRP_OK;
+            }
     }
     rc = choose_plan(ndim, dims, R, k, sbytes, tn, tuned, pl);
     if (rc == MTTKRP_OK && !tuned) {
         std::lock_guard<std::mutex> lock(g_mutex);
-        e.key = key;
-        e.plan = pl;
-        e.used = true;
+        keep_plan(h, key, pl);
     }
     return rc;
 }
