@@ -320,6 +320,7 @@ int mttkrp_tune_set(const char* key, int64_t value);
  * workspace bytes) into buf (always NUL-terminated when buflen > 0).  For a small tensor
  * that runs on the kernel for small tensors the line begins with "small_route=1" and that
  * kernel's figures; the decomposition after the bar is what "small_route" = 2 would run.
+ * "lds=1" after "shape=rows": the kernel of "lds_contract" runs, then a sum in "segments" pieces.
  */
 int mttkrp_plan_describe(int ndim, const int64_t* dims, int R, int k,
                          int dtype_bytes, char* buf, size_t buflen);

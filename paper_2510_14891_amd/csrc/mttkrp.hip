@@ -3559,9 +3559,11 @@ int mttkrp_plan_describe(int ndim, const int64_t* dims, int R, int k, int dtype_
         snprintf(buf, buflen,
                  "shape=rows cols_per_wave=%d col_chunks=%d col_blocks=%d j_chunks=%d batch=%d "
                  "row_splits=%d outer_splits=1 inner_splits=1 "
-                 "items=%lld steps_per_item=%lld slots=%lld ws_bytes=%zu fused_modes=-1 fused_rows=0 fused_bytes=%zu",
+                 "items=%lld steps_per_item=%lld slots=%lld ws_bytes=%zu fused_modes=-1 fused_rows=0 fused_bytes=%zu "
+                 "lds=%d segments=%d",
                  16 * pl.CB, pl.n_cchunk, pl.JB, pl.n_jchunk, pl.n_batch, pl.n_rsplit, (long long)pl.n_items,
-                 (long long)pl.steps_per_item, (long long)pl.n_slots, pl.ws_bytes, pl.fused_bytes);
+                 (long long)pl.steps_per_item, (long long)pl.n_slots, pl.ws_bytes, pl.fused_bytes, pl.cp.ok ? 1 : 0,
+                 pl.cp.ok ? pl.cp_segs : 0);
         return MTTKRP_OK;
     }
     snprintf(buf, buflen,

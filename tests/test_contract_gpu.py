@@ -55,9 +55,11 @@ def test_contraction_through_lds(mt, oracle, P, Q, R, tune, dtype):
         assert torch.equal(T[:, :R], again) and bool((T[:, R:] == 3.0).all())
 
 
+# Every mode but the first of these runs on the contraction and the weighted sum of its result (asserted from the plan): one
+# and several segments of that sum, row splits, modes of one entry, the output mode first, between and last among the others.
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("dims,R", [((3000, 20, 20), 32), ((2573, 7, 9), 5), ((4001, 3, 1, 2, 4), 17), ((9000, 65, 3), 16),
-                                    ((4000, 30, 29), 8)])
+@pytest.mark.parametrize("dims,R", [((30000, 3, 5), 4), ((840, 2, 3, 2, 1), 4), ((53899, 2, 5, 2), 4), ((12024, 28, 1), 5),
+                                    ((60000, 7, 9), 5)])
 def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
     X = inputs.uniform(7, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
     A = [inputs.uniform(8 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
@@ -65,11 +67,13 @@ def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
     Xd, Ad = X.cuda(), [a.cuda() for a in A]
     lam = inputs.uniform(9, R, 0.5, 1.5, dtype=dtype)
     for k in range(1, len(dims)):
-        print("modes from the contraction dims=%s R=%d k=%d %s" % (
-            dims, R, k, mt.mttkrp_plan_describe(dims, R, k, X.element_size())), flush=True)
+        mt.mttkrp_tune_set("small_route", 2)
+        plan = mt.mttkrp_plan_describe(dims, R, k, X.element_size())
+        mt.mttkrp_tune_set("small_route", 0)
+        print("modes from the contraction dims=%s R=%d k=%d %s" % (dims, R, k, plan), flush=True)
+        assert "shape=rows" in plan and "lds=1" in plan
         ref = oracle.mttkrp(Xn, An, k)
         mt.mttkrp_tune_set("small_route", 2)
-        mt.mttkrp_tune_set("lds_contract", 1)
         got = mt.mttkrp_dense(Xd, dims, Ad, k)
         wide = [torch.full((I, R + 1), float("nan"), dtype=dtype, device="cuda") for I in dims]
         for w, a in zip(wide, Ad):
@@ -77,11 +81,35 @@ def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
         Mw = torch.full((dims[k], R + 3), 1.0, dtype=dtype, device="cuda")
         mt.mttkrp_dense_ld(Xd, dims, [w[:, :R] for w in wide], k, Mw[:, :R], R, lam=lam.cuda(), beta=0.5)
         mt.mttkrp_tune_set("small_route", 0)
-        mt.mttkrp_tune_set("lds_contract", 0)
         assert oracle.normwise_rel_err(got.cpu().numpy(), ref) <= TOL[dtype], k
         ref2 = oracle.mttkrp(Xn, An, k, lam=lam.numpy()) + 0.5
         assert oracle.normwise_rel_err(Mw[:, :R].cpu().numpy(), ref2) <= TOL[dtype], k
         assert bool((Mw[:, R:] == 1.0).all())
+
+
+# The same with two and three blocks of output columns, which this route takes for longer first modes only: against float64
+# products on the GPU.
+@pytest.mark.parametrize("dims,R,k,dtype", [((120000, 3, 130), 20, 2, torch.float64), ((120000, 3, 130), 20, 2, torch.float32),
+                                            ((100001, 20, 20), 17, 1, torch.float64), ((280001, 20, 20), 48, 2, torch.float64),
+                                            ((1100000, 20, 20), 32, 1, torch.float32)])
+def test_modes_from_the_contraction_at_higher_ranks(mt, dims, R, k, dtype):
+    plan = mt.mttkrp_plan_describe(dims, R, k, torch.empty((), dtype=dtype).element_size())
+    print("modes from the contraction dims=%s R=%d k=%d %s" % (dims, R, k, plan), flush=True)
+    assert "shape=rows" in plan and "lds=1" in plan
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    X = torch.rand((dims[2], dims[1], dims[0]), dtype=dtype, device="cuda", generator=g) - 0.5
+    A = [torch.rand((I, R), dtype=dtype, device="cuda", generator=g) - 0.5 for I in dims]
+    S = torch.stack([X[i].double() @ A[0].double() for i in range(dims[2])])          # i_2, i_1, j
+    want = torch.zeros((dims[k], R), dtype=torch.float64, device="cuda")
+    for i in range(dims[3 - k]):
+        want += (S[i] if k == 1 else S[:, i]) * A[3 - k][i].double()
+    got = mt.mttkrp_dense(X.view(-1), dims, A, k)
+    assert float((got.double() - want).norm() / want.norm()) <= TOL[dtype]
+    lam = torch.rand(R, dtype=dtype, device="cuda", generator=g) + 0.5
+    acc = mt.mttkrp_dense(X.view(-1), dims, A, k, M=got.clone(), lam=lam, beta=-0.5)
+    want = want * lam.double() - 0.5 * got.double()
+    assert float((acc.double() - want).norm() / want.norm()) <= 2.0 * TOL[dtype]
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
