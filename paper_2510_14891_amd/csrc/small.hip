@@ -62,14 +62,18 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
     const int js0 = min(jt0, R - LC::n0), js1 = LC::n1 > 0 ? min(jt1, R - LC::n1) : 0;
     auto column = [&](int jb) { return jb < LC::n0 ? js0 + jb : js1 + (jb - LC::n0); };
     auto owned = [&](int jb) { return jb < LC::n0 ? column(jb) >= jt0 : column(jb) >= jt1; };
+    // (the first entry's address is formed before the others are counted from it: a 32-bit index for each of them could
+    // wrap as far as the compiler knows, and they stay separate loads)
     auto load_cols = [&](const T* a, uint32_t off, T (&v)[JB]) {
+        const T* const a0 = a + (off + (uint32_t)js0);
 #pragma unroll
         for (int jb = 0; jb < LC::n0; ++jb)
-            v[jb] = a[off + (uint32_t)js0 + jb];
+            v[jb] = a0[jb];
         if constexpr (LC::n1 > 0) {
+            const T* const a1 = a + (off + (uint32_t)js1);
 #pragma unroll
             for (int jb = 0; jb < LC::n1; ++jb)
-                v[LC::n0 + jb] = a[off + (uint32_t)js1 + jb];
+                v[LC::n0 + jb] = a1[jb];
         }
     };
     const T* const xb = FIRST ? p.X : p.X + (int64_t)blockIdx.x * p.sx_batch;
