@@ -2205,14 +2205,58 @@ int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, c
     return MTTKRP_OK;
 }
 
-// One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times in us, fitted
-// to 2600 calls (fp64 and fp32, two to eight modes, 2^7 to 2^27 values, R = 1 to 147; median error 14 and 9 %).
-// A launch costs 2.3 to 3.6 us, whatever it does, on top of the first.  The small kernel is bound by the
-// instructions of the few compute units it runs on (MFMAs and the address arithmetic of its columns), the general
-// one by its launches and the length of its items.  Taken when its estimate is below 0.8 of the other: over those
-// calls 1.20 times faster in the mean (1.5 times below 2^13 values, 1.2 at 2^18, 1.05 at 2^21, none from 2^24 on), 2 %
-// of the calls more than 10 % slower.
-double small_cost(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
+// One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times on the GPU in us, fitted
+// to one half of 5650 calls (fp64 and fp32, two to eight modes, 2^8 to 2^23 values, R = 2 to 1000, each with one to three
+// numbers of groups).  On the other half the median error is 10 and 9 %.  Over 11 000 further calls that
+// the rule below gives to the small kernel they take 0.56 times as long in the mean (0.53 below 2^16 values, 0.59 at 2^18, 0.71
+// at 2^20, 0.79 at 2^21); 1.9 % of them are more than 5 % slower, the worst 1.8 times.
+// The small kernel by its number of column modes (one, two, others), per workgroup:
+struct SmallFit {
+    double base, mfma, loads, alu, sweep;      // launch; matrix cores, load instructions, address arithmetic; a sweep's start and end
+    double crowd, rounds;                      // the share of each workgroup beyond one a compute unit; beyond what is resident
+    double combine, part;                      // the second launch and its MB
+    double cold, bytes, spill;                 // batches of loads from beyond L2; MB of X; spilled registers (fp64, four blocks of columns)
+};
+const SmallFit small_fit[3] = {{2.00, 1.67, 1.93, 0.00, 1.65, 1.92, 0.73, 2.46, 0.70, 0.03, 0.059, 1.09},
+                               {2.00, 1.27, 0.00, 0.75, 1.84, 1.72, 1.13, 2.59, 1.06, 0.00, 0.107, 5.72},
+                               {2.73, 0.71, 4.60, 1.35, 2.87, 1.72, 1.11, 3.12, 0.57, 1.25, 0.149, 3.55}};
+double small_cost(const SmallPlan& sp, int sbytes, int n_modes, int64_t N, double part_bytes, bool first)
+{
+    const SmallFit& f = small_fit[n_modes == 1 ? 0 : (n_modes == 2 ? 1 : 2)];
+    const int batch = sp.RB * sp.JB <= 2 ? 8 : 4;
+    const double units = (double)sp.n_tiles * sp.n_ranges, per = (double)(sp.cols_per_range / 4), steps = units * per / 2200.0;
+    const double sweeps = ceil(units / sp.waves), mb = 1e-6 * (double)N * sbytes;
+    const double busy = f.mfma * steps * sp.RB * sp.JB * (sbytes == 8 ? 16.0 : 8.0) +
+                        f.loads * steps * (sp.RB + n_modes * (double)ceil_div(sp.JB, 16 / sbytes)) +
+                        f.alu * steps * (n_modes * (6 + sp.JB * (sbytes / 4)) + 8 + 4 * sp.RB);
+    const double groups = (double)sp.blocks * sp.n_jchunk * sp.n_groups / 256.0, rounds = groups / (16 / sp.waves);
+    double t = f.base + busy + f.sweep * sweeps + f.crowd * (groups > 1.0 ? groups - 1.0 : 0.0) * busy +
+               f.rounds * (rounds > 1.0 ? rounds - 1.0 : 0.0) * (f.base - 2.0 + f.sweep * sweeps) +
+               f.cold * sweeps * ceil(per / batch) * (mb < 16.0 ? mb / 16.0 : 1.0) + f.bytes * mb;
+    if (sp.n_groups > 1)
+        t += f.combine + f.part * 1e-6 * part_bytes;
+    if (sbytes == 8 && sp.JB == 4 && !first)
+        t += f.spill * sweeps;
+    return t;
+}
+
+double general_cost(const Plan& pl, int ndim)
+{
+    const bool paired_second = pl.seg > 0 && !pl.seg_first;
+    const bool prepare = pl.fused_bytes > 0 || paired_second || pl.contract_rows;
+    const bool combine = pl.n_slots > 1 || pl.seg > 0;
+    const int tiles = (pl.contract_rows || pl.lead_route ? 1 : pl.RB) * (pl.lead_route ? pl.lead.JB : pl.JB);
+    const double items = (double)pl.n_items, steps = (double)pl.steps_per_item;
+    return 3.38 + (prepare ? 2.52 : 0.0) + (combine ? 2.45 : 0.0) + (pl.seg > 0 ? 2.71 : 0.0) + (pl.lead_route ? 0.78 : 0.0) +
+           (ndim > 3 ? 0.92 : 0.0) + 0.045 * steps * (items > 3072.0 ? items / 3072.0 : 1.0) +
+           1.31 * (items > 1024.0 ? items / 1024.0 : 1.0) * tiles * (pl.sbytes == 8 ? 64.0 : 32.0) * steps / 2200.0 +
+           0.0406e-6 * (double)pl.N * pl.sbytes + 1.15e-3 * items + 0.837e-6 * (double)pl.ws_bytes + 0.197 * tiles;
+}
+
+// From 2^20 values on, where there is less to gain, a second fit has to agree (2600 other calls, timed with their host
+// work, fewer terms): calls that only the first would take there are 0.84 times as long in the mean and 24 % of them more than
+// 5 % slower, those that both take 0.76 and 11 %.
+double small_cost_from_2_20(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
 {
     const double steps = (double)sp.n_tiles * sp.n_ranges * (sp.cols_per_range / 4);       // of one workgroup
     const double cycles = sbytes == 8 ? 64.0 : 32.0;
@@ -2226,7 +2270,7 @@ double small_cost(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
            0.027e-6 * (double)N * sbytes;
 }
 
-double general_cost(const Plan& pl)
+double general_cost_from_2_20(const Plan& pl)
 {
     const bool paired_second = pl.seg > 0 && !pl.seg_first;
     const bool prepare = pl.fused_bytes > 0 || paired_second || pl.contract_rows;
@@ -2360,7 +2404,12 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         return rc;
     const int n_modes = k == 0 ? ndim - 1 : ndim - 2;
     SmallPlan best;
-    double best_cost = tn.small_route == 1 ? 1e300 : 0.8 * general_cost(pl);
+    // At 0.8 the calls that get slower are few (half of the fit's data: 1.8 % more than 5 % slower, at 0.9 3.8 %, for 0.765 instead
+    // of 0.775 times as long in the mean over all calls); beyond 2^22 values most would.
+    if (tn.small_route == 0 && N > ((int64_t)1 << 22))
+        return rc;
+    const bool both = tn.small_route == 0 && N >= ((int64_t)1 << 20);
+    double best_cost = tn.small_route == 1 ? 1e300 : 0.8 * general_cost(pl, ndim);
     bool take = false;
     for (int groups = 1; groups <= 64; groups = groups == 1 ? 4 : 2 * groups) {
         if (tn.small_groups > 0)
@@ -2373,8 +2422,8 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         const double bytes = groups > 1 ? (double)sp.n_groups * (double)dims[k] * R * sbytes : 0.0;
         if ((sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) &&
             (bytes <= 16777216.0 || bytes <= (double)pl.ws_bytes)) {
-            const double cost = small_cost(sp, sbytes, n_modes, N);
-            if (cost < best_cost) {
+            const double cost = small_cost(sp, sbytes, n_modes, N, bytes, k == 0);
+            if (cost < best_cost && (!both || small_cost_from_2_20(sp, sbytes, n_modes, N) < 0.8 * general_cost_from_2_20(pl))) {
                 best = sp;
                 best_cost = cost;
                 take = true;

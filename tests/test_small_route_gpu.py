@@ -130,6 +130,16 @@ def test_small_route_is_for_small_tensors():
         binding.mttkrp_tune_set("row_blocks", 0)
 
 
+# Calls that took the kernel for small tensors and were 1.3 to 2.1 times slower there than without it: large ones, high ranks
+# beside few or many columns, two modes.
+@pytest.mark.parametrize("b,dims,R,k", [(8, (4558, 14055), 4, 0), (8, (93, 132680), 5, 1), (8, (119, 248464), 4, 0),
+                                        (8, (9, 76, 72, 4, 7), 61, 1), (8, (24, 66, 20, 31), 122, 1), (8, (16, 3, 95, 318), 53, 2),
+                                        (8, (11, 9, 10, 7, 15, 10), 47, 5), (8, (1293, 14063), 6, 0), (8, (141, 413, 41), 51, 2)])
+def test_calls_that_the_small_kernel_slows_down_do_without_it(b, dims, R, k):
+    from paper_2510_14891_amd import binding
+    assert "small_route=1" not in binding.mttkrp_plan_describe(dims, R, k, b)
+
+
 @pytest.mark.gpu
 def test_workspace_hand_over_and_growth_without_events(mt, oracle):
     """No event follows a call until a ninth stream takes over a workspace: growth on a stream with a call in
