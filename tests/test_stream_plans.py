@@ -148,6 +148,21 @@ def test_listed_plans_differ(mt, b, dims, R, k):
     assert base != now and "small_route" not in text
 
 
+# Calls for which a plan was chosen by its estimate that ran 1.3 to 2.3 times longer: items a little over one for each SIMD, items of
+# two or three steps, a first mode that walks five modes.
+@pytest.mark.parametrize("b,dims,R,k", [(8, (16900, 4449), 27, 0), (8, (147, 198, 37, 41), 106, 1), (8, (8, 8, 8, 53035), 6, 3),
+                                        (8, (133, 41, 91, 50), 120, 2), (8, (17, 27, 58, 20, 60), 86, 4)])
+def test_plans_that_the_estimate_misjudged_stay(mt, b, dims, R, k):
+    (base, now), _ = plans(mt, dims, R, k, b)
+    assert base == now
+
+
+@pytest.mark.parametrize("b,dims,R", [(8, (5, 2, 2, 2, 26, 8, 28, 49), 27), (8, (16, 2, 3, 4, 11, 65, 2, 83), 14)])
+def test_first_modes_over_many_short_ones_walk_fewer_than_five(mt, b, dims, R):
+    (base, now), _ = plans(mt, dims, R, 0, b)
+    assert base == now or int(now["outer_modes"]) < 5
+
+
 def check(mt, oracle, dims, R, k, dtype, seed):
     X = inputs.uniform(seed, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
     A = [inputs.uniform(seed + 100 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
