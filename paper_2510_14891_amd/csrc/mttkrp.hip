@@ -2207,9 +2207,9 @@ int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, c
 
 // One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times on the GPU in us, fitted
 // to one half of 5650 calls (fp64 and fp32, two to eight modes, 2^8 to 2^23 values, R = 2 to 1000, each with one to three
-// numbers of groups).  On the other half the median error is 10 and 9 %.  Over 11 000 further calls that
-// the rule below gives to the small kernel they take 0.56 times as long in the mean (0.53 below 2^16 values, 0.59 at 2^18, 0.71
-// at 2^20, 0.79 at 2^21); 1.9 % of them are more than 5 % slower, the worst 1.8 times.
+// numbers of groups).  On the other half the median error is 10 and 9 %.  4900 further calls that the
+// rule below gives to the small kernel take 0.55 times as long in the mean (0.52 below 2^17 values, 0.57 at 2^18, 0.69 at
+// 2^20, 0.75 at 2^21); 1.6 % of them are more than 5 % slower, the worst 1.7 times.
 // The small kernel by its number of column modes (one, two, others), per workgroup:
 struct SmallFit {
     double base, mfma, loads, alu, sweep;      // launch; matrix cores, load instructions, address arithmetic; a sweep's start and end
@@ -2253,10 +2253,10 @@ double general_cost(const Plan& pl, int ndim)
            0.0406e-6 * (double)pl.N * pl.sbytes + 1.15e-3 * items + 0.837e-6 * (double)pl.ws_bytes + 0.197 * tiles;
 }
 
-// From 2^20 values on, where there is less to gain, a second fit has to agree (2600 other calls, timed with their host
-// work, fewer terms): calls that only the first would take there are 0.84 times as long in the mean and 24 % of them more than
-// 5 % slower, those that both take 0.76 and 11 %.
-double small_cost_from_2_20(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
+// The fit of 2600 other calls timed with their host work, with fewer terms, has to agree: the first estimate takes calls back that this
+// one misjudges.  Calls that only the first would take stay where they are (0.7 times as long below 2^20 values, but another
+// order of the sums; above 0.84 times and 24 % of them more than 5 % slower).
+double small_cost_with_host(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
 {
     const double steps = (double)sp.n_tiles * sp.n_ranges * (sp.cols_per_range / 4);       // of one workgroup
     const double cycles = sbytes == 8 ? 64.0 : 32.0;
@@ -2270,7 +2270,7 @@ double small_cost_from_2_20(const SmallPlan& sp, int sbytes, int n_modes, int64_
            0.027e-6 * (double)N * sbytes;
 }
 
-double general_cost_from_2_20(const Plan& pl)
+double general_cost_with_host(const Plan& pl)
 {
     const bool paired_second = pl.seg > 0 && !pl.seg_first;
     const bool prepare = pl.fused_bytes > 0 || paired_second || pl.contract_rows;
@@ -2415,7 +2415,6 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
     // of 0.775 times as long in the mean over all calls); beyond 2^22 values most would.
     if (tn.small_route == 0 && N > ((int64_t)1 << 22))
         return rc;
-    const bool both = tn.small_route == 0 && N >= ((int64_t)1 << 20);
     double best_cost = tn.small_route == 1 ? 1e300 : 0.8 * general_cost(pl, ndim);
     bool take = false;
     for (int groups = 1; groups <= 64; groups = groups == 1 ? 4 : 2 * groups) {
@@ -2430,7 +2429,8 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         if ((sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) &&
             (bytes <= 16777216.0 || bytes <= (double)pl.ws_bytes)) {
             const double cost = small_cost(sp, sbytes, n_modes, N, bytes, k == 0);
-            if (cost < best_cost && (!both || small_cost_from_2_20(sp, sbytes, n_modes, N) < 0.8 * general_cost_from_2_20(pl))) {
+            if (cost < best_cost &&
+                (tn.small_route == 1 || small_cost_with_host(sp, sbytes, n_modes, N) < 0.8 * general_cost_with_host(pl))) {
                 best = sp;
                 best_cost = cost;
                 take = true;
