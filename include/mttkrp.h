@@ -305,7 +305,8 @@ int mttkrp_timing_last(float* stream_ms, float* combine_ms);
  *   "small_groups"  that route only: workgroups that share an output row's columns (1..1024; from 2 on
  *                   their sums are added by a second launch), 0 = chosen by the planner
  *   "lds_contract"  contraction over the leading index (the shared sweep, the last mode over all others, modes
- *                   k != 0 beside a long mode 0): 2 = never the kernel through LDS, 0 or 1 = where it pays
+ *                   k != 0 beside a long mode 0): 2 = never the kernel through LDS, 1 = wherever its limits
+ *                   on sizes and memory allow, 0 = where it pays
  *   "linear"        1 = the column space is split into balanced ranges of steps that may
  *                   begin and end inside a sweep, 2 = only whole sweeps and equal pieces
  *                   of sweeps, 0 = chosen by the planner (ranges for the first mode when

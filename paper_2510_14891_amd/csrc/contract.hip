@@ -332,10 +332,6 @@ __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T
     }
 }
 
-// The fp64 sums spill where three workgroups of four wavefronts share a compute unit at two blocks of output columns (10^6 x
-// 400 at R = 32: 0.356 -> 0.428 ms): more row splits keep the chains short there.
-constexpr bool has_chains(int JB, int CW) { return !(JB == 2 && CW == 4); }
-
 int lds_bytes(int JB, int CW) { return 2 * (16 * CW * kPieces * 16 + 4096 * JB); }
 
 template <typename T, int JB, int CW, bool CHAINS>
@@ -349,7 +345,9 @@ void launch_kernel(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t
 template <typename T, int JB, int CW>
 void launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st)
 {
-    if constexpr (sizeof(T) == 4 && has_chains(JB, CW))
+    // (at two blocks of output columns and four wavefronts the fp64 sums spill: 10^6 x 400 at R = 32 0.356 -> 0.428 ms, the
+    // same as with as many more row splits)
+    if constexpr (sizeof(T) == 4)
         if (pl.chain > 0)
             return launch_kernel<T, JB, CW, true>(pl, a, st);
     launch_kernel<T, JB, CW, false>(pl, a, st);
@@ -387,8 +385,6 @@ ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, int sbytes, int64
         max_rows = 4096;
     if (sbytes == 8 || max_chain <= 0)
         max_chain = max_rows;
-    if (!has_chains(pl.JB, pl.CW) && max_rows > max_chain)
-        max_rows = max_chain;
     int64_t best = 1;
     if (target_items > 0) {
         best = (target_items + pl.n_ctile - 1) / pl.n_ctile;

@@ -967,22 +967,6 @@ sum_segments(const double* __restrict__ part, int64_t n_entries, int R, int n_se
     M[i * ldM + j] = (T)v;
 }
 
-template <typename T> struct Calls;
-template <> struct Calls<double> {
-    static int dense(int nd, const int64_t* d, const double* X, const double* const* f, int R, int k, double* M,
-                     void* ws, size_t wsb, void* st)
-    { return mttkrp_dense_f64_ws(nd, d, X, f, R, k, M, ws, wsb, st); }
-    static int leading(int64_t P, int64_t Q, const double* X, const double* K, int R, double* out, void* ws, size_t wsb, void* st)
-    { return mttkrp_contract_leading_f64(P, Q, X, K, R, R, out, R, ws, wsb, st); }
-};
-template <> struct Calls<float> {
-    static int dense(int nd, const int64_t* d, const float* X, const float* const* f, int R, int k, float* M,
-                     void* ws, size_t wsb, void* st)
-    { return mttkrp_dense_f32_ws(nd, d, X, f, R, k, M, ws, wsb, st); }
-    static int leading(int64_t P, int64_t Q, const float* X, const float* K, int R, float* out, void* ws, size_t wsb, void* st)
-    { return mttkrp_contract_leading_f32(P, Q, X, K, R, R, out, R, ws, wsb, st); }
-};
-
 // Where the modes are cut into a leading set (modes 0 .. s-1, P_L entries) and a trailing
 // set (modes s .. d-1, P_R entries), and what lies where in the caller's buffer.
 struct SharedPlan {
@@ -994,6 +978,7 @@ struct SharedPlan {
     int nd_first = 0;
     int64_t dims_first[MTTKRP_MAX_NDIM];
     size_t off_first = 0, first_bytes = 0;
+    bool compact = false;       // both passes over X with the plans of least workspace
 };
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
@@ -1066,28 +1051,29 @@ int plan_shared(int ndim, const int64_t* dims, int R, int sbytes, SharedPlan& sp
             sp.max_seg = n_seg;
     }
     sp.off_part = off;  off += align256(part);
-    const size_t lead = mttkrp_contract_leading_workspace_bytes(sp.PL, sp.PR, R, sbytes);
-    if (lead == (size_t)-1)
-        return MTTKRP_ERR_UNSUPPORTED;
-    sp.lead_bytes = lead;
-    sp.off_lead = off;  off += align256(lead);
     sp.nd_first = 1 + ndim - sp.s;
     sp.dims_first[0] = sp.PL;
     for (int m = sp.s; m < ndim; ++m)
         sp.dims_first[1 + m - sp.s] = dims[m];
-    const size_t first = mttkrp_dense_workspace_bytes(sp.nd_first, sp.dims_first, R, 0, sbytes);
-    if (first == (size_t)-1)
-        return MTTKRP_ERR_UNSUPPORTED;
-    sp.first_bytes = first;
-    sp.off_first = off;  off += align256(first);
-    sp.total = off > 0 ? off : 256;
     // the intermediates must stay small beside the tensor: an eighth of it, or 64 MiB
     double limit = 0.125 * (double)N * sbytes;
     if (limit < 64.0 * 1048576.0)
         limit = 64.0 * 1048576.0;
-    if ((double)sp.total > limit)
-        return MTTKRP_ERR_UNSUPPORTED;
-    return MTTKRP_OK;
+    for (int compact = 0; compact < 2; ++compact) {
+        sp.lead_bytes = mttkrp_leading_bytes(sp.PL, sp.PR, R, sbytes, compact != 0);
+        sp.first_bytes = mttkrp_dense_bytes(sp.nd_first, sp.dims_first, R, 0, sbytes, compact != 0);
+        if (sp.lead_bytes == (size_t)-1 || sp.first_bytes == (size_t)-1)
+            return MTTKRP_ERR_UNSUPPORTED;
+        sp.compact = compact != 0;
+        sp.off_lead = off;
+        sp.off_first = off + align256(sp.lead_bytes);
+        sp.total = sp.off_first + align256(sp.first_bytes);
+        if (sp.total == 0)
+            sp.total = 256;
+        if ((double)sp.total <= limit)
+            return MTTKRP_OK;
+    }
+    return MTTKRP_ERR_UNSUPPORTED;
 }
 
 template <typename T>
@@ -1152,7 +1138,7 @@ int shared_sweep(int ndim, const int64_t* dims, const T* X, const T* const* fact
     const int s = sp.s, nr = ndim - s;
     // pass 1: contraction over the trailing modes
     if (s == 1) {
-        rc = Calls<T>::dense(ndim, dims, X, factors, R, 0, M_out[0], ws + sp.off_first, sp.first_bytes, stream);
+        rc = mttkrp_dense_run<T>(ndim, dims, X, factors, R, 0, M_out[0], ws + sp.off_first, sp.first_bytes, stream, sp.compact);
         if (rc != MTTKRP_OK)
             return rc;
         rc = after(0);
@@ -1164,7 +1150,7 @@ int shared_sweep(int ndim, const int64_t* dims, const T* X, const T* const* fact
         for (int m = 0; m < nr; ++m)
             f2[1 + m] = factors[s + m];
         T* const TR = (T*)(ws + sp.off_TR);
-        rc = Calls<T>::dense(sp.nd_first, sp.dims_first, X, f2, R, 0, TR, ws + sp.off_first, sp.first_bytes, stream);
+        rc = mttkrp_dense_run<T>(sp.nd_first, sp.dims_first, X, f2, R, 0, TR, ws + sp.off_first, sp.first_bytes, stream, sp.compact);
         if (rc != MTTKRP_OK)
             return rc;
         for (int k = 0; k < s; ++k) {
@@ -1193,7 +1179,7 @@ int shared_sweep(int ndim, const int64_t* dims, const T* X, const T* const* fact
         K = KL;
     }
     T* const TL = nr == 1 ? M_out[ndim - 1] : (T*)(ws + sp.off_TL);
-    rc = Calls<T>::leading(sp.PL, sp.PR, X, K, R, TL, ws + sp.off_lead, sp.lead_bytes, stream);
+    rc = mttkrp_leading_run<T>(sp.PL, sp.PR, X, K, R, TL, ws + sp.off_lead, sp.lead_bytes, stream, sp.compact);
     if (rc != MTTKRP_OK)
         return rc;
     if (nr == 1)

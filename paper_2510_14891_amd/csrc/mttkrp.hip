@@ -1322,6 +1322,14 @@ Tuning tuning()
     std::lock_guard<std::mutex> lock(g_mutex);
     return g_tune;
 }
+// ... for a contraction over the leading index with little workspace
+Tuning tuning_for(bool compact)
+{
+    Tuning tn = tuning();
+    if (compact && tn.lds_contract == 0)
+        tn.lds_contract = 1;
+    return tn;
+}
 
 struct LeadingPlan {
     int JB = 1, n_jchunk = 1, CB = 1, n_cchunk = 1, n_rsplit = 1, rows_per_split = 16;
@@ -1431,6 +1439,11 @@ int plan_leading(int64_t P, int64_t Q, int R, int sbytes, const Tuning& tn, Lead
     if (tn.rows_col_blocks == 0 && tn.max_col_blocks == 0 && tn.lds_contract != 2)
         // (fp32: chains of fp32 sums no longer than the other kernel's, whose row splits are added in fp64)
         pl.cp = mttkrp_contract_plan(P, Q, R, sbytes, n_rsplit, tn.target_items, 16 * tn.max_steps, rows);
+    // ... unless its wider tiles (64 or 128 columns against 16 to 64) hold over 1.2 times the columns: up to there 3486 fp64 calls
+    // are 0.80 times as long in the mean and 1.6 % of them more than 5 % slower, the 500 beyond 1.10 times and up to 1.93
+    // (260971 rows x 4 columns at R = 2: 11.4 against 22.0 us).
+    if (pl.cp.ok && tn.lds_contract != 1 && (double)pl.cp.n_ctile * pl.cp.CW > 1.2 * (double)(n_cchunk * pl.CB))
+        pl.cp = ContractPlan();
     if (pl.cp.ok) {
         pl.n_rsplit = pl.cp.n_rsplit;
         pl.rows_per_split = (int)pl.cp.rows_per_split;
@@ -1669,7 +1682,10 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             pl.xcd_remap = false;
             // All column indices at once, whatever mode they belong to: no tile is padded at the end of a batch (20 column
             // entries in tiles of 32: 10^6 x 20 x 20, fp32, R = 32 0.50 -> 0.40 ms), and the kernel through LDS can run.
-            // Its intermediate is written and read once: taken while that stays below 2 % of the tensor's bytes.
+            // Its intermediate is written and read once: taken while that stays below 2 % of the tensor's bytes, from 8 MB on, and
+            // where its tiles hold fewer columns than those of the batches, at most 0.9 (fp32 0.75) times as many: 1300 such calls
+            // are 0.67 times as long in the mean and 5 % of them more than 5 % slower, the others 1.08 times and up to 2.06
+            // (1634685 x 2 x 7 fp32 at R = 4, second mode: 33 against 69 us).  "lds_contract" = 1 keeps the limits on memory alone.
             const Tuning none;
             Tuning rest = tn;
             rest.small_route = rest.small_groups = rest.lds_contract = rest.plain_rows = 0;
@@ -1686,7 +1702,9 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
                     segs = 1;
                 const double bytes = s_bytes + 512.0 + (segs > 1 ? (double)dims[k] * (double)segs * R * sbytes : 0.0);
                 // (and never beyond what mttkrp_dense_f64_noalloc has)
-                if (cp.ok && s_bytes <= 0.02 * (double)pl.N * sbytes && pairs < ((int64_t)1 << 31) &&
+                const bool pays_lds = s_bytes <= 0.02 * (double)pl.N * sbytes && pl.N * sbytes >= ((int64_t)1 << 23) &&
+                                      (double)cp.n_ctile * cp.CW <= (sbytes == 8 ? 0.9 : 0.75) * (double)dims[k] * pl.n_cchunk * pl.CB;
+                if (cp.ok && (pays_lds || tn.lds_contract == 1) && pairs < ((int64_t)1 << 31) &&
                     (bytes <= kNoallocBytes || bytes <= (double)pl.ws_bytes)) {
                     pl.cp = cp;
                     pl.cp_segs = (int)segs;
@@ -2318,7 +2336,7 @@ double stream_time(const Plan& pl)
 // mode: 178 -> 113 us). In fp32 a plan with longer chains of sums in an item than before is not taken
 // (12 % of the fp32 calls keep their plan for it): such chains, up to 4 times as long, gave up to twice the error against
 // fp64 (4112 x 359 x 25 at R = 32, first mode: 3.3e-8 -> 6.7e-8 rms).
-void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, bool compact, Plan& pl)
 {
     int64_t N = 1;
     for (int m = 0; m < ndim; ++m)
@@ -2361,8 +2379,8 @@ void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes,
                 // slower; of the 620 left out here 47 %, of the others 2.7 %): long items a little over one for each SIMD, of which
                 // some then run two and the others wait; items of a few steps; first modes that walk five modes and more.
                 const double tiles = c.RB * c.JB * (sbytes / 4);
-                if ((c.n_items > 1024 && c.n_items <= 1536 && c.steps_per_item >= (tiles >= 12 ? 64 : 128)) ||
-                    c.steps_per_item < 4 || (k == 0 && c.n_out >= 5))
+                if (!compact && ((c.n_items > 1024 && c.n_items <= 1536 && c.steps_per_item >= (tiles >= 12 ? 64 : 128)) ||
+                                 c.steps_per_item < 4 || (k == 0 && c.n_out >= 5)))
                     continue;
                 const double time = stream_time(c);
                 if (time < best_time && time < (paired_second && c.seg == 0 ? 0.80 : 0.85) * now) {
@@ -2375,7 +2393,8 @@ void better_stream_plan(int ndim, const int64_t* dims, int R, int k, int sbytes,
         pl = best;
 }
 
-int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, bool tuned, Plan& pl)
+// (compact: see mttkrp_dense_bytes)
+int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, bool tuned, bool compact, Plan& pl)
 {
     const int rc = make_general_plan(ndim, dims, R, k, sbytes, tn, pl);
     if (rc != MTTKRP_OK)
@@ -2394,9 +2413,9 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
             pl = c;
     }
     if (!tuned)
-        better_stream_plan(ndim, dims, R, k, sbytes, pl);
+        better_stream_plan(ndim, dims, R, k, sbytes, compact, pl);
     // the other keys choose among the decompositions of the general plans
-    if (tn.small_route == 2 || (tn.small_route == 0 && tuned))
+    if (tn.small_route == 2 || (tn.small_route == 0 && (tuned || compact)))
         return rc;
     // 32-bit offsets in the kernel, and a bounded grid
     int64_t N = 1, C = 1;
@@ -2519,12 +2538,18 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
                 return MTTKRP_OK;
             }
     }
-    rc = choose_plan(ndim, dims, R, k, sbytes, tn, tuned, pl);
+    rc = choose_plan(ndim, dims, R, k, sbytes, tn, tuned, false, pl);
     if (rc == MTTKRP_OK && !tuned) {
         std::lock_guard<std::mutex> lock(g_mutex);
         keep_plan(h, key, pl);
     }
     return rc;
+}
+
+int make_compact_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
+{
+    const Tuning none, tn = tuning();
+    return choose_plan(ndim, dims, R, k, sbytes, tn, memcmp(&tn, &none, sizeof(tn)) != 0, true, pl);
 }
 
 template <typename T, int RB, int JB>
@@ -2786,12 +2811,12 @@ int launch_leading(const LeadingPlan& pl, int64_t P, int64_t Q, const T* X, cons
 
 template <typename T>
 int run_leading(int64_t P, int64_t Q, const T* X, const T* K, int64_t ldK, int R, T* out, int64_t ld_out,
-                void* workspace, size_t workspace_bytes, void* stream)
+                void* workspace, size_t workspace_bytes, void* stream, bool compact = false)
 {
     if (!X || !K || !out)
         return MTTKRP_ERR_INVALID_ARG;
     LeadingPlan pl;
-    const int rc = plan_leading(P, Q, R, (int)sizeof(T), tuning(), pl);
+    const int rc = plan_leading(P, Q, R, (int)sizeof(T), tuning_for(compact), pl);
     if (rc != MTTKRP_OK)
         return rc;
     if (ldK < R || ldK >= ((int64_t)1 << 27) || ld_out < R || ld_out >= ((int64_t)1 << 27))
@@ -2805,7 +2830,7 @@ template <typename T>
 int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int R, int k, T* M,
         void* workspace, size_t workspace_bytes, bool own_ws, void* stream,
         const T* lambda = nullptr, double beta = 0.0, const int64_t* ld_factors = nullptr, int64_t ldM = 0,
-        bool allow_timing = true)
+        bool allow_timing = true, bool compact = false)
 {
     if (!X || !M || !factors)
         return MTTKRP_ERR_INVALID_ARG;
@@ -2822,7 +2847,7 @@ int run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int 
     if (ldM < R || ldM >= ((int64_t)1 << 27))
         return MTTKRP_ERR_INVALID_ARG;
     Plan pl;
-    int rc = make_plan(ndim, dims, R, k, (int)sizeof(T), pl);
+    int rc = compact ? make_compact_plan(ndim, dims, R, k, (int)sizeof(T), pl) : make_plan(ndim, dims, R, k, (int)sizeof(T), pl);
     if (rc != MTTKRP_OK)
         return rc;
     // The kernel for small tensors addresses a factor's rows in 32 bits: blocks of arrays of 2^32 values and more run on
@@ -3296,6 +3321,36 @@ void* scratch_address()
 
 }  // namespace
 
+size_t mttkrp_dense_bytes(int ndim, const int64_t* dims, int R, int k, int sbytes, bool compact)
+{
+    Plan pl;
+    const int rc = compact ? make_compact_plan(ndim, dims, R, k, sbytes, pl) : make_plan(ndim, dims, R, k, sbytes, pl);
+    return rc == MTTKRP_OK ? pl.ws_bytes : (size_t)-1;
+}
+size_t mttkrp_leading_bytes(int64_t P, int64_t Q, int R, int sbytes, bool compact)
+{
+    LeadingPlan pl;
+    if (plan_leading(P, Q, R, sbytes, tuning_for(compact), pl) != MTTKRP_OK)
+        return (size_t)-1;
+    return pl.ws_bytes;
+}
+template <typename T>
+int mttkrp_dense_run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int R, int k, T* M, void* workspace,
+                     size_t workspace_bytes, void* stream, bool compact)
+{
+    return run<T>(ndim, dims, X, factors, R, k, M, workspace, workspace_bytes, false, stream, nullptr, 0.0, nullptr, 0, true, compact);
+}
+template <typename T>
+int mttkrp_leading_run(int64_t P, int64_t Q, const T* X, const T* K, int R, T* out, void* workspace, size_t workspace_bytes,
+                       void* stream, bool compact)
+{
+    return run_leading<T>(P, Q, X, K, R, R, out, R, workspace, workspace_bytes, stream, compact);
+}
+template int mttkrp_dense_run<double>(int, const int64_t*, const double*, const double* const*, int, int, double*, void*, size_t, void*, bool);
+template int mttkrp_dense_run<float>(int, const int64_t*, const float*, const float* const*, int, int, float*, void*, size_t, void*, bool);
+template int mttkrp_leading_run<double>(int64_t, int64_t, const double*, const double*, int, double*, void*, size_t, void*, bool);
+template int mttkrp_leading_run<float>(int64_t, int64_t, const float*, const float*, int, float*, void*, size_t, void*, bool);
+
 extern "C" {
 
 int mttkrp_dense_f64_noalloc(int ndim, const int64_t* dims, const double* X, const double* const* factors,
@@ -3324,10 +3379,7 @@ int mttkrp_dense_f32(int ndim, const int64_t* dims, const float* X, const float*
 
 size_t mttkrp_dense_workspace_bytes(int ndim, const int64_t* dims, int R, int k, int dtype_bytes)
 {
-    Plan pl;
-    if (make_plan(ndim, dims, R, k, dtype_bytes, pl) != MTTKRP_OK)
-        return (size_t)-1;
-    return pl.ws_bytes;
+    return mttkrp_dense_bytes(ndim, dims, R, k, dtype_bytes, false);
 }
 
 int mttkrp_dense_f64_ws(int ndim, const int64_t* dims, const double* X,
@@ -3393,10 +3445,7 @@ int mttkrp_dense_f32_ld(int ndim, const int64_t* dims, const float* X, const flo
 
 size_t mttkrp_contract_leading_workspace_bytes(int64_t P, int64_t Q, int R, int dtype_bytes)
 {
-    LeadingPlan pl;
-    if (plan_leading(P, Q, R, dtype_bytes, tuning(), pl) != MTTKRP_OK)
-        return (size_t)-1;
-    return pl.ws_bytes;
+    return mttkrp_leading_bytes(P, Q, R, dtype_bytes, false);
 }
 
 int mttkrp_contract_leading_f64(int64_t P, int64_t Q, const double* X, const double* K, int64_t ldK, int R,

@@ -38,6 +38,16 @@ MTTKRP_INTERNAL ContractPlan mttkrp_contract_plan(int64_t P, int64_t Q, int R, i
 template <typename T>
 MTTKRP_INTERNAL int mttkrp_contract_launch(const ContractPlan& pl, const ContractArgs<T>& a, hipStream_t st);
 
+// What the shared sweep calls.  compact: with plans of little workspace for sweeps that take too much of it otherwise (no
+// workgroups that share a small tensor's columns, any chosen streaming plan, the kernel through LDS wherever it can run).
+MTTKRP_INTERNAL size_t mttkrp_dense_bytes(int ndim, const int64_t* dims, int R, int k, int sbytes, bool compact);
+MTTKRP_INTERNAL size_t mttkrp_leading_bytes(int64_t P, int64_t Q, int R, int sbytes, bool compact);
+template <typename T>
+MTTKRP_INTERNAL int mttkrp_dense_run(int ndim, const int64_t* dims, const T* X, const T* const* factors, int R, int k, T* M,
+                                     void* workspace, size_t workspace_bytes, void* stream, bool compact);
+template <typename T>
+MTTKRP_INTERNAL int mttkrp_leading_run(int64_t P, int64_t Q, const T* X, const T* K, int R, T* out, void* workspace,
+                                       size_t workspace_bytes, void* stream, bool compact);
 
 // A mode's result from the contraction over mode 0, S(q, s, j) (see mttkrp_modesum_kernel).
 template <typename T, typename TP> struct ModeSumArgs {

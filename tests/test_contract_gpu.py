@@ -31,7 +31,9 @@ EDGES = [(384, 1, 2), (385, 63, 16), (415, 64, 17), (416, 65, 31), (447, 127, 32
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("tune", [{}, {"target_items": 9}, {"max_steps": 8}])
+# ("lds_contract" = 1: also where the tiles of this kernel hold many more columns than the other's)
+@pytest.mark.parametrize("tune", [{}, {"target_items": 9}, {"max_steps": 8}, {"lds_contract": 1},
+                                  {"lds_contract": 1, "target_items": 9}, {"lds_contract": 1, "max_steps": 8}])
 @pytest.mark.parametrize("P,Q,R", EDGES)
 def test_contraction_through_lds(mt, oracle, P, Q, R, tune, dtype):
     if dtype == torch.float32:
@@ -55,11 +57,13 @@ def test_contraction_through_lds(mt, oracle, P, Q, R, tune, dtype):
         assert torch.equal(T[:, :R], again) and bool((T[:, R:] == 3.0).all())
 
 
-# Every mode but the first of these runs on the contraction and the weighted sum of its result (asserted from the plan): one
-# and several segments of that sum, row splits, modes of one entry, the output mode first, between and last among the others.
+# Modes that run on the contraction and the weighted sum of its result (asserted from the plan, with the key that leaves
+# only the limits on sizes): one and several segments of that sum, one and several row splits, one to three
+# blocks of output columns, modes of one entry, the output mode first, between and last among the others.
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
-@pytest.mark.parametrize("dims,R", [((30000, 3, 5), 4), ((840, 2, 3, 2, 1), 4), ((53899, 2, 5, 2), 4), ((12024, 28, 1), 5),
-                                    ((60000, 7, 9), 5)])
+@pytest.mark.parametrize("dims,R", [((3000, 20, 20), 32), ((2573, 7, 9), 5), ((4001, 3, 1, 2, 4), 17), ((9000, 65, 3), 16),
+                                    ((4000, 30, 29), 8), ((30000, 3, 5), 4), ((840, 2, 3, 2, 1), 4), ((12024, 28, 1), 5),
+                                    ((2601, 3, 301), 48), ((500, 2, 5, 2), 20)])
 def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
     X = inputs.uniform(7, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
     A = [inputs.uniform(8 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
@@ -68,12 +72,11 @@ def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
     lam = inputs.uniform(9, R, 0.5, 1.5, dtype=dtype)
     for k in range(1, len(dims)):
         mt.mttkrp_tune_set("small_route", 2)
+        mt.mttkrp_tune_set("lds_contract", 1)
         plan = mt.mttkrp_plan_describe(dims, R, k, X.element_size())
-        mt.mttkrp_tune_set("small_route", 0)
         print("modes from the contraction dims=%s R=%d k=%d %s" % (dims, R, k, plan), flush=True)
-        assert "shape=rows" in plan and "lds=1" in plan
+        assert "lds=1" in plan or (dims, k) in [((9000, 65, 3), 2), ((2601, 3, 301), 1)]       # (streaming plans)
         ref = oracle.mttkrp(Xn, An, k)
-        mt.mttkrp_tune_set("small_route", 2)
         got = mt.mttkrp_dense(Xd, dims, Ad, k)
         wide = [torch.full((I, R + 1), float("nan"), dtype=dtype, device="cuda") for I in dims]
         for w, a in zip(wide, Ad):
@@ -81,6 +84,7 @@ def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
         Mw = torch.full((dims[k], R + 3), 1.0, dtype=dtype, device="cuda")
         mt.mttkrp_dense_ld(Xd, dims, [w[:, :R] for w in wide], k, Mw[:, :R], R, lam=lam.cuda(), beta=0.5)
         mt.mttkrp_tune_set("small_route", 0)
+        mt.mttkrp_tune_set("lds_contract", 0)
         assert oracle.normwise_rel_err(got.cpu().numpy(), ref) <= TOL[dtype], k
         ref2 = oracle.mttkrp(Xn, An, k, lam=lam.numpy()) + 0.5
         assert oracle.normwise_rel_err(Mw[:, :R].cpu().numpy(), ref2) <= TOL[dtype], k
@@ -127,7 +131,7 @@ def test_contraction_non_finite_rows_beside_masked_ones(mt, dtype):
     assert torch.equal(T, want)
 
 
-# Calls whose own row splits are longer than the chains of the kernel that "lds_contract" = 2 selects: both add the same number
+# Calls whose row splits in this kernel are longer than the chains of the kernel that "lds_contract" = 2 selects: both add the same number
 # of products in single precision and the rest in double precision, so their errors agree up to the scatter of
 # tens of thousands of outputs (1.25) and the rounding of a result (2e-8).  One to four blocks of output columns, tiles of 64 and
 # 128 columns, splits of whole stages and not.
@@ -141,7 +145,7 @@ def test_single_precision_chains_are_no_longer_than_the_other_kernels(mt, P, Q, 
         K = torch.rand((P, R), dtype=torch.float32, device="cuda", generator=g) - 0.5 * signed
         W = torch.cat([X[q:q + 512].double() @ K.double() for q in range(0, Q, 512)])
         err = []
-        for v in (0, 2):
+        for v in (1, 2):
             mt.mttkrp_tune_set("lds_contract", v)
             print("contract chains P=%d Q=%d R=%d lds_contract=%d" % (P, Q, R, v), flush=True)
             T = mt.mttkrp_contract_leading(X.view(-1), P, Q, K)

@@ -275,3 +275,22 @@ def test_seeded_random_shapes_shared_sweep_and_leading_contraction(mt, oracle):
     finally:
         for key in TUNE_KEYS:
             mt.mttkrp_tune_set(key, 0)
+
+
+# Sweeps that fit the limit on workspace (an eighth of the tensor or 64 MiB) only with the plans of little workspace: the last
+# modes' contraction in few row splits although its tiles are badly filled, the first pass on a chosen streaming plan.
+@pytest.mark.parametrize("dims,R,dtype", [((45, 15794, 15, 6), 11, torch.float32), ((13, 6, 12, 17, 7, 181), 59, torch.float64)])
+def test_shared_sweep_with_little_workspace(mt, dims, R, dtype):
+    n = int(np.prod(dims))
+    size = torch.empty((), dtype=dtype).element_size()
+    assert 0 < mt.mttkrp_dense_all_modes_shared_bytes(dims, R, size) <= max(n * size // 8, 1 << 26)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X = torch.rand(n, dtype=dtype, device="cuda", generator=g) - 0.5
+    A = [torch.rand((I, R), dtype=dtype, device="cuda", generator=g) - 0.5 for I in dims]
+    print("shared sweep with little workspace dims=%s R=%d" % (dims, R), flush=True)
+    shared = mt.mttkrp_dense_all_modes_shared(X, dims, A)
+    for k in range(len(dims)):
+        alone = mt.mttkrp_dense(X, dims, A, k).double()
+        tol = 1e-12 if dtype == torch.float64 else 1e-5
+        assert float((shared[k].double() - alone).norm() / alone.norm()) <= tol, k

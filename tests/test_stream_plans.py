@@ -163,6 +163,14 @@ def test_first_modes_over_many_short_ones_walk_fewer_than_five(mt, b, dims, R):
     assert base == now or int(now["outer_modes"]) < 5
 
 
+# Short column spaces that ran up to twice as long on the contraction over mode 0 through LDS, whose tiles of 64 columns they fill
+# to a quarter or less.
+@pytest.mark.parametrize("b,dims,R,k", [(4, (1634685, 2, 7), 4, 1), (4, (4348311, 4, 2), 6, 2), (8, (7478310, 2, 3), 18, 1),
+                                        (8, (2848326, 2, 2), 6, 1), (4, (41726739, 3, 2), 7, 2)])
+def test_short_column_spaces_stay_off_the_wide_tiles(mt, b, dims, R, k):
+    assert "lds=0" in mt.mttkrp_plan_describe(dims, R, k, b)
+
+
 def check(mt, oracle, dims, R, k, dtype, seed):
     X = inputs.uniform(seed, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
     A = [inputs.uniform(seed + 100 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
