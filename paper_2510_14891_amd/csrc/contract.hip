@@ -8,8 +8,8 @@
 // LDS, K's rows beside them, so that K is read once per workgroup.  Workgroups are persistent and the loads of the next
 // tile start while the last stages of a tile are consumed, so short columns cost no drain.
 //
-// What bounds it: fp64 at R = 32 the power budget (matrix cores 62 % busy and HBM at 4.8 TB/s, the clock down to 1.7
-// GHz), at R <= 16 HBM.  1024 x 524288 (4.3 GB): 0.864 -> 0.763 ms at R = 8 (5.6 TB/s), 0.950 -> 0.895 at R = 32;
+// What bounds it: at R <= 16 HBM; fp64 at R = 32 reads 4.8 TB/s beside 38 TFLOP/s of the matrix cores (72 in a large product),
+// and neither goes faster beside the other.  1024 x 524288 (4.3 GB): 0.864 -> 0.763 ms at R = 8 (5.6 TB/s), 0.950 -> 0.895 at R = 32;
 // 16641 x 60372 (8 GB): 1.63 -> 1.37 ms at R = 10; 10^6 x 400, fp32, R = 32: 0.41 -> 0.37 ms.
 #include "mttkrp_contract.h"
 

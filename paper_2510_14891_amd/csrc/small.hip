@@ -6,14 +6,14 @@
 // sums in a second launch; each launch takes about 4 us whatever it does, and its items of 16 steps and more
 // leave most of the chip idle on a 2 MB tensor.  Here a workgroup owns whole output rows: one i_k (k != 0) or 16
 // rows of mode 0 (k = 0).  Its up to 16 wavefronts take pieces of the column space (and row tiles), keep their
-// sums in MFMA accumulators and add them up in LDS in a fixed order: no workspace, no second launch, weights
-// and accumulation applied on the way out.
+// sums in MFMA accumulators and add them up in LDS in a fixed order; weights and accumulation are applied on the way
+// out.  With few output rows several workgroups share a row's columns, leave partial sums in a workspace, and the combine kernel
+// adds them in a second launch (two launches instead of three).
 //
 // Columns are decoded by every lane for itself (a multiply-high per mode above the lowest): that hides
-// behind the loads, and short modes need no fused product matrices.  With few output rows several workgroups share
-// a row's columns and the combine kernel adds their sums (two launches instead of three).  fp64, us a call, before and
-// now: 64^3 at R = 16 15.7 / 8.4 / 8.4 -> 8.3 / 5.1 / 5.0, 40 x 66 x 17 at R = 36 second mode 14.7 -> 6.7; 100 x 80 x 60 at
-// R = 10, CP-ALS, 12 sweeps 1482 -> 1214.  mttkrp.hip says where the line between the two paths lies.
+// behind the loads, and short modes need no fused product matrices.  fp64, us a call, before and now: 64^3 at R = 16 15.7 /
+// 8.4 / 8.4 -> 8.3 / 5.1 / 5.0; 100 x 80 x 60 at R = 10, CP-ALS, 12 sweeps 1482 -> 1190; 4947 calls that take it 0.55 times as
+// long in the mean.  mttkrp.hip says where the line between the two paths lies.
 #include "mttkrp_small.h"
 
 namespace {
