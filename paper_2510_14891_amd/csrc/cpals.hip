@@ -306,8 +306,6 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
     __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP], scale[RP];
     __shared__ double Ys[YR * (RP + 1)];
-    if (failed_before(flag))      // an earlier update failed: every factor stays as it is
-        return;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ti = tid & 15, tc = (tid >> 4) & 15, grp = tid >> 8;
     const int64_t RR = (int64_t)R * R;
@@ -326,6 +324,8 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
             }
             own[p][q] = v;
         }
+    if (failed_before(flag))      // an earlier update failed: every factor stays as it is (asked behind the loads, so that it does not delay them)
+        return;
     if (tid < 256 && ti == tc) {
 #pragma unroll
         for (int p = 0; p < NT; ++p)
