@@ -13,7 +13,13 @@ loads of the inner factor's entries for the JB column blocks (both in the lane
 layout the kernel defines: `Lay` / `LayRows` in mttkrp.hip), JB multiplies by
 the sweep weight and RB * JB 16x16x4 MFMAs.  A run covers any n >= D consecutive
 unmasked steps of one sweep: the X pointer and the factor offsets advance by
-constant strides.  Operand sets live in a ring of S = D + 1 register sets at
+constant strides.  Both bases lie in scalar registers and are advanced by the
+scalar unit; a lane's offsets from them are 32-bit registers that never change.
+That matters in fp64: while an fp64 MFMA runs, the SIMD issues no vector
+instruction, and a group of them between two MFMAs costs about 10 cycles and 2 to
+4 more for each (register-only loop of RB = 2, JB = 4 steps: 568 cycles a step
+with a 64-bit and two 32-bit pointer additions, 544 without, of 512 for the MFMAs
+alone).  Operand sets live in a ring of S = D + 1 register sets at
 fixed registers at the top of the wavefront's register budget (declared as
 clobbers); the loads of step t go to set t mod S; every wait names how many
 younger loads may still be outstanding (loads return in issue order).
@@ -35,6 +41,8 @@ import os
 
 D_MAX = 5
 D_MIN = 3
+S0 = 84                      # scalar registers of a run: X base, X step, base of the inner factor (two each)
+XB, BB = "s[%d:%d]" % (S0, S0 + 1), "s[%d:%d]" % (S0 + 4, S0 + 5)
 OTHERS = {2: 60, 1: 56}      # registers the rest of the kernel keeps live across a run (fp64, fp32)
 
 
@@ -54,21 +62,21 @@ class Inst:
         self.xloads = []
         if w == 2:
             if rb in (2, 4):                             # one 8-byte load per row block
-                self.xloads = [(2 * r, 2, "xq", 128 * r) for r in range(rb)]
+                self.xloads = [(2 * r, 2, "xo0", 128 * r) for r in range(rb)]
             elif rb == 1:
-                self.xloads = [(0, 2, "xq", 0)]
+                self.xloads = [(0, 2, "xo0", 0)]
             else:                                        # rb == 3: rows 2m, 2m+1 then row 32 + m
-                self.xloads = [(0, 4, "xq", 0), (4, 2, "xq1", 0)]
+                self.xloads = [(0, 4, "xo0", 0), (4, 2, "xo1", 0)]
             g = 2
         else:
-            self.xloads = [(0, rb, "xq", 0)]
+            self.xloads = [(0, rb, "xo0", 0)]
             g = 4
         n0 = min(jb, g)
         n1 = jb - n0
         self.bloads = [(0, n0 * w, "bo0")]
         if n1:
             self.bloads.append((n0 * w, n1 * w, "bo1"))
-        self.two_x = any(p == "xq1" for _, _, p, _ in self.xloads)
+        self.two_x = any(p == "xo1" for _, _, p, _ in self.xloads)
         self.two_b = n1 > 0
         self.loads = len(self.xloads) + len(self.bloads)
         self.pick()
@@ -117,17 +125,15 @@ class Inst:
     def issue(self, s, nt):
         o = []
         width = {1: "dword", 2: "dwordx2", 3: "dwordx3", 4: "dwordx4"}
-        for off, n, ptr, byte in self.xloads:
-            o.append("global_load_%s %s, %%[%s], off%s%s" % (
-                width[n], self.reg(self.xbase(s) + off, n), ptr, " offset:%d" % byte if byte else "", nt))
-        for off, n, ptr in self.bloads:
-            o.append("global_load_%s %s, %%[%s], %%[bb]" % (width[n], self.reg(self.xbase(s) + self.xregs + off, n), ptr))
-        o.append("v_lshl_add_u64 %[xq], %[xq], 0, %[xs]")
-        if self.two_x:
-            o.append("v_lshl_add_u64 %[xq1], %[xq1], 0, %[xs]")
-        o.append("v_add_u32 %[bo0], %[bs], %[bo0]")
-        if self.two_b:
-            o.append("v_add_u32 %[bo1], %[bs], %[bo1]")
+        for off, n, lane, byte in self.xloads:
+            o.append("global_load_%s %s, %%[%s], %s%s%s" % (
+                width[n], self.reg(self.xbase(s) + off, n), lane, XB, " offset:%d" % byte if byte else "", nt))
+        for off, n, lane in self.bloads:
+            o.append("global_load_%s %s, %%[%s], %s" % (width[n], self.reg(self.xbase(s) + self.xregs + off, n), lane, BB))
+        o.append("s_add_u32 s%d, s%d, s%d" % (S0, S0, S0 + 2))
+        o.append("s_addc_u32 s%d, s%d, s%d" % (S0 + 1, S0 + 1, S0 + 3))
+        o.append("s_add_u32 s%d, s%d, %%[bs]" % (S0 + 4, S0 + 4))
+        o.append("s_addc_u32 s%d, s%d, 0" % (S0 + 5, S0 + 5))
         return o
 
     def consume(self, s, wait):
@@ -145,7 +151,7 @@ class Inst:
 
     def block(self, nt):
         d, s_n, l = self.d, self.d + 1, self.loads
-        o = ["s_nop 4"]
+        o = ["s_nop 4", "s_mov_b64 %s, %%[xb]" % XB, "s_mov_b64 s[%d:%d], %%[xs]" % (S0 + 2, S0 + 3), "s_mov_b64 %s, %%[bb]" % BB]
         for k in range(d):
             o += self.issue(k, nt)
         o.append("1:")
@@ -176,21 +182,22 @@ class Inst:
             out += "#define MTTKRP_PIPE_%s_ASM%s \\\n" % (t, suffix)
             out += " \\\n".join('    "%s\\n"' % line for line in self.block(nt)) + "\n"
         clob = ", ".join('"v%d"' % v for v in range(self.t0, self.last_reg() + 1))
+        clob += ", " + ", ".join('"s%d"' % v for v in range(S0, S0 + 6))
         accs = ", ".join('[a%d%d] "+v"(acc[%d][%d])' % (r, j, r, j) for r in range(self.rb) for j in range(self.jb))
-        outs = '[xq] "+v"(xq), ' + ('[xq1] "+v"(xq1), ' if self.two_x else "") + '[bo0] "+v"(bo0), ' + \
-               ('[bo1] "+v"(bo1), ' if self.two_b else "") + '[n] "+s"(n_more), ' + accs
-        ins = '[xs] "s"(x_step_bytes), [bb] "s"(bbase), [bs] "s"(b_step_bytes), ' + \
+        outs = '[n] "+s"(n_more), ' + accs
+        ins = '[xb] "s"(xbase), [xs] "s"(x_step_bytes), [bb] "s"(bbase), [bs] "s"(b_step_bytes), [xo0] "v"(xo0), [bo0] "v"(bo0), ' + \
+              ('[xo1] "v"(xo1), ' if self.two_x else "") + ('[bo1] "v"(bo1), ' if self.two_b else "") + \
               ", ".join('[q%d] "v"(q[%d])' % (j, j) for j in range(self.jb))
         out += "template <> struct Pipe<%s, %d, %d> {\n" % (c, self.rb, self.jb)
         out += "    static constexpr bool value = true;\n"
         out += "    static constexpr int depth = %d;\n    static constexpr int waves = %d;\n" % (self.d, self.waves)
         out += "    template <bool NT>\n"
-        out += "    static __device__ __forceinline__ void run(typename Mfma<%s>::acc_t (&acc)[%d][%d], const %s*& xq,\n" % (c, self.rb, self.jb, c)
-        out += "                                               const %s* xq1, int64_t x_step_bytes, const %s* bbase,\n" % (c, c)
+        out += "    static __device__ __forceinline__ void run(typename Mfma<%s>::acc_t (&acc)[%d][%d], const %s* xbase,\n" % (c, self.rb, self.jb, c)
+        out += "                                               uint32_t xo0, uint32_t xo1, int64_t x_step_bytes, const %s* bbase,\n" % c
         out += "                                               uint32_t bo0, uint32_t bo1, uint32_t b_step_bytes,\n"
         out += "                                               const %s (&q)[%d], int n_more)\n    {\n" % (c, self.jb)
         if not self.two_x:
-            out += "        (void)xq1;\n"
+            out += "        (void)xo1;\n"
         if not self.two_b:
             out += "        (void)bo1;\n"
         if self.w == 2:
@@ -212,7 +219,7 @@ def main(path=None):
     out += "    static constexpr bool value = false;\n    static constexpr int depth = 1 << 30;\n"
     out += "    static constexpr int waves = 0;\n"
     out += "    template <bool NT>\n"
-    out += "    static __device__ __forceinline__ void run(typename Mfma<T>::acc_t (&)[RB][JB], const T*&, const T*, int64_t,\n"
+    out += "    static __device__ __forceinline__ void run(typename Mfma<T>::acc_t (&)[RB][JB], const T*, uint32_t, uint32_t, int64_t,\n"
     out += "                                               const T*, uint32_t, uint32_t, uint32_t, const T (&)[JB], int)\n    {\n    }\n};\n\n"
     for i in insts:
         out += i.emit()

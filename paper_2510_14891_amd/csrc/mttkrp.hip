@@ -84,8 +84,9 @@ template <> struct Mfma<float> {
 // conservatively around control flow, which keeps a wavefront from overlapping
 // its own loads with its own MFMAs; the hand-scheduled loop keeps several steps
 // of loads in flight while the MFMAs of an earlier one run.  It covers any run of
-// at least that many consecutive unmasked steps of one sweep: the X pointer and
-// the factor offsets advance by constant strides, one weight Q per column block.
+// at least that many consecutive unmasked steps of one sweep: the bases of X and of
+// the inner factor advance by constant strides (in scalar registers; lanes keep
+// constant 32-bit offsets from them), one weight Q per column block.
 // Temporaries live in fixed registers (declared as clobbers); the loads of step
 // t go to operand set t modulo the ring size; every wait names how many later
 // loads may still be outstanding (memory operations return in issue order).
@@ -334,7 +335,9 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
         o_count = 0;
     }
 
-    const T* const xlane = p.X + (int64_t)batch * p.sx_batch + (row_base + lrow);
+    // X is addressed from a wave-uniform base (the tile's first row at the step's first column) and a lane's constant offset
+    const T* const xtile = p.X + (int64_t)batch * p.sx_batch + row_base;
+    const int64_t xl = lrow + (int64_t)kk * p.sx_in;
     const int64_t x_step = 4 * p.sx_in;
     const bool no_inner = p.no_inner != 0;   // then A_in is a readable dummy and b = 1
     const int dim_mid = p.dim_out[0];        // 1 when there is no outer mode
@@ -396,7 +399,7 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
 
     // Cursor of the issue side: it points at the next step to issue.
     int s_in = s_first;                 // step inside the current sweep
-    const T* xp = xlane + xoff_far + (int64_t)i_mid * sx_mid + (int64_t)(ia_begin + 4 * s_first + kk) * p.sx_in;
+    const T* xp = xtile + xoff_far + (int64_t)i_mid * sx_mid + (int64_t)(ia_begin + 4 * s_first) * p.sx_in;
     const T* bbase = p.A_in + (int64_t)(ia_begin + 4 * s_first) * p.ld_in;   // wave-uniform: factor row of the step's first column
     // per-lane byte offsets of (column kk, first output column of chunk 0 / chunk 1)
     const uint32_t boff0 = ((uint32_t)kk * (uint32_t)p.ld_in + (uint32_t)js0) * (uint32_t)sizeof(T);
@@ -436,7 +439,7 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
             load_far();
         }
         load_Q();
-        xp = xlane + xoff_far + (int64_t)i_mid * sx_mid + (int64_t)(ia_begin + kk) * p.sx_in;
+        xp = xtile + xoff_far + (int64_t)i_mid * sx_mid + (int64_t)ia_begin * p.sx_in;
     };
     // Generic single step: issue the loads of the cursor's step into one operand set ...
     // A lane whose part of the step is padding (a column past the inner range, or a step past the
@@ -447,7 +450,7 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
         const bool last = s_in == steps_in - 1;           // wave-uniform
         const bool pad = parked || (last && !lane_ok);
         const T* const zero = reinterpret_cast<const T*>(p.zeros);
-        const T* xe = pad ? zero : xp;
+        const T* xe = pad ? zero : xp + xl;
         const char* be = pad ? (const char*)zero - boff0 : (const char*)bbase;   // (load_b adds boff0 / boff1 again)
         load_blocks<NT, RB>(xe, xd1, xn);
         load_b(be, bn);
@@ -489,17 +492,22 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
     // Other wavefronts of the SIMD fill the gaps between batches.
     //   plain batch:   U unmasked steps of one sweep: one weight Q, constant strides
     //   generic batch: any steps (sweep boundaries, masked last step, parked padding)
-    // the pipelined run addresses the inner factor with 32-bit offsets
-    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31);
+    // the pipelined run takes a lane's offsets as 32-bit numbers (an inner mode of this many steps with a stride beyond
+    // that needs a tensor of over 180 GB; it runs in batches)
+    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31) &&
+                         (3 * p.sx_in + 64) * (int64_t)sizeof(T) < ((int64_t)1 << 32);
     int done = 0;
     while (done < n_steps) {
         if constexpr (kPipe) {
             const int avail = parked || !pipe_ok || no_inner ? 0 : min(remaining, steps_plain - s_in);
             if (avail >= Pipe<T, RB, JB>::depth) {
                 const int n_run = avail;
-                Pipe<T, RB, JB>::template run<NT>(acc, xp, xp + xd1, x_step * (int64_t)sizeof(T), bbase, boff0, boff1,
+                Pipe<T, RB, JB>::template run<NT>(acc, (const T*)(uintptr_t)uni64((int64_t)(uintptr_t)xp),
+                                                  (uint32_t)xl * (uint32_t)sizeof(T), (uint32_t)(xl + xd1) * (uint32_t)sizeof(T),
+                                                  x_step * (int64_t)sizeof(T), bbase, boff0, boff1,
                                                   4u * (uint32_t)p.ld_in * (uint32_t)sizeof(T), Q,
                                                   avail - Pipe<T, RB, JB>::depth);
+                xp += n_run * x_step;
                 bbase += (int64_t)n_run * 4 * p.ld_in;
                 s_in += n_run;
                 remaining -= n_run;
@@ -518,7 +526,7 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
         T xs[U][RB], bs[U][JB], qs[U][JB];
         done += U;
         if (!parked && remaining >= U && s_in + U <= steps_plain) {
-            const T* xu = xp;
+            const T* xu = xp + xl;
             const char* bu = (const char*)bbase;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
