@@ -8,6 +8,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "../../include/mttkrp.h"
 #include "../../include/mttkrp_cpals.h"
 #include "mttkrp_contract.h"
@@ -126,12 +128,20 @@ __global__ void __launch_bounds__(256) gram_reduce(const double* __restrict__ ws
 // numbers for start factors of any scale.
 __device__ __forceinline__ double unit_scale(double d) { return d > 0.0 && d < INFINITY ? ldexp(1.0, -(ilogb(d) >> 1)) : 1.0; }
 
-// S V S with V = Hadamard product of the Gram matrices of all modes but `skip`, and the diagonal of S.
-__global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__ G, int ndim, int R, int skip, double* V, double* S)
+// S V S with V = Hadamard product of the Gram matrices of all modes but `skip`, and the diagonal of S.  L (ldL x ldL) gets zeros
+// in its rows and columns from R on.
+__global__ void __launch_bounds__(256) hadamard_grams(const double* __restrict__ G, int ndim, int R, int skip, double* V, double* S,
+                                                      double* L, int ldL)
 {
     const int e = blockIdx.x * 256 + threadIdx.x, RR = R * R;
-    if (e >= RR)
+    if (e >= RR) {
+        const int pad = ldL - R, t = e - RR;         // columns R .. of all rows, then rows R .. of the others
+        if (t < ldL * pad)
+            L[(int64_t)(t / pad) * ldL + R + t % pad] = 0.0;
+        else if (t < ldL * pad + pad * R)
+            L[(int64_t)R * ldL + (int64_t)((t - ldL * pad) / R) * ldL + (t - ldL * pad) % R] = 0.0;
         return;
+    }
     const int a = e / R, c = e - a * R;
     double v = 1.0, da = 1.0, dc = 1.0;
     for (int m = 0; m < ndim; ++m)
@@ -169,53 +179,93 @@ __device__ __forceinline__ double reciprocal(double d)
 }
 
 // L D L^T of an R x R matrix, R <= RP, by one workgroup.  Thread (ti, tc) = (tid & 15, tid >> 4) of the first
-// 256 holds the entries (ti + 16 p, tc + 16 q) in registers; only the column that is eliminated next passes
-// through LDS, so a step costs one barrier (~250 cycles at R = 10, where scaling the column and updating
-// the triangle in LDS took two).  Result: Lf[c * (RP + 1) + i] = L(i, c) for i > c, 0 elsewhere (the padding
+// 256 holds the entries (ti + 16 p, tc + 16 q) in registers (zeros from row and column R on); the four columns that are
+// eliminated next pass through LDS.  Every thread factorises their 4 x 4 diagonal block and takes its rows and columns
+// through it by itself, so four columns cost one exchange and one barrier (~800 cycles; one column at a time 250 each).
+// Every entry sees the operations of column-by-column elimination in its order.  Blocks of 16 x 16 entries
+// above the diagonal are left alone.  Result: Lf[c * (RP + 1) + i] = L(i, c) for i > c, 0 elsewhere (the padding
 // up to RP too); dinv[c] = 1 / D(c), 0 for c >= R.  False (for every thread) when a pivot is not positive.
 template <int RP>
-__device__ __forceinline__ bool factorise(double (&own)[RP / 16][RP / 16], int R, double (*col)[RP], double* Lf, double* dinv)
+__device__ __forceinline__ bool factorise(double (&own)[RP / 16][RP / 16], int R, double (*col)[4][RP], double* Lf, double* dinv)
 {
     constexpr int NT = RP / 16;
     const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4;
     const bool mine = tid < 256;
     if (tid < RP)
         dinv[tid] = 0.0;
-    if (mine && tc == 0) {
+    if (mine && tc < 4) {
 #pragma unroll
         for (int p = 0; p < NT; ++p)
-            col[0][ti + 16 * p] = own[p][0];
+            col[0][tc][ti + 16 * p] = own[p][0];
     }
     __syncthreads();
-    for (int j = 0; j < R; ++j) {
-        const double* const cj = col[j & 1];
-        const double d = cj[j];
-        if (!(d > 0.0))
-            return false;      // uniform: every thread sees the same pivot
-        const double rd = reciprocal(d);
+    for (int j = 0; j < R; j += 4) {
+        const double (*const cj)[RP] = col[(j >> 2) & 1];
+        const int q0 = j >> 4, nk = R - j < 4 ? R - j : 4;
+        // the diagonal block: y_k of its rows, l(k, m) = y_m(j + k) / d_m
+        double l[4][4], r[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double y[4];
+#pragma unroll
+            for (int m = 0; m <= k; ++m) {
+                y[m] = cj[m][j + k];
+#pragma unroll
+                for (int n = 0; n < m; ++n)
+                    y[m] -= y[n] * l[m][n];
+                if (m < k)
+                    l[k][m] = y[m] * r[m];
+            }
+            if (k < nk && !(y[k] > 0.0))
+                return false;      // uniform: every thread sees the same pivot
+            r[k] = k < nk ? reciprocal(y[k]) : 0.0;
+        }
         if (mine) {
-            double x[NT];
+            auto through = [&](int i, double (&y)[4]) {      // entries of row i in the four columns as they are eliminated
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    y[k] = cj[k][i];
+#pragma unroll
+                    for (int m = 0; m < k; ++m)
+                        y[k] -= y[m] * l[k][m];
+                }
+            };
+            double x[NT][4];
 #pragma unroll
             for (int p = 0; p < NT; ++p)
-                x[p] = cj[ti + 16 * p];
+                if (p >= q0)
+                    through(ti + 16 * p, x[p]);
 #pragma unroll
-            for (int q = 0; q < NT; ++q) {
-                const int c = tc + 16 * q;
-                if (c > j && c < R) {
-                    const double xc = cj[c] * rd;
+            for (int q = 0; q < NT; ++q)
+                if (q >= q0) {
+                    const int c = tc + 16 * q;
+                    double w[4];
+                    through(c, w);
 #pragma unroll
-                    for (int p = 0; p < NT; ++p)
-                        own[p][q] -= x[p] * xc;
-                    if (c == j + 1) {
+                    for (int k = 0; k < 4; ++k)
+                        w[k] *= r[k];
 #pragma unroll
-                        for (int p = 0; p < NT; ++p)
-                            col[(j + 1) & 1][ti + 16 * p] = own[p][q];
+                    for (int p = q; p < NT; ++p)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            if (k < nk) {
+                                const double v = own[p][q] - x[p][k] * w[k];
+                                own[p][q] = q > q0 || c > j + k ? v : own[p][q];
+                            }
+                    const int k = c - (j + 4);
+                    if (k >= 0 && k < 4) {
+#pragma unroll
+                        for (int p = q; p < NT; ++p)
+                            col[((j >> 2) + 1) & 1][k][ti + 16 * p] = own[p][q];
                     }
                 }
-            }
         }
-        if (tid == 0)
-            dinv[j] = rd;
+        if (tid == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < nk)
+                    dinv[j + k] = r[k];
+        }
         __syncthreads();
     }
     if (mine) {
@@ -304,7 +354,7 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     constexpr int NT = RP / 16, THREADS = 64 * WAVES, TR = 16 * WAVES;
     constexpr int YR = RP == 64 ? 32 : TR;          // rows of a tile that pass through LDS at once
     constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
-    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][RP], nrm[RP], scale[RP];
+    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][4][RP], nrm[RP], scale[RP];
     __shared__ double Ys[YR * (RP + 1)];
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ti = tid & 15, tc = (tid >> 4) & 15, grp = tid >> 8;
@@ -527,6 +577,7 @@ __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict_
 // at a time, every sum still in a fixed order.
 // ---------------------------------------------------------------------------
 constexpr int kNB = 32;
+typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // G = A^T A: a 16 x 16 tile of G per workgroup, the rows of A in chunks of 16 through LDS, summed
 // in row order.  G(p, q) and G(q, p) add the same products in the same order: G is symmetric bit for bit.
@@ -550,93 +601,230 @@ __global__ void __launch_bounds__(256) gram_tiled(const double* __restrict__ A, 
         G[(int64_t)(p0 + ty) * R + q0 + tx] = s;
 }
 
-// One launch per 32 columns of V = L D L^T, V holding what is still to be factorised.  Workgroup (tj, ti),
-// ti >= tj, owns the 32 x 32 tile (ti, tj) of the trailing lower triangle.  It factorises the diagonal block for
-// itself, solves the two 32-row pieces of the block column that its tile needs against it, and subtracts
-// their product: no workgroup waits for another, and a step is one launch of 14 us (before: a launch for the
-// diagonal block, one for the panel and one for the update, 47 us at R = 500).  The block column of V is only
-// read; the tiles on the diagonal write their rows of L, workgroup (0, 0) the block's own rows and dinv = 1 / D.
-__global__ void __launch_bounds__(256)
-factorise_panel(double* V, int R, int j0, double* L, double* dinv_out, int* flag)
+// The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
+// a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
+template <int n> __device__ __forceinline__ double row_value(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + n, 0xf, 0xf, true); }
+// WAIT = false: only where at least two instructions lie between the write of a and this (volatile, which keeps them in their order).
+template <int n, bool WAIT = true> __device__ __forceinline__ void row_fma(double& acc, double a, double b)
 {
-    __shared__ double Lf[kNB * (kNB + 1)], dinv[kNB], col[2][kNB];
-    __shared__ double W[2][kNB][kNB + 1];
+    if constexpr (!WAIT)
+        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+    else
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+}
+
+// Steps 0 .. N - 1, with the step as a constant.
+template <int N, int n = 0, typename Step> __device__ __forceinline__ void steps(Step step)
+{
+    if constexpr (n < N) {
+        step(std::integral_constant<int, n>());
+        steps<N, n + 1>(step);
+    }
+}
+
+// L D L^T of a 16 x 16 block by one wavefront without barriers: lane c of each 16 lanes (all four hold the same) has column c in
+// a[0 .. 15], the whole symmetric block, so that the pivot row is a register and the pivot column a lane's registers.
+// Afterwards a[i] = L(i, c) D(c) for i > c; dinv[0 .. 15] (LDS) = 1 / D.  False when a pivot is not positive.
+__device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv)
+{
+    const int c = (int)threadIdx.x & 15;
+    bool ok = true;
+    steps<16>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        const double d = row_value<j>(a[j]);
+        ok = ok && d > 0.0;
+        const double r = reciprocal(d);
+        dinv[j] = r;
+        const double w = c > j ? -a[j] * r : 0.0;
+#pragma unroll
+        for (int i = j + 1; i < 16; ++i)
+            row_fma<j, j == 0 || j >= 12>(a[i], a[i], w);      // (a[i] was written a column of at least four such instructions ago)
+    });
+    return ok;
+}
+
+// One launch per 64 columns of V = L D L^T, V holding what is still to be factorised.  Workgroup (tj, ti),
+// ti >= tj, owns the 64 x 64 tile (ti, tj) of the trailing lower triangle.  It takes 192 rows of the block column through LDS, the diagonal
+// block and the 64 rows of its tile's rows and of its columns, 16 columns at a time: the first wavefront factorises the
+// 16 x 16 diagonal block, the rows below are solved against it (a wavefront for 16 rows) and subtracted from the
+// columns that follow on the matrix cores, the next diagonal block first, which the first wavefront then factorises
+// while the others go on.  At the end the tile's rows and columns are multiplied and subtracted from the tile: no workgroup waits for
+// another, and a step is one launch.  The chain of the columns bounds it (16 columns
+// take 3 us: 1.5 for their reciprocals and row operations, the rest for the exchanges): 24 us a launch, eight at R = 500 (one a 32 columns, a
+// column a barrier: sixteen of 14.4 us).
+// The block column of V is only read; the tiles on the diagonal write their rows of -L (which is what the solves add) and the same
+// above the diagonal, transposed, so that both solves read whole lines; workgroup (0, 0) the block's own rows and dinv = 1 / D.
+constexpr int kPB = 64;
+constexpr int kPanelLds = 3 * kPB * (kPB + 1) * (int)sizeof(double);
+__global__ void __launch_bounds__(512)
+factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, int* flag)
+{
+    extern __shared__ double P[];               // [3 kPB][LD]: L D of the diagonal block, of the tile's rows and of its columns
+    __shared__ double Lg[2][16 * 17], dinv[kPB];
+    __shared__ int bad;
+    constexpr int LD = kPB + 1;
     if (blockIdx.x > blockIdx.y)
         return;
-    const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4, lane = tid & 63, wave = tid >> 6;
-    const int nb = R - j0 < kNB ? R - j0 : kNB, j1 = j0 + nb;
-    // rows of the block column for this wavefront: 16 rows of tile row ti (wavefronts 0, 1) or tj (2, 3)
-    const int side = wave >> 1, part = lane & 3, wrow = 16 * (wave & 1) + (lane >> 2);
-    const int row = j1 + kNB * (int)(side == 0 ? blockIdx.y : blockIdx.x) + wrow;
-    double y[kNB / 4], own[2][2], v[2][2];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3;
+    const int nb = R - j0 < kPB ? R - j0 : kPB, j1 = j0 + nb;
+    const int ng = (nb + 15) / 16;
+    const bool trailing = j1 < R;               // then nb == 64
+    auto v_row = [&](int r) { return r < kPB ? j0 + r : j1 + kPB * (int)(r < 2 * kPB ? blockIdx.y : blockIdx.x) + (r & (kPB - 1)); };
+    {
+        // (every lane loads, from the last row or column where its own does not exist: behind branches each load would be waited for)
+        double x[24];
+        const int c = lane, cl = c < nb ? c : nb - 1;
 #pragma unroll
-    for (int q = 0; q < kNB / 4; ++q)
-        y[q] = row < R ? V[(int64_t)row * R + j0 + 4 * q + part] : 0.0;     // a trailing row: nb == 32
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int i = ti + 16 * p, c = tc + 16 * q;
-            own[p][q] = i < nb && c < nb ? V[(int64_t)(j0 + (i > c ? i : c)) * R + j0 + (i > c ? c : i)] : 0.0;
-            const int vi = j1 + kNB * (int)blockIdx.y + i, vc = j1 + kNB * (int)blockIdx.x + c;
-            v[p][q] = vi < R && vc <= vi ? V[(int64_t)vi * R + vc] : 0.0;
+        for (int i = 0; i < 24; ++i) {
+            const int vi = v_row(wave + 8 * i);
+            x[i] = V[(int64_t)(vi < R ? vi : R - 1) * R + j0 + cl];
         }
+#pragma unroll
+        for (int i = 0; i < 24; ++i) {
+            const int r = wave + 8 * i;
+            P[r * LD + c] = c < nb && v_row(r) < R && (r >= kPB || (r >= c && r < nb)) ? x[i] : 0.0;
+        }
+    }
+    // this wavefront's 16 x 16 pieces of the tile: row wave / 4 + 2 t, column wave % 4 (none above the diagonal)
+    double4_t v[2];
+    int vr[2];
+    const int vc = j1 + kPB * (int)blockIdx.x + 16 * (wave & 3);
+    bool has[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        vr[t] = j1 + kPB * (int)blockIdx.y + 16 * ((wave >> 2) + 2 * t);
+        has[t] = trailing && vr[t] >= vc && vr[t] < R;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            v[t][q] = V[(int64_t)min(vr[t] + 4 * q + kq, R - 1) * R + min(vc + n16, R - 1)];       // (what does not exist is not stored)
+    }
+    if (tid == 0)
+        bad = 0;
     if (failed_before(flag))      // (behind the loads, so that it does not delay them)
         return;
-    if (!factorise<kNB>(own, nb, col, Lf, dinv)) {
+    // rows [r0, r0 + 16) of P solved against the diagonal block of columns 16 g ..
+    auto solve = [&](int r0, int g) {
+        double y[4];
+        double* const row = P + (r0 + (lane >> 2)) * LD + 16 * g + part;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            y[q] = row[4 * q];
+        solve_forward<16>(y, Lg[g & 1], 16, part);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            row[4 * q] = y[q];
+    };
+    // piece (rows r0 .., columns 16 u ..) of P minus the product of its rows' and the column rows' solved columns 16 g ..
+    auto update = [&](int r0, int u, int g) {
+        double4_t acc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc[q] = P[(r0 + 4 * q + kq) * LD + 16 * u + n16];
+#pragma unroll
+        for (int k = 16 * g; k < 16 * g + 16; k += 4)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-P[(r0 + n16) * LD + k + kq], P[(16 * u + n16) * LD + k + kq] * dinv[k + kq], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            P[(r0 + 4 * q + kq) * LD + 16 * u + n16] = acc[q];
+    };
+    auto factor = [&](int g) {            // by the first wavefront; columns from R on as those of the identity
+        double a[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const double p = P[(16 * g + (i > n16 ? i : n16)) * LD + 16 * g + (i > n16 ? n16 : i)];
+            a[i] = i == n16 && 16 * g + i >= nb ? 1.0 : p;
+        }
+        if (!factorise16(a, dinv + 16 * g) && lane == 0)
+            bad = 1;
+        const double rd = dinv[16 * g + n16];
+        if (kq == 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                Lg[g & 1][n16 * 17 + i] = i > n16 ? a[i] * rd : 0.0;
+                if (i > n16)
+                    P[(16 * g + i) * LD + 16 * g + n16] = a[i];
+            }
+        }
+    };
+    // (one copy of each step's code: what runs once or twice waits for its instructions)
+    for (int g = 0; g <= ng; ++g) {
+        if (wave == 0) {
+            if (g < ng) {
+                if (g > 0)
+                    update(16 * g, g, g - 1);
+                factor(g);
+            }
+        } else if (g > 0) {
+            // columns 16 (g - 1) .. are solved for the diagonal block's rows: what they take from its other pieces, and the
+            // tile's rows and columns (8 pieces of 16 rows, two of them for one wavefront)
+            int n = 0;
+            for (int t = g + 1; t < ng; ++t)
+                for (int u = g; u <= t; ++u)
+                    if (n++ % 7 == wave - 1)
+                        update(16 * t, u, g - 1);
+            if (trailing)
+                for (int t = wave; t < 9; t += 7) {
+                    solve(kPB + 16 * (t - 1), g - 1);
+                    for (int u = g; u < 4; ++u)
+                        update(kPB + 16 * (t - 1), u, g - 1);
+                }
+        }
+        __syncthreads();
+        if (wave < ng - 1 - g)
+            solve(16 * (g + 1 + wave), g);
+        __syncthreads();
+    }
+    if (bad) {
         if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0)
             flag[0] = 1;
         return;
     }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        for (int t = tid; t < nb * nb; t += 256) {
-            const int i = t / nb, c = t - i * nb;
-            if (c < i)
-                L[(int64_t)(j0 + i) * R + j0 + c] = Lf[c * (kNB + 1) + i];
-        }
+        for (int r = wave; r < nb; r += 8)
+            if (lane != r && lane < nb)
+                L[(int64_t)(j0 + r) * ldL + j0 + lane] = lane < r ? -P[r * LD + lane] * dinv[lane] : -P[lane * LD + r] * dinv[r];
         if (tid < nb)
             dinv_out[j0 + tid] = dinv[tid];
     }
-    if (j1 >= R)
+    if (!trailing)
         return;
-    solve_forward<kNB>(y, Lf, kNB, part);
-#pragma unroll
-    for (int q = 0; q < kNB / 4; ++q) {
-        if (side == 1)
-            y[q] *= dinv[4 * q + part];        // rows of L itself
-        W[side][wrow][4 * q + part] = y[q];
-        if (side == 1 && blockIdx.x == blockIdx.y && row < R)
-            L[(int64_t)row * R + j0 + 4 * q + part] = y[q];
+    if (blockIdx.x == blockIdx.y) {
+        const int row0 = v_row(2 * kPB);
+        for (int r = wave; r < kPB; r += 8) {
+            if (row0 + r < R)
+                L[(int64_t)(row0 + r) * ldL + j0 + lane] = -P[(2 * kPB + r) * LD + lane] * dinv[lane];
+            if (row0 + lane < R)
+                L[(int64_t)(j0 + r) * ldL + row0 + lane] = -P[(2 * kPB + lane) * LD + r] * dinv[r];
+        }
     }
-    __syncthreads();
+    const double* const wb = P + (2 * kPB + 16 * (wave & 3) + n16) * LD + kq;
 #pragma unroll
-    for (int k = 0; k < kNB; ++k) {
-        const double a0 = W[0][ti][k], a1 = W[0][ti + 16][k], b0 = W[1][tc][k], b1 = W[1][tc + 16][k];
-        v[0][0] -= a0 * b0;
-        v[0][1] -= a0 * b1;
-        v[1][0] -= a1 * b0;
-        v[1][1] -= a1 * b1;
-    }
+    for (int t = 0; t < 2; ++t)
+        if (has[t]) {
+            const double* const wa = P + (kPB + 16 * ((wave >> 2) + 2 * t) + n16) * LD + kq;
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+            for (int k = 0; k < kPB; k += 4)
+                v[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-wa[k], wb[k] * dinv[k + kq], v[t], 0, 0, 0);
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int vi = j1 + kNB * (int)blockIdx.y + ti + 16 * p, vc = j1 + kNB * (int)blockIdx.x + tc + 16 * q;
-            if (vi < R && vc <= vi)
-                V[(int64_t)vi * R + vc] = v[p][q];
+            for (int q = 0; q < 4; ++q) {
+                const int vi = vr[t] + 4 * q + kq;
+                if (vi < R && vc + n16 <= vi)
+                    V[(int64_t)vi * R + vc + n16] = v[t][q];
+            }
         }
 }
 
 // Rows of A = M V^{-1} = M S (L D L^T)^{-1} S.  A workgroup owns 16 rows and takes them through the whole forward and
-// backward solve: per block of 32 unknowns the first wavefront solves against the diagonal block (quads of lanes
-// as above), then all wavefronts subtract the block's multiples from the columns that follow, 16 at a time on the
-// matrix cores.  The 16 x R slab lies in LDS (LDSY, R <= 1024) or in A itself.  One launch instead of four
-// per block: 129 rows at R = 500 0.89 -> 0.135 ms; bound by the chain of 2 R / 32 block solves, so what matters is
-// that loads of L are under way before a block is solved.
-typedef double double4_t __attribute__((ext_vector_type(4)));
+// backward solve, a block of 32 unknowns at a time.  Four wavefronts solve four rows each against the diagonal block (16
+// lanes hold a row's unknowns, and one that is final goes to them by DPP) while the others wait: an fp64 MFMA keeps its SIMD for 64
+// cycles, and every step of the chain would wait for one.  Then all subtract the block's multiples from the columns
+// that follow, 16 at a time on the matrix cores.  The 16 x R slab lies in LDS (LDSY, R <= 1024) or in A itself.
+// Bound by the chain of 2 R / 32 blocks, 0.55 us for the solve and about 2 for the operands and MFMAs on few compute units: 129 rows at
+// R = 500 137 -> 106 us.
 template <int WAVES, bool LDSY>
 __global__ void __launch_bounds__(64 * WAVES)
-solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv, const double* __restrict__ S, int R,
+solve_rows_blocked(const double* __restrict__ L, int ldL, const double* __restrict__ dinv, const double* __restrict__ S, int R,
                    const double* __restrict__ M, double* A, int64_t I, const int* flag)
 {
     extern __shared__ double slab[];
@@ -644,7 +832,7 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
     constexpr int THREADS = 64 * WAVES;
     if (flag[0])
         return;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, kq = lane >> 4, part = lane & 3;
     const int64_t r0 = (int64_t)blockIdx.x * 16;
     const int rows = (int)(I - r0 < 16 ? I - r0 : 16);
@@ -664,103 +852,120 @@ solve_rows_blocked(const double* __restrict__ L, const double* __restrict__ dinv
     for (int r = wave; r < 16; r += WAVES)
         for (int c = lane; c < nblk * kNB; c += 64)
             put(r, c, r < rows && c < R ? M[(r0 + r) * R + c] * S[c] : 0.0);
-    auto load_diag = [&](int b, int t0, int step) {        // entry (c, a), c > a, of the diagonal block b
-        double* const o = Ld[b & 1];
-        for (int t = t0; t < kNB * kNB; t += step) {
-            const int a = t & (kNB - 1), c = t / kNB, j0 = b * kNB;
-            o[a * (kNB + 1) + c] = c > a && j0 + c < R ? L[(int64_t)(j0 + c) * R + j0 + a] : 0.0;
-        }
+    // entry t = 32 c + a of the diagonal block b, -L(c, a) for c > a, and where it lies in Ld
+    auto diag_entry = [&](int b, int t) {
+        const int a = t & (kNB - 1), c = t / kNB, j0 = b * kNB;
+        const double l = L[(int64_t)(j0 + c) * ldL + j0 + a];
+        return c > a ? l : 0.0;
     };
-    // columns [16 ct, 16 ct + 16) -= (the block's 16 x 32 unknowns) * bt, bt[s] = row 8 kq + s of the 32 x 16 operand
-    auto update = [&](int b, int ct, const double (&bt)[8]) {
-        double4_t acc;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            acc[q] = get(4 * q + kq, 16 * ct + n16);
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-get(n16, b * kNB + 8 * kq + s), bt[s], acc, 0, 0, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            put(4 * q + kq, 16 * ct + n16, acc[q]);
-    };
-    auto diag_solve = [&](int b, bool forward) {
-        double y[kNB / 4];
-        const int r = lane >> 2;
-#pragma unroll
-        for (int q = 0; q < kNB / 4; ++q)
-            y[q] = get(r, b * kNB + 4 * q + part);
-        if (forward)
-            solve_forward<kNB>(y, Ld[b & 1], kNB, part);
-        else
-            solve_backward<kNB>(y, Ld[b & 1], kNB, part);
-#pragma unroll
-        for (int q = 0; q < kNB / 4; ++q)
-            put(r, b * kNB + 4 * q + part, y[q]);
-    };
+    auto diag_at = [](int t) { return (t & (kNB - 1)) * (kNB + 1) + t / kNB; };
     const int ncol = (R + 15) / 16;
-    load_diag(0, tid, THREADS);
-    __syncthreads();
-    for (int b = 0; b < nblk; ++b) {
-        auto load_b = [&](int ct, double (&bt)[8]) {       // L(16 ct + n, 32 b + 8 kq + s): a following row, so block b is full
-            const int c = 16 * ct + n16;
-            const double* const src = L + (int64_t)c * R + b * kNB + 8 * kq;
+    auto sweep = [&](auto forward) {
+        constexpr bool F = decltype(forward)::value;
+        const int step = F ? 1 : -1, first = F ? 0 : nblk - 1;
+        // A wavefront takes a block's unknowns to the pieces of 16 columns first_piece(b) + i WAVES.  Their operands, entry (32 b + 8 kq + s,
+        // 16 ct + n) of the symmetric -L, are requested a block ahead for the first two; always, since behind a branch they would be
+        // waited for at once: past the last piece all lanes read one value, which costs next to nothing.
+        constexpr int kAhead = 2;
+        auto first_piece = [&](int b) { return (F ? 2 * (b + 1) : 0) + wave; };
+        auto end_piece = [&](int b) { return F ? ncol : 2 * b; };
+        // (from a base in scalar registers: address arithmetic of the lanes would wait for the other wavefronts' MFMAs)
+        const uint32_t lane_off = (uint32_t)(8 * kq * ldL + n16) * (uint32_t)sizeof(double);
+        auto load = [&](int b, int ct, double (&bt)[8]) {
+            const bool some = ct < end_piece(b);
+            const char* const src = (const char*)(L + (some ? (int64_t)b * kNB * ldL + 16 * ct : 0));
+            const uint32_t off = some ? lane_off : 0u;
 #pragma unroll
             for (int s = 0; s < 8; ++s)
-                bt[s] = c < R ? src[s] : 0.0;
+                bt[s] = *(const double*)(src + (int64_t)s * ldL * (int64_t)sizeof(double) + off);
         };
-        double bt[8];
-        int ct = 2 * (b + 1) + wave;
-        if (ct < ncol)
-            load_b(ct, bt);
-        if (wave == 0)
-            diag_solve(b, true);
-        else if (b + 1 < nblk)
-            load_diag(b + 1, tid - 64, THREADS - 64);
-        __syncthreads();
-        for (; ct < ncol; ct += WAVES) {
-            double nx[8];
-            if (ct + WAVES < ncol)
-                load_b(ct + WAVES, nx);
-            update(b, ct, bt);
+        auto update = [&](int b, int ct, const double (&bt)[8]) {
+            double4_t acc;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[q] = get(4 * q + kq, 16 * ct + n16);
 #pragma unroll
             for (int s = 0; s < 8; ++s)
-                bt[s] = nx[s];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(get(n16, b * kNB + 8 * kq + s), bt[s], acc, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                put(4 * q + kq, 16 * ct + n16, acc[q]);
+        };
+        double bt[kAhead][8], diag[kNB * kNB / THREADS];       // ... and the diagonal block after the next one
+#pragma unroll
+        for (int i = 0; i < kNB * kNB / THREADS; ++i)
+            diag[i] = diag_entry(F ? min(1, nblk - 1) : max(nblk - 2, 0), tid + i * THREADS);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            load(first, first_piece(first) + i * WAVES, bt[i]);
+        for (int b = first; b >= 0 && b < nblk; b += step) {
+            if (wave < 4) {
+                double y[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    y[t] = get(4 * wave + kq, kNB * b + 16 * t + n16);
+                const double* const Lb = Ld[b & 1];
+                if (F) {
+                    steps<16>([&](auto A) {
+                        constexpr int a = decltype(A)::value;
+                        row_fma<a>(y[1], y[0], Lb[a * (kNB + 1) + 16 + n16]);
+                        row_fma<a>(y[0], y[0], Lb[a * (kNB + 1) + n16]);
+                    });
+                    steps<16>([&](auto A) {
+                        constexpr int a = decltype(A)::value;
+                        row_fma<a>(y[1], y[1], Lb[(16 + a) * (kNB + 1) + 16 + n16]);
+                    });
+                } else {
+                    steps<16>([&](auto A) {
+                        constexpr int a = 15 - decltype(A)::value;
+                        row_fma<a>(y[0], y[1], Lb[n16 * (kNB + 1) + 16 + a]);
+                        row_fma<a>(y[1], y[1], Lb[(16 + n16) * (kNB + 1) + 16 + a]);
+                    });
+                    steps<16>([&](auto A) {
+                        constexpr int a = 15 - decltype(A)::value;
+                        row_fma<a>(y[0], y[0], Lb[n16 * (kNB + 1) + a]);
+                    });
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    put(4 * wave + kq, kNB * b + 16 * t + n16, y[t]);
+            }
+            __syncthreads();
+            const int follow = F ? min(b + 1, nblk - 1) : max(b - 1, 0), after = F ? min(b + 2, nblk - 1) : max(b - 2, 0);
+            if (follow != b) {
+#pragma unroll
+                for (int i = 0; i < kNB * kNB / THREADS; ++i)
+                    Ld[follow & 1][diag_at(tid + i * THREADS)] = diag[i];
+            }
+#pragma unroll
+            for (int i = 0; i < kNB * kNB / THREADS; ++i)
+                diag[i] = diag_entry(after, tid + i * THREADS);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                if (first_piece(b) + i * WAVES < end_piece(b))
+                    update(b, first_piece(b) + i * WAVES, bt[i]);
+                load(follow, first_piece(follow) + i * WAVES, bt[i]);
+            }
+            for (int ct = first_piece(b) + kAhead * WAVES; ct < end_piece(b); ct += 2 * WAVES) {
+                double rest[2][8];
+                load(b, ct, rest[0]);
+                load(b, ct + WAVES, rest[1]);
+                update(b, ct, rest[0]);
+                if (ct + WAVES < end_piece(b))
+                    update(b, ct + WAVES, rest[1]);
+            }
+            __syncthreads();
         }
-        __syncthreads();
-    }
+    };
+    for (int t = tid; t < kNB * kNB; t += THREADS)
+        Ld[0][diag_at(t)] = diag_entry(0, t);
+    __syncthreads();
+    sweep(std::true_type());
     for (int r = wave; r < 16; r += WAVES)
         for (int c = lane; c < R; c += 64)
             put(r, c, get(r, c) * dinv[c]);
     __syncthreads();
-    for (int b = nblk - 1; b >= 0; --b) {                   // Ld[b & 1] holds block b: the last one is still there
-        auto load_b = [&](int ct, double (&bt)[8]) {       // L(32 b + 8 kq + s, 16 ct + n)
-#pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const int k = b * kNB + 8 * kq + s;
-                bt[s] = k < R ? L[(int64_t)k * R + 16 * ct + n16] : 0.0;
-            }
-        };
-        double bt[8];
-        int ct = wave;
-        if (ct < 2 * b)
-            load_b(ct, bt);
-        if (wave == 0)
-            diag_solve(b, false);
-        else if (b > 0)
-            load_diag(b - 1, tid - 64, THREADS - 64);
-        __syncthreads();
-        for (; ct < 2 * b; ct += WAVES) {
-            double nx[8];
-            if (ct + WAVES < 2 * b)
-                load_b(ct + WAVES, nx);
-            update(b, ct, bt);
-#pragma unroll
-            for (int s = 0; s < 8; ++s)
-                bt[s] = nx[s];
-        }
-        __syncthreads();
-    }
+    sweep(std::false_type());          // Ld[b & 1] holds block b: the last one is still there
     for (int r = wave; r < rows; r += WAVES)
         for (int c = lane; c < R; c += 64)
             A[(r0 + r) * R + c] = get(r, c) * S[c];
@@ -841,7 +1046,7 @@ struct Buffers {
     double* M = nullptr;        // max_n I_n x R
     double* G = nullptr;        // d x R x R Gram matrices
     double* V = nullptr;        // R x R (ranks above 64)
-    double* L = nullptr;        // R x R, then R values 1 / D and the R scales (ranks above 64)
+    double* L = nullptr;        // R x R padded to whole blocks, then R values 1 / D and the R scales (ranks above 64)
     double* gram_ws = nullptr;  // partial Gram matrices, or the fit's partial sums
     double* inner = nullptr;    // column sums of M * A (ranks up to 64)
     double* partial = nullptr;  // kNormBlocks values
@@ -906,18 +1111,18 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
 
 // Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns; many: four, so
 // that several workgroups fit a compute unit.  Above rank 1024 the slab does not fit the 160 KB of LDS.
-void solve_big(const double* L, const double* dinv, const double* S, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
+void solve_big(const double* L, int ldL, const double* dinv, const double* S, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
 {
     const unsigned grid = (unsigned)ceil_div(I, 16);
     const size_t lds = (size_t)16 * (ceil_div(R, kNB) * kNB + 1) * sizeof(double);
     if (R > 1024) {
-        hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, dinv, S, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, ldL, dinv, S, R, M, A, I, flag);
     } else if (grid <= 512) {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, dinv, S, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, ldL, dinv, S, R, M, A, I, flag);
     } else {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((solve_rows_blocked<4, true>), dim3(grid), dim3(256), lds, st, L, dinv, S, R, M, A, I, flag);
+        hipLaunchKernelGGL((solve_rows_blocked<4, true>), dim3(grid), dim3(256), lds, st, L, ldL, dinv, S, R, M, A, I, flag);
     }
 }
 
@@ -1278,6 +1483,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
     *iters = 0;
     hipStream_t st = (hipStream_t)stream;
     const int RR = R * R;
+    const int ldL = (int)ceil_div(R, kNB) * kNB;      // L in whole blocks (ranks above 64)
     // shared sweeps: the intermediates' buffer; without a cut that fits, d separate passes
     SharedPlan sp;
     if (shared && plan_shared(ndim, dims, R, (int)sizeof(double), sp) != MTTKRP_OK)
@@ -1293,7 +1499,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         };
         const int64_t chunks = ceil_div(max_I, kChunkRows);      // of the initial Gram matrices
         const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
-                     o_L = take(big ? (size_t)RR + 2 * R : 0),
+                     o_L = take(big ? (size_t)ldL * ldL + 2 * R : 0),
                      o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * RR),
                      o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4);
         const size_t o_shared = off;
@@ -1336,14 +1542,15 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         if (!big) {
             n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, st);
         } else {
-            hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(RR, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V,
-                               b.L + RR + R);
-            double* const dinv = b.L + RR;
-            for (int j0 = 0; j0 < R; j0 += kNB) {
-                const unsigned nt = R - j0 > kNB ? (unsigned)ceil_div(R - j0 - kNB, kNB) : 1u;
-                hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(256), 0, st, b.V, R, j0, b.L, dinv, b.flag);
+            double* const dinv = b.L + (size_t)ldL * ldL;
+            hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(ldL * ldL, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V,
+                               dinv + R, b.L, ldL);
+            (void)hipFuncSetAttribute((const void*)factorise_panel, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds);
+            for (int j0 = 0; j0 < R; j0 += kPB) {
+                const unsigned nt = R - j0 > kPB ? (unsigned)ceil_div(R - j0 - kPB, kPB) : 1u;
+                hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(512), kPanelLds, st, b.V, R, j0, b.L, ldL, dinv, b.flag);
             }
-            solve_big(b.L, dinv, dinv + R, R, b.M, factors[k], I, b.flag, st);
+            solve_big(b.L, ldL, dinv, dinv + R, R, b.M, factors[k], I, b.flag, st);
             gram(factors[k], I, R, b.gram_ws, b.V, st);
             const int64_t want = ceil_div(I * R + RR, 1024);
             hipLaunchKernelGGL(scale_by_gram, dim3((unsigned)(want < 4096 ? want : 4096)), dim3(256), 0, st, b.V, R, factors[k],
