@@ -1319,6 +1319,7 @@ struct Tuning {
     int64_t small_route = 0;
     int64_t small_groups = 0;
     int64_t lds_contract = 0;
+    int64_t compact = 0;        // no key of its own: a plan of little workspace (make_compact_plan)
     int64_t plain_rows = 0;     // no key of its own: row blocks of wide fp64 tiles by the general costs (choose_plan)
 };
 Tuning g_tune;
@@ -1696,7 +1697,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             // (1634685 x 2 x 7 fp32 at R = 4, second mode: 33 against 69 us).  "lds_contract" = 1 keeps the limits on memory alone.
             const Tuning none;
             Tuning rest = tn;
-            rest.small_route = rest.small_groups = rest.lds_contract = rest.plain_rows = 0;
+            rest.small_route = rest.small_groups = rest.lds_contract = rest.plain_rows = rest.compact = 0;
             const int64_t Q = pl.N / dims[0];
             if (tn.lds_contract != 2 && memcmp(&rest, &none, sizeof(rest)) == 0 && dims[0] < ((int64_t)1 << 31) && Q < ((int64_t)1 << 31) - 256) {
                 // (fp32: accumulation chains no longer than the other kernel's)
@@ -1942,12 +1943,17 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     int64_t max_steps = tn.max_steps > 0 ? tn.max_steps
                         : (sbytes == 4 ? 1024 : ((int64_t)1 << 40));   // fp32: short accumulation chains
     bool whole_rounds = false;      // F was chosen to fill whole rounds of the chip (first mode)
+    const bool matrix_bound = pl.JB >= (sbytes == 8 ? 2 : 3);       // by the matrix cores rather than by HBM
     int64_t F = ceil_div(target, base_items);
     if (F > steps_all / min_steps)
         F = steps_all / min_steps;
     if (F < 1)
         F = 1;
     if (k == 0) {
+        // Wavefronts per SIMD.  Plans of little workspace count three for large fp32 tiles, though two are resident: whole rounds
+        // of two can take more splits and more partial sums (27 x 21 x 15 x 12 x 31 at R = 2038: 10.7 -> 15.3 MB, and the
+        // sweep beyond its limit).
+        const int64_t waves = tn.compact != 0 && sbytes == 4 && pl.JB == 4 && pl.RB >= 3 ? 3 : stream_waves(sbytes, pl.RB, pl.JB);
         // One partial tile per workgroup (four splits) is written once and read once: keep
         // that traffic below ws_percent of the bytes of X, or 32 MiB if that is more.
         const double pct = tn.ws_percent > 0 ? (double)tn.ws_percent : 2.0;
@@ -1971,7 +1977,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
         // 1000 x 3 x 1000 x 100: 0.51 -> 0.45 ms; with the chip filled either way it loses 5 to 10 %)
         if (tn.first_group == 0 && pl.group == 1) {
             const double cap1 = budget / (2.0 * (double)I0 * (double)R * sbytes);
-            const double resident = 256.0 * 4.0 * stream_waves(sbytes, pl.RB, pl.JB);
+            const double resident = 1024.0 * (double)waves;
             if (cap1 < (double)F && (double)base_items * (cap1 < 1.0 ? 1.0 : cap1) < 0.9 * resident)
                 pl.group = kWaves;
         }
@@ -1991,17 +1997,20 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
         // columns are not line-aligned: those launches are bound by the lines fetched twice, not by
         // the matrix cores, and ran 3 to 9 % slower with fewer, longer items.
         if (!unaligned) {
-            const int64_t resident = 256 * 4 * (int64_t)stream_waves(sbytes, pl.RB, pl.JB);
+            const int64_t resident = 1024 * waves;
             const int64_t items = base_items * F;
             if (tn.linear != 2 && tn.target_items == 0 && items < 4 * resident && base_items <= resident) {
-                int64_t rounds = (items + resident / 2) / resident;
-                if (rounds < 1)
-                    rounds = 1;
-                int64_t Fr = rounds * resident / base_items;
-                Fr -= Fr % pl.group;
-                if (Fr >= pl.group && (double)Fr <= 1.25 * cap && steps_all / Fr >= 32 && steps_all / Fr <= max_steps) {
-                    F = Fr;
-                    whole_rounds = true;
+                const int64_t nearest = items < resident / 2 ? 1 : (items + resident / 2) / resident;
+                // (one round fewer where the cap on memory forbids the nearest number, if the matrix cores bound the launch: 77 of
+                // 82 such calls 0.85 times as long in the mean, 129^3 x 12 at R = 500 0.64 -> 0.50 ms; at lower ranks fewer, longer
+                // items lose up to 1.5 times)
+                for (int64_t rounds = nearest; rounds >= 1 && rounds >= nearest - (matrix_bound && sbytes == 8 ? 1 : 0) && !whole_rounds; --rounds) {
+                    int64_t Fr = rounds * resident / base_items;
+                    Fr -= Fr % pl.group;
+                    if (Fr >= pl.group && (double)Fr <= 1.25 * cap && steps_all / Fr >= 32 && steps_all / Fr <= max_steps) {
+                        F = Fr;
+                        whole_rounds = true;
+                    }
                 }
             }
         }
@@ -2027,7 +2036,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     // F = outer splits x inner splits.  Among the inner splits (each at least eight
     // steps long) take the pair whose largest item is closest to the average item, with the
     // fixed cost of a sweep counted in and a mild preference for reaching the wanted count.
-    {
+    auto cut = [&](int64_t F) {
         double best_eff = -1.0;
         // (candidates: 1 .. 64, then steps of an eighth up to 16384: one long column mode next to few
         // row tiles needs thousands of pieces, 400 x 10^6 at R = 32: 448 items 0.95 ms)
@@ -2066,6 +2075,36 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
                 pl.n_isplit = (int)n_in;
             }
         }
+    };
+    cut(F);
+    // Every SIMD takes a whole number of items, and where the matrix cores bound the launch it takes equally long for
+    // each: 8328 items run as long as 9216.  So a number of splits near F that leaves the least of the last item idle, an
+    // item's start and end counted as twelve steps (65 x 66 x 36 x 24 at R = 36, last mode 28.1 -> 19.8 us; 159
+    // calls that it changes 0.92 times as long in the mean, five more than 5 % slower).  Partial sums stay within what F
+    // asked for, or within 5 % of X and 64 MiB, and fp32 chains no longer than with F.
+    if (k != 0 && pl.seg == 0 && matrix_bound && tn.target_items == 0 && tn.linear == 0 && tn.inner_splits == 0) {
+        auto simd_steps = [&]() {
+            const double per_simd = (double)(base_items * pl.n_osplit * pl.n_isplit) / 1024.0;
+            return per_simd < 16.0 ? ceil(per_simd) * (double)(pl.o_per_item * (pl.cols_per_isplit / 4) + 12) : -1.0;
+        };
+        const int64_t longest = sbytes == 4 ? pl.o_per_item * (pl.cols_per_isplit / 4) : max_steps;
+        const double now = simd_steps(), row = (double)pl.n_rowblk * (double)dims[k] * (double)R * sbytes;
+        double budget = 0.05 * (double)pl.N * sbytes < kNoallocBytes ? 0.05 * (double)pl.N * sbytes : kNoallocBytes;
+        if (row * (double)(pl.n_osplit * pl.n_isplit) > budget)
+            budget = row * (double)(pl.n_osplit * pl.n_isplit);
+        double best = 0.97 * now;
+        int64_t best_F = F;
+        if (now > 0.0)
+            for (int64_t f = F - F / 3 > 1 ? F - F / 3 : 1; f <= F + F / 3; f += 1 + F / 24) {
+                cut(f);
+                const int64_t steps = pl.o_per_item * (pl.cols_per_isplit / 4);
+                const double t = simd_steps();
+                if (t > 0.0 && t < best && steps >= 32 && steps <= longest && row * (double)(pl.n_osplit * pl.n_isplit) <= budget) {
+                    best = t;
+                    best_F = f;
+                }
+            }
+        cut(best_F);
     }
     pl.steps_per_item = pl.o_per_item * (pl.cols_per_isplit / 4);
     // Linear splits: F balanced ranges of the whole step sequence, cutting sweeps where they fall.
@@ -2556,8 +2595,11 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 
 int make_compact_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 {
-    const Tuning none, tn = tuning();
-    return choose_plan(ndim, dims, R, k, sbytes, tn, memcmp(&tn, &none, sizeof(tn)) != 0, true, pl);
+    const Tuning none;
+    Tuning tn = tuning();
+    const bool tuned = memcmp(&tn, &none, sizeof(tn)) != 0;
+    tn.compact = 1;
+    return choose_plan(ndim, dims, R, k, sbytes, tn, tuned, true, pl);
 }
 
 template <typename T, int RB, int JB>

@@ -1,0 +1,32 @@
+"""Numbers of column-space splits where the matrix cores bound a launch (host only): items fill whole rounds of the chip, fp32
+chains of sums and the workspaces that callers provide stay within what they were."""
+import re
+
+import pytest
+
+from paper_2510_14891_amd import binding as mt
+
+
+def describe(dims, R, k, sbytes):
+    return {a: b for a, b in re.findall(r"(\w+)=(-?\d+)", mt.mttkrp_plan_describe(dims, R, k, sbytes).split("|")[-1])}
+
+
+def test_first_mode_takes_a_round_fewer_where_memory_forbids_the_nearest():
+    p = describe([129, 129, 129, 12], 500, 0, 8)
+    assert int(p["items"]) <= 2048 and int(p["items"]) > 1900
+    # at low rank, HBM bounds the launch and shorter items win
+    assert int(describe([224, 184, 616], 9, 0, 8)["items"]) != 4080
+
+
+@pytest.mark.parametrize("dims,R,k", [([65, 66, 36, 24], 36, 3), ([16, 16, 16, 16, 24, 8], 85, 5), ([16, 8, 16, 8, 16, 16], 52, 3)])
+def test_other_modes_leave_little_of_the_last_item_of_a_simd_idle(dims, R, k):
+    items = int(describe(dims, R, k, 8)["items"])
+    assert items / (1024.0 * -(-items // 1024)) > 0.85
+
+
+@pytest.mark.parametrize("dims,R", [([27, 21, 15, 12, 31], 2038), ([10, 6, 15, 2, 9, 6, 39], 959), ([3, 28, 12, 10, 1, 7, 49], 842)])
+def test_sweeps_near_their_limit_stay_supported(dims, R):
+    n = 4
+    for d in dims:
+        n *= d
+    assert 0 < mt.mttkrp_dense_all_modes_shared_bytes(dims, R, 4) <= max(64 << 20, n // 8)
