@@ -281,28 +281,35 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
 // part[i_t][segment][R] = this segment's share of  sum_o w(o, j) sum_s S(q, s, j),  w(o, j) = the product of the other modes'
 // factor rows: the mode-t result from the contraction over the leading index.  q runs over the modes in `p`
 // (lowest fastest), o over all of them but t, s over the row splits of the contraction.  A workgroup owns (i_t, a
-// segment of the pairs (o, s), TJ output columns); thread (tj, te) adds the pairs te, te + TE, ... in fp64 and the TE
-// subtotals are added in order.  Bound by the latency of its loads: four pairs are decoded (32-bit divisions) and
-// requested before the first is added (a 134 MB intermediate, one pair at a time with 64-bit divisions: 58 us).
-template <typename T, typename TP, int TJ>
+// segment of the pairs (o, s), TJ output columns); a thread has JV consecutive columns (the last group ends at R, columns that
+// two groups share are stored by the first) and adds the pairs te, te + TE, ... in fp64, then the TE subtotals are added
+// in order.  Decoding a pair takes some fifty instructions: for one column a thread it bounded the kernel, for four
+// 16 to 32 bytes come with it (134 MB at R = 32: 46 -> 27 us; 51 MB in fp32 27 -> 14).  Four pairs are requested before the first is added.
+template <typename T, typename TP, int TJ, int JV>
 __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T, TP> p)
 {
-    constexpr int TE = 256 / TJ, U = 4;
+    constexpr int LJ = TJ / JV, TE = 256 / LJ, U = 4;
     __shared__ double red[TE][TJ + 1];
-    const int tj = (int)threadIdx.x % TJ, te = (int)threadIdx.x / TJ;
+    const int tj = (int)threadIdx.x % LJ, te = (int)threadIdx.x / LJ;
     const uint32_t it = blockIdx.x;
-    const int j = (int)blockIdx.z * TJ + tj, jj = min(j, p.R - 1);
+    const int j = (int)blockIdx.z * TJ + tj * JV, jj = min(j, p.R - JV);
     const uint32_t e0 = blockIdx.y * p.per_seg, e1 = min(p.n_pairs, e0 + p.per_seg);
-    double acc = 0.0;
+    auto load = [](const T* src, T (&v)[JV]) { __builtin_memcpy(v, src, sizeof(v)); };     // (rows are only aligned to a value)
+    double acc[JV];
+#pragma unroll
+    for (int c = 0; c < JV; ++c)
+        acc[c] = 0.0;
     for (uint32_t e = e0 + te; e < e1; e += U * TE) {
-        T v[U];
-        double w[U];
+        T v[U][JV];
+        double w[U][JV];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool ok = e + u * TE < e1;
             const uint32_t pair = ok ? e + u * TE : e, o = p.n_split > 1 ? pair / p.n_split : pair;
             uint32_t rem = o, q = 0, stride = 1;
-            w[u] = 1.0;
+#pragma unroll
+            for (int c = 0; c < JV; ++c)
+                w[u][c] = 1.0;
             for (int m = 0; m < p.n; ++m) {
                 if (m == p.t) {
                     q += it * stride;
@@ -310,25 +317,37 @@ __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T
                     const uint32_t d = (uint32_t)p.dim[m], nx = rem / d, im = rem - nx * d;
                     rem = nx;
                     q += im * stride;
-                    w[u] *= (double)p.A[m][(int64_t)im * p.ld[m] + jj];
+                    T a[JV];
+                    load(p.A[m] + (int64_t)im * p.ld[m] + jj, a);
+#pragma unroll
+                    for (int c = 0; c < JV; ++c)
+                        w[u][c] *= (double)a[c];
                 }
                 stride *= (uint32_t)p.dim[m];
             }
-            v[u] = p.S[((int64_t)q * p.n_split + (pair - o * p.n_split)) * p.R + jj];
+            load(p.S + ((int64_t)q * p.n_split + (pair - o * p.n_split)) * p.R + jj, v[u]);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const double t = (double)v[u] * w[u];
-            acc += e + u * TE < e1 ? t : 0.0;
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < JV; ++c) {
+                const double t = (double)v[u][c] * w[u][c];
+                acc[c] += e + u * TE < e1 ? t : 0.0;
+            }
     }
-    red[te][tj] = acc;
+#pragma unroll
+    for (int c = 0; c < JV; ++c)
+        red[te][tj * JV + c] = acc[c];
     __syncthreads();
-    if (te == 0 && j < p.R) {
-        double v = 0.0;
-        for (int q = 0; q < TE; ++q)
-            v += red[q][tj];
-        p.part[((int64_t)it * gridDim.y + blockIdx.y) * p.ld_part + j] = (TP)v;
+    if (threadIdx.x < TJ) {
+        const int c = (int)threadIdx.x, first = (int)blockIdx.z * TJ + c / JV * JV;        // of the column's group
+        const int col = min(first, p.R - JV) + c % JV;
+        if (first < p.R && col >= first) {
+            double v = 0.0;
+            for (int q = 0; q < TE; ++q)
+                v += red[q][c];
+            p.part[((int64_t)it * gridDim.y + blockIdx.y) * p.ld_part + col] = (TP)v;
+        }
     }
 }
 
@@ -442,14 +461,21 @@ template <typename T> int mttkrp_contract_launch(const ContractPlan& pl, const C
 template int mttkrp_contract_launch<double>(const ContractPlan&, const ContractArgs<double>&, hipStream_t);
 template int mttkrp_contract_launch<float>(const ContractPlan&, const ContractArgs<float>&, hipStream_t);
 
-template <typename T, typename TP> int mttkrp_modesum_launch(const ModeSumArgs<T, TP>& a, int64_t I_t, int n_seg, hipStream_t st)
+template <typename T, typename TP, int JV> void modesum(const ModeSumArgs<T, TP>& a, int64_t I_t, int n_seg, hipStream_t st)
 {
     if (a.R > 16)
-        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 32>), dim3((unsigned)I_t, (unsigned)n_seg, (unsigned)((a.R + 31) / 32)), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 32, JV>), dim3((unsigned)I_t, (unsigned)n_seg, (unsigned)((a.R + 31) / 32)), dim3(256), 0, st, a);
     else if (a.R > 8)
-        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 16>), dim3((unsigned)I_t, (unsigned)n_seg, 1), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 16, JV>), dim3((unsigned)I_t, (unsigned)n_seg, 1), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 8>), dim3((unsigned)I_t, (unsigned)n_seg, 1), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((mttkrp_modesum_kernel<T, TP, 8, JV>), dim3((unsigned)I_t, (unsigned)n_seg, 1), dim3(256), 0, st, a);
+}
+template <typename T, typename TP> int mttkrp_modesum_launch(const ModeSumArgs<T, TP>& a, int64_t I_t, int n_seg, hipStream_t st)
+{
+    if (a.R >= 4)
+        modesum<T, TP, 4>(a, I_t, n_seg, st);
+    else
+        modesum<T, TP, 1>(a, I_t, n_seg, st);
     return hipGetLastError() == hipSuccess ? MTTKRP_OK : MTTKRP_ERR_DEVICE;
 }
 template int mttkrp_modesum_launch<double, double>(const ModeSumArgs<double, double>&, int64_t, int, hipStream_t);

@@ -1167,8 +1167,19 @@ sum_segments(const double* __restrict__ part, int64_t n_entries, int R, int n_se
     const int64_t i = e / R;
     const int j = (int)(e - i * R);
     double v = 0.0;
-    for (int q = 0; q < n_seg; ++q)
-        v += part[(i * n_seg + q) * R + j];
+    const double* src = part + i * n_seg * R + j;
+    int q = 0;
+    for (; q + 8 <= n_seg; q += 8) {         // eight requested before the first is added
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            t[u] = src[(int64_t)(q + u) * R];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v += t[u];
+    }
+    for (; q < n_seg; ++q)
+        v += src[(int64_t)q * R];
     M[i * ldM + j] = (T)v;
 }
 
