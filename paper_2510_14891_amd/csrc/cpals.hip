@@ -549,10 +549,36 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
     }
 }
 
-// Fit terms up to rank 64, one workgroup: out[0] = sum_j lambda_j (sum over the blocks of inner[b][j]) = <X, X^>,
-// out[1] = lambda^T (Hadamard product of all Gram matrices) lambda = ||X^||^2.
+// The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
+// the flag that ends the updates (kStopped) when it has changed by less than tol.  The host reads the records of many sweeps
+// at once: a wait for the GPU and the launches after it cost 40 us, as much as a sweep over a small tensor.
+constexpr int kFailed = 1, kStopped = 2;       // values of the flag: a pivot that is not positive; the fit has settled
+constexpr int kRecords = 64;                   // sweeps between two reads at most
+struct SweepRecord { double fit; int64_t status; };      // status: 0 go on, kStopped this was the last sweep, -1 not run, kFailed
+__device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, double inner, double model2, double tol, bool first)
+{
+    if (flag[0] != 0) {
+        record->status = flag[0] == kFailed ? kFailed : -1;
+        return;
+    }
+    const double norm2 = scalars[0], norm = sqrt(norm2);
+    double resid2 = norm2 + model2 - 2.0 * inner;
+    if (resid2 < 0.0)
+        resid2 = 0.0;
+    const double fit = norm > 0.0 ? 1.0 - sqrt(resid2) / norm : 1.0;
+    const bool settled = !first && fabs(fit - scalars[1]) < tol;
+    scalars[1] = fit;
+    record->fit = fit;
+    record->status = settled ? kStopped : 0;
+    if (settled)
+        flag[0] = kStopped;
+}
+
+// Fit terms up to rank 64, one workgroup: sum_j lambda_j (sum over the blocks of inner[b][j]) = <X, X^> and
+// lambda^T (Hadamard product of all Gram matrices) lambda = ||X^||^2, then the sweep's record.
 __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict__ G, int ndim, int R, const double* __restrict__ lambda,
-                                                        const double* __restrict__ inner, int n_inner, double* out)
+                                                        const double* __restrict__ inner, int n_inner, double* scalars, int* flag,
+                                                        SweepRecord* record, double tol, bool first)
 {
     __shared__ double lds[256];
     double s = 0.0, t = 0.0;
@@ -566,10 +592,8 @@ __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict_
     }
     s = block_sum_256(s, lds);
     t = block_sum_256(t, lds);
-    if (threadIdx.x == 0) {
-        out[0] = s;
-        out[1] = t;
-    }
+    if (threadIdx.x == 0)
+        end_sweep(scalars, flag, record, s, t, tol, first);
 }
 
 // ---------------------------------------------------------------------------
@@ -1027,17 +1051,20 @@ fit_terms_partial(const double* __restrict__ G, int ndim, int R, const double* _
         part[blockIdx.x] = s;
 }
 
-// out[b] = sum of part[first[b] ..): the two fit terms, one workgroup each, fixed order.
-__global__ void __launch_bounds__(256) fit_terms_sum(const double* __restrict__ part, int n_chunks, int R, double* out)
+// The two fit terms from their partial sums, one workgroup, fixed order, then the sweep's record.
+__global__ void __launch_bounds__(256) fit_terms_sum(const double* __restrict__ part, int n_chunks, int R, double* scalars, int* flag,
+                                                      SweepRecord* record, double tol, bool first)
 {
     __shared__ double lds[256];
-    const int i0 = blockIdx.x == 0 ? 0 : n_chunks, i1 = blockIdx.x == 0 ? n_chunks : n_chunks + R;
-    double s = 0.0;
-    for (int i = i0 + threadIdx.x; i < i1; i += 256)
+    double s = 0.0, t = 0.0;
+    for (int i = threadIdx.x; i < n_chunks; i += 256)
         s += part[i];
+    for (int i = n_chunks + threadIdx.x; i < n_chunks + R; i += 256)
+        t += part[i];
     s = block_sum_256(s, lds);
+    t = block_sum_256(t, lds);
     if (threadIdx.x == 0)
-        out[blockIdx.x] = s;
+        end_sweep(scalars, flag, record, s, t, tol, first);
 }
 
 // The driver's device memory: one allocation, cut up by cpals_run.
@@ -1050,8 +1077,9 @@ struct Buffers {
     double* gram_ws = nullptr;  // partial Gram matrices, or the fit's partial sums
     double* inner = nullptr;    // column sums of M * A (ranks up to 64)
     double* partial = nullptr;  // kNormBlocks values
-    double* scalars = nullptr;  // ||X||^2, <X, X^>, ||X^||^2, then the pivot flag
+    double* scalars = nullptr;  // ||X||^2, the fit of the sweep before, then the flag
     int* flag = nullptr;
+    SweepRecord* records = nullptr;     // kRecords of them
     void* shared_ws = nullptr;  // intermediates of the sweeps that share partial contractions
     ~Buffers() { (void)hipFree(base); }
 };
@@ -1512,7 +1540,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
                      o_L = take(big ? (size_t)ldL * ldL + 2 * R : 0),
                      o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * RR),
-                     o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4);
+                     o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4), o_rec = take(kRecords * sizeof(SweepRecord) / sizeof(double));
         const size_t o_shared = off;
         if (hipMalloc(&b.base, off + (shared ? sp.total : 0)) != hipSuccess) {
             (void)hipGetLastError();
@@ -1528,6 +1556,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         b.partial = (double*)(b.base + o_part);
         b.scalars = (double*)(b.base + o_sc);
         b.flag = (int*)(b.scalars + 3);
+        b.records = (SweepRecord*)(b.base + o_rec);
         b.shared_ws = b.base + o_shared;
     }
 
@@ -1569,50 +1598,54 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         }
         return (int)MTTKRP_OK;
     };
-    double fit_prev = 0.0;
-    for (int sweep = 0; sweep < max_iters; ++sweep) {
-        if (shared) {
-            const int rc = shared_sweep<double>(ndim, dims, X, cf, R, mo, b.shared_ws, sp.total, stream, update);
-            if (rc != MTTKRP_OK)
-                return rc;
-        } else {
-            for (int k = 0; k < ndim; ++k) {
-                const int rc = mttkrp_dense_f64(ndim, dims, X, cf, R, k, b.M, stream);
+    // Sweeps are enqueued ahead of the records that say whether they were needed: all that one read can hold where no fit
+    // ends the iteration (tol = 0), half as many as have run where a sweep costs about what the wait does (up to 2^22 values;
+    // sweeps behind the last one change nothing but b.M), one at a time otherwise.
+    SweepRecord rec[kRecords];
+    for (int done = 0; done < max_iters;) {
+        int ahead = tol == 0.0 ? kRecords : (N <= ((int64_t)1 << 22) && done > 2 ? (done / 2 < kRecords ? done / 2 : kRecords) : 1);
+        if (ahead > max_iters - done)
+            ahead = max_iters - done;
+        for (int n = 0; n < ahead; ++n) {
+            if (shared) {
+                const int rc = shared_sweep<double>(ndim, dims, X, cf, R, mo, b.shared_ws, sp.total, stream, update);
                 if (rc != MTTKRP_OK)
                     return rc;
-                update(k);
+            } else {
+                for (int k = 0; k < ndim; ++k) {
+                    const int rc = mttkrp_dense_f64(ndim, dims, X, cf, R, k, b.M, stream);
+                    if (rc != MTTKRP_OK)
+                        return rc;
+                    update(k);
+                }
+            }
+            // fit terms: b.M still holds the last mode's MTTKRP
+            const bool first = done + n == 0;
+            if (big) {
+                const int64_t I = dims[ndim - 1];
+                const int64_t per = ceil_div(I, kFitChunks) > 16 ? ceil_div(I, kFitChunks) : 16;
+                const int chunks = (int)ceil_div(I, per);
+                hipLaunchKernelGGL(fit_terms_partial, dim3((unsigned)(chunks + R)), dim3(256), 0, st, b.G, ndim, R, lambda, b.M,
+                                   factors[ndim - 1], I, chunks, per, b.gram_ws);
+                hipLaunchKernelGGL(fit_terms_sum, dim3(1), dim3(256), 0, st, b.gram_ws, chunks, R, b.scalars, b.flag,
+                                   b.records + n, tol, first);
+            } else {
+                hipLaunchKernelGGL(fit_terms_small, dim3(1), dim3(256), 0, st, b.G, ndim, R, lambda, b.inner, n_inner, b.scalars,
+                                   b.flag, b.records + n, tol, first);
             }
         }
-        // fit terms: b.M still holds the last mode's MTTKRP
-        if (big) {
-            const int64_t I = dims[ndim - 1];
-            const int64_t per = ceil_div(I, kFitChunks) > 16 ? ceil_div(I, kFitChunks) : 16;
-            const int chunks = (int)ceil_div(I, per);
-            hipLaunchKernelGGL(fit_terms_partial, dim3((unsigned)(chunks + R)), dim3(256), 0, st, b.G, ndim, R, lambda, b.M,
-                               factors[ndim - 1], I, chunks, per, b.gram_ws);
-            hipLaunchKernelGGL(fit_terms_sum, dim3(2), dim3(256), 0, st, b.gram_ws, chunks, R, b.scalars + 1);
-        } else {
-            hipLaunchKernelGGL(fit_terms_small, dim3(1), dim3(256), 0, st, b.G, ndim, R, lambda, b.inner, n_inner, b.scalars + 1);
-        }
-        double h[4];
-        if (hipMemcpyAsync(h, b.scalars, 4 * sizeof(double), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        if (hipMemcpyAsync(rec, b.records, (size_t)ahead * sizeof(SweepRecord), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return MTTKRP_ERR_DEVICE;
-        int flag = 0;
-        memcpy(&flag, h + 3, sizeof(int));
-        if (flag)
-            return MTTKRP_ERR_NUMERICAL;   // a Gram Hadamard product was not positive definite
-        const double normX = sqrt(h[0]);
-        double resid2 = h[0] + h[2] - 2.0 * h[1];
-        if (resid2 < 0.0)
-            resid2 = 0.0;
-        const double fit = normX > 0.0 ? 1.0 - sqrt(resid2) / normX : 1.0;
-        if (fits)
-            fits[sweep] = fit;
-        *iters = sweep + 1;
-        if (sweep > 0 && fabs(fit - fit_prev) < tol)
-            break;
-        fit_prev = fit;
+        for (int n = 0; n < ahead; ++n) {
+            if (rec[n].status == kFailed)
+                return MTTKRP_ERR_NUMERICAL;   // a Gram Hadamard product was not positive definite
+            if (fits)
+                fits[done] = rec[n].fit;
+            *iters = ++done;
+            if (rec[n].status == kStopped)
+                return hipGetLastError() == hipSuccess ? MTTKRP_OK : MTTKRP_ERR_DEVICE;
+        }
     }
     return hipGetLastError() == hipSuccess ? MTTKRP_OK : MTTKRP_ERR_DEVICE;
 }
