@@ -22,6 +22,7 @@ constexpr int kNormBlocks = 4096;  // partial sums of ||X||^2
 constexpr int kGramBlocks = 128;   // workgroups of an update (ranks up to 64) at most
 constexpr int kScaleBlocks = 256;  // ... of its second launch
 constexpr int kFitChunks = 256;    // row chunks of the fit's inner product (ranks above 64)
+constexpr int kFailed = 1, kStopped = 2;       // values of the flag: a pivot that is not positive; the fit has settled
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -45,6 +46,7 @@ __device__ __forceinline__ double block_sum_256(double v, double* lds)
 // (8 GB: 1.41 ms with one 8-byte load in flight, contiguous shares; 1.20 ms so).  X is 8-byte aligned;
 // an odd first value and a last one are added by block 0.
 typedef double double2_t __attribute__((ext_vector_type(2)));
+typedef double double4_t __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) sumsq_partial(const double* __restrict__ X, int64_t N, double* partial)
 {
     __shared__ double lds[256];
@@ -320,6 +322,51 @@ template <int RP> __device__ __forceinline__ void solve_backward(double (&y)[RP 
         }
 }
 
+// The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
+// a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
+template <int n> __device__ __forceinline__ double row_value(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + n, 0xf, 0xf, true); }
+// WAIT = false: only where at least two instructions lie between the write of a and this (volatile, which keeps them in their order).
+template <int n, bool WAIT = true> __device__ __forceinline__ void row_fma(double& acc, double a, double b)
+{
+    if constexpr (!WAIT)
+        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+    else
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+}
+
+// Steps 0 .. N - 1, with the step as a constant.
+template <int N, int n = 0, typename Step> __device__ __forceinline__ void steps(Step step)
+{
+    if constexpr (n < N) {
+        step(std::integral_constant<int, n>());
+        steps<N, n + 1>(step);
+    }
+}
+
+// L D L^T of a 16 x 16 block by one wavefront without barriers: lane c of each 16 lanes (all four hold the same) has column c in
+// a[0 .. 15], the whole symmetric block, so that the pivot row is a register and the pivot column a lane's registers.
+// Afterwards a[i] = L(i, c) D(c) for i > c; dinv[0 .. n - 1] (LDS) = 1 / D for the first n columns, the others are left as
+// they are.  False when a pivot is not positive.
+__device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv, int n = 16)
+{
+    const int c = (int)threadIdx.x & 15;
+    bool ok = true;
+    steps<16>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        if (j >= n)
+            return;
+        const double d = row_value<j>(a[j]);
+        ok = ok && d > 0.0;
+        const double r = reciprocal(d);
+        dinv[j] = r;
+        const double w = c > j ? -a[j] * r : 0.0;
+#pragma unroll
+        for (int i = j + 1; i < 16; ++i)
+            row_fma<j, j == 0 || j >= 12>(a[i], a[i], w);      // (a[i] was written a column of at least four such instructions ago)
+    });
+    return ok;
+}
+
 // Rows [row0, row0 + n) of A (R columns): divided by their columns' norms; returns this thread's share of the
 // column sums of M * A, which belong to column threadIdx.x % RP.
 template <int RP>
@@ -502,6 +549,146 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     }
 }
 
+// The whole update of a short factor (R <= 16, at most 16 rows a wavefront) in one workgroup, a chain of six exchanges: the Gram
+// matrices come with a wavefront each, the first wavefront multiplies and factorises them (factorise16), a wavefront solves
+// 16 rows and keeps them in registers, the Gram matrix of the new rows comes from the matrix cores and its sum over the
+// wavefronts, and the rows are scaled and written once.  100 x 80 x 60 at R = 10: 11.1 us a mode in als_update (factorisation 2.4,
+// Gram sums 2.9, rows read again 0.8, column sums 1.3) -> 6.7 (loads 0.8, product and scaling 0.9,
+// factorisation 1.1, solves 1.6, Gram matrix 0.6, scaling and sums 1.3).
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
+als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, double* lambda,
+                 double* inner, int* flag)
+{
+    static_assert(WAVES >= MTTKRP_MAX_NDIM, "a wavefront for every Gram matrix");
+    __shared__ double Gs[MTTKRP_MAX_NDIM][256], Lf[16 * 17], dinv[16], nrm[16], scale[16];
+    __shared__ double Ys[16 * WAVES * 17], red[WAVES][256], cols[WAVES][16];
+    __shared__ int bad;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3, trow = 16 * wave + (lane >> 2);
+    const int64_t RR = (int64_t)R * R;
+    // (every lane loads, from the last row or column where its own does not exist: behind branches each load is waited for)
+    const int stop = flag[0];
+    double m[4], g[4];
+    const int64_t row = trow < I ? trow : I - 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        m[q] = M[row * R + min(4 * q + part, R - 1)];
+    const double* const Gm = G + (wave < ndim ? wave : 0) * RR;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        g[q] = Gm[min(4 * q + kq, R - 1) * R + min(n16, R - 1)];
+    if (wave < ndim) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            Gs[wave][16 * (4 * q + kq) + n16] = g[q];
+    }
+    if (__syncthreads_or(stop) != 0)
+        return;
+    if (wave == 0) {
+        double a[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            a[i] = 1.0;
+        for (int t = 0; t < ndim; ++t)
+            if (t != k) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    a[i] *= Gs[t][16 * i + n16];
+            }
+        double d = 1.0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            d = i == n16 ? a[i] : d;
+        const double sc = unit_scale(d);
+        steps<16>([&](auto J) {
+            constexpr int i = decltype(J)::value;
+            a[i] = a[i] * row_value<i>(sc) * sc;
+        });
+        const bool ok = factorise16(a, dinv, R);
+        if (lane == 0)
+            bad = ok ? 0 : 1;
+        const double rd = dinv[n16 < R ? n16 : 0];
+        if (kq == 0) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                Lf[n16 * 17 + i] = i > n16 && i < R ? a[i] * rd : 0.0;
+            scale[n16] = sc;
+        }
+    }
+    __syncthreads();
+    if (bad) {
+        if (tid == 0)
+            flag[0] = kFailed;
+        return;
+    }
+    double y[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool mine = trow < I && 4 * q + part < R;
+        m[q] = mine ? m[q] : 0.0;
+        y[q] = mine ? m[q] * scale[4 * q + part] : 0.0;
+    }
+    solve_forward<16>(y, Lf, R, part);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        y[q] = 4 * q + part < R ? y[q] * dinv[4 * q + part] : 0.0;
+    solve_backward<16>(y, Lf, R, part);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        y[q] *= scale[4 * q + part];
+        Ys[trow * 17 + 4 * q + part] = y[q];
+    }
+    // Y^T Y of this wavefront's 16 rows: both operands of a step are row 4 s + kq, column n16 (from other lanes of the wavefront)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const double v = Ys[(16 * wave + 4 * s + kq) * 17 + n16];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        red[wave][16 * (4 * q + kq) + n16] = acc[q];
+    __syncthreads();
+    double sum = 0.0;
+    if (tid < 256) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+            sum += red[w][tid];
+        if ((tid >> 4) == (tid & 15)) {
+            const double n = sqrt(sum);
+            nrm[tid & 15] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+            if ((tid & 15) < R)
+                lambda[tid & 15] = n;
+        }
+    }
+    __syncthreads();
+    if (tid < 256 && (tid >> 4) < R && (tid & 15) < R)
+        G[k * RR + (tid >> 4) * R + (tid & 15)] = sum / (nrm[tid >> 4] * nrm[tid & 15]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double v = y[q] / nrm[4 * q + part];
+        if (trow < I && 4 * q + part < R)
+            A[trow * R + 4 * q + part] = v;
+        double t = m[q] * v;
+        t += __shfl_xor(t, 4);
+        t += __shfl_xor(t, 8);
+        t += __shfl_xor(t, 16);
+        t += __shfl_xor(t, 32);
+        if (lane < 4)
+            cols[wave][4 * q + part] = t;
+    }
+    __syncthreads();
+    if (tid < R) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+            v += cols[w][tid];
+        inner[tid] = v;
+    }
+}
+
 // Second launch of the update for longer factors: every workgroup adds up the columns' squared norms (n_gram
 // partial Gram matrices, in order), normalises its rows and its share of the Gram matrix, and leaves its
 // column sums of M * A in inner[block][R].
@@ -552,7 +739,6 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
 // The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
 // the flag that ends the updates (kStopped) when it has changed by less than tol.  The host reads the records of many sweeps
 // at once: a wait for the GPU and the launches after it cost 40 us, as much as a sweep over a small tensor.
-constexpr int kFailed = 1, kStopped = 2;       // values of the flag: a pivot that is not positive; the fit has settled
 constexpr int kRecords = 64;                   // sweeps between two reads at most
 struct SweepRecord { double fit; int64_t status; };      // status: 0 go on, kStopped this was the last sweep, -1 not run, kFailed
 __device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, double inner, double model2, double tol, bool first)
@@ -601,7 +787,6 @@ __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict_
 // at a time, every sum still in a fixed order.
 // ---------------------------------------------------------------------------
 constexpr int kNB = 32;
-typedef double double4_t __attribute__((ext_vector_type(4)));
 
 // G = A^T A: a 16 x 16 tile of G per workgroup, the rows of A in chunks of 16 through LDS, summed
 // in row order.  G(p, q) and G(q, p) add the same products in the same order: G is symmetric bit for bit.
@@ -623,48 +808,6 @@ __global__ void __launch_bounds__(256) gram_tiled(const double* __restrict__ A, 
     }
     if (p0 + ty < R && q0 + tx < R)
         G[(int64_t)(p0 + ty) * R + q0 + tx] = s;
-}
-
-// The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
-// a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
-template <int n> __device__ __forceinline__ double row_value(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + n, 0xf, 0xf, true); }
-// WAIT = false: only where at least two instructions lie between the write of a and this (volatile, which keeps them in their order).
-template <int n, bool WAIT = true> __device__ __forceinline__ void row_fma(double& acc, double a, double b)
-{
-    if constexpr (!WAIT)
-        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
-    else
-        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
-}
-
-// Steps 0 .. N - 1, with the step as a constant.
-template <int N, int n = 0, typename Step> __device__ __forceinline__ void steps(Step step)
-{
-    if constexpr (n < N) {
-        step(std::integral_constant<int, n>());
-        steps<N, n + 1>(step);
-    }
-}
-
-// L D L^T of a 16 x 16 block by one wavefront without barriers: lane c of each 16 lanes (all four hold the same) has column c in
-// a[0 .. 15], the whole symmetric block, so that the pivot row is a register and the pivot column a lane's registers.
-// Afterwards a[i] = L(i, c) D(c) for i > c; dinv[0 .. 15] (LDS) = 1 / D.  False when a pivot is not positive.
-__device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv)
-{
-    const int c = (int)threadIdx.x & 15;
-    bool ok = true;
-    steps<16>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-        const double d = row_value<j>(a[j]);
-        ok = ok && d > 0.0;
-        const double r = reciprocal(d);
-        dinv[j] = r;
-        const double w = c > j ? -a[j] * r : 0.0;
-#pragma unroll
-        for (int i = j + 1; i < 16; ++i)
-            row_fma<j, j == 0 || j >= 12>(a[i], a[i], w);      // (a[i] was written a column of at least four such instructions ago)
-    });
-    return ok;
 }
 
 // One launch per 64 columns of V = L D L^T, V holding what is still to be factorised.  Workgroup (tj, ti),
@@ -1103,6 +1246,14 @@ void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t 
 int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, hipStream_t st)
 {
     double* const Gk = b.G + (int64_t)k * R * R;
+    if (R <= 16 && I <= 128) {
+        hipLaunchKernelGGL((als_update_short<8>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag);
+        return 1;
+    }
+    if (R <= 16 && I <= 256) {
+        hipLaunchKernelGGL((als_update_short<16>), dim3(1), dim3(1024), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag);
+        return 1;
+    }
     if (R <= 32 && I * (R <= 16 ? 16 : 32) <= 16384) {
         const int64_t tiles = ceil_div(I, 128);
         if (R <= 16)
@@ -1598,12 +1749,14 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         }
         return (int)MTTKRP_OK;
     };
-    // Sweeps are enqueued ahead of the records that say whether they were needed: all that one read can hold where no fit
-    // ends the iteration (tol = 0), half as many as have run where a sweep costs about what the wait does (up to 2^22 values;
-    // sweeps behind the last one change nothing but b.M), one at a time otherwise.
+    // Sweeps are enqueued ahead of the records that say whether they were needed (those behind the last one change
+    // nothing but b.M): about 2 ms of them where no fit ends the iteration (tol = 0), else half as many as have run, and
+    // one at a time where a sweep takes much longer than the wait.
+    const double us = 100.0 + 1e6 * ndim * (double)N * (2.0 * R / 6e13 > 8.0 / 6e12 ? 2.0 * R / 6e13 : 8.0 / 6e12);    // a sweep, roughly
+    const int most = us > 2000.0 ? 1 : (2000.0 / us < kRecords ? (int)(2000.0 / us) : kRecords);
     SweepRecord rec[kRecords];
     for (int done = 0; done < max_iters;) {
-        int ahead = tol == 0.0 ? kRecords : (N <= ((int64_t)1 << 22) && done > 2 ? (done / 2 < kRecords ? done / 2 : kRecords) : 1);
+        int ahead = tol == 0.0 || done / 2 > most ? most : (done > 2 ? done / 2 : 1);
         if (ahead > max_iters - done)
             ahead = max_iters - done;
         for (int n = 0; n < ahead; ++n) {
