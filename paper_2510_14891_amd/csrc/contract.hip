@@ -9,7 +9,9 @@
 // tile start while the last stages of a tile are consumed, so short columns cost no drain.
 //
 // What bounds it: at R <= 16 HBM; fp64 at R = 32 reads 4.8 TB/s beside 38 TFLOP/s of the matrix cores (72 in a large product),
-// and neither goes faster beside the other.  1024 x 524288 (4.3 GB): 0.864 -> 0.763 ms at R = 8 (5.6 TB/s), 0.950 -> 0.895 at R = 32;
+// and neither goes faster beside the other.  1024 x 524288 (4.3 GB): 0.864 -> 0.763 ms at R = 8 (5.6 TB/s), 0.950 -> 0.895 at R = 32
+// (0.84 with the barrier before a stage's last quarter instead of at its end, where all wavefronts waited for LDS at once: 70
+// contractions 0.98 times as long in the mean);
 // 16641 x 60372 (8 GB): 1.63 -> 1.37 ms at R = 10; 10^6 x 400, fp32, R = 32: 0.41 -> 0.37 ms.
 #include "mttkrp_contract.h"
 
@@ -62,7 +64,7 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
     piece_t* const Xs = reinterpret_cast<piece_t*>(lds_raw);                         // [2][column][piece ^ (column & 15)]
     T* const Ks = reinterpret_cast<T*>(lds_raw + 2 * kCols * kPieces * 16);          // [2][row][NC]
 
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cw = wave, il = lane & 15, kq = lane >> 4;
     // contiguous item ranges per XCD: tiles that share the lines at their boundary meet behind one L2
     const int64_t wg = (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
@@ -78,14 +80,19 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
         return o;
     };
 
+    // stages of an item (whole ones and one that is shifted back to end with the range: the rows it repeats are masked)
+    auto stages_of = [&](const Item& o) { return (int)((o.r1 - o.r0 + SR - 1) / SR); };
+
     // --- producer: loads of (item, stage), two stages ahead of the consumer
-    int64_t p_item = wg, p_row = 0, p_end = 0;
+    int64_t p_item = wg, p_row = 0, p_last = 0;
+    int p_left = 0;                            // stages of the item not yet requested
     const T* xsrc[XL];
     const T* ksrc[KL];
     auto enter = [&]() {
         const Item o = item_of(p_item);
         p_row = o.r0;
-        p_end = o.r1;
+        p_last = o.r1 - SR;
+        p_left = stages_of(o);
 #pragma unroll
         for (int i = 0; i < XL; ++i) {
             const int id = tid + i * THREADS;
@@ -102,8 +109,7 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
     // (never skipped: behind a branch the compiler could not tell these loads from the older ones it waits for; past
     // the last item the last stage is read again and dropped)
     auto issue = [&](piece_t (&x)[XL], piece_t (&k)[KL]) {
-        // the last stage of a range is shifted back to end with it (the rows it repeats are masked)
-        const int64_t r = p_row + SR <= p_end ? p_row : p_end - SR;
+        const int64_t r = p_left > 1 ? p_row : p_last;
 #pragma unroll
         for (int i = 0; i < XL; ++i)
             x[i] = load_piece<T>(xsrc[i] + r);
@@ -111,8 +117,9 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
 #pragma unroll
         for (int i = 0; i < KL; ++i)
             k[i] = load_piece<T>(ksrc[i] + kr);
-        if (p_row + SR < p_end) {
+        if (p_left > 1) {
             p_row += SR;
+            --p_left;
         } else if (p_item + gridDim.x < p.n_items) {
             p_item += gridDim.x;
             enter();
@@ -170,49 +177,39 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
         const int ch = jb / G, n = ch < JB / G ? G : last;
         return 16 * G * ch + n * il + (jb - G * ch);
     };
-    // one stage; rows below `skip` are masked (zeros for both operands).  The LDS reads of a quarter run while the
-    // MFMAs of the one before do; the empty asm keeps the compiler from moving them down to their use.
-    auto compute = [&](int buf, int skip) {
-        const piece_t* const xa = Xs + (buf * kCols + 16 * cw + il) * kPieces;
+    // Operands of quarter t of a stage: a[t], and b[t & 1] (read one quarter ahead of its MFMAs).
+    constexpr int NTQ = kPieces / 4;
+    static_assert(NTQ == 4, "the order of a stage below");
+    piece_t a[NTQ];
+    T b[2][G][JB];
+    auto read_a = [&](int buf, int t) { a[t] = (Xs + (buf * kCols + 16 * cw + il) * kPieces)[(4 * t + kq) ^ il]; };
+    auto read_b = [&](int buf, int t) {
         const T* const kb = Ks + buf * SR * NC;
-        constexpr int NTQ = kPieces / 4;
-        piece_t a[NTQ];
-        T b[2][G][JB];
-        auto read_b = [&](int t, T (&o)[G][JB]) {
+#pragma unroll
+        for (int e = 0; e < G; ++e) {
+            const T* const row = kb + ((4 * t + kq) * G + e) * NC;
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+                b[t & 1][e][jb] = row[natural(jb)];
+        }
+    };
+    // rows below `skip` are masked (zeros for both operands)
+    auto multiply = [&](int t, int skip) {
+        if (skip > 0) {
 #pragma unroll
             for (int e = 0; e < G; ++e) {
-                const T* const row = kb + ((4 * t + kq) * G + e) * NC;
+                const bool ok = (4 * t + kq) * G + e >= skip;
+                a[t][e] = ok ? a[t][e] : (T)0;
 #pragma unroll
                 for (int jb = 0; jb < JB; ++jb)
-                    o[e][jb] = row[natural(jb)];
+                    b[t & 1][e][jb] = ok ? b[t & 1][e][jb] : (T)0;
             }
-        };
-        a[0] = xa[kq ^ il];
-        read_b(0, b[0]);
-#pragma unroll
-        for (int t = 1; t < NTQ; ++t)
-            a[t] = xa[(4 * t + kq) ^ il];
-#pragma unroll
-        for (int t = 0; t < NTQ; ++t) {
-            if (t + 1 < NTQ)
-                read_b(t + 1, b[(t + 1) & 1]);
-            asm volatile("" ::: "memory");
-            if (skip > 0) {
-#pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    const bool ok = (4 * t + kq) * G + e >= skip;
-                    a[t][e] = ok ? a[t][e] : (T)0;
-#pragma unroll
-                    for (int jb = 0; jb < JB; ++jb)
-                        b[t & 1][e][jb] = ok ? b[t & 1][e][jb] : (T)0;
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < G; ++e)
-#pragma unroll
-                for (int jb = 0; jb < JB; ++jb)
-                    acc[jb] = TT::mfma(a[t][e], b[t & 1][e][jb], acc[jb]);
         }
+#pragma unroll
+        for (int e = 0; e < G; ++e)
+#pragma unroll
+            for (int jb = 0; jb < JB; ++jb)
+                acc[jb] = TT::mfma(a[t][e], b[t & 1][e][jb], acc[jb]);
     };
     auto store = [&](const Item& o) {
         auto value = [&](int jb, int q) {
@@ -241,37 +238,54 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
         return;
     enter();
     Item cur = item_of(wg);
-    int64_t c_item = wg, c_row = cur.r0;
+    int64_t c_item = wg;
+    int c_left = stages_of(cur);
     piece_t xr[2][XL], kr[2][KL];
     issue(xr[0], kr[0]);
     issue(xr[1], kr[1]);
     stash(xr[0], kr[0], 0);
     __syncthreads();
     clear();
-    // stage n lies in buffer n & 1, stage n + 1 in register set (n + 1) & 1, stage n + 2 is requested
+    read_a(0, 0);
+    read_b(0, 0);
+    // Stage n lies in buffer n & 1, stage n + 1 in register set (n + 1) & 1, stage n + 2 is requested.  LDS is filled and the
+    // first operands of the next stage are read while MFMAs of this one run, the barrier lies before its last quarter: at the end of
+    // a stage nothing is left to wait for (all wavefronts of a compute unit may be in this one workgroup).  The empty asm keeps
+    // the compiler from moving the reads down to their use.
     auto stage = [&](int par) -> bool {
         issue(xr[par], kr[par]);
-        const int skip = c_row + SR <= cur.r1 ? 0 : (int)(c_row + SR - cur.r1);
-        if (skip == 0)
-            compute(par, 0);
-        else
-            compute(par, skip);
-        c_row += SR;
+        const int skip = c_left > 1 ? 0 : (int)(cur.r0 + (int64_t)stages_of(cur) * SR - cur.r1);
+        read_a(par, 1);
+        read_b(par, 1);
+        read_a(par, 2);
+        read_a(par, 3);
+        asm volatile("" ::: "memory");
+        multiply(0, skip);
+        read_b(par, 2);
+        asm volatile("" ::: "memory");
+        multiply(1, skip);
+        stash(xr[par ^ 1], kr[par ^ 1], par ^ 1);
+        read_b(par, 3);
+        asm volatile("" ::: "memory");
+        multiply(2, skip);
+        __syncthreads();
+        read_a(par ^ 1, 0);
+        read_b(par ^ 1, 0);
+        asm volatile("" ::: "memory");
+        multiply(3, skip);
         bool more = true;
-        if (c_row >= cur.r1) {
+        if (--c_left == 0) {
             store(cur);
             clear();
             c_item += gridDim.x;
             more = c_item < p.n_items;
             if (more) {
                 cur = item_of(c_item);
-                c_row = cur.r0;
+                c_left = stages_of(cur);
             }
         } else if (CHAINS && --chain == 0) {
             end_chain();
         }
-        stash(xr[par ^ 1], kr[par ^ 1], par ^ 1);
-        __syncthreads();
         return more;
     };
     while (stage(0) && stage(1)) {
