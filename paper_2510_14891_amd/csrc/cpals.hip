@@ -549,6 +549,37 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     }
 }
 
+// The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
+// the flag that ends the updates (kStopped) when it has changed by less than tol.  The host reads the records of many sweeps
+// at once: a wait for the GPU and the launches after it cost 40 us, as much as a sweep over a small tensor.
+constexpr int kRecords = 64;                   // sweeps between two reads at most
+struct SweepRecord { double fit; int64_t status; };      // status: 0 go on, kStopped this was the last sweep, -1 not run, kFailed
+__device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, double inner, double model2, double tol, bool first)
+{
+    if (flag[0] != 0) {
+        record->status = flag[0] == kFailed ? kFailed : -1;
+        return;
+    }
+    const double norm2 = scalars[0], norm = sqrt(norm2);
+    double resid2 = norm2 + model2 - 2.0 * inner;
+    if (resid2 < 0.0)
+        resid2 = 0.0;
+    const double fit = norm > 0.0 ? 1.0 - sqrt(resid2) / norm : 1.0;
+    const bool settled = !first && fabs(fit - scalars[1]) < tol;
+    scalars[1] = fit;
+    record->fit = fit;
+    record->status = settled ? kStopped : 0;
+    if (settled)
+        flag[0] = kStopped;
+}
+// ... and where a sweep's last update leaves it (record == nullptr: not the last one)
+struct SweepEnd {
+    double* scalars;
+    SweepRecord* record;
+    double tol;
+    bool first;
+};
+
 // The whole update of a short factor (R <= 16, at most 16 rows a wavefront) in one workgroup, a chain of six exchanges: the Gram
 // matrices come with a wavefront each, the first wavefront multiplies and factorises them (factorise16), a wavefront solves
 // 16 rows and keeps them in registers, the Gram matrix of the new rows comes from the matrix cores and its sum over the
@@ -558,10 +589,10 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
 template <int WAVES>
 __global__ void __launch_bounds__(64 * WAVES)
 als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, double* lambda,
-                 double* inner, int* flag)
+                 double* inner, int* flag, SweepEnd end)
 {
     static_assert(WAVES >= MTTKRP_MAX_NDIM, "a wavefront for every Gram matrix");
-    __shared__ double Gs[MTTKRP_MAX_NDIM][256], Lf[16 * 17], dinv[16], nrm[16], scale[16];
+    __shared__ double Gs[MTTKRP_MAX_NDIM][256], Lf[16 * 17], dinv[16], nrm[16], scale[16], weight[16], model[4];
     __shared__ double Ys[16 * WAVES * 17], red[WAVES][256], cols[WAVES][16];
     __shared__ int bad;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -583,8 +614,11 @@ als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M
         for (int q = 0; q < 4; ++q)
             Gs[wave][16 * (4 * q + kq) + n16] = g[q];
     }
-    if (__syncthreads_or(stop) != 0)
+    if (__syncthreads_or(stop) != 0) {
+        if (end.record && tid == 0)
+            end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
         return;
+    }
     if (wave == 0) {
         double a[16];
 #pragma unroll
@@ -618,8 +652,11 @@ als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M
     }
     __syncthreads();
     if (bad) {
-        if (tid == 0)
+        if (tid == 0) {
             flag[0] = kFailed;
+            if (end.record)
+                end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
+        }
         return;
     }
     double y[4];
@@ -659,13 +696,29 @@ als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M
         if ((tid >> 4) == (tid & 15)) {
             const double n = sqrt(sum);
             nrm[tid & 15] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+            weight[tid & 15] = n;
             if ((tid & 15) < R)
                 lambda[tid & 15] = n;
         }
     }
     __syncthreads();
-    if (tid < 256 && (tid >> 4) < R && (tid & 15) < R)
-        G[k * RR + (tid >> 4) * R + (tid & 15)] = sum / (nrm[tid >> 4] * nrm[tid & 15]);
+    double model2 = 0.0;                             // this thread's share of ||X^||^2 (the sweep's last update)
+    if (tid < 256 && (tid >> 4) < R && (tid & 15) < R) {
+        const double gk = sum / (nrm[tid >> 4] * nrm[tid & 15]);
+        G[k * RR + (tid >> 4) * R + (tid & 15)] = gk;
+        if (end.record) {
+            model2 = weight[tid >> 4] * weight[tid & 15];
+            for (int t = 0; t < ndim; ++t)
+                model2 *= t == k ? gk : Gs[t][tid];
+        }
+    }
+    if (end.record && tid < 256) {
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1)
+            model2 += __shfl_xor(model2, d);
+        if (lane == 0)
+            model[wave] = model2;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const double v = y[q] / nrm[4 * q + part];
@@ -686,6 +739,16 @@ als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M
         for (int w = 0; w < WAVES; ++w)
             v += cols[w][tid];
         inner[tid] = v;
+        cols[0][tid] = v * weight[tid];
+    }
+    if (end.record) {
+        __syncthreads();
+        if (tid == 0) {
+            double v = 0.0;
+            for (int j = 0; j < R; ++j)
+                v += cols[0][j];
+            end_sweep(end.scalars, flag, end.record, v, (model[0] + model[1]) + (model[2] + model[3]), end.tol, end.first);
+        }
     }
 }
 
@@ -734,30 +797,6 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
             v += red[q];
         inner[(int64_t)blockIdx.x * R + tid] = v;
     }
-}
-
-// The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
-// the flag that ends the updates (kStopped) when it has changed by less than tol.  The host reads the records of many sweeps
-// at once: a wait for the GPU and the launches after it cost 40 us, as much as a sweep over a small tensor.
-constexpr int kRecords = 64;                   // sweeps between two reads at most
-struct SweepRecord { double fit; int64_t status; };      // status: 0 go on, kStopped this was the last sweep, -1 not run, kFailed
-__device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, double inner, double model2, double tol, bool first)
-{
-    if (flag[0] != 0) {
-        record->status = flag[0] == kFailed ? kFailed : -1;
-        return;
-    }
-    const double norm2 = scalars[0], norm = sqrt(norm2);
-    double resid2 = norm2 + model2 - 2.0 * inner;
-    if (resid2 < 0.0)
-        resid2 = 0.0;
-    const double fit = norm > 0.0 ? 1.0 - sqrt(resid2) / norm : 1.0;
-    const bool settled = !first && fabs(fit - scalars[1]) < tol;
-    scalars[1] = fit;
-    record->fit = fit;
-    record->status = settled ? kStopped : 0;
-    if (settled)
-        flag[0] = kStopped;
 }
 
 // Fit terms up to rank 64, one workgroup: sum_j lambda_j (sum over the blocks of inner[b][j]) = <X, X^> and
@@ -1243,15 +1282,18 @@ void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t 
 // The update of a factor up to rank 64: one workgroup for short factors, else two launches.  Returns the number
 // of blocks that left column sums of M * A in b.inner.  One workgroup takes I * RP values up to 16384 (RP = the
 // rank rounded up to 16 or 32): its tiles then take about as long as a second launch.
-int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, hipStream_t st)
+// The update that ends a sweep also leaves its record where it can: `end` then has none any more.
+int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, SweepEnd& end, hipStream_t st)
 {
     double* const Gk = b.G + (int64_t)k * R * R;
-    if (R <= 16 && I <= 128) {
-        hipLaunchKernelGGL((als_update_short<8>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag);
-        return 1;
-    }
     if (R <= 16 && I <= 256) {
-        hipLaunchKernelGGL((als_update_short<16>), dim3(1), dim3(1024), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag);
+        const SweepEnd now = k == ndim - 1 ? end : SweepEnd{nullptr, nullptr, 0.0, false};
+        if (I <= 128)
+            hipLaunchKernelGGL((als_update_short<8>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag, now);
+        else
+            hipLaunchKernelGGL((als_update_short<16>), dim3(1), dim3(1024), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag, now);
+        if (k == ndim - 1)
+            end.record = nullptr;
         return 1;
     }
     if (R <= 32 && I * (R <= 16 ? 16 : 32) <= 16384) {
@@ -1726,12 +1768,13 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         mo[m] = b.M;
     }
     int n_inner = 1;            // blocks that left column sums of M * A at the last update
+    SweepEnd end = {nullptr, nullptr, 0.0, false};
     // the update of factor k from its MTTKRP in b.M
     auto update = [&](int k) {
         double* const Gk = b.G + (int64_t)k * RR;
         const int64_t I = dims[k];
         if (!big) {
-            n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, st);
+            n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, end, st);
         } else {
             double* const dinv = b.L + (size_t)ldL * ldL;
             hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(ldL * ldL, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V,
@@ -1760,6 +1803,8 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         if (ahead > max_iters - done)
             ahead = max_iters - done;
         for (int n = 0; n < ahead; ++n) {
+            const bool first = done + n == 0;
+            end = {b.scalars, b.records + n, tol, first};
             if (shared) {
                 const int rc = shared_sweep<double>(ndim, dims, X, cf, R, mo, b.shared_ws, sp.total, stream, update);
                 if (rc != MTTKRP_OK)
@@ -1772,8 +1817,9 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
                     update(k);
                 }
             }
-            // fit terms: b.M still holds the last mode's MTTKRP
-            const bool first = done + n == 0;
+            // fit terms, unless the last update has left them: b.M still holds the last mode's MTTKRP
+            if (!end.record)
+                continue;
             if (big) {
                 const int64_t I = dims[ndim - 1];
                 const int64_t per = ceil_div(I, kFitChunks) > 16 ? ceil_div(I, kFitChunks) : 16;
