@@ -2134,6 +2134,10 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     if (pl.n_splits >= ((int64_t)1 << 30))
         return MTTKRP_ERR_UNSUPPORTED;
     if (k == 0) {
+        // One range of the column space: there is nothing to share, and three of four wavefronts of a group would be idle
+        // (10^6 x 20 x 20 fp32 at R = 32 374 -> 342 us).
+        if (pl.n_splits == 1 && tn.first_group == 0)
+            pl.group = 1;
         pl.n_slots = ceil_div(pl.n_splits, pl.group);    // one partial tile per group of wavefronts
         pl.n_items = base_items * pl.n_slots * pl.group;
     } else if (pl.seg_store) {

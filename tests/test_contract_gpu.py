@@ -91,6 +91,29 @@ def test_modes_from_the_contraction(mt, oracle, dims, R, dtype):
         assert bool((Mw[:, R:] == 1.0).all())
 
 
+# Ranks below a thread's four consecutive columns, and ranks whose last group of four overlaps the one before it.
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("R", [2, 3, 6, 7, 9, 18, 30, 31])
+def test_modes_from_the_contraction_at_ragged_ranks(mt, oracle, R, dtype):
+    dims = (3000, 20, 21)
+    X = inputs.uniform(17, int(np.prod(dims)), -1.0, 1.0, dtype=dtype)
+    A = [inputs.uniform(18 + m, (I, R), -1.0, 1.0, dtype=dtype) for m, I in enumerate(dims)]
+    Xn, An = inputs.as_ndarray_view(X, dims), [a.numpy() for a in A]
+    Xd, Ad = X.cuda(), [a.cuda() for a in A]
+    for k in (1, 2):
+        mt.mttkrp_tune_set("small_route", 2)
+        mt.mttkrp_tune_set("lds_contract", 1)
+        plan = mt.mttkrp_plan_describe(dims, R, k, X.element_size())
+        print("modes from the contraction, ragged rank dims=%s R=%d k=%d %s" % (dims, R, k, plan), flush=True)
+        M = torch.full((dims[k], R + 3), 1.0, dtype=dtype, device="cuda")
+        mt.mttkrp_dense_ld(Xd, dims, Ad, k, M[:, :R], R)
+        mt.mttkrp_tune_set("small_route", 0)
+        mt.mttkrp_tune_set("lds_contract", 0)
+        assert "lds=1" in plan or (R < 4 and dtype == torch.float32)          # (streaming plans)
+        assert oracle.normwise_rel_err(M[:, :R].cpu().numpy(), oracle.mttkrp(Xn, An, k)) <= TOL[dtype], k
+        assert bool((M[:, R:] == 1.0).all())
+
+
 # The same with two and three blocks of output columns, which this route takes for longer first modes only: against float64
 # products on the GPU.
 @pytest.mark.parametrize("dims,R,k,dtype", [((120000, 3, 130), 20, 2, torch.float64), ((120000, 3, 130), 20, 2, torch.float32),

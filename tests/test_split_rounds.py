@@ -30,3 +30,9 @@ def test_sweeps_near_their_limit_stay_supported(dims, R):
     for d in dims:
         n *= d
     assert 0 < mt.mttkrp_dense_all_modes_shared_bytes(dims, R, 4) <= max(64 << 20, n // 8)
+
+
+@pytest.mark.parametrize("dims,R,sbytes", [([1000000, 20, 20], 32, 4), ([400000, 7, 6], 40, 8)])
+def test_one_range_of_the_column_space_leaves_no_wavefront_idle(dims, R, sbytes):
+    p = describe(dims, R, 0, sbytes)
+    assert p["outer_splits"] == p["inner_splits"] == "1" and p["items"] == p["row_blocks"], p
