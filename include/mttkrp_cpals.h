@@ -21,15 +21,16 @@
  * The paper's CP-ALS experiment (Sec. IV-C) runs ranks 10, 500, 1000 and 2000; up to rank
  * 64 the R x R work (Hadamard product of the Gram matrices, its L D L^T factor, row solves) runs
  * in registers of one workgroup per block of rows, in one or two launches per mode; above that blocked
- * from global memory, 32 columns a launch of the factor and one launch for the solves (then also
+ * from global memory, 64 columns a launch of the factor and one launch for the solves (then also
  * every I_n <= 1048560).
  *
  * Everything runs on the GPU in fp64 with fixed-order reductions (reruns are
- * bit-identical); the host only reads three scalars per sweep to evaluate the
- * stopping rule.  Layouts, index base and pointer ownership are those of
+ * bit-identical), the fit and the stopping rule among them; sweeps are enqueued ahead
+ * of the host's read of their fits (about 2 ms of them, 64 at most; those enqueued
+ * behind the last one leave the factors alone).  Layouts, index base and pointer ownership are those of
  * mttkrp.h.  The driver allocates its own device buffers (O(R * max_n I_n +
  * d * R^2) values besides the MTTKRP workspace) and frees them before it
- * returns; it synchronises the stream once per sweep.
+ * returns; it synchronises the stream once for each such group of sweeps.
  */
 #ifndef MTTKRP_CPALS_H
 #define MTTKRP_CPALS_H

@@ -7,7 +7,7 @@ Default: the shape of the paper's 5-way tensor (129 x 129 x 129 x 12 x 39) fille
 rank-10 Kruskal tensor plus 1 % noise, R = 10, tolerance 1e-4 (the setting of the paper's CP-ALS
 experiment, Sec. IV-C, at its smallest rank).  The MTTKRP share comes from the HIP events the
 library records around its own kernels; the rest is "other CP-ALS operations" (Gram matrices,
-Cholesky solve, normalisation, fit) plus one stream synchronisation per sweep.  With --shared
+Cholesky solve, normalisation, fit) plus the host's reads of the fits.  With --shared
 the sweeps share partial contractions between the modes (mttkrp_cpals_shared_f64: two passes
 over X per sweep); the run is then followed by the plain driver on the same start, for the
 time per sweep side by side and the largest difference of the fits.
