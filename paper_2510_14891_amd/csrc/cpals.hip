@@ -1039,7 +1039,7 @@ solve_rows_blocked(const double* __restrict__ L, int ldL, const double* __restri
     if (flag[0])
         return;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3;
+    const int n16 = lane & 15, kq = lane >> 4;
     const int64_t r0 = (int64_t)blockIdx.x * 16;
     const int rows = (int)(I - r0 < 16 ? I - r0 : 16);
     const int nblk = (R + kNB - 1) / kNB;
