@@ -2173,7 +2173,10 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     // of X; contiguous workgroup ranges per XCD put them behind one L2 (measured 3 % at R = 128).
     pl.xcd_remap = tn.xcd_remap == 1 || (tn.xcd_remap == 0 && k == 0 && pl.n_jchunk > 1);
     pl.wave_cap = (int)tn.waves_per_simd;
-    pl.nt_off = tn.nt_loads == 1;
+    // Several chunks of output columns read the same piece of X, which a non-temporal load lets the L2 drop before the next
+    // one has come: fp64 with line-aligned columns, 16384 x 2048 x 64 at R = 128, first and last mode 8.73 -> 8.19 and 8.22 ->
+    // 7.87 ms, 1024 x 1024 x 512 at R = 96 1.66 -> 1.56; 18 calls at R = 96 to 500 0.963 times as long in the mean, none slower.
+    pl.nt_off = tn.nt_loads == 1 || pl.n_jchunk > 1;
     // short items: their prologue and epilogue dominate, more resident wavefronts win
     pl.deep = tn.deep == 1 ? true : tn.deep == 2 ? false : pl.steps_per_item >= 32;
     return MTTKRP_OK;
