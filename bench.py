@@ -495,8 +495,8 @@ def main() -> int:
         "floor_over_kernel_ms": round(floor_ms / kernel_ms, 4),
         "how": "mttkrp_calibrate_stream over X (non-temporal 16-byte loads only) and mttkrp_calibrate_mfma "
                "(independent 16x16x4 MFMAs on register operands, 2 N R flops per launch); floor = the larger "
-               "of bytes / stream rate and flops / MFMA rate; the MFMA probe runs 32 wavefronts per CU and "
-               "its clock drops further than the kernel's, so a ratio above 1 can occur",
+               "of bytes / stream rate and flops / MFMA rate; the MFMA probe keeps its sums in "
+               "accumulation registers, where fp64 products run slower than in the kernel's, so a ratio above 1 can occur",
     }
     # beside the headline (d separate MTTKRPs per step): the same d results from the sweep that
     # shares partial contractions between the modes
