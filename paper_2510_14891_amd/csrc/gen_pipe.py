@@ -11,7 +11,7 @@ MFMAs of an earlier step run.
 One step = four tensor columns: the X loads of the tile's RB row blocks, the
 loads of the inner factor's entries for the JB column blocks (both in the lane
 layout the kernel defines: `Lay` / `LayRows` in mttkrp.hip), JB multiplies by
-the sweep weight (or none, see POST) and RB * JB 16x16x4 MFMAs.  A run covers any n >= D consecutive
+the sweep weight and RB * JB 16x16x4 MFMAs.  A run covers any n >= D consecutive
 unmasked steps of one sweep: the X pointer and the factor offsets advance by
 constant strides.  Both bases lie in scalar registers and are advanced by the
 scalar unit; a lane's offsets from them are 32-bit registers that never change.
@@ -52,13 +52,13 @@ def others(i):
     return OTHERS[i.w] + (14 if i.w == 2 and i.rb * i.jb == 12 else 0)
 
 
-def POST(i):
-    """Runs that sum their steps' products without the sweep's weight; the weight then multiplies the sums once (RB * JB * 4
-    FMAs a run for JB multiplies a step, which cost 15 to 25 cycles of the 512 of a step: see above).  Taken where the
-    second set of sums fits beside the operands and the matrix cores bound the kernel: 401 x 201 x 12 x 501 at R = 1000
-    15.58 -> 15.17 ms, 1024 x 1024 x 512 at R = 32 1.3 % a pass, 48^5 fp32 at R = 64 2 %; fp32 with four row blocks, whose
-    other build kept 66 registers in scratch memory, 6 % in the mean of 30 calls and up to 25 %."""
-    return i.rb * i.jb >= 8 if i.w == 2 else i.jb == 4 and i.rb >= 3
+# A step's factor entries take the sweep's weight before they meet X, as everywhere else in the kernel.  Runs that summed X times
+# the inner factor and multiplied the sums by the weight afterwards were 1 % faster in the mean (RB * JB * 4 FMAs a run for JB
+# multiplies a step, 401 x 201 x 12 x 501 at R = 1000 2.5 %), but such a sum can leave the type's range where the weight brings
+# it back (fp32: X 1e25, inner factor 1e15, outer 1e-15 became infinite), and a guard against that costs what they gain.  (fp32
+# tiles of three or four row and four column blocks run three wavefronts a SIMD, though that keeps up to 66 registers in scratch
+# memory outside the runs: two wavefronts without any took 1.02 times as long in the mean of 20 calls at R = 50 to 200, 16384 x 256
+# x 64 at R = 128 508 -> 561 us.)
 
 
 def even(n):
@@ -97,25 +97,19 @@ class Inst:
         self.pick()
 
     def ring(self, d):
-        return self.set * (d + 1) + (0 if self.post else self.bc)
+        return self.set * (d + 1) + self.bc
 
     def pick(self):
-        for self.post in (POST(self), False):
-            if self.fit():
-                return
-
-    def fit(self):
         for budget, waves in ((128, 4), (168, 3), (256, 2)):
             for d in range(D_MAX, D_MIN - 1, -1):
                 if d * self.loads > 63:
                     continue
-                if self.acc * (2 if self.post else 1) + others(self) + self.ring(d) <= budget:
+                if self.acc + others(self) + self.ring(d) <= budget:
                     self.budget, self.waves, self.d = budget, waves, d
                     self.t0 = budget - self.ring(d)
                     self.t0 -= self.t0 & 1
-                    return True
+                    return
         self.budget = 0      # nothing fits: no pipelined run for this instantiation
-        return False
 
     def tag(self):
         return "%s%d%d" % ("d" if self.w == 2 else "f", self.rb, self.jb)
@@ -157,19 +151,17 @@ class Inst:
         o.append("s_addc_u32 s%d, s%d, 0" % (S0 + 5, S0 + 5))
         return o
 
-    def consume(self, s, wait, first=False):
+    def consume(self, s, wait):
         mul = "v_mul_f64" if self.w == 2 else "v_mul_f32"
         mfma = "v_mfma_f64_16x16x4_f64" if self.w == 2 else "v_mfma_f32_16x16x4_f32"
         o = ["s_waitcnt vmcnt(%d)" % wait]
-        if not self.post:
-            for j in range(self.jb):
-                o.append("%s %s, %s, %%[q%d]" % (mul, self.bcval(j), self.bval(s, j), j))
-            o.append("s_nop 1")
+        for j in range(self.jb):
+            o.append("%s %s, %s, %%[q%d]" % (mul, self.bcval(j), self.bval(s, j), j))
+        o.append("s_nop 1")
         for r in range(self.rb):
             for j in range(self.jb):
                 a = "%%[a%d%d]" % (r, j)
-                b = self.bval(s, j) if self.post else self.bcval(j)
-                o.append("%s %s, %s, %s, %s" % (mfma, a, self.xval(s, r), b, "0" if first else a))
+                o.append("%s %s, %s, %s, %s" % (mfma, a, self.xval(s, r), self.bcval(j), a))
         return o
 
     def block(self, nt):
@@ -177,17 +169,8 @@ class Inst:
         o = ["s_nop 4", "s_mov_b64 %s, %%[xb]" % XB, "s_mov_b64 s[%d:%d], %%[xs]" % (S0 + 2, S0 + 3), "s_mov_b64 %s, %%[bb]" % BB]
         for k in range(d):
             o += self.issue(k, nt)
-        if self.post:        # the first step starts the sums
-            o.append("s_cmp_eq_u32 %[n], 0")
-            o.append("s_cbranch_scc1 20f")
-            o += self.issue(d, nt)
-            o.append("s_sub_u32 %[n], %[n], 1")
-            o += self.consume(0, d * l, True)
-            o.append("s_branch 2f")
         o.append("1:")
         for u in range(s_n):
-            if self.post and u == 1:
-                o.append("2:")
             o.append("s_cmp_eq_u32 %[n], 0")
             o.append("s_cbranch_scc1 %df" % (10 + u))
             o += self.issue((u + d) % s_n, nt)
@@ -198,12 +181,8 @@ class Inst:
             o.append("%d:" % (10 + u))
             for k in range(d):
                 o += self.consume((u + k) % s_n, (d - 1 - k) * l)
-            if self.post or u < s_n - 1:
+            if u < s_n - 1:
                 o.append("s_branch 9f")
-        if self.post:
-            o.append("20:")
-            for k in range(d):
-                o += self.consume(k, (d - 1 - k) * l, k == 0)
         o.append("9:")
         o += ["s_nop 7", "s_nop 7", "s_nop 7"]
         return o
@@ -219,13 +198,11 @@ class Inst:
             out += " \\\n".join('    "%s\\n"' % line for line in self.block(nt)) + "\n"
         clob = ", ".join('"v%d"' % v for v in range(self.t0, self.last_reg() + 1))
         clob += ", " + ", ".join('"s%d"' % v for v in range(S0, S0 + 6))
-        accs = ", ".join('[a%d%d] "%s"(%s[%d][%d])' % (r, j, "=&v" if self.post else "+v", "run" if self.post else "acc", r, j)
-                         for r in range(self.rb) for j in range(self.jb))
-        outs = '[n] "+s"(n_more), ' + accs
+        accs = ", ".join('[a%d%d] "+v"(acc[%d][%d])' % (r, j, r, j) for r in range(self.rb) for j in range(self.jb))
+        outs = '[n] "+&s"(n_more), ' + accs
         ins = '[xb] "s"(xbase), [xs] "s"(x_step_bytes), [bb] "s"(bbase), [bs] "s"(b_step_bytes), [xo0] "v"(xo0), [bo0] "v"(bo0), ' + \
-              ('[xo1] "v"(xo1)' + ", " if self.two_x else "") + ('[bo1] "v"(bo1), ' if self.two_b else "") + \
-              ("" if self.post else ", ".join('[q%d] "v"(q[%d])' % (j, j) for j in range(self.jb)))
-        ins = ins.rstrip(", ")
+              ('[xo1] "v"(xo1), ' if self.two_x else "") + ('[bo1] "v"(bo1), ' if self.two_b else "") + \
+              ", ".join('[q%d] "v"(q[%d])' % (j, j) for j in range(self.jb))
         out += "template <> struct Pipe<%s, %d, %d> {\n" % (c, self.rb, self.jb)
         out += "    static constexpr bool value = true;\n"
         out += "    static constexpr int depth = %d;\n    static constexpr int waves = %d;\n" % (self.d, self.waves)
@@ -238,16 +215,11 @@ class Inst:
             out += "        (void)xo1;\n"
         if not self.two_b:
             out += "        (void)bo1;\n"
-        if self.post:
-            out += "        typename Mfma<%s>::acc_t run[%d][%d];\n" % (c, self.rb, self.jb)
         if self.w == 2:
             out += "        if (NT)\n"
             out += "            asm volatile(MTTKRP_PIPE_%s_ASM_NT : %s : %s : %s, \"scc\", \"memory\");\n" % (t, outs, ins, clob)
             out += "        else\n    "
         out += "        asm volatile(MTTKRP_PIPE_%s_ASM : %s : %s : %s, \"scc\", \"memory\");\n" % (t, outs, ins, clob)
-        if self.post:
-            out += "#pragma unroll\n        for (int r = 0; r < %d; ++r)\n#pragma unroll\n            for (int j = 0; j < %d; ++j)\n" % (self.rb, self.jb)
-            out += "                acc[r][j] += run[r][j] * q[j];\n"
         out += "    }\n};\n\n"
         return out
 
@@ -271,8 +243,8 @@ def main(path=None):
     with open(path, "w") as f:
         f.write(out)
     for i in insts:
-        print("%s%s: acc %3d, set %2d, depth %d, budget %d (%d waves), ring v[%d:%d], loads/step %d" % (
-            i.tag(), " post" if i.post else "", i.acc, i.set, i.d, i.budget, i.waves, i.t0, i.last_reg(), i.loads))
+        print("%s: acc %3d, set %2d, depth %d, budget %d (%d waves), ring v[%d:%d], loads/step %d" % (
+            i.tag(), i.acc, i.set, i.d, i.budget, i.waves, i.t0, i.last_reg(), i.loads))
     return path
 
 

@@ -1319,8 +1319,6 @@ struct Tuning {
     int64_t small_route = 0;
     int64_t small_groups = 0;
     int64_t lds_contract = 0;
-    int64_t compact = 0;        // no key of its own: a plan of little workspace (make_compact_plan)
-    int64_t plain_rows = 0;     // no key of its own: row blocks of wide fp64 tiles by the general costs (choose_plan)
 };
 Tuning g_tune;
 std::mutex g_mutex;
@@ -1339,6 +1337,14 @@ Tuning tuning_for(bool compact)
         tn.lds_contract = 1;
     return tn;
 }
+
+// The keys, and what the library itself asks of one plan among others (choose_plan).
+struct Wanted : Tuning {
+    Wanted() = default;
+    Wanted(const Tuning& keys) : Tuning(keys) {}
+    bool plain_rows = false;    // row blocks of wide fp64 tiles by the general costs
+    int waves = 0;              // wavefronts a SIMD that whole rounds are counted with (0: those that run)
+};
 
 struct LeadingPlan {
     int JB = 1, n_jchunk = 1, CB = 1, n_cchunk = 1, n_rsplit = 1, rows_per_split = 16;
@@ -1572,7 +1578,7 @@ int choose_row_blocks(int64_t rows, int R, int sbytes, double (&eff)[5], int& rb
     return best;
 }
 
-int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl, bool prefer_rows,
+int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const Wanted& tn, Plan& pl, bool prefer_rows,
                   bool no_pair_first = false)
 {
     const int64_t* const dims_in = dims;
@@ -1697,7 +1703,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             // (1634685 x 2 x 7 fp32 at R = 4, second mode: 33 against 69 us).  "lds_contract" = 1 keeps the limits on memory alone.
             const Tuning none;
             Tuning rest = tn;
-            rest.small_route = rest.small_groups = rest.lds_contract = rest.plain_rows = rest.compact = 0;
+            rest.small_route = rest.small_groups = rest.lds_contract = 0;
             const int64_t Q = pl.N / dims[0];
             if (tn.lds_contract != 2 && memcmp(&rest, &none, sizeof(rest)) == 0 && dims[0] < ((int64_t)1 << 31) && Q < ((int64_t)1 << 31) - 256) {
                 // (fp32: accumulation chains no longer than the other kernel's)
@@ -1793,7 +1799,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
         auto tile_rows = [&](int64_t rows, int& rb_out) {
             double eff[5];
             int rb_max = 1;
-            rb_out = choose_row_blocks(rows, R, sbytes, eff, rb_max, tn.plain_rows != 0);
+            rb_out = choose_row_blocks(rows, R, sbytes, eff, rb_max, tn.plain_rows);
             if (tn.row_blocks >= 1 && tn.row_blocks <= rb_max)
                 rb_out = (int)tn.row_blocks;
             return eff[rb_out];
@@ -1877,7 +1883,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     {
         double eff[5];
         int rb_max = 1;
-        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max, tn.plain_rows != 0, k == 0);
+        int best = choose_row_blocks(I0, R, sbytes, eff, rb_max, tn.plain_rows, k == 0);
         double best_eff = 0.0;
         for (int rb = 1; rb <= rb_max; ++rb)
             if (eff[rb] > best_eff)
@@ -1950,10 +1956,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     if (F < 1)
         F = 1;
     if (k == 0) {
-        // Wavefronts per SIMD.  Plans of little workspace count three for large fp32 tiles, though two are resident: whole rounds
-        // of two can take more splits and more partial sums (27 x 21 x 15 x 12 x 31 at R = 2038: 10.7 -> 15.3 MB, and the
-        // sweep beyond its limit).
-        const int64_t waves = tn.compact != 0 && sbytes == 4 && pl.JB == 4 && pl.RB >= 3 ? 3 : stream_waves(sbytes, pl.RB, pl.JB);
+        const int64_t waves = tn.waves > 0 ? tn.waves : stream_waves(sbytes, pl.RB, pl.JB);
         // One partial tile per workgroup (four splits) is written once and read once: keep
         // that traffic below ws_percent of the bytes of X, or 32 MiB if that is more.
         const double pct = tn.ws_percent > 0 ? (double)tn.ws_percent : 2.0;
@@ -2190,7 +2193,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
 // workspace), i.e. the contraction over the leading index.  Taken when K stays cache-resident
 // (4 MiB) and mode 0 alone fills the streaming kernel's row tiles badly: then neither kernel has a
 // plan with long work items (20 x 20 x 10^6 at R = 32: 2.1 ms on the second schedule, 0.68 ms here).
-void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl)
+void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, const Wanted& tn, Plan& pl)
 {
     if (k != ndim - 1 || ndim < 2 || tn.lead_last == 2 || (tn.contract_rows == 1 && tn.lead_last != 1))
         return;
@@ -2203,7 +2206,7 @@ void maybe_lead_route(int ndim, const int64_t* dims, int R, int k, int sbytes, c
     if (tn.lead_last != 1) {
         double eff[5];
         int rb_max = 1;
-        const int rb = choose_row_blocks(dims[0], R, sbytes, eff, rb_max, tn.plain_rows != 0);
+        const int rb = choose_row_blocks(dims[0], R, sbytes, eff, rb_max, tn.plain_rows);
         if (eff[rb] >= 0.9 && rb > 2)
             return;
     }
@@ -2251,7 +2254,7 @@ double plan_cost(const Plan& pl)
            (1.0 + 2.0 * (double)pl.part_bytes / ((double)pl.N * pl.sbytes));
 }
 
-int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Tuning& tn, Plan& pl)
+int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const Wanted& tn, Plan& pl)
 {
     int rc = make_plan_for(ndim, dims, R, k, sbytes, tn, pl, false);
     if (rc == MTTKRP_OK && pl.seg_store) {
@@ -2456,14 +2459,23 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
     if (tn.row_blocks == 0 && sbytes == 8 && R > 48) {
         // Fewer row blocks a wavefront can mean more partial rows (446 x 118 x 9560 at R = 64, third mode: 49 -> 69 MB): the
         // costs of wide tiles choose only within min(5 % of the tensor, 64 MiB) or the memory of the other plan.
-        Tuning general = tn;
-        general.plain_rows = 1;
+        Wanted general = tn;
+        general.plain_rows = true;
         Plan c;
         double most = 0.05 * (double)pl.N * sbytes;
         if (most > kNoallocBytes)
             most = kNoallocBytes;
         if ((double)pl.ws_bytes > most && make_general_plan(ndim, dims, R, k, sbytes, general, c) == MTTKRP_OK &&
             c.ws_bytes < pl.ws_bytes)
+            pl = c;
+    }
+    if (compact && sbytes == 4 && R > 48) {
+        // Whole rounds of three wavefronts a SIMD can take more splits than those of two, and more partial sums (1 x 13 x 55 x 12 x 2 x
+        // 152 x 30 at R = 263: the sweep beyond its limit).
+        Wanted two = tn;
+        two.waves = 2;
+        Plan c;
+        if (make_general_plan(ndim, dims, R, k, sbytes, two, c) == MTTKRP_OK && c.ws_bytes < pl.ws_bytes)
             pl = c;
     }
     if (!tuned)
@@ -2602,11 +2614,8 @@ int make_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 
 int make_compact_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, Plan& pl)
 {
-    const Tuning none;
-    Tuning tn = tuning();
-    const bool tuned = memcmp(&tn, &none, sizeof(tn)) != 0;
-    tn.compact = 1;
-    return choose_plan(ndim, dims, R, k, sbytes, tn, tuned, true, pl);
+    const Tuning none, tn = tuning();
+    return choose_plan(ndim, dims, R, k, sbytes, tn, memcmp(&tn, &none, sizeof(tn)) != 0, true, pl);
 }
 
 template <typename T, int RB, int JB>

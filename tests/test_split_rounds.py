@@ -24,7 +24,8 @@ def test_other_modes_leave_little_of_the_last_item_of_a_simd_idle(dims, R, k):
     assert items / (1024.0 * -(-items // 1024)) > 0.85
 
 
-@pytest.mark.parametrize("dims,R", [([27, 21, 15, 12, 31], 2038), ([10, 6, 15, 2, 9, 6, 39], 959), ([3, 28, 12, 10, 1, 7, 49], 842)])
+@pytest.mark.parametrize("dims,R", [([27, 21, 15, 12, 31], 2038), ([10, 6, 15, 2, 9, 6, 39], 959), ([3, 28, 12, 10, 1, 7, 49], 842),
+                                    ([1, 13, 55, 12, 2, 152, 30], 263), ([16, 36, 14, 108, 2, 10], 398)])
 def test_sweeps_near_their_limit_stay_supported(dims, R):
     n = 4
     for d in dims:
