@@ -26,9 +26,10 @@
  *
  * Everything runs on the GPU in fp64 with fixed-order reductions (reruns are
  * bit-identical), the fit and the stopping rule among them; sweeps are enqueued ahead
- * of the host's read of their fits (about 2 ms of them, 64 at most; those enqueued
- * behind the last one leave the factors alone).  Layouts, index base and pointer ownership are those of
- * mttkrp.h.  The driver allocates its own device buffers (O(R * max_n I_n +
+ * of the host's read of their fits: with tol = 0 about 2 ms of them, 16 at most, with a
+ * tolerance only as many as the fit's last changes promise not to settle.  Those enqueued behind the
+ * last one leave the factors alone; a factorisation that fails is reported after them.
+ * Layouts, index base and pointer ownership are those of mttkrp.h.  The driver allocates its own device buffers (O(R * max_n I_n +
  * d * R^2) values besides the MTTKRP workspace) and frees them before it
  * returns; it synchronises the stream once for each such group of sweeps.
  */

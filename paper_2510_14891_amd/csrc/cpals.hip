@@ -8,6 +8,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <chrono>
 #include <type_traits>
 
 #include "../../include/mttkrp.h"
@@ -552,7 +553,8 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
 // The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
 // the flag that ends the updates (kStopped) when it has changed by less than tol.  The host reads the records of many sweeps
 // at once: a wait for the GPU and the launches after it cost 40 us, as much as a sweep over a small tensor.
-constexpr int kRecords = 64;                   // sweeps between two reads at most
+constexpr int kRecords = 16;                   // sweeps between two reads at most
+constexpr double kWaitUs = 40.0, kAheadUs = 2000.0;
 struct SweepRecord { double fit; int64_t status; };      // status: 0 go on, kStopped this was the last sweep, -1 not run, kFailed
 __device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, double inner, double model2, double tol, bool first)
 {
@@ -1690,6 +1692,29 @@ int mttkrp_dense_all_modes_shared_f32(int ndim, const int64_t* dims, const float
 
 namespace {
 
+// How many sweeps to enqueue before the host reads their records, after `done` sweeps with the last fits f[0], f[1], f[2], when a
+// sweep takes about `us`.  Without a tolerance every sweep is wanted: as many as take 2 ms (a factorisation that fails is
+// reported so much later).  With one, those behind the last sweep would run their MTTKRPs for nothing, so only as many go
+// ahead as will not settle if the fit's changes shrink as they did from the last sweep but one to the last, by a margin
+// of two; and what is lost when that prediction fails stays below what a wait for each of the sweeps so far costs.  60 CP-ALS
+// runs of 5 to 200 sweeps (numpy), against a wait a sweep: 0.84 times as long in the mean at 60 us a sweep and a tolerance of 1e-4, 0.93 at 150,
+// 0.98 at 350, at worst 1.08 (half as many as have run, whatever the fits: 0.92, 1.03, 1.06, at worst 1.24).
+int sweeps_ahead(int done, const double (&f)[3], double tol, double us)
+{
+    const int most = us > kAheadUs ? 1 : (kAheadUs / us < kRecords ? (int)(kAheadUs / us) : kRecords);
+    if (tol == 0.0)
+        return most;
+    if (done < 3)
+        return 1;
+    const double before = fabs(f[1] - f[0]), last = fabs(f[2] - f[1]);
+    const double shrinks = last < 0.95 * before ? last / before : 0.95;
+    const int affordable = 1 + (int)(kWaitUs * done / us < kRecords ? kWaitUs * done / us : kRecords);
+    int n = 1;
+    for (double change = last * shrinks; n < most && n < affordable && change > 2.0 * tol; change *= shrinks)
+        ++n;
+    return n;
+}
+
 int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* factors, double* lambda,
               int R, int max_iters, double tol, int* iters, double* fits, void* stream, bool shared)
 {
@@ -1792,16 +1817,21 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         }
         return (int)MTTKRP_OK;
     };
-    // Sweeps are enqueued ahead of the records that say whether they were needed (those behind the last one change
-    // nothing but b.M): about 2 ms of them where no fit ends the iteration (tol = 0), else half as many as have run, and
-    // one at a time where a sweep takes much longer than the wait.
-    const double us = 100.0 + 1e6 * ndim * (double)N * (2.0 * R / 6e13 > 8.0 / 6e12 ? 2.0 * R / 6e13 : 8.0 / 6e12);    // a sweep, roughly
-    const int most = us > 2000.0 ? 1 : (2000.0 / us < kRecords ? (int)(2000.0 / us) : kRecords);
+    // A sweep's time, estimated and then measured (the fastest group so far): MTTKRPs, launches, above rank 64 the chains of the
+    // factorisation and the solves (0.6 us a column: 300 us a mode at R = 500) and their products.
+    double us = 60.0 + 1e6 * ndim * (double)N * (2.0 * R / 6e13 > 8.0 / 6e12 ? 2.0 * R / 6e13 : 8.0 / 6e12);
+    if (big)
+        for (int m = 0; m < ndim; ++m)
+            us += 0.6 * R + 1e6 * (double)RR * (4.0 * (double)dims[m] + R) / 3e13;
+    // Sweeps are enqueued ahead of the records that say whether they were needed (those behind the last one change nothing but
+    // b.M and V).
     SweepRecord rec[kRecords];
+    double last_fits[3] = {0.0, 0.0, 0.0};
     for (int done = 0; done < max_iters;) {
-        int ahead = tol == 0.0 || done / 2 > most ? most : (done > 2 ? done / 2 : 1);
+        int ahead = sweeps_ahead(done, last_fits, tol, us);
         if (ahead > max_iters - done)
             ahead = max_iters - done;
+        const auto start = std::chrono::steady_clock::now();
         for (int n = 0; n < ahead; ++n) {
             const bool first = done + n == 0;
             end = {b.scalars, b.records + n, tol, first};
@@ -1836,11 +1866,16 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         if (hipMemcpyAsync(rec, b.records, (size_t)ahead * sizeof(SweepRecord), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return MTTKRP_ERR_DEVICE;
+        const double took = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - start).count() / ahead;
+        us = done == 0 || took < us ? took : us;
         for (int n = 0; n < ahead; ++n) {
             if (rec[n].status == kFailed)
                 return MTTKRP_ERR_NUMERICAL;   // a Gram Hadamard product was not positive definite
             if (fits)
                 fits[done] = rec[n].fit;
+            last_fits[0] = last_fits[1];
+            last_fits[1] = last_fits[2];
+            last_fits[2] = rec[n].fit;
             *iters = ++done;
             if (rec[n].status == kStopped)
                 return hipGetLastError() == hipSuccess ? MTTKRP_OK : MTTKRP_ERR_DEVICE;
