@@ -221,6 +221,9 @@ template <typename T, int RB, int JB> struct Budget {
     static constexpr int steps = raw > kMaxBatchSteps ? kMaxBatchSteps : (raw < 2 ? 2 : raw);
 };
 
+// Offsets of a step's four columns from the first one's start fit 32 bits: an inner mode's stride (values) below 1.4 GB.
+__host__ __device__ inline bool lane_offsets_fit(int64_t sx_in, int64_t sbytes) { return (3 * sx_in + 64) * sbytes < ((int64_t)1 << 32); }
+
 // One wavefront = one work item = (row block, column-block chunk, batch value,
 // inner split, outer split).  No LDS, no barriers.
 //
@@ -492,10 +495,8 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
     // Other wavefronts of the SIMD fill the gaps between batches.
     //   plain batch:   U unmasked steps of one sweep: one weight Q, constant strides
     //   generic batch: any steps (sweep boundaries, masked last step, parked padding)
-    // the pipelined run takes a lane's offsets as 32-bit numbers (an inner mode of this many steps with a stride beyond
-    // that needs a tensor of over 180 GB; it runs in batches)
-    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31) &&
-                         (3 * p.sx_in + 64) * (int64_t)sizeof(T) < ((int64_t)1 << 32);
+    // the pipelined run takes a lane's offsets as 32-bit numbers
+    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31) && lane_offsets_fit(p.sx_in, sizeof(T));
     int done = 0;
     while (done < n_steps) {
         if constexpr (kPipe) {
@@ -2180,8 +2181,11 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     // one has come: fp64 with line-aligned columns, 16384 x 2048 x 64 at R = 128, first and last mode 8.73 -> 8.19 and 8.22 ->
     // 7.87 ms, 1024 x 1024 x 512 at R = 96 1.66 -> 1.56; 18 calls at R = 96 to 500 0.963 times as long in the mean, none slower.
     pl.nt_off = tn.nt_loads == 1 || pl.n_jchunk > 1;
-    // short items: their prologue and epilogue dominate, more resident wavefronts win
-    pl.deep = tn.deep == 1 ? true : tn.deep == 2 ? false : pl.steps_per_item >= 32;
+    // Short items: their prologue and epilogue dominate, more resident wavefronts win.  Where the run's offsets do not fit, its
+    // build would be left with two-step batches at few wavefronts (tensors from 35 GB on, 100000 x 16 x 120 x 32 at R = 32, third
+    // mode 10.3 ms, with the batches' own build 8.9; at R = 64 19.0 and 15.8; fp32 200000 x 16 x 140 x 30 at R = 64 19.2 and 18.3).
+    pl.deep = tn.deep == 1 ? true : tn.deep == 2 ? false
+              : pl.steps_per_item >= 32 && (pl.inner < 0 || lane_offsets_fit(pl.strides[pl.inner], sbytes));
     return MTTKRP_OK;
 }
 
@@ -3741,13 +3745,13 @@ int mttkrp_plan_describe(int ndim, const int64_t* dims, int R, int k, int dtype_
              "shape=%s rows_per_wave=%d row_blocks=%d col_blocks=%d j_chunks=%d inner_mode=%d "
              "outer_modes=%d batch=%d o_per_item=%lld outer_splits=%lld inner_splits=%d "
              "items=%lld steps_per_item=%lld slots=%lld ws_bytes=%zu fused_modes=%d fused_rows=%d fused_bytes=%zu "
-             "paired_rows=%d",
+             "paired_rows=%d deep=%d",
              k == 0 ? "first" : (k == ndim - 1 ? "last" : "middle"), 16 * pl.RB, pl.n_rowblk,
              pl.JB, pl.n_jchunk, pl.inner, pl.n_out, pl.n_batch, (long long)pl.o_per_item,
              (long long)pl.n_osplit, pl.n_isplit, (long long)pl.n_items,
              (long long)pl.steps_per_item, (long long)pl.n_slots, pl.ws_bytes,
              pl.fuse_a >= 0 ? pl.orig[pl.fuse_a] : -1, pl.n_fuse > 0 && pl.fus[0].red == 0 ? 1 : 0, pl.fused_bytes,
-             pl.seg > 0 ? (pl.seg_store ? 3 : (pl.seg_first ? 2 : 1)) : 0);
+             pl.seg > 0 ? (pl.seg_store ? 3 : (pl.seg_first ? 2 : 1)) : 0, pl.deep ? 1 : 0);
     return MTTKRP_OK;
 }
 

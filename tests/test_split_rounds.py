@@ -1,5 +1,6 @@
-"""Numbers of column-space splits where the matrix cores bound a launch (host only): items fill whole rounds of the chip, fp32
-chains of sums and the workspaces that callers provide stay within what they were."""
+"""Plans of the streaming kernel (host only): numbers of column-space splits where the matrix cores bound a launch (items fill
+whole rounds of the chip, fp32 chains of sums and the workspaces that callers provide stay within what they were), and
+which of its two builds runs."""
 import re
 
 import pytest
@@ -37,3 +38,17 @@ def test_sweeps_near_their_limit_stay_supported(dims, R):
 def test_one_range_of_the_column_space_leaves_no_wavefront_idle(dims, R, sbytes):
     p = describe(dims, R, 0, sbytes)
     assert p["outer_splits"] == p["inner_splits"] == "1" and p["items"] == p["row_blocks"], p
+
+
+# (stride of the inner mode times four columns: below and beyond 2^32 bytes; extents of one kind otherwise)
+@pytest.mark.parametrize("dims,R,k,sbytes,deep", [([100000, 16, 80, 32], 32, 2, 8, 1), ([100000, 16, 120, 32], 32, 2, 8, 0),
+                                                  ([100000, 16, 120, 32], 32, 2, 4, 1), ([200000, 16, 140, 30], 64, 2, 4, 0),
+                                                  ([200000, 16, 100, 30], 64, 2, 4, 1)])
+def test_the_run_is_built_in_only_where_its_offsets_fit(dims, R, k, sbytes, deep):
+    p = describe(dims, R, k, sbytes)
+    inner = int(p["inner_mode"])
+    stride = 1
+    for d in dims[:inner]:
+        stride *= d
+    assert ((3 * stride + 64) * sbytes < 2 ** 32) == bool(deep)
+    assert int(p["steps_per_item"]) >= 32 and int(p["deep"]) == deep, p
