@@ -47,8 +47,10 @@ OTHERS = {2: 60, 1: 56}      # registers the rest of the kernel keeps live acros
 
 
 def others(i):
-    """The same for one instantiation.  (With twelve fp64 accumulators and 60 the addresses of a run's loads lay in scratch
-    memory and every run waited for them: 124387 x 4^5 at R = 397, first mode, 7.84 -> 5.66 ms, 3 % in the mean of 56 calls.)"""
+    """The same for one instantiation.  (With twelve fp64 accumulators 60 would let D = 5 fit.  D = 4 takes sweeps of four
+    steps through the run too, 124387 x 4^5 at R = 397, first mode 2.87 -> 2.16 ms, and is 1 % faster in the mean of 20 other
+    calls.  The tile of three row and four column blocks reloads its lanes' offsets of X from scratch memory before each run
+    either way; forming them from the lane number there instead gave nothing, 0.997 in the mean of 21 calls.)"""
     return OTHERS[i.w] + (14 if i.w == 2 and i.rb * i.jb == 12 else 0)
 
 
