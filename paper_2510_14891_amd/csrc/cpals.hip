@@ -326,13 +326,21 @@ template <int RP> __device__ __forceinline__ void solve_backward(double (&y)[RP 
 // The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
 // a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
 template <int n> __device__ __forceinline__ double row_value(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + n, 0xf, 0xf, true); }
-// WAIT = false: only where at least two instructions lie between the write of a and this (volatile, which keeps them in their order).
-template <int n, bool WAIT = true> __device__ __forceinline__ void row_fma(double& acc, double a, double b)
+template <int n> __device__ __forceinline__ void row_fma(double& acc, double a, double b)
 {
-    if constexpr (!WAIT)
-        asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
-    else
-        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
+}
+// a[i] += (a[i] of lane n) * b for i = n + 1 .. 15, in one block, so that nothing can come between its instructions: each takes and
+// writes registers of its own, and the two wait states in front cover the ones written right before the block.
+template <int n> __device__ __forceinline__ void row_fmas(double (&a)[16], double b)
+{
+#define ROW_FMA(i) "\n\t.if " #i " > %c17\n\tv_fmac_f64_dpp %" #i ", %" #i ", %16 row_newbcast:%c17 row_mask:0xf bank_mask:0xf\n\t.endif"
+    asm("s_nop 1" ROW_FMA(1) ROW_FMA(2) ROW_FMA(3) ROW_FMA(4) ROW_FMA(5) ROW_FMA(6) ROW_FMA(7) ROW_FMA(8) ROW_FMA(9) ROW_FMA(10)
+            ROW_FMA(11) ROW_FMA(12) ROW_FMA(13) ROW_FMA(14) ROW_FMA(15)
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]),
+          "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
+        : "v"(b), "n"(n));
+#undef ROW_FMA
 }
 
 // Steps 0 .. N - 1, with the step as a constant.
@@ -361,9 +369,8 @@ __device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv, int n
         const double r = reciprocal(d);
         dinv[j] = r;
         const double w = c > j ? -a[j] * r : 0.0;
-#pragma unroll
-        for (int i = j + 1; i < 16; ++i)
-            row_fma<j, j == 0 || j >= 12>(a[i], a[i], w);      // (a[i] was written a column of at least four such instructions ago)
+        if constexpr (j < 15)
+            row_fmas<j>(a, w);
     });
     return ok;
 }
