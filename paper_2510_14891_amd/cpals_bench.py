@@ -7,7 +7,8 @@ Default: the shape of the paper's 5-way tensor (129 x 129 x 129 x 12 x 39) fille
 rank-10 Kruskal tensor plus 1 % noise, R = 10, tolerance 1e-4 (the setting of the paper's CP-ALS
 experiment, Sec. IV-C, at its smallest rank).  The MTTKRP share comes from the HIP events the
 library records around its own kernels; the rest is "other CP-ALS operations" (Gram matrices,
-Cholesky solve, normalisation, fit) plus the host's reads of the fits.  With --shared
+Cholesky solve, normalisation, fit) plus the host's reads of the fits; sweeps that were enqueued
+ahead of the fit that ended the iteration are counted apart.  With --shared
 the sweeps share partial contractions between the modes (mttkrp_cpals_shared_f64: two passes
 over X per sweep); the run is then followed by the plain driver on the same start, for the
 time per sweep side by side and the largest difference of the fits.
@@ -22,6 +23,20 @@ import time
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
+
+
+KEPT_CALLS = 512        # whose events the library keeps
+
+
+def mttkrp_times(timing_get, n_calls, n_wanted):
+    """Milliseconds of the first n_wanted of n_calls timed MTTKRPs, and of those behind them: with a tolerance the driver
+    enqueues sweeps ahead of the fit that ends the iteration, and those behind the last one are discarded.  Only the events of
+    the last calls are kept; the wanted ones among them stand for all."""
+    first = max(0, n_calls - KEPT_CALLS)
+    ms = [sum(timing_get(i)) for i in range(first, n_calls)]
+    wanted = ms[:max(0, n_wanted - first)]
+    scale = n_wanted / len(wanted) if wanted else 0.0
+    return scale * sum(wanted), sum(ms[len(wanted):])
 
 
 def main() -> int:
@@ -58,21 +73,16 @@ def main() -> int:
     t = time.perf_counter() - t0
     n_calls = mt.mttkrp_timing_count()
     mt.mttkrp_timing_enable(False)
-    first = max(0, n_calls - 512)
-    mttkrp_ms = 0.0
-    for i in range(first, n_calls):
-        a, b = mt.mttkrp_timing_get(i)
-        mttkrp_ms += a + b
-    if first > 0:       # only the last 512 calls are kept: scale to all of them
-        mttkrp_ms *= n_calls / float(n_calls - first)
     sweeps = len(fits)
+    wanted_ms, discarded_ms = mttkrp_times(mt.mttkrp_timing_get, n_calls, w.ndim * sweeps)
     print("# CP-ALS: %s, R = %d, tolerance %g, one MI355X" % (w.name, R, args.tol))
     print()
-    print("| sweeps | final fit | total s | ms per sweep | MTTKRP ms per sweep (%d calls) | MTTKRP share | other ms per sweep |" % w.ndim)
-    print("|---|---|---|---|---|---|---|")
+    print("| sweeps | discarded | final fit | total s | ms per sweep | MTTKRP ms per sweep (%d calls) | MTTKRP share | other ms per sweep |" % w.ndim)
+    print("|---|---|---|---|---|---|---|---|")
     per = 1e3 * t / sweeps
-    mper = mttkrp_ms / sweeps
-    print("| %d | %.6f | %.3f | %.3f | %.3f | %.1f %% | %.3f |" % (sweeps, fits[-1], t, per, mper, 100 * mper / per, per - mper))
+    mper = wanted_ms / sweeps
+    print("| %d | %d | %.6f | %.3f | %.3f | %.3f | %.1f %% | %.3f |" % (sweeps, n_calls // w.ndim - sweeps, fits[-1], t, per, mper, 100 * mper / per,
+                                                                  per - mper - discarded_ms / sweeps))
     print()
     print("fit per sweep: " + " ".join("%.5f" % f for f in fits))
     if args.shared:
