@@ -15,8 +15,15 @@ def describe(dims, R, k, sbytes):
 def test_first_mode_takes_a_round_fewer_where_memory_forbids_the_nearest():
     p = describe([129, 129, 129, 12], 500, 0, 8)
     assert int(p["items"]) <= 2048 and int(p["items"]) > 1900
-    # at low rank, HBM bounds the launch and shorter items win
-    assert int(describe([224, 184, 616], 9, 0, 8)["items"]) != 4080
+
+
+# At low rank, HBM bounds the launch and shorter items win.  The nearest number of rounds is beyond the cap on memory for these
+# calls, and a round fewer (4080, 6072 and 8192 items of 33 to 45 steps) is within it.
+@pytest.mark.parametrize("dims,R,items,steps", [([160, 163, 10, 65], 9, 6500, 21), ([1440, 39, 1206], 14, 7360, 37), ([96, 24, 16, 1425], 6, 11400, 24)])
+def test_first_mode_at_low_rank_keeps_its_items(dims, R, items, steps):
+    p = describe(dims, R, 0, 8)
+    assert p["col_blocks"] == "1" and p["paired_rows"] == "0"
+    assert int(p["items"]) == items and int(p["steps_per_item"]) == steps, p
 
 
 @pytest.mark.parametrize("dims,R,k", [([65, 66, 36, 24], 36, 3), ([16, 16, 16, 16, 24, 8], 85, 5), ([16, 8, 16, 8, 16, 16], 52, 3)])
