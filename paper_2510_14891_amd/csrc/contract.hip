@@ -296,8 +296,8 @@ __global__ void __launch_bounds__(64 * CW, CW == 4 && JB <= 2 ? 3 : 2) mttkrp_co
 // factor rows: the mode-t result from the contraction over the leading index.  q runs over the modes in `p`
 // (lowest fastest), o over all of them but t, s over the row splits of the contraction.  A workgroup owns (i_t, a
 // segment of the pairs (o, s), TJ output columns); a thread has JV consecutive columns (the last group ends at R, columns that
-// two groups share are stored by the first) and adds the pairs te, te + TE, ... in fp64, then the TE subtotals are added
-// in order.  Decoding a pair takes some fifty instructions: for one column a thread it bounded the kernel, for four
+// two groups share are stored by the first) and adds the pairs te, te + TE, ... in fp64, then the first wavefront adds the TE
+// subtotals, several lanes a column (one lane: 128 dependent additions up to R = 8, 0 to 5 % of a sweep over small tensors).  Decoding a pair takes some fifty instructions: for one column a thread it bounded the kernel, for four
 // 16 to 32 bytes come with it (134 MB at R = 32: 46 -> 27 us; 51 MB in fp32 27 -> 14).  Four pairs are requested before the first is added.
 template <typename T, typename TP, int TJ, int JV>
 __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T, TP> p)
@@ -353,13 +353,18 @@ __global__ void __launch_bounds__(256) mttkrp_modesum_kernel(const ModeSumArgs<T
     for (int c = 0; c < JV; ++c)
         red[te][tj * JV + c] = acc[c];
     __syncthreads();
-    if (threadIdx.x < TJ) {
-        const int c = (int)threadIdx.x, first = (int)blockIdx.z * TJ + c / JV * JV;        // of the column's group
+    if (threadIdx.x < 64) {
+        constexpr int TG = 64 / TJ;                   // lanes that share a column's subtotals
+        const int c = (int)threadIdx.x % TJ, g = (int)threadIdx.x / TJ, first = (int)blockIdx.z * TJ + c / JV * JV;        // of the column's group
         const int col = min(first, p.R - JV) + c % JV;
-        if (first < p.R && col >= first) {
-            double v = 0.0;
-            for (int q = 0; q < TE; ++q)
-                v += red[q][c];
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < TE / TG; ++q)
+            v += red[g * (TE / TG) + q][c];
+#pragma unroll
+        for (int d = TJ; d < 64; d <<= 1)
+            v += __shfl_xor(v, d);
+        if (g == 0 && first < p.R && col >= first) {
             p.part[((int64_t)it * gridDim.y + blockIdx.y) * p.ld_part + col] = (TP)v;
         }
     }
