@@ -8,11 +8,11 @@
 // LDS, K's rows beside them, so that K is read once per workgroup.  Workgroups are persistent and the loads of the next
 // tile start while the last stages of a tile are consumed, so short columns cost no drain.
 //
-// What bounds it: at R <= 16 HBM; fp64 at R = 32 reads 4.8 TB/s beside 38 TFLOP/s of the matrix cores (72 in a large product),
-// and neither goes faster beside the other.  1024 x 524288 (4.3 GB): 0.864 -> 0.763 ms at R = 8 (5.6 TB/s), 0.950 -> 0.895 at R = 32
-// (0.84 with the barrier before a stage's last quarter instead of at its end, where all wavefronts waited for LDS at once: 70
-// contractions 0.98 times as long in the mean);
-// 16641 x 60372 (8 GB): 1.63 -> 1.37 ms at R = 10; 10^6 x 400, fp32, R = 32: 0.41 -> 0.37 ms.
+// What bounds it: at R <= 16 HBM; fp64 at R = 32 reads 5.0 TB/s beside 40 TFLOP/s of the matrix cores (72 in a large product),
+// and neither goes faster beside the other.  Against mttkrp_rowsum_kernel, 20 to 80 calls in a row: 1024 x 524288 (4.3 GB) 0.863 ->
+// 0.777 ms at R = 8 (5.5 TB/s), 0.954 -> 0.866 at R = 32; 16641 x 60372 (8 GB) at R = 10 1.63 -> 1.37; 10^6 x 400, fp32, R = 32 0.410 ->
+// 0.409.  The barrier before a stage's last quarter instead of at its end, where all wavefronts waited for LDS at once: 70
+// contractions 0.98 times as long in the mean (the last of these 0.425 -> 0.409, 1024 x 524288 at R = 32 0.875 -> 0.866).
 #include "mttkrp_contract.h"
 
 #include <math.h>

@@ -2006,7 +2006,7 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
             if (tn.linear != 2 && tn.target_items == 0 && items < 4 * resident && base_items <= resident) {
                 const int64_t nearest = items < resident / 2 ? 1 : (items + resident / 2) / resident;
                 // (one round fewer where the cap on memory forbids the nearest number, if the matrix cores bound the launch: 77 of
-                // 82 such calls 0.85 times as long in the mean, 129^3 x 12 at R = 500 0.64 -> 0.50 ms; at lower ranks fewer, longer
+                // 82 such calls 0.85 times as long in the mean, 129^3 x 12 at R = 500 0.60 -> 0.46 ms; at lower ranks fewer, longer
                 // items lose up to 1.5 times)
                 for (int64_t rounds = nearest; rounds >= 1 && rounds >= nearest - (matrix_bound && sbytes == 8 ? 1 : 0) && !whole_rounds; --rounds) {
                     int64_t Fr = rounds * resident / base_items;
@@ -2178,8 +2178,9 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     pl.xcd_remap = tn.xcd_remap == 1 || (tn.xcd_remap == 0 && k == 0 && pl.n_jchunk > 1);
     pl.wave_cap = (int)tn.waves_per_simd;
     // Several chunks of output columns read the same piece of X, which a non-temporal load lets the L2 drop before the next
-    // one has come: fp64 with line-aligned columns, 16384 x 2048 x 64 at R = 128, first and last mode 8.73 -> 8.19 and 8.22 ->
-    // 7.87 ms, 1024 x 1024 x 512 at R = 96 1.66 -> 1.56; 18 calls at R = 96 to 500 0.963 times as long in the mean, none slower.
+    // one has come: fp64 with line-aligned columns, ten calls in a row of 16384 x 2048 x 64 at R = 128, first and last mode 8.63 ->
+    // 8.06 and 8.14 -> 7.77 ms (on a card that clocks lower 8.84 -> 8.28 and 8.36 -> 7.99), 1024 x 1024 x 512 at R = 96, first mode
+    // 1.64 -> 1.54; 18 calls at R = 96 to 500 0.963 times as long in the mean, none slower.
     pl.nt_off = tn.nt_loads == 1 || pl.n_jchunk > 1;
     // Short items: their prologue and epilogue dominate, more resident wavefronts win.  Where the run's offsets do not fit, its
     // build would be left with two-step batches at few wavefronts (tensors from 35 GB on, 100000 x 16 x 120 x 32 at R = 32, third
