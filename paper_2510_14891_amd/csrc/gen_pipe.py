@@ -14,7 +14,8 @@ layout the kernel defines: `Lay` / `LayRows` in mttkrp.hip), JB multiplies by
 the sweep weight and RB * JB 16x16x4 MFMAs.  A run covers any n >= D consecutive
 unmasked steps of one sweep: the X pointer and the factor offsets advance by
 constant strides.  Both bases lie in scalar registers and are advanced by the
-scalar unit; a lane's offsets from them are 32-bit registers that never change.
+scalar unit; a lane's offsets from them are 32-bit registers that never change
+(but see lane_pointers).
 That matters in fp64: while an fp64 MFMA runs, the SIMD issues no vector
 instruction, and a group of them between two MFMAs costs about 10 cycles and 2 to
 4 more for each (register-only loop of RB = 2, JB = 4 steps: 568 cycles a step
@@ -63,6 +64,18 @@ def others(i):
 # x 64 at R = 128 508 -> 561 us.)
 
 
+def lane_pointers(i):
+    """Whether a run keeps X's addresses in 64-bit pointers of the lanes and advances them, and the inner factor's offsets, by
+    vector additions, as the batches do.  Where a step has one or two MFMAs, or fp32 MFMAs for one column block, the scalar
+    bases save little: their set-up per run and four dependent scalar additions a step cost as much, and wavefronts drift apart on
+    short columns (fp32, one column block: 60 calls 1.009 times as long with scalar bases, up to 1.09; one row and two column
+    blocks 1.009 and up to 1.18: 5^4 x 205350 x 5 at R = 25, fourth mode 1.14 against 1.35 ms; with more MFMAs a step 0.97 in the mean
+    of 65 calls, at most 1.08).  fp64 with three row and two column blocks: the registers of the lanes' offsets lie in scratch memory (8 calls 1.02)."""
+    if i.w == 2:
+        return i.rb == 3 and i.jb == 2
+    return i.jb == 1 or i.rb * i.jb <= 2
+
+
 def even(n):
     return n + (n & 1)
 
@@ -75,6 +88,7 @@ class Inst:
         self.set = self.xregs + self.bregs
         self.bc = even(jb * w)
         self.acc = rb * jb * 4 * w
+        self.lane = lane_pointers(self)
         # loads of one step: (destination offset in the set, registers, which pointer, byte offset)
         self.xloads = []
         if w == 2:
@@ -143,10 +157,16 @@ class Inst:
         o = []
         width = {1: "dword", 2: "dwordx2", 3: "dwordx3", 4: "dwordx4"}
         for off, n, lane, byte in self.xloads:
-            o.append("global_load_%s %s, %%[%s], %s%s%s" % (
-                width[n], self.reg(self.xbase(s) + off, n), lane, XB, " offset:%d" % byte if byte else "", nt))
+            addr = "%%[%s], off" % lane.replace("xo", "xp") if self.lane else "%%[%s], %s" % (lane, XB)
+            o.append("global_load_%s %s, %s%s%s" % (width[n], self.reg(self.xbase(s) + off, n), addr, " offset:%d" % byte if byte else "", nt))
         for off, n, lane in self.bloads:
-            o.append("global_load_%s %s, %%[%s], %s" % (width[n], self.reg(self.xbase(s) + self.xregs + off, n), lane, BB))
+            o.append("global_load_%s %s, %%[%s], %s" % (width[n], self.reg(self.xbase(s) + self.xregs + off, n), lane, "%[bb]" if self.lane else BB))
+        if self.lane:
+            for p in ("xp0", "xp1")[:2 if self.two_x else 1]:
+                o.append("v_lshl_add_u64 %%[%s], %%[%s], 0, %%[xs]" % (p, p))
+            for p in ("bo0", "bo1")[:2 if self.two_b else 1]:
+                o.append("v_add_u32 %%[%s], %%[bs], %%[%s]" % (p, p))
+            return o
         o.append("s_add_u32 s%d, s%d, s%d" % (S0, S0, S0 + 2))
         o.append("s_addc_u32 s%d, s%d, s%d" % (S0 + 1, S0 + 1, S0 + 3))
         o.append("s_add_u32 s%d, s%d, %%[bs]" % (S0 + 4, S0 + 4))
@@ -168,7 +188,9 @@ class Inst:
 
     def block(self, nt):
         d, s_n, l = self.d, self.d + 1, self.loads
-        o = ["s_nop 4", "s_mov_b64 %s, %%[xb]" % XB, "s_mov_b64 s[%d:%d], %%[xs]" % (S0 + 2, S0 + 3), "s_mov_b64 %s, %%[bb]" % BB]
+        o = ["s_nop 4"]
+        if not self.lane:
+            o += ["s_mov_b64 %s, %%[xb]" % XB, "s_mov_b64 s[%d:%d], %%[xs]" % (S0 + 2, S0 + 3), "s_mov_b64 %s, %%[bb]" % BB]
         for k in range(d):
             o += self.issue(k, nt)
         o.append("1:")
@@ -199,22 +221,29 @@ class Inst:
             out += "#define MTTKRP_PIPE_%s_ASM%s \\\n" % (t, suffix)
             out += " \\\n".join('    "%s\\n"' % line for line in self.block(nt)) + "\n"
         clob = ", ".join('"v%d"' % v for v in range(self.t0, self.last_reg() + 1))
-        clob += ", " + ", ".join('"s%d"' % v for v in range(S0, S0 + 6))
+        if not self.lane:
+            clob += ", " + ", ".join('"s%d"' % v for v in range(S0, S0 + 6))
         accs = ", ".join('[a%d%d] "+v"(acc[%d][%d])' % (r, j, r, j) for r in range(self.rb) for j in range(self.jb))
+        lanes = ["%so%d" % (a, n) for a, two in (("x", self.two_x), ("b", self.two_b)) for n in range(2 if two else 1)]
         outs = '[n] "+&s"(n_more), ' + accs
-        ins = '[xb] "s"(xbase), [xs] "s"(x_step_bytes), [bb] "s"(bbase), [bs] "s"(b_step_bytes), [xo0] "v"(xo0), [bo0] "v"(bo0), ' + \
-              ('[xo1] "v"(xo1), ' if self.two_x else "") + ('[bo1] "v"(bo1), ' if self.two_b else "") + \
-              ", ".join('[q%d] "v"(q[%d])' % (j, j) for j in range(self.jb))
+        ins = '[xs] "s"(x_step_bytes), [bb] "s"(bbase), [bs] "s"(b_step_bytes), ' + ", ".join('[q%d] "v"(q[%d])' % (j, j) for j in range(self.jb))
+        if self.lane:
+            outs = "".join('[%s] "+&v"(%s), ' % (v, v) for v in (a.replace("xo", "xp") for a in lanes)) + outs
+        else:
+            ins = '[xb] "s"(xp0), ' + "".join('[%s] "v"(%s), ' % (v, v) for v in lanes) + ins
         out += "template <> struct Pipe<%s, %d, %d> {\n" % (c, self.rb, self.jb)
         out += "    static constexpr bool value = true;\n"
         out += "    static constexpr int depth = %d;\n    static constexpr int waves = %d;\n" % (self.d, self.waves)
+        out += "    static constexpr bool lane = %s;\n" % ("true" if self.lane else "false")
         out += "    template <bool NT>\n"
-        out += "    static __device__ __forceinline__ void run(typename Mfma<%s>::acc_t (&acc)[%d][%d], const %s* xbase,\n" % (c, self.rb, self.jb, c)
-        out += "                                               uint32_t xo0, uint32_t xo1, int64_t x_step_bytes, const %s* bbase,\n" % c
+        out += "    static __device__ __forceinline__ void run(typename Mfma<%s>::acc_t (&acc)[%d][%d], const %s*%s xp0,\n" % (
+            c, self.rb, self.jb, c, "&" if self.lane else "")
+        out += "                                               %s, int64_t x_step_bytes, const %s* bbase,\n" % (
+            "const %s* xp1" % c if self.lane else "uint32_t xo0, uint32_t xo1", c)
         out += "                                               uint32_t bo0, uint32_t bo1, uint32_t b_step_bytes,\n"
         out += "                                               const %s (&q)[%d], int n_more)\n    {\n" % (c, self.jb)
         if not self.two_x:
-            out += "        (void)xo1;\n"
+            out += "        (void)%s;\n" % ("xp1" if self.lane else "xo1")
         if not self.two_b:
             out += "        (void)bo1;\n"
         if self.w == 2:
@@ -234,7 +263,7 @@ def main(path=None):
     out += "// Primary template: no pipelined run for an instantiation (the kernel then uses batches only).\n"
     out += "template <typename T, int RB, int JB> struct Pipe {\n"
     out += "    static constexpr bool value = false;\n    static constexpr int depth = 1 << 30;\n"
-    out += "    static constexpr int waves = 0;\n"
+    out += "    static constexpr int waves = 0;\n    static constexpr bool lane = false;\n"
     out += "    template <bool NT>\n"
     out += "    static __device__ __forceinline__ void run(typename Mfma<T>::acc_t (&)[RB][JB], const T*, uint32_t, uint32_t, int64_t,\n"
     out += "                                               const T*, uint32_t, uint32_t, uint32_t, const T (&)[JB], int)\n    {\n    }\n};\n\n"

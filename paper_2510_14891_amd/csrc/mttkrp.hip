@@ -85,8 +85,8 @@ template <> struct Mfma<float> {
 // its own loads with its own MFMAs; the hand-scheduled loop keeps several steps
 // of loads in flight while the MFMAs of an earlier one run.  It covers any run of
 // at least that many consecutive unmasked steps of one sweep: the bases of X and of
-// the inner factor advance by constant strides (in scalar registers; lanes keep
-// constant 32-bit offsets from them), one weight Q per column block.
+// the inner factor advance by constant strides (in scalar registers, lanes keep
+// constant 32-bit offsets from them, or in lanes), one weight Q per column block.
 // Temporaries live in fixed registers (declared as clobbers); the loads of step
 // t go to operand set t modulo the ring size; every wait names how many later
 // loads may still be outstanding (memory operations return in issue order).
@@ -221,7 +221,12 @@ template <typename T, int RB, int JB> struct Budget {
     static constexpr int steps = raw > kMaxBatchSteps ? kMaxBatchSteps : (raw < 2 ? 2 : raw);
 };
 
-// Offsets of a step's four columns from the first one's start fit 32 bits: an inner mode's stride (values) below 1.4 GB.
+// Runs of these tiles keep X's addresses in pointers of the lanes (gen_pipe.py: lane_pointers).
+__host__ __device__ constexpr bool run_of_lane_pointers(int sbytes, int RB, int JB)
+{
+    return sbytes == 8 ? RB == 3 && JB == 2 : JB == 1 || RB * JB <= 2;
+}
+// The others take offsets of a step's four columns from the first one's start in 32 bits: an inner mode's stride (values) below 1.4 GB.
 __host__ __device__ inline bool lane_offsets_fit(int64_t sx_in, int64_t sbytes) { return (3 * sx_in + 64) * sbytes < ((int64_t)1 << 32); }
 
 // One wavefront = one work item = (row block, column-block chunk, batch value,
@@ -338,9 +343,15 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
         o_count = 0;
     }
 
-    // X is addressed from a wave-uniform base (the tile's first row at the step's first column) and a lane's constant offset
-    const T* const xtile = p.X + (int64_t)batch * p.sx_batch + row_base;
-    const int64_t xl = lrow + (int64_t)kk * p.sx_in;
+    // X is addressed from a wave-uniform base (the tile's first row at the step's first column) and a lane's constant offset, or
+    // (kLane) by a pointer of each lane that holds both.  Without the run, in fp32 and with one row block, the sum of the two costs more
+    // than the pointer: 45 calls with one row block 1.016 times as long, up to 1.08 (fp32 5 x 12 x 63878 x 7 at R = 6, third
+    // mode 149 against 160 us), fp32 with more 1.002; fp64 with two and more row blocks is even (four by two 0.95, 4 calls).
+    constexpr bool kLane = kPipe ? Pipe<T, RB, JB>::lane : RB == 1 || sizeof(T) == 4;
+    static_assert(!kPipe || Pipe<T, RB, JB>::lane == run_of_lane_pointers(sizeof(T), RB, JB), "gen_pipe.py: lane_pointers");
+    const int64_t xlane = lrow + (int64_t)kk * p.sx_in;
+    const T* const xtile = p.X + (int64_t)batch * p.sx_batch + row_base + (kLane ? xlane : 0);
+    const int64_t xl = kLane ? 0 : xlane;
     const int64_t x_step = 4 * p.sx_in;
     const bool no_inner = p.no_inner != 0;   // then A_in is a readable dummy and b = 1
     const int dim_mid = p.dim_out[0];        // 1 when there is no outer mode
@@ -495,20 +506,26 @@ mttkrp_stream_kernel(const StreamArgs<T> p)
     // Other wavefronts of the SIMD fill the gaps between batches.
     //   plain batch:   U unmasked steps of one sweep: one weight Q, constant strides
     //   generic batch: any steps (sweep boundaries, masked last step, parked padding)
-    // the pipelined run takes a lane's offsets as 32-bit numbers
-    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31) && lane_offsets_fit(p.sx_in, sizeof(T));
+    // the pipelined run takes a lane's offsets as 32-bit numbers (of X only without lane pointers)
+    const bool pipe_ok = kPipe && (int64_t)p.I_in * p.ld_in * (int64_t)sizeof(T) < ((int64_t)1 << 31) &&
+                         (kLane || lane_offsets_fit(p.sx_in, sizeof(T)));
     int done = 0;
     while (done < n_steps) {
         if constexpr (kPipe) {
             const int avail = parked || !pipe_ok || no_inner ? 0 : min(remaining, steps_plain - s_in);
             if (avail >= Pipe<T, RB, JB>::depth) {
                 const int n_run = avail;
-                Pipe<T, RB, JB>::template run<NT>(acc, (const T*)(uintptr_t)uni64((int64_t)(uintptr_t)xp),
-                                                  (uint32_t)xl * (uint32_t)sizeof(T), (uint32_t)(xl + xd1) * (uint32_t)sizeof(T),
-                                                  x_step * (int64_t)sizeof(T), bbase, boff0, boff1,
-                                                  4u * (uint32_t)p.ld_in * (uint32_t)sizeof(T), Q,
-                                                  avail - Pipe<T, RB, JB>::depth);
-                xp += n_run * x_step;
+                const uint32_t b_step = 4u * (uint32_t)p.ld_in * (uint32_t)sizeof(T);
+                if constexpr (kLane) {
+                    Pipe<T, RB, JB>::template run<NT>(acc, xp, xp + xd1, x_step * (int64_t)sizeof(T), bbase, boff0, boff1, b_step, Q,
+                                                      avail - Pipe<T, RB, JB>::depth);
+                } else {
+                    Pipe<T, RB, JB>::template run<NT>(acc, (const T*)(uintptr_t)uni64((int64_t)(uintptr_t)xp),
+                                                      (uint32_t)xl * (uint32_t)sizeof(T), (uint32_t)(xl + xd1) * (uint32_t)sizeof(T),
+                                                      x_step * (int64_t)sizeof(T), bbase, boff0, boff1, b_step, Q,
+                                                      avail - Pipe<T, RB, JB>::depth);
+                    xp += n_run * x_step;
+                }
                 bbase += (int64_t)n_run * 4 * p.ld_in;
                 s_in += n_run;
                 remaining -= n_run;
@@ -2186,7 +2203,8 @@ int make_plan_for(int ndim, const int64_t* dims, int R, int k, int sbytes, const
     // build would be left with two-step batches at few wavefronts (tensors from 35 GB on, 100000 x 16 x 120 x 32 at R = 32, third
     // mode 10.3 ms, with the batches' own build 8.9; at R = 64 19.0 and 15.8; fp32 200000 x 16 x 140 x 30 at R = 64 19.2 and 18.3).
     pl.deep = tn.deep == 1 ? true : tn.deep == 2 ? false
-              : pl.steps_per_item >= 32 && (pl.inner < 0 || lane_offsets_fit(pl.strides[pl.inner], sbytes));
+              : pl.steps_per_item >= 32 &&
+                    (pl.inner < 0 || run_of_lane_pointers(sbytes, pl.RB, pl.JB) || lane_offsets_fit(pl.strides[pl.inner], sbytes));
     return MTTKRP_OK;
 }
 

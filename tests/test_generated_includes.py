@@ -47,3 +47,13 @@ def test_ring_registers_stay_inside_the_budget():
                 assert inst.t0 % 2 == 0 and inst.set % 2 == 0, (gen, w, a, b)
                 assert inst.t0 >= inst.acc + mod.OTHERS[w], (gen, w, a, b)
                 assert inst.d * inst.loads <= 63, (gen, w, a, b)
+
+
+@pytest.mark.parametrize("w,rb,jb,lane", [(1, 1, 1, True), (1, 1, 2, True), (1, 4, 1, True), (1, 1, 3, False), (1, 2, 2, False), (1, 3, 4, False),
+                                          (2, 3, 2, True), (2, 1, 1, False), (2, 4, 2, False), (2, 3, 4, False)])
+def test_runs_advance_their_addresses_in_lanes_or_in_scalar_registers(w, rb, jb, lane):
+    inst = _load("gen_pipe").Inst(w, rb, jb)
+    code = "\n".join(inst.block(""))
+    assert inst.lane == lane
+    assert ("v_lshl_add_u64" in code) == ("v_add_u32" in code) == lane
+    assert ("s_addc_u32" in code) != lane

@@ -47,6 +47,15 @@ def test_one_range_of_the_column_space_leaves_no_wavefront_idle(dims, R, sbytes)
     assert p["outer_splits"] == p["inner_splits"] == "1" and p["items"] == p["row_blocks"], p
 
 
+# (one column block in fp32: the run keeps X's addresses in 64-bit pointers of the lanes)
+@pytest.mark.parametrize("dims,R,k,sbytes,rows,cols", [([200000, 16, 140, 30], 16, 2, 4, 64, 1), ([200000, 16, 140, 128], 10, 2, 4, 64, 1)])
+def test_runs_of_lane_pointers_take_any_stride(dims, R, k, sbytes, rows, cols):
+    p = describe(dims, R, k, sbytes)
+    assert p["rows_per_wave"] == str(rows) and p["col_blocks"] == str(cols) and p["inner_mode"] == "3"
+    assert 3 * dims[0] * dims[1] * dims[2] * sbytes > 2 ** 32
+    assert int(p["steps_per_item"]) >= 32 and p["deep"] == "1", p
+
+
 # (stride of the inner mode times four columns: below and beyond 2^32 bytes; extents of one kind otherwise)
 @pytest.mark.parametrize("dims,R,k,sbytes,deep", [([100000, 16, 80, 32], 32, 2, 8, 1), ([100000, 16, 120, 32], 32, 2, 8, 0),
                                                   ([100000, 16, 120, 32], 32, 2, 4, 1), ([200000, 16, 140, 30], 64, 2, 4, 0),
