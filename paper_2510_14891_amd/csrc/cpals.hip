@@ -1339,7 +1339,9 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
     return n_scale;
 }
 
-// Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns; many: four, so
+// Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns from rank 320 on, below it four, since a
+// block has no more than a few pieces for each and the barriers of sixteen cost more (a sweep over 16 x 495 x 217: R = 66 352 against
+// 342 us, 128 400 and 383, 256 675 and 647, 384 958 and 957, 512 1264 and 1316).  Many rows: four, so
 // that several workgroups fit a compute unit.  Above rank 1024 the slab does not fit the 160 KB of LDS.
 void solve_big(const double* L, int ldL, const double* dinv, const double* S, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
 {
@@ -1347,7 +1349,7 @@ void solve_big(const double* L, int ldL, const double* dinv, const double* S, in
     const size_t lds = (size_t)16 * (ceil_div(R, kNB) * kNB + 1) * sizeof(double);
     if (R > 1024) {
         hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, ldL, dinv, S, R, M, A, I, flag);
-    } else if (grid <= 512) {
+    } else if (grid <= 512 && R > 320) {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, ldL, dinv, S, R, M, A, I, flag);
     } else {

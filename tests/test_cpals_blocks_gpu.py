@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [((17, 16, 15), R) for R in (1, 3, 4, 5, 15, 16, 17, 31, 33, 63, 64)] + \
          [((33, 17, 40), R) for R in (65, 79, 80, 81, 96, 97, 127, 128, 129, 160, 193)] + \
          [((128, 129, 9), 2), ((255, 256, 7), 8), ((257, 5, 6), 9), ((127, 257, 256), 16), ((2, 90, 1), 2)] + \
-         [((4, 3, 5, 3), 11), ((4, 3, 4, 3, 4, 3, 4, 3), 7), ((2, 90, 80), 70), ((16, 50, 40), 257), ((700, 40, 30), 288), ((9000, 24, 20), 130), ((40, 45, 50), 545), ((40, 45, 50), 1030)]
+         [((4, 3, 5, 3), 11), ((4, 3, 4, 3, 4, 3, 4, 3), 7), ((2, 90, 80), 70), ((16, 50, 40), 257), ((700, 40, 30), 288), ((9000, 24, 20), 130), ((40, 45, 50), 320), ((40, 45, 50), 321), ((40, 45, 50), 545), ((40, 45, 50), 1030)]
 
 
 @pytest.mark.parametrize("dims,R", SHAPES)
