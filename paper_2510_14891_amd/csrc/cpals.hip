@@ -181,109 +181,6 @@ __device__ __forceinline__ double reciprocal(double d)
     return r;
 }
 
-// L D L^T of an R x R matrix, R <= RP, by one workgroup.  Thread (ti, tc) = (tid & 15, tid >> 4) of the first
-// 256 holds the entries (ti + 16 p, tc + 16 q) in registers (zeros from row and column R on); the four columns that are
-// eliminated next pass through LDS.  Every thread factorises their 4 x 4 diagonal block and takes its rows and columns
-// through it by itself, so four columns cost one exchange and one barrier (~800 cycles; one column at a time 250 each).
-// Every entry sees the operations of column-by-column elimination in its order.  Blocks of 16 x 16 entries
-// above the diagonal are left alone.  Result: Lf[c * (RP + 1) + i] = L(i, c) for i > c, 0 elsewhere (the padding
-// up to RP too); dinv[c] = 1 / D(c), 0 for c >= R.  False (for every thread) when a pivot is not positive.
-template <int RP>
-__device__ __forceinline__ bool factorise(double (&own)[RP / 16][RP / 16], int R, double (*col)[4][RP], double* Lf, double* dinv)
-{
-    constexpr int NT = RP / 16;
-    const int tid = (int)threadIdx.x, ti = tid & 15, tc = tid >> 4;
-    const bool mine = tid < 256;
-    if (tid < RP)
-        dinv[tid] = 0.0;
-    if (mine && tc < 4) {
-#pragma unroll
-        for (int p = 0; p < NT; ++p)
-            col[0][tc][ti + 16 * p] = own[p][0];
-    }
-    __syncthreads();
-    for (int j = 0; j < R; j += 4) {
-        const double (*const cj)[RP] = col[(j >> 2) & 1];
-        const int q0 = j >> 4, nk = R - j < 4 ? R - j : 4;
-        // the diagonal block: y_k of its rows, l(k, m) = y_m(j + k) / d_m
-        double l[4][4], r[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            double y[4];
-#pragma unroll
-            for (int m = 0; m <= k; ++m) {
-                y[m] = cj[m][j + k];
-#pragma unroll
-                for (int n = 0; n < m; ++n)
-                    y[m] -= y[n] * l[m][n];
-                if (m < k)
-                    l[k][m] = y[m] * r[m];
-            }
-            if (k < nk && !(y[k] > 0.0))
-                return false;      // uniform: every thread sees the same pivot
-            r[k] = k < nk ? reciprocal(y[k]) : 0.0;
-        }
-        if (mine) {
-            auto through = [&](int i, double (&y)[4]) {      // entries of row i in the four columns as they are eliminated
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    y[k] = cj[k][i];
-#pragma unroll
-                    for (int m = 0; m < k; ++m)
-                        y[k] -= y[m] * l[k][m];
-                }
-            };
-            double x[NT][4];
-#pragma unroll
-            for (int p = 0; p < NT; ++p)
-                if (p >= q0)
-                    through(ti + 16 * p, x[p]);
-#pragma unroll
-            for (int q = 0; q < NT; ++q)
-                if (q >= q0) {
-                    const int c = tc + 16 * q;
-                    double w[4];
-                    through(c, w);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        w[k] *= r[k];
-#pragma unroll
-                    for (int p = q; p < NT; ++p)
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            if (k < nk) {
-                                const double v = own[p][q] - x[p][k] * w[k];
-                                own[p][q] = q > q0 || c > j + k ? v : own[p][q];
-                            }
-                    const int k = c - (j + 4);
-                    if (k >= 0 && k < 4) {
-#pragma unroll
-                        for (int p = q; p < NT; ++p)
-                            col[((j >> 2) + 1) & 1][k][ti + 16 * p] = own[p][q];
-                    }
-                }
-        }
-        if (tid == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < nk)
-                    dinv[j + k] = r[k];
-        }
-        __syncthreads();
-    }
-    if (mine) {
-#pragma unroll
-        for (int q = 0; q < NT; ++q)
-#pragma unroll
-            for (int p = 0; p < NT; ++p) {
-                const int i = ti + 16 * p, c = tc + 16 * q;
-                Lf[c * (RP + 1) + i] = i > c && i < R ? own[p][q] * dinv[c] : 0.0;
-            }
-    }
-    __syncthreads();
-    return true;
-}
-
 // The value of lane 4 * (lane / 4) + p in all four lanes of the quad.
 __device__ __forceinline__ double quad_value(double v, int p)
 {
@@ -373,188 +270,6 @@ __device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv, int n
             row_fmas<j>(a, w);
     });
     return ok;
-}
-
-// Rows [row0, row0 + n) of A (R columns): divided by their columns' norms; returns this thread's share of the
-// column sums of M * A, which belong to column threadIdx.x % RP.
-template <int RP>
-__device__ __forceinline__ double scale_rows(double* A, const double* __restrict__ M, int64_t row0, int64_t n, int R, const double* nrm)
-{
-    const int j = threadIdx.x % RP;
-    double s = 0.0;
-    if (j < R)
-        for (int64_t i = threadIdx.x / RP; i < n; i += blockDim.x / RP) {
-            const int64_t e = (row0 + i) * R + j;
-            const double v = A[e] / nrm[j];
-            A[e] = v;
-            s += M[e] * v;
-        }
-    return s;
-}
-
-// Up to rank 64.  V is formed (Hadamard product of the Gram matrices of the other modes) and factorised
-// by every workgroup for itself: that costs no time beside the launches it saves.  A wavefront
-// solves 16 rows at a time; the tile's rows then go through LDS into the Gram matrix, which also holds
-// the columns' squared norms.
-//   WHOLE (one workgroup, short factors): the norms, the normalised rows, the Gram matrix and the column
-//   sums of M * A follow in the same launch.  Otherwise every workgroup leaves its Gram matrix in gram_ws and
-//   als_normalise does the rest.
-// 100 x 80 x 60 at R = 10: six launches of 23 us a mode and the gaps between them -> one of 11 us; the call of
-// 12 sweeps 2.35 -> 1.48 ms.
-template <int RP, int WAVES, bool WHOLE>
-__global__ void __launch_bounds__(64 * WAVES)
-als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, int64_t n_tiles,
-           double* gram_ws, double* lambda, double* inner, int* flag)
-{
-    constexpr int NT = RP / 16, THREADS = 64 * WAVES, TR = 16 * WAVES;
-    constexpr int YR = RP == 64 ? 32 : TR;          // rows of a tile that pass through LDS at once
-    constexpr int NG = THREADS / 256;               // thread groups that share the rows of the Gram sums
-    __shared__ double Lf[RP * (RP + 1)], dinv[RP], col[2][4][RP], nrm[RP], scale[RP];
-    __shared__ double Ys[YR * (RP + 1)];
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int ti = tid & 15, tc = (tid >> 4) & 15, grp = tid >> 8;
-    const int64_t RR = (int64_t)R * R;
-    double own[NT][NT];
-#pragma unroll
-    for (int p = 0; p < NT; ++p)
-#pragma unroll
-        for (int q = 0; q < NT; ++q) {
-            const int i = ti + 16 * p, c = tc + 16 * q;
-            double v = 0.0;
-            if (i < R && c < R) {
-                v = 1.0;
-                for (int m = 0; m < ndim; ++m)
-                    if (m != k)
-                        v *= G[m * RR + i * R + c];
-            }
-            own[p][q] = v;
-        }
-    if (failed_before(flag))      // an earlier update failed: every factor stays as it is (asked behind the loads, so that it does not delay them)
-        return;
-    if (tid < 256 && ti == tc) {
-#pragma unroll
-        for (int p = 0; p < NT; ++p)
-            scale[ti + 16 * p] = unit_scale(own[p][p]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < NT; ++p)
-#pragma unroll
-        for (int q = 0; q < NT; ++q)
-            own[p][q] = own[p][q] * scale[ti + 16 * p] * scale[tc + 16 * q];
-    if (!factorise<RP>(own, R, col, Lf, dinv)) {
-        if (blockIdx.x == 0 && tid == 0)
-            flag[0] = 1;
-        return;
-    }
-    double acc[NT][NT];
-#pragma unroll
-    for (int p = 0; p < NT; ++p)
-#pragma unroll
-        for (int q = 0; q < NT; ++q)
-            acc[p][q] = 0.0;
-    const int part = lane & 3, trow = 16 * wave + (lane >> 2);
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t row = tile * TR + trow;
-        double y[RP / 4];
-#pragma unroll
-        for (int q = 0; q < RP / 4; ++q)
-            y[q] = row < I && 4 * q + part < R ? M[row * R + 4 * q + part] * scale[4 * q + part] : 0.0;
-        solve_forward<RP>(y, Lf, R, part);
-#pragma unroll
-        for (int q = 0; q < RP / 4; ++q)
-            y[q] *= dinv[4 * q + part];
-        solve_backward<RP>(y, Lf, R, part);
-#pragma unroll
-        for (int q = 0; q < RP / 4; ++q)
-            y[q] *= scale[4 * q + part];
-        if (row < I) {
-#pragma unroll
-            for (int q = 0; q < RP / 4; ++q)
-                if (4 * q + part < R)
-                    A[row * R + 4 * q + part] = y[q];
-        }
-#pragma unroll
-        for (int h = 0; h < TR / YR; ++h) {
-            if (trow / YR == h) {
-#pragma unroll
-                for (int q = 0; q < RP / 4; ++q)
-                    Ys[(trow % YR) * (RP + 1) + 4 * q + part] = y[q];
-            }
-            __syncthreads();
-            for (int r = grp; r < YR; r += NG) {
-                double a[NT], b[NT];
-#pragma unroll
-                for (int p = 0; p < NT; ++p) {
-                    a[p] = Ys[r * (RP + 1) + ti + 16 * p];
-                    b[p] = Ys[r * (RP + 1) + tc + 16 * p];
-                }
-#pragma unroll
-                for (int p = 0; p < NT; ++p)
-#pragma unroll
-                    for (int q = 0; q < NT; ++q)
-                        acc[p][q] += a[p] * b[q];
-            }
-            __syncthreads();
-        }
-    }
-    if (!WHOLE) {
-        static_assert(WHOLE || NG == 1, "one group of threads per partial Gram matrix");
-        double* const o = gram_ws + (int64_t)blockIdx.x * RR;
-#pragma unroll
-        for (int p = 0; p < NT; ++p)
-#pragma unroll
-            for (int q = 0; q < NT; ++q)
-                if (ti + 16 * p < R && tc + 16 * q < R)
-                    o[(ti + 16 * p) * R + tc + 16 * q] = acc[p][q];
-        return;
-    }
-    // the groups' Gram sums in group order
-    for (int g = 1; g < NG; ++g) {
-        if (grp == g) {
-#pragma unroll
-            for (int p = 0; p < NT; ++p)
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    Ys[(p * NT + q) * 256 + (tid & 255)] = acc[p][q];
-        }
-        __syncthreads();
-        if (grp == 0) {
-#pragma unroll
-            for (int p = 0; p < NT; ++p)
-#pragma unroll
-                for (int q = 0; q < NT; ++q)
-                    acc[p][q] += Ys[(p * NT + q) * 256 + tid];
-        }
-        __syncthreads();
-    }
-    if (grp == 0 && ti == tc) {
-#pragma unroll
-        for (int p = 0; p < NT; ++p) {
-            const double n = sqrt(acc[p][p]);
-            nrm[ti + 16 * p] = n > 0.0 ? n : 1.0;       // a zero column is left alone
-            if (ti + 16 * p < R)
-                lambda[ti + 16 * p] = n;
-        }
-    }
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-        for (int p = 0; p < NT; ++p)
-#pragma unroll
-            for (int q = 0; q < NT; ++q)
-                if (ti + 16 * p < R && tc + 16 * q < R)
-                    G[k * RR + (ti + 16 * p) * R + tc + 16 * q] = acc[p][q] / (nrm[ti + 16 * p] * nrm[tc + 16 * q]);
-    }
-    const double s = scale_rows<RP>(A, M, 0, I, R, nrm);
-    Ys[tid] = s;
-    __syncthreads();
-    if (tid < R) {
-        double v = 0.0;
-        for (int q = tid; q < THREADS; q += RP)
-            v += Ys[q];
-        inner[tid] = v;
-    }
 }
 
 // The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
@@ -761,28 +476,472 @@ als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M
     }
 }
 
+// y[t] += (y[t] of lane a of each 16 lanes) * f[a] for a = 0 .. 15 in order (FORWARD) or 15 .. 0: the substitution with a unit triangular 16 x 16
+// block, for 16 rows of which a lane has column lane % 16 of four.  One block of instructions: four rows take turns, so that a
+// register is read by DPP three instructions after it was written; the waits in front and behind are those of matrix
+// instructions beside it, which the compiler does not see through the block.
+template <bool FORWARD> __device__ __forceinline__ void substitute16(double (&y)[4], const double (&f)[16])
+{
+#define SUB_ROW(t, a, fa) "v_fmac_f64_dpp %" #t ", %" #t ", %" #fa " row_newbcast:" #a " row_mask:0xf bank_mask:0xf\n\t"
+#define SUB_STEP(a, fa) SUB_ROW(0, a, fa) SUB_ROW(1, a, fa) SUB_ROW(2, a, fa) SUB_ROW(3, a, fa)
+#define SUB_OPERANDS : "+&v"(y[0]), "+&v"(y[1]), "+&v"(y[2]), "+&v"(y[3]) \
+        : "v"(f[0]), "v"(f[1]), "v"(f[2]), "v"(f[3]), "v"(f[4]), "v"(f[5]), "v"(f[6]), "v"(f[7]), "v"(f[8]), "v"(f[9]), "v"(f[10]), \
+          "v"(f[11]), "v"(f[12]), "v"(f[13]), "v"(f[14]), "v"(f[15])
+    if constexpr (FORWARD)
+        asm("s_nop 15\n\ts_nop 7\n\t" SUB_STEP(0, 4) SUB_STEP(1, 5) SUB_STEP(2, 6) SUB_STEP(3, 7) SUB_STEP(4, 8) SUB_STEP(5, 9) SUB_STEP(6, 10)
+                SUB_STEP(7, 11) SUB_STEP(8, 12) SUB_STEP(9, 13) SUB_STEP(10, 14) SUB_STEP(11, 15) SUB_STEP(12, 16) SUB_STEP(13, 17)
+                    SUB_STEP(14, 18) "s_nop 3" SUB_OPERANDS);
+    else
+        asm("s_nop 15\n\ts_nop 7\n\t" SUB_STEP(15, 19) SUB_STEP(14, 18) SUB_STEP(13, 17) SUB_STEP(12, 16) SUB_STEP(11, 15) SUB_STEP(10, 14)
+                SUB_STEP(9, 13) SUB_STEP(8, 12) SUB_STEP(7, 11) SUB_STEP(6, 10) SUB_STEP(5, 9) SUB_STEP(4, 8) SUB_STEP(3, 7)
+                    SUB_STEP(2, 6) SUB_STEP(1, 5) "s_nop 3" SUB_OPERANDS);
+#undef SUB_OPERANDS
+#undef SUB_STEP
+#undef SUB_ROW
+}
+
+// What als_update keeps in LDS: V = L D L^T (then -L), one step's rows of L D, tiles of 16 rows of the factor.  Rows of four doubles
+// more than the columns: both operand layouts of the matrix cores then meet each bank twice.
+constexpr int update_ld(int nb) { return 16 * nb + 4; }
+constexpr int update_waves(int nb) { return nb <= 2 ? 16 : 8; }
+constexpr int update_sums(int nb) { return nb == 1 ? 7 * 256 : (nb == 2 ? 9 * 256 : 0); }       // blocks of the Gram matrix from several wavefronts
+constexpr int update_lds_doubles(int nb, int tiles) { return 16 * nb * update_ld(nb) + 16 * (nb - 1) * 20 + update_sums(nb) + tiles * 16 * update_ld(nb); }
+// tiles of a factor that fit the 160 KB beside V and 6 KB of smaller arrays
+constexpr int update_most_tiles(int nb) { return (154 * 1024 / 8 - update_lds_doubles(nb, 0)) / (16 * update_ld(nb)); }
+
+// Up to rank 64, NB blocks of 16 columns.  V is formed (Hadamard product of the Gram matrices of the other modes) and factorised
+// by every workgroup for itself, 16 columns at a time: the first wavefront factorises the diagonal block, one wavefront for 16 rows solves
+// the rows below against it, and the pieces to the right are updated on the matrix cores while the first wavefront goes on.  Then a
+// wavefront takes 16 rows of M at a time through both substitutions in the matrix cores' own accumulator layout: 16 unknowns by
+// DPP (substitute16), the columns that follow by matrix instructions.  The Gram matrix of the new rows, by pairs of column
+// blocks, also holds the columns' squared norms.
+//   WHOLE (one workgroup, all rows stay in LDS): the norms, the normalised rows, the Gram matrix and after a sweep's last mode its
+//   record follow in the same launch.  Otherwise every workgroup leaves its Gram matrix in gram_ws and als_normalise does the rest.
+// Bound by the chain of the pivots, by latency and by instruction fetches.  A row a quad of lanes, V in the threads' registers, four columns
+// a barrier and all of it unrolled (67 KB of code at R = 49 to 64, where the cache holds 64) took, against this: 293 rows at R = 62 59 us
+// and 12 in the second launch -> 26 and 10; 62 rows 59 and 12 -> 21; 96 rows at R = 48 40 and 12 -> 18; 32 rows at R = 24 22 -> 13; 145071 rows at R = 10
+// 91 and 40 -> 26 and 11.  36 drawn CP-ALS calls run 0.886 times as long in the mean.
+template <int NB, bool WHOLE>
+__global__ void __launch_bounds__(64 * update_waves(NB))
+als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, int64_t n_tiles,
+           double* gram_ws, double* lambda, double* inner, int* flag, SweepEnd end)
+{
+    constexpr int WAVES = update_waves(NB), THREADS = 64 * WAVES, LD = update_ld(NB), RP = 16 * NB, TILE = 16 * LD;
+    constexpr int PAIRS = NB * (NB + 1) / 2;                                 // blocks (p, q), p >= q, of a symmetric matrix
+    constexpr int KS = NB == 1 ? 8 : (NB == 2 ? 4 : 1);                      // wavefronts that share a block of the Gram matrix
+    constexpr int UNITS = PAIRS * KS, PER = (UNITS + WAVES - 1) / WAVES;
+    extern __shared__ double lds[];
+    double* const P = lds;                       // [RP][LD]
+    double* const W = P + RP * LD;               // [NB - 1][16][20]
+    double* const Sums = W + 16 * (NB - 1) * 20;
+    double* const T = Sums + update_sums(NB);    // tiles
+    __shared__ double dinv[RP], nrm[RP], weight[RP], scale[RP], red[WAVES];
+    __shared__ int bad;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kq = lane >> 4;
+    const int64_t RR = (int64_t)R * R;
+    auto block_row = [](int b) { return b < 1 ? 0 : (b < 3 ? 1 : (b < 6 ? 2 : 3)); };
+    auto block_col = [&](int b) { const int p = block_row(b); return b - p * (p + 1) / 2; };
+    // rows of tile t in the accumulator layout: entry (4 q + kq, 16 u + n16)
+    auto load_rows = [&](int64_t t, double (&m)[NB][4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t r = 16 * t + 4 * q + kq;
+            const double* const row = M + (r < I ? r : I - 1) * R;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                m[u][q] = row[min(16 * u + n16, R - 1)];
+        }
+    };
+    // (every lane loads, from the last row or column where its own does not exist: behind branches each load is waited for)
+    const int stop = flag[0];
+    {
+        constexpr int NV = (PAIRS * 256 + THREADS - 1) / THREADS;
+        double v[NV], d = 1.0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            v[i] = 1.0;
+        const int others = ndim - 1;
+        for (int m0 = 0; m0 < others; m0 += 2) {
+            double g[2][NV + 1];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int o = min(m0 + h, others - 1);
+                const double* const Gm = G + (int64_t)(o + (o >= k ? 1 : 0)) * RR;
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    const int b = min((tid >> 8) + i * (THREADS / 256), PAIRS - 1);
+                    const int r = 16 * block_row(b) + ((tid >> 4) & 15), c = 16 * block_col(b) + (tid & 15);
+                    g[h][i] = Gm[min(r, R - 1) * R + min(c, R - 1)];
+                }
+                const int j = min(tid, R - 1);
+                g[h][NV] = Gm[(int64_t)j * R + j];
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (m0 + h < others) {
+#pragma unroll
+                    for (int i = 0; i < NV; ++i)
+                        v[i] *= g[h][i];
+                    d *= g[h][NV];
+                }
+        }
+        if (__syncthreads_or(stop) != 0) {      // an earlier update failed or the fit has settled: every factor stays as it is
+            if (WHOLE && end.record && tid == 0)
+                end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
+            return;
+        }
+        if (tid < RP)
+            scale[tid] = tid < R ? unit_scale(d) : 1.0;
+        if (tid == 0)
+            bad = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int b = (tid >> 8) + i * (THREADS / 256);
+            const int r = 16 * block_row(b) + ((tid >> 4) & 15), c = 16 * block_col(b) + (tid & 15);
+            if (b < PAIRS)
+                P[r * LD + c] = r < R && c < R ? v[i] * scale[r] * scale[c] : (r == c ? 1.0 : 0.0);
+        }
+    }
+    double m[NB][4];                 // the first tile's rows: on their way while V is factorised
+    load_rows((int64_t)blockIdx.x * WAVES + wave, m);
+    __syncthreads();
+    // piece (t, u) of V minus the product of what the columns of step g - 1 have become: (-L)(t, g - 1) times (L D)(u, g - 1)^T
+    auto update_piece = [&](int t, int u, int g) {
+        double4_t acc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc[q] = P[(16 * t + 4 * q + kq) * LD + 16 * u + n16];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(16 * t + n16) * LD + 16 * (g - 1) + 4 * s + kq], W[((u - 1) * 16 + n16) * 20 + 4 * s + kq], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            P[(16 * t + 4 * q + kq) * LD + 16 * u + n16] = acc[q];
+    };
+    for (int g = 0; g < NB; ++g) {
+        if (wave == 0) {
+            if (g > 0)
+                update_piece(g, g, g);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            double a[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                a[i] = P[(16 * g + (i > n16 ? i : n16)) * LD + 16 * g + (i > n16 ? n16 : i)];
+            const bool ok = factorise16(a, dinv + 16 * g);
+            if (!ok && lane == 0)
+                bad = 1;
+            const double rd = dinv[16 * g + n16];
+            if (kq == 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    P[(16 * g + i) * LD + 16 * g + n16] = i > n16 ? -a[i] * rd : 0.0;
+            }
+        } else if (g > 0) {
+            int n = 1;
+            for (int t = g + 1; t < NB; ++t)
+                for (int u = g; u <= t; ++u, ++n)
+                    if (n == wave)
+                        update_piece(t, u, g);
+        }
+        __syncthreads();
+        if (wave < NB - 1 - g) {
+            const int t = g + 1 + wave;
+            double y[4], f[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                y[q] = P[(16 * t + 4 * q + kq) * LD + 16 * g + n16];
+#pragma unroll
+            for (int a = 0; a < 16; ++a)
+                f[a] = P[(16 * g + n16) * LD + 16 * g + a];
+            substitute16<true>(y, f);
+            const double rd = dinv[16 * g + n16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                W[((t - 1) * 16 + 4 * q + kq) * 20 + n16] = y[q];
+                P[(16 * t + 4 * q + kq) * LD + 16 * g + n16] = -y[q] * rd;
+            }
+        }
+        __syncthreads();
+    }
+    if (bad) {
+        if (blockIdx.x == 0 && tid == 0) {
+            flag[0] = kFailed;
+            if (WHOLE && end.record)
+                end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
+        }
+        return;
+    }
+    double sc[NB], dv[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        sc[u] = scale[16 * u + n16];
+        dv[u] = 16 * u + n16 < R ? dinv[16 * u + n16] : 0.0;
+    }
+    double4_t acc[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        acc[i] = {0.0, 0.0, 0.0, 0.0};
+    // this wavefront's blocks of Y^T Y over the tiles in LDS
+    auto gram_of = [&](int tiles) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int unit = wave + i * WAVES;
+            if (unit < UNITS) {
+                const int b = unit / KS, p = 16 * block_row(b), q = 16 * block_col(b);
+                for (int t = unit % KS; t < tiles; t += KS) {
+                    double x[4], z[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        x[s] = T[t * TILE + (4 * s + kq) * LD + p + n16];
+                        z[s] = T[t * TILE + (4 * s + kq) * LD + q + n16];
+                    }
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s], z[s], acc[i], 0, 0, 0);
+                }
+            }
+        }
+    };
+    const int64_t step = (int64_t)gridDim.x * WAVES;
+    for (int64_t t0 = (int64_t)blockIdx.x * WAVES; t0 < n_tiles; t0 += step) {
+        const int64_t tile = t0 + wave;
+        double* const Y = T + (WHOLE ? (tile < n_tiles ? (int)tile : 0) : wave) * TILE;
+        if (!WHOLE || tile < n_tiles) {
+            double y[NB][4];
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    y[u][q] = 16 * tile + 4 * q + kq < I && 16 * u + n16 < R ? m[u][q] * sc[u] : 0.0;
+            if (t0 + step < n_tiles)
+                load_rows(tile + step, m);
+            asm volatile("" ::: "memory");          // (or the operands of all tiles are read once, into more registers than there are)
+            double a[4], f[16];
+            // (the tile's place in LDS takes a block's unknowns from the accumulator layout to that of a left operand)
+            auto turn = [&](int g) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    Y[(4 * q + kq) * LD + 16 * g + n16] = y[g][q];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    a[s] = Y[n16 * LD + 16 * g + 4 * s + kq];
+            };
+            auto take = [&](int u, const double (&l)[4]) {
+                double4_t c = {y[u][0], y[u][1], y[u][2], y[u][3]};
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], l[s], c, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    y[u][q] = c[q];
+            };
+#pragma unroll
+            for (int g = 0; g < NB; ++g) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    f[i] = P[(16 * g + n16) * LD + 16 * g + i];
+                substitute16<true>(y[g], f);
+                if (g + 1 < NB)
+                    turn(g);
+#pragma unroll
+                for (int u = g + 1; u < NB; ++u) {
+                    double l[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        l[s] = P[(16 * u + n16) * LD + 16 * g + 4 * s + kq];
+                    take(u, l);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    y[u][q] *= dv[u];
+#pragma unroll
+            for (int g = NB - 1; g >= 0; --g) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    f[i] = P[(16 * g + i) * LD + 16 * g + n16];
+                substitute16<false>(y[g], f);
+                if (g > 0)
+                    turn(g);
+#pragma unroll
+                for (int u = 0; u < g; ++u) {
+                    double l[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        l[s] = P[(16 * g + 4 * s + kq) * LD + 16 * u + n16];
+                    take(u, l);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t r = 16 * tile + 4 * q + kq;
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    const double v = y[u][q] * sc[u];
+                    Y[(4 * q + kq) * LD + 16 * u + n16] = v;
+                    if (!WHOLE && r < I && 16 * u + n16 < R)
+                        A[r * R + 16 * u + n16] = v;
+                }
+            }
+        }
+        if (!WHOLE) {
+            __syncthreads();
+            gram_of(WAVES);
+            __syncthreads();
+        }
+    }
+    if (WHOLE) {
+        __syncthreads();
+        gram_of((int)n_tiles);
+    }
+    const bool owner = wave % KS == 0;
+    if (KS > 1) {          // a block's sums in the order of their wavefronts
+        double* const mine = Sums + (wave / KS * (KS - 1) + wave % KS - 1) * 256 + lane;
+        if (!owner && wave < UNITS) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                mine[64 * q] = acc[0][q];
+        }
+        __syncthreads();
+        if (owner && wave < UNITS) {
+            for (int i = 0; i < KS - 1; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[0][q] += Sums[(wave / KS * (KS - 1) + i) * 256 + 64 * q + lane];
+        }
+    }
+    // entry q of this lane's part of a block, (r, c), of the blocks whose sums this wavefront has
+    auto entries = [&](auto take) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int unit = wave + i * WAVES;
+            if (unit < UNITS && owner) {
+                const int b = unit / KS, p = block_row(b), q = block_col(b);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * p + 4 * e + kq, c = 16 * q + n16;
+                    if (r < R && c < R)
+                        take(r, c, acc[i][e], p != q);
+                }
+            }
+        }
+    };
+    if (!WHOLE) {
+        double* const o = gram_ws + (int64_t)blockIdx.x * RR;
+        double* const diag = gram_ws + (int64_t)gridDim.x * RR + (int64_t)blockIdx.x * R;
+        entries([&](int r, int c, double v, bool off) {
+            o[r * R + c] = v;
+            if (off)
+                o[c * R + r] = v;
+            if (r == c)
+                diag[r] = v;
+        });
+        return;
+    }
+    entries([&](int r, int c, double v, bool) {
+        if (r == c) {
+            const double n = sqrt(v);
+            nrm[r] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+            weight[r] = n;
+            lambda[r] = n;
+        }
+    });
+    __syncthreads();
+    double model2 = 0.0;                     // this thread's share of ||X^||^2 (a sweep's last update)
+    entries([&](int r, int c, double v, bool off) {
+        const double gk = v / (nrm[r] * nrm[c]);
+        G[k * RR + r * R + c] = gk;
+        if (off)
+            G[k * RR + c * R + r] = gk;
+        if (end.record) {
+            double t = weight[r] * weight[c] * gk;
+            for (int o = 0; o < ndim; ++o)
+                if (o != k)
+                    t *= G[o * RR + r * R + c];
+            model2 += off ? 2.0 * t : t;
+        }
+    });
+    constexpr int J = NB == 3 ? 64 : RP;     // threads of a row
+    const int j = tid % J;
+    double s = 0.0;
+    if (j < R)
+        for (int i = tid / J; i < (int)I; i += THREADS / J) {
+            const double v = T[(i >> 4) * TILE + (i & 15) * LD + j] / nrm[j];
+            A[(int64_t)i * R + j] = v;
+            if (end.record)
+                s += M[(int64_t)i * R + j] * v;
+        }
+    if (!end.record)
+        return;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1)
+        model2 += __shfl_xor(model2, d);
+    if (lane == 0)
+        red[wave] = model2;
+    double* const cols = KS > 1 ? Sums : P;
+    __syncthreads();                         // (the blocks' sums have been added)
+    cols[tid] = s;
+    __syncthreads();
+    double v = 0.0;
+    if (tid < R) {
+        for (int q = tid; q < THREADS; q += J)
+            v += cols[q];
+        v *= weight[tid];
+    }
+    __syncthreads();
+    if (tid < R)
+        cols[tid] = v;
+    __syncthreads();
+    if (tid == 0) {
+        double fit = 0.0, m2 = 0.0;
+        for (int q = 0; q < R; ++q)
+            fit += cols[q];
+        for (int q = 0; q < WAVES; ++q)
+            m2 += red[q];
+        end_sweep(end.scalars, flag, end.record, fit, m2, end.tol, end.first);
+    }
+}
+
+// Sum of v[b * stride] for b = first, first + by, ... below n, eight requested before the first is added, in order.
+__device__ __forceinline__ double sum_strided(const double* __restrict__ v, int first, int by, int n, int64_t stride)
+{
+    double s = 0.0;
+    for (int b = first; b < n; b += 8 * by) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            t[u] = v[(int64_t)min(b + u * by, n - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            s += b + u * by < n ? t[u] : 0.0;
+    }
+    return s;
+}
+
 // Second launch of the update for longer factors: every workgroup adds up the columns' squared norms (n_gram
-// partial Gram matrices, in order), normalises its rows and its share of the Gram matrix, and leaves its
-// column sums of M * A in inner[block][R].
+// partial diagonals), normalises its rows and its share of the Gram matrix (64 entries at a time, a wavefront for an eighth of
+// the partial matrices), and after a sweep's last mode (inner != nullptr) leaves its column sums of M * A in inner[block][R].
+// Bound by latency: eight requests in flight a thread.
 template <int RP>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
 als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, const double* __restrict__ M, int64_t I,
               int64_t rows_per_block, double* Gk, double* lambda, double* inner, const int* flag)
 {
-    __shared__ double red[256], nrm[RP];
+    __shared__ double red[512], nrm[RP];
     if (flag[0])
         return;
-    const int tid = (int)threadIdx.x, j = tid % RP;
-    const int64_t RR = (int64_t)R * R;
-    double s = 0.0;
-    if (j < R)
-        for (int b = tid / RP; b < n_gram; b += 256 / RP)
-            s += gram_ws[b * RR + (int64_t)j * R + j];
-    red[tid] = s;
+    const int tid = (int)threadIdx.x, j = tid % RP, lane = tid & 63, wave = tid >> 6;
+    const int RR = R * R;
+    red[tid] = j < R ? sum_strided(gram_ws + (int64_t)n_gram * RR + j, tid / RP, 512 / RP, n_gram, R) : 0.0;
     __syncthreads();
     if (tid < RP) {
         double v = 0.0;
-        for (int q = tid; q < 256; q += RP)
+        for (int q = tid; q < 512; q += RP)
             v += red[q];
         const double n = sqrt(v);
         nrm[tid] = n > 0.0 ? n : 1.0;       // a zero column is left alone
@@ -790,19 +949,46 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
             lambda[tid] = n;
     }
     __syncthreads();
-    for (int64_t e = (int64_t)blockIdx.x * 256 + tid; e < RR; e += (int64_t)gridDim.x * 256) {
-        const int a = (int)(e / R), c = (int)(e - (int64_t)a * R);
-        double v = 0.0;
-        for (int b = 0; b < n_gram; ++b)
-            v += gram_ws[b * RR + e];
-        Gk[e] = v / (nrm[a] * nrm[c]);
+    for (int e0 = (int)blockIdx.x * 64; e0 < RR; e0 += (int)gridDim.x * 64) {
+        const int e = min(e0 + lane, RR - 1);
+        red[tid] = sum_strided(gram_ws + e, wave, 8, n_gram, RR);
+        __syncthreads();
+        if (wave == 0 && e0 + lane < RR) {
+            double v = 0.0;
+            for (int q = 0; q < 8; ++q)
+                v += red[64 * q + lane];
+            Gk[e] = v / (nrm[e / R] * nrm[e % R]);
+        }
+        __syncthreads();
     }
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-    red[tid] = scale_rows<RP>(A, M, r0, I - r0 < rows_per_block ? I - r0 : rows_per_block, R, nrm);
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block, r1 = I < r0 + rows_per_block ? I : r0 + rows_per_block;
+    constexpr int64_t STEP = 512 / RP;
+    double s = 0.0;
+    if (j < R)
+        for (int64_t i = r0 + tid / RP; i < r1; i += 4 * STEP) {
+            double a[4], m[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t e = (i + u * STEP < r1 ? i + u * STEP : r1 - 1) * R + j;
+                a[u] = A[e];
+                if (inner)
+                    m[u] = M[e];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u * STEP < r1) {
+                    const double v = a[u] / nrm[j];
+                    A[(i + u * STEP) * R + j] = v;
+                    s += m[u] * v;
+                }
+        }
+    if (!inner)
+        return;
+    red[tid] = s;
     __syncthreads();
     if (tid < R) {
         double v = 0.0;
-        for (int q = tid; q < 256; q += RP)
+        for (int q = tid; q < 512; q += RP)
             v += red[q];
         inner[(int64_t)blockIdx.x * R + tid] = v;
     }
@@ -816,8 +1002,9 @@ __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict_
 {
     __shared__ double lds[256];
     double s = 0.0, t = 0.0;
-    for (int e = threadIdx.x; e < n_inner * R; e += 256)
-        s += inner[e] * lambda[e % R];
+    const int per = 256 / R, j = (int)threadIdx.x % R;          // threads of a column
+    if ((int)threadIdx.x < per * R)
+        s = sum_strided(inner + j, (int)threadIdx.x / R, per, n_inner, R) * lambda[j];
     for (int e = threadIdx.x; e < R * R; e += 256) {
         double v = lambda[e / R] * lambda[e % R];
         for (int m = 0; m < ndim; ++m)
@@ -1288,9 +1475,8 @@ void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t 
 }
 
 
-// The update of a factor up to rank 64: one workgroup for short factors, else two launches.  Returns the number
-// of blocks that left column sums of M * A in b.inner.  One workgroup takes I * RP values up to 16384 (RP = the
-// rank rounded up to 16 or 32): its tiles then take about as long as a second launch.
+// The update of a factor up to rank 64: one workgroup where its rows fit the workgroup's LDS (then a second launch would take
+// longer than its further tiles), else two launches.  Returns the number of blocks that left column sums of M * A in b.inner.
 // The update that ends a sweep also leaves its record where it can: `end` then has none any more.
 int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, SweepEnd& end, hipStream_t st)
 {
@@ -1305,38 +1491,40 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
             end.record = nullptr;
         return 1;
     }
-    if (R <= 32 && I * (R <= 16 ? 16 : 32) <= 16384) {
-        const int64_t tiles = ceil_div(I, 128);
-        if (R <= 16)
-            hipLaunchKernelGGL((als_update<16, 8, true>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, tiles,
-                               b.gram_ws, lambda, b.inner, b.flag);
-        else
-            hipLaunchKernelGGL((als_update<32, 8, true>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, tiles,
-                               b.gram_ws, lambda, b.inner, b.flag);
-        return 1;
-    }
-    const int64_t tiles = ceil_div(I, 64);
-    const int n_gram = (int)(tiles < kGramBlocks ? tiles : kGramBlocks);
-    const int64_t want = ceil_div(I * R, 2048);
-    const int64_t rows = ceil_div(I, want < kScaleBlocks ? want : kScaleBlocks);
-    const int n_scale = (int)ceil_div(I, rows);
-    if (R <= 16) {
-        hipLaunchKernelGGL((als_update<16, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
-                           tiles, b.gram_ws, lambda, b.inner, b.flag);
-        hipLaunchKernelGGL((als_normalise<16>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
-                           rows, Gk, lambda, b.inner, b.flag);
-    } else if (R <= 32) {
-        hipLaunchKernelGGL((als_update<32, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
-                           tiles, b.gram_ws, lambda, b.inner, b.flag);
-        hipLaunchKernelGGL((als_normalise<32>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
-                           rows, Gk, lambda, b.inner, b.flag);
-    } else {
-        hipLaunchKernelGGL((als_update<64, 4, false>), dim3((unsigned)n_gram), dim3(256), 0, st, b.G, ndim, k, R, b.M, A, I,
-                           tiles, b.gram_ws, lambda, b.inner, b.flag);
-        hipLaunchKernelGGL((als_normalise<64>), dim3((unsigned)n_scale), dim3(256), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
-                           rows, Gk, lambda, b.inner, b.flag);
-    }
-    return n_scale;
+    const SweepEnd now = k == ndim - 1 ? end : SweepEnd{nullptr, nullptr, 0.0, false};
+    auto go = [&](auto nb, auto rp) {
+        constexpr int NB = decltype(nb)::value, RP = decltype(rp)::value, WAVES = update_waves(NB);
+        const int64_t tiles = ceil_div(I, 16);
+        if (tiles <= update_most_tiles(NB)) {
+            const int lds = update_lds_doubles(NB, (int)tiles) * (int)sizeof(double);
+            (void)hipFuncSetAttribute((const void*)als_update<NB, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipLaunchKernelGGL((als_update<NB, true>), dim3(1), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I, tiles,
+                               b.gram_ws, lambda, b.inner, b.flag, now);
+            if (k == ndim - 1)
+                end.record = nullptr;
+            return 1;
+        }
+        const int64_t groups = ceil_div(tiles, WAVES);
+        const int n_gram = (int)(groups < kGramBlocks ? groups : kGramBlocks);
+        const int64_t want = ceil_div(I * R, 2048);
+        const int64_t rows = ceil_div(I, want < kScaleBlocks ? want : kScaleBlocks);
+        const int n_scale = (int)ceil_div(I, rows);
+        const int lds = update_lds_doubles(NB, WAVES) * (int)sizeof(double);
+        (void)hipFuncSetAttribute((const void*)als_update<NB, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipLaunchKernelGGL((als_update<NB, false>), dim3((unsigned)n_gram), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I,
+                           tiles, b.gram_ws, lambda, b.inner, b.flag, SweepEnd{nullptr, nullptr, 0.0, false});
+        hipLaunchKernelGGL((als_normalise<RP>), dim3((unsigned)n_scale), dim3(512), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
+                           rows, Gk, lambda, k == ndim - 1 ? b.inner : nullptr, b.flag);
+        return n_scale;
+    };
+    using std::integral_constant;
+    if (R <= 16)
+        return go(integral_constant<int, 1>(), integral_constant<int, 16>());
+    if (R <= 32)
+        return go(integral_constant<int, 2>(), integral_constant<int, 32>());
+    if (R <= 48)
+        return go(integral_constant<int, 3>(), integral_constant<int, 64>());
+    return go(integral_constant<int, 4>(), integral_constant<int, 64>());
 }
 
 // Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns from rank 320 on, below it four, since a
@@ -1766,7 +1954,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         const int64_t chunks = ceil_div(max_I, kChunkRows);      // of the initial Gram matrices
         const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
                      o_L = take(big ? (size_t)ldL * ldL + 2 * R : 0),
-                     o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * RR),
+                     o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * (RR + R)),
                      o_in = take(big ? 0 : (size_t)kScaleBlocks * R), o_part = take(kNormBlocks), o_sc = take(4), o_rec = take(kRecords * sizeof(SweepRecord) / sizeof(double));
         const size_t o_shared = off;
         if (hipMalloc(&b.base, off + (shared ? sp.total : 0)) != hipSuccess) {
