@@ -18,14 +18,13 @@
 namespace {
 
 constexpr int kSmallRank = 64;     // up to here the R x R matrices are handled in one workgroup's LDS
-constexpr int kChunkRows = 64;     // rows of a factor one workgroup turns into a partial Gram matrix
 constexpr int kNormBlocks = 4096;  // partial sums of ||X||^2
 constexpr int kGramBlocks = 128;   // workgroups of an update (ranks up to 64) at most
 constexpr int kScaleBlocks = 256;  // ... of its second launch
 constexpr int kFitChunks = 256;    // row chunks of the fit's inner product (ranks above 64)
 constexpr int kFailed = 1, kStopped = 2;       // values of the flag: a pivot that is not positive; the fit has settled
 
-int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+__host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Sum of 256 per-thread values in a fixed tree order; result in every thread.
 __device__ __forceinline__ double block_sum_256(double v, double* lds)
@@ -81,49 +80,132 @@ __global__ void __launch_bounds__(256) sumsq_partial(const double* __restrict__ 
         partial[blockIdx.x] = s;
 }
 
-// out[0] = sum of n values, one workgroup, fixed order; clears the pivot flag.
-__global__ void __launch_bounds__(256) sum_fixed(const double* __restrict__ v, int n, double* out, int* flag)
+// Sum of v[b * stride] for b = first, first + by, ... below n, eight requested before the first is added, in order.
+__device__ __forceinline__ double sum_strided(const double* __restrict__ v, int first, int by, int n, int64_t stride)
 {
-    __shared__ double lds[256];
     double s = 0.0;
-    for (int i = threadIdx.x; i < n; i += 256)
-        s += v[i];
-    s = block_sum_256(s, lds);
-    if (threadIdx.x == 0) {
-        out[0] = s;
-        flag[0] = 0;
+    for (int b = first; b < n; b += 8 * by) {
+        double t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            t[u] = v[(int64_t)min(b + u * by, n - 1) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            s += b + u * by < n ? t[u] : 0.0;
     }
+    return s;
 }
 
-// Partial Gram matrix of rows [64 b, 64 b + 64) of A (I x R): ws[b][a * R + c] = sum_r A(r, a) A(r, c).
-__global__ void __launch_bounds__(256) gram_partial(const double* __restrict__ A, int64_t I, int R, double* ws)
+// The Gram matrices of the factors a call starts from (ranks up to 64): workgroups [first[m], first[m + 1]) take the rows of mode m, a
+// wavefront 16 at a time, and leave partial matrices ws[workgroup][R * R]; gram_reduce adds a mode's.
+struct GramSet {
+    const double* A[MTTKRP_MAX_NDIM];
+    int64_t I[MTTKRP_MAX_NDIM];
+    int32_t first[MTTKRP_MAX_NDIM + 1];
+};
+// workgroups for a mode: 1 to 4 MB of partial matrices at most
+int gram_blocks(int64_t I, int R)
 {
-    extern __shared__ double tile[];   // kChunkRows x R
-    const int64_t r0 = (int64_t)blockIdx.x * kChunkRows;
-    const int rows = (int)(I - r0 < kChunkRows ? I - r0 : kChunkRows);
-    for (int t = threadIdx.x; t < rows * R; t += 256)
-        tile[t] = A[r0 * R + t];
+    const int64_t n = ceil_div(I, 64), most = R <= 16 ? 512 : (R <= 32 ? 256 : 128);
+    return (int)(n < most ? n : most);
+}
+// The accumulators of the pairs of column blocks (p, q), p >= q: += Y^T Y of 16 rows, of which lane (n16, kq) holds y[u][s] = (4 s + kq, 16 u + n16).
+template <int NB> __device__ __forceinline__ void gram_rows(double4_t (&acc)[NB * (NB + 1) / 2], const double (&y)[NB][4])
+{
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int q = 0; q <= p; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                acc[p * (p + 1) / 2 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[p][s], y[q][s], acc[p * (p + 1) / 2 + q], 0, 0, 0);
+}
+template <int NB> __global__ void __launch_bounds__(256) gram_partial(const GramSet g, int ndim, int R, double* __restrict__ ws)
+{
+    constexpr int PAIRS = NB * (NB + 1) / 2;
+    __shared__ double red[3][PAIRS][256];
+    int m = 0;
+    while (m + 1 < ndim && (int)blockIdx.x >= g.first[m + 1])
+        ++m;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n16 = lane & 15, kq = lane >> 4;
+    const double* const A = g.A[m];
+    const int64_t I = g.I[m], n_tiles = ceil_div(I, 16), step = 4 * (g.first[m + 1] - g.first[m]);
+    double4_t acc[PAIRS];
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i)
+        acc[i] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t t = 4 * ((int)blockIdx.x - g.first[m]) + wave; t < n_tiles; t += step) {
+        double y[NB][4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int64_t r = 16 * t + 4 * s + kq;
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const double v = A[(r < I ? r : I - 1) * R + min(16 * u + n16, R - 1)];
+                y[u][s] = r < I && 16 * u + n16 < R ? v : 0.0;
+            }
+        }
+        gram_rows<NB>(acc, y);
+    }
+    if (wave > 0) {
+#pragma unroll
+        for (int i = 0; i < PAIRS; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                red[wave - 1][i][64 * q + lane] = acc[i][q];
+    }
     __syncthreads();
-    double* out = ws + (int64_t)blockIdx.x * R * R;
-    for (int e = threadIdx.x; e < R * R; e += 256) {
-        const int a = e / R, c = e - a * R;
-        double s = 0.0;
-        for (int r = 0; r < rows; ++r)
-            s += tile[r * R + a] * tile[r * R + c];
-        out[e] = s;
-    }
+    if (wave > 0)
+        return;
+    double* const out = ws + (int64_t)blockIdx.x * R * R;
+#pragma unroll
+    for (int p = 0; p < NB; ++p)
+#pragma unroll
+        for (int q = 0; q <= p; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int i = p * (p + 1) / 2 + q, r = 16 * p + 4 * e + kq, c = 16 * q + n16;
+                const double v = ((acc[i][e] + red[0][i][64 * e + lane]) + red[1][i][64 * e + lane]) + red[2][i][64 * e + lane];
+                if (r < R && c < R) {
+                    out[r * R + c] = v;
+                    if (p != q)
+                        out[c * R + r] = v;
+                }
+            }
 }
 
-// G[e] = sum over chunks of ws[chunk][e], in chunk order.
-__global__ void __launch_bounds__(256) gram_reduce(const double* __restrict__ ws, int n_chunks, int RR, double* G)
+// G[m] = sum of mode m's partial matrices, 64 entries a workgroup, a wavefront for an eighth of the matrices; and where blockIdx.y is
+// ndim, norm2[0] = ||X||^2 from its n_norm partial sums and the flag cleared.  Fixed orders.
+__global__ void __launch_bounds__(512) gram_reduce(const GramSet g, const double* __restrict__ ws, int ndim, int RR, double* G,
+                                                   const double* __restrict__ norm_part, int n_norm, double* norm2, int* flag)
 {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= RR)
+    __shared__ double red[512];
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = tid >> 6, m = (int)blockIdx.y;
+    if (m == ndim) {
+        if (blockIdx.x > 0)
+            return;
+        red[tid] = sum_strided(norm_part, tid, 512, n_norm, 1);
+        __syncthreads();
+        for (int s = 256; s > 0; s >>= 1) {
+            if (tid < s)
+                red[tid] += red[tid + s];
+            __syncthreads();
+        }
+        if (tid == 0) {
+            norm2[0] = red[0];
+            flag[0] = 0;
+        }
         return;
-    double s = 0.0;
-    for (int c = 0; c < n_chunks; ++c)
-        s += ws[(int64_t)c * RR + e];
-    G[e] = s;
+    }
+    const int e = min((int)blockIdx.x * 64 + lane, RR - 1);
+    red[tid] = sum_strided(ws + (int64_t)g.first[m] * RR + e, wave, 8, g.first[m + 1] - g.first[m], RR);
+    __syncthreads();
+    if (wave == 0 && (int)blockIdx.x * 64 + lane < RR) {
+        double v = 0.0;
+        for (int q = 0; q < 8; ++q)
+            v += red[64 * q + lane];
+        G[(int64_t)m * RR + e] = v;
+    }
 }
 
 // The power of two whose square brings a diagonal entry of V to [1, 4).  V is factorised as S V S and the rows of M and A
@@ -907,22 +989,6 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     }
 }
 
-// Sum of v[b * stride] for b = first, first + by, ... below n, eight requested before the first is added, in order.
-__device__ __forceinline__ double sum_strided(const double* __restrict__ v, int first, int by, int n, int64_t stride)
-{
-    double s = 0.0;
-    for (int b = first; b < n; b += 8 * by) {
-        double t[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            t[u] = v[(int64_t)min(b + u * by, n - 1) * stride];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            s += b + u * by < n ? t[u] : 0.0;
-    }
-    return s;
-}
-
 // Second launch of the update for longer factors: every workgroup adds up the columns' squared norms (n_gram
 // partial diagonals), normalises its rows and its share of the Gram matrix (64 entries at a time, a wavefront for an eighth of
 // the partial matrices), and after a sweep's last mode (inner != nullptr) leaves its column sums of M * A in inner[block][R].
@@ -1023,26 +1089,52 @@ __global__ void __launch_bounds__(256) fit_terms_small(const double* __restrict_
 // ---------------------------------------------------------------------------
 constexpr int kNB = 32;
 
-// G = A^T A: a 16 x 16 tile of G per workgroup, the rows of A in chunks of 16 through LDS, summed
-// in row order.  G(p, q) and G(q, p) add the same products in the same order: G is symmetric bit for bit.
-__global__ void __launch_bounds__(256) gram_tiled(const double* __restrict__ A, int64_t I, int R, double* G)
+// G = A^T A: a 16 x 16 block of G (on or below the diagonal) per workgroup, a wavefront for every eighth 16 rows of A, on the matrix cores;
+// the wavefronts' sums are added in their order.  G(p, q) and G(q, p) are one value.  Bound by latency: two tiles requested before the first
+// is used (129 rows at R = 500 in chunks of 16 through LDS with two barriers each: 11 us -> 5).
+__global__ void __launch_bounds__(512) gram_tiled(const double* __restrict__ A, int64_t I, int R, double* G)
 {
-    __shared__ double ta[16][17], tb[16][17];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int p0 = blockIdx.y * 16, q0 = blockIdx.x * 16;
-    double s = 0.0;
-    for (int64_t i0 = 0; i0 < I; i0 += 16) {
-        const int64_t i = i0 + ty;
-        ta[ty][tx] = i < I && p0 + tx < R ? A[i * R + p0 + tx] : 0.0;
-        tb[ty][tx] = i < I && q0 + tx < R ? A[i * R + q0 + tx] : 0.0;
-        __syncthreads();
-        const int rows = (int)(I - i0 < 16 ? I - i0 : 16);
-        for (int r = 0; r < rows; ++r)
-            s += ta[r][ty] * tb[r][tx];
-        __syncthreads();
+    __shared__ double red[8][256];
+    if (blockIdx.x > blockIdx.y)
+        return;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n16 = lane & 15, kq = lane >> 4;
+    const int p = (int)blockIdx.y * 16 + n16, q = (int)blockIdx.x * 16 + n16;
+    const int64_t n_tiles = ceil_div(I, 16);
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t t = wave; t < n_tiles; t += 16) {
+        double x[2][4], y[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int64_t r = 16 * (t + 8 * h) + 4 * s + kq;
+                const double* const row = A + (r < I ? r : I - 1) * R;
+                x[h][s] = row[min(p, R - 1)];
+                y[h][s] = row[min(q, R - 1)];
+            }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const bool real = 16 * (t + 8 * h) + 4 * s + kq < I;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(real ? x[h][s] : 0.0, real ? y[h][s] : 0.0, acc, 0, 0, 0);
+            }
     }
-    if (p0 + ty < R && q0 + tx < R)
-        G[(int64_t)(p0 + ty) * R + q0 + tx] = s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        red[wave][64 * e + lane] = acc[e];
+    __syncthreads();
+    if (tid >= 256)
+        return;
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w)
+        v += red[w][tid];
+    const int r = (int)blockIdx.y * 16 + 4 * (tid >> 6) + kq, c = q;
+    if (r < R && c < R) {
+        G[(int64_t)r * R + c] = v;
+        G[(int64_t)c * R + r] = v;
+    }
 }
 
 // One launch per 64 columns of V = L D L^T, V holding what is still to be factorised.  Workgroup (tj, ti),
@@ -1462,18 +1554,11 @@ struct Buffers {
     ~Buffers() { (void)hipFree(base); }
 };
 
-void gram(const double* A, int64_t I, int R, double* ws, double* G, hipStream_t st)
+void gram_big(const double* A, int64_t I, int R, double* G, hipStream_t st)
 {
-    if (R > kSmallRank) {
-        const unsigned nt = (unsigned)ceil_div(R, 16);
-        hipLaunchKernelGGL(gram_tiled, dim3(nt, nt), dim3(256), 0, st, A, I, R, G);
-        return;
-    }
-    const int n_chunks = (int)ceil_div(I, kChunkRows);
-    hipLaunchKernelGGL(gram_partial, dim3(n_chunks), dim3(256), (size_t)kChunkRows * R * sizeof(double), st, A, I, R, ws);
-    hipLaunchKernelGGL(gram_reduce, dim3((unsigned)ceil_div(R * R, 256)), dim3(256), 0, st, ws, n_chunks, R * R, G);
+    const unsigned nt = (unsigned)ceil_div(R, 16);
+    hipLaunchKernelGGL(gram_tiled, dim3(nt, nt), dim3(512), 0, st, A, I, R, G);
 }
-
 
 // The update of a factor up to rank 64: one workgroup where its rows fit the workgroup's LDS (then a second launch would take
 // longer than its further tiles), else two launches.  Returns the number of blocks that left column sums of M * A in b.inner.
@@ -1944,6 +2029,8 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         shared = false;
     // One allocation: an allocation and a free each cost about as much as a sweep over a small tensor.
     Buffers b;
+    GramSet gs;
+    memset(&gs, 0, sizeof(gs));
     {
         size_t off = 0;
         auto take = [&](size_t values) {
@@ -1951,7 +2038,15 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
             off += align256(values * sizeof(double));
             return at;
         };
-        const int64_t chunks = ceil_div(max_I, kChunkRows);      // of the initial Gram matrices
+        int64_t chunks = 0;      // partial Gram matrices of the initial factors
+        if (!big)
+            for (int m = 0; m < ndim; ++m) {
+                gs.first[m] = (int32_t)chunks;
+                gs.A[m] = factors[m];
+                gs.I[m] = dims[m];
+                chunks += gram_blocks(dims[m], R);
+                gs.first[m + 1] = (int32_t)chunks;
+            }
         const size_t o_M = take((size_t)max_I * R), o_G = take((size_t)ndim * RR), o_V = take(big ? RR : 0),
                      o_L = take(big ? (size_t)ldL * ldL + 2 * R : 0),
                      o_ws = take(big ? (size_t)kFitChunks + R : (size_t)(chunks > kGramBlocks ? chunks : kGramBlocks) * (RR + R)),
@@ -1975,13 +2070,26 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
         b.shared_ws = b.base + o_shared;
     }
 
-    // ||X||^2 once (which also clears the pivot flag), Gram matrices of the initial factors
+    // ||X||^2 once, Gram matrices of the initial factors, and the flag cleared
     const int64_t want_nb = ceil_div(N, 2048);
     const int nb = (int)(want_nb < kNormBlocks ? want_nb : kNormBlocks);
     hipLaunchKernelGGL(sumsq_partial, dim3(nb), dim3(256), 0, st, X, N, b.partial);
-    hipLaunchKernelGGL(sum_fixed, dim3(1), dim3(256), 0, st, b.partial, nb, b.scalars + 0, b.flag);
-    for (int m = 0; m < ndim; ++m)
-        gram(factors[m], dims[m], R, b.gram_ws, b.G + (int64_t)m * RR, st);
+    if (big) {
+        for (int m = 0; m < ndim; ++m)
+            gram_big(factors[m], dims[m], R, b.G + (int64_t)m * RR, st);
+    } else {
+        const dim3 grid((unsigned)gs.first[ndim]);
+        if (R <= 16)
+            hipLaunchKernelGGL((gram_partial<1>), grid, dim3(256), 0, st, gs, ndim, R, b.gram_ws);
+        else if (R <= 32)
+            hipLaunchKernelGGL((gram_partial<2>), grid, dim3(256), 0, st, gs, ndim, R, b.gram_ws);
+        else if (R <= 48)
+            hipLaunchKernelGGL((gram_partial<3>), grid, dim3(256), 0, st, gs, ndim, R, b.gram_ws);
+        else
+            hipLaunchKernelGGL((gram_partial<4>), grid, dim3(256), 0, st, gs, ndim, R, b.gram_ws);
+    }
+    hipLaunchKernelGGL(gram_reduce, dim3(big ? 1u : (unsigned)ceil_div(RR, 64), big ? 1u : (unsigned)(ndim + 1)), dim3(512), 0, st, gs, b.gram_ws,
+                       big ? 0 : ndim, RR, b.G, b.partial, nb, b.scalars, b.flag);
 
     const double* cf[MTTKRP_MAX_NDIM];
     double* mo[MTTKRP_MAX_NDIM];
@@ -2007,7 +2115,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
                 hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(512), kPanelLds, st, b.V, R, j0, b.L, ldL, dinv, b.flag);
             }
             solve_big(b.L, ldL, dinv, dinv + R, R, b.M, factors[k], I, b.flag, st);
-            gram(factors[k], I, R, b.gram_ws, b.V, st);
+            gram_big(factors[k], I, R, b.V, st);
             const int64_t want = ceil_div(I * R + RR, 1024);
             hipLaunchKernelGGL(scale_by_gram, dim3((unsigned)(want < 4096 ? want : 4096)), dim3(256), 0, st, b.V, R, factors[k],
                                I * (int64_t)R, Gk, lambda, b.flag);
