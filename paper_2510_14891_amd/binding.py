@@ -14,6 +14,7 @@ from typing import Optional, Sequence
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmttkrp_hip.so")
+CALL_PATH = os.path.join(_HERE, "_dense_call.so")
 
 MTTKRP_OK = 0
 MTTKRP_ERR_INVALID_ARG = 1
@@ -234,6 +235,29 @@ def _t():
     return _torch
 
 
+_dense_call = None
+
+
+def _load_dense_call():
+    """The extension module's dense(), bound to the library's entry points; where it has not been built, a
+    function that leaves every call to the code below."""
+    global _dense_call
+    L = lib()
+    torch = _t()
+    if not os.path.exists(CALL_PATH):
+        _dense_call = lambda *args: None
+        return _dense_call
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_dense_call", CALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    address = [ctypes.cast(getattr(L, "mttkrp_dense_" + name), ctypes.c_void_p).value
+               for name in ("f64", "f32", "f64_ws", "f32_ws", "f64_ex", "f32_ex")]
+    module.bind(*address, torch._C._cuda_getCurrentRawStream)
+    _dense_call = module.dense
+    return _dense_call
+
+
 class _OnDevice:
     """Makes a device current for one call; nothing to do when it is already."""
 
@@ -328,6 +352,12 @@ def mttkrp_dense(X, dims: Sequence[int], factors: Sequence, k: int, M=None,
     Returns M.  The call is asynchronous on the stream.
     """
     L = _lib or lib()
+    # (what the extension module does not take, it leaves: None)
+    done = (_dense_call or _load_dense_call())(X, dims, factors, k, M, workspace, stream, lam, beta)
+    if done is not None:
+        if type(done) is int:
+            _check(done)
+        return done
     suffix, d, ptrs, R, M, stream = _marshal(X, dims, factors, k, M, stream)
     if lam is not None and (lam.dtype != X.dtype or lam.device != X.device
                             or not lam.is_contiguous() or lam.numel() != R):

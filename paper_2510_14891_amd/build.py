@@ -17,6 +17,8 @@ HEADER_CONTRACT = os.path.join(HERE, "csrc", "mttkrp_contract.h")
 HEADER = os.path.join(os.path.dirname(HERE), "include", "mttkrp.h")
 HEADER_ABLATION = os.path.join(os.path.dirname(HERE), "include", "mttkrp_ablation.h")
 LIB = os.path.join(HERE, "libmttkrp_hip.so")
+SRC_CALL = os.path.join(HERE, "csrc", "dense_call.cpp")
+CALL = os.path.join(HERE, "_dense_call.so")      # mttkrp_dense() of the binding without ctypes
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-shared",
@@ -26,8 +28,31 @@ HIPCC_FLAGS = [
 ]
 
 
+def build_call(force: bool = True, verbose: bool = False) -> str:
+    """Compile csrc/dense_call.cpp (host code) into the extension module next to this file."""
+    if not force and os.path.exists(CALL) and os.path.getmtime(CALL) >= max(os.path.getmtime(SRC_CALL), os.path.getmtime(HEADER)):
+        return CALL
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + sysconfig.get_paths()["include"]]
+    for path in cpp_extension.include_paths():
+        cmd += ["-isystem", path]
+    cmd += ["-o", CALL, SRC_CALL]
+    for path in cpp_extension.library_paths():
+        cmd += ["-L" + path]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile csrc/mttkrp.hip into libmttkrp_hip.so next to this file."""
+    """Compile csrc/*.hip into libmttkrp_hip.so next to this file, and the binding's extension module."""
+    build_call(force, verbose)
     if (not force and os.path.exists(LIB)
             and os.path.getmtime(LIB) >= max(os.path.getmtime(SRC), os.path.getmtime(HEADER),
                                              os.path.getmtime(SRC_ABLATION), os.path.getmtime(HEADER_ABLATION),
