@@ -290,17 +290,6 @@ template <int RP> __device__ __forceinline__ void solve_forward(double (&y)[RP /
                 y[q] -= Lf[a * (RP + 1) + 4 * q + part] * ya;
         }
 }
-template <int RP> __device__ __forceinline__ void solve_backward(double (&y)[RP / 4], const double* Lf, int R, int part)
-{
-#pragma unroll
-    for (int a = RP - 1; a >= 0; --a)
-        if (a < R) {
-            const double ya = quad_value(y[a >> 2], a & 3);
-#pragma unroll
-            for (int q = 0; q <= a >> 2; ++q)
-                y[q] -= Lf[(4 * q + part) * (RP + 1) + a] * ya;
-        }
-}
 
 // The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
 // a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
@@ -309,19 +298,6 @@ template <int n> __device__ __forceinline__ void row_fma(double& acc, double a, 
 {
     asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(n));
 }
-// a[i] += (a[i] of lane n) * b for i = n + 1 .. 15, in one block, so that nothing can come between its instructions: each takes and
-// writes registers of its own, and the two wait states in front cover the ones written right before the block.
-template <int n> __device__ __forceinline__ void row_fmas(double (&a)[16], double b)
-{
-#define ROW_FMA(i) "\n\t.if " #i " > %c17\n\tv_fmac_f64_dpp %" #i ", %" #i ", %16 row_newbcast:%c17 row_mask:0xf bank_mask:0xf\n\t.endif"
-    asm("s_nop 1" ROW_FMA(1) ROW_FMA(2) ROW_FMA(3) ROW_FMA(4) ROW_FMA(5) ROW_FMA(6) ROW_FMA(7) ROW_FMA(8) ROW_FMA(9) ROW_FMA(10)
-            ROW_FMA(11) ROW_FMA(12) ROW_FMA(13) ROW_FMA(14) ROW_FMA(15)
-        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]),
-          "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15])
-        : "v"(b), "n"(n));
-#undef ROW_FMA
-}
-
 // Steps 0 .. N - 1, with the step as a constant.
 template <int N, int n = 0, typename Step> __device__ __forceinline__ void steps(Step step)
 {
@@ -331,27 +307,67 @@ template <int N, int n = 0, typename Step> __device__ __forceinline__ void steps
     }
 }
 
+// Column j of the factorisation below: a[i] += (a[i] of lane j) * t * r for i = j + 1 .. 15, t being minus the pivot row where it is still to
+// be used and r the reciprocal of the pivot; and the next pivot d and its reciprocal (as reciprocal() has it), whose chain of
+// dependent instructions lies between the row operations: those of a column after it took 165 cycles a column.  One block, so that nothing
+// comes between its instructions: a register is read by DPP two wait states after it was written, and the estimate of the reciprocal one.
+template <int j> __device__ __forceinline__ void pivot_column(double (&a)[16], double t, double& d, double& r)
+{
+    double w, e, dn, rn;
+#define PC_ROW(i) ".if " #i " > %c21\n\tv_fmac_f64_dpp %" #i ", %" #i ", %16 row_newbcast:%c21 row_mask:0xf bank_mask:0xf\n\t.endif\n\t"
+#define PC_AT(i, k, op) ".if " #i " == %c21 + " #k "\n\t" op "\n\t.endif\n\t"
+#define PC_PIVOT(i) "v_mov_b64_dpp %18, %" #i " row_newbcast:" #i " row_mask:0xf bank_mask:0xf"
+#define PC_RCP "v_rcp_f64 %19, %18"
+#define PC_E "v_fma_f64 %17, -%18, %19, 1.0"
+#define PC_R "v_fma_f64 %19, %17, %19, %19"
+// (i: the row; p: the row three before it, the next pivot's where i == j + 4)
+#define PC_STEP(i, p) PC_AT(i, 4, PC_PIVOT(p)) PC_AT(i, 5, PC_RCP) PC_AT(i, 7, PC_E) PC_AT(i, 8, PC_R) PC_AT(i, 9, PC_E) PC_AT(i, 10, PC_R) PC_ROW(i)
+// (what the rows left have no place for)
+#define PC_LAST(k, op) ".if %c21 + " #k " > 15\n\ts_nop 1\n\t" op "\n\t.endif\n\t"
+#define PC_LAST_PIVOT(i) ".if " #i " == %c21 + 1 && %c21 + 4 > 15\n\ts_nop 1\n\t" PC_PIVOT(i) "\n\t.endif\n\t"
+    asm("s_nop 1\n\tv_mul_f64 %16, %20, %22\n\t" PC_ROW(1) PC_ROW(2) PC_ROW(3) PC_STEP(4, 1) PC_STEP(5, 2) PC_STEP(6, 3) PC_STEP(7, 4) PC_STEP(8, 5)
+            PC_STEP(9, 6) PC_STEP(10, 7) PC_STEP(11, 8) PC_STEP(12, 9) PC_STEP(13, 10) PC_STEP(14, 11) PC_STEP(15, 12)
+                PC_LAST_PIVOT(13) PC_LAST_PIVOT(14) PC_LAST_PIVOT(15) PC_LAST(5, PC_RCP) PC_LAST(7, PC_E) PC_LAST(8, PC_R) PC_LAST(9, PC_E) PC_LAST(10, PC_R)
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]), "+v"(a[9]),
+          "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "=&v"(w), "=&v"(e), "=&v"(dn), "=&v"(rn)
+        : "v"(t), "n"(j), "v"(r));
+#undef PC_LAST_PIVOT
+#undef PC_LAST
+#undef PC_STEP
+#undef PC_R
+#undef PC_E
+#undef PC_RCP
+#undef PC_PIVOT
+#undef PC_AT
+#undef PC_ROW
+    d = dn;
+    r = rn;
+}
+
 // L D L^T of a 16 x 16 block by one wavefront without barriers: lane c of each 16 lanes (all four hold the same) has column c in
 // a[0 .. 15], the whole symmetric block, so that the pivot row is a register and the pivot column a lane's registers.
-// Afterwards a[i] = L(i, c) D(c) for i > c; dinv[0 .. n - 1] (LDS) = 1 / D for the first n columns, the others are left as
-// they are.  False when a pivot is not positive.
-__device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv, int n = 16)
+// Afterwards a[i] = L(i, c) D(c) for i > c; dinv[0 .. 15] (LDS) = 1 / D.  False when a pivot is not positive.
+__device__ __forceinline__ bool factorise16(double (&a)[16], double* dinv)
 {
     const int c = (int)threadIdx.x & 15;
-    bool ok = true;
-    steps<16>([&](auto J) {
+    double d = row_value<0>(a[0]), r = reciprocal(d);
+    bool ok = d > 0.0;
+    dinv[0] = r;
+    steps<15>([&](auto J) {
         constexpr int j = decltype(J)::value;
-        if (j >= n)
-            return;
-        const double d = row_value<j>(a[j]);
+        pivot_column<j>(a, c > j ? -a[j] : 0.0, d, r);
         ok = ok && d > 0.0;
-        const double r = reciprocal(d);
-        dinv[j] = r;
-        const double w = c > j ? -a[j] * r : 0.0;
-        if constexpr (j < 15)
-            row_fmas<j>(a, w);
+        dinv[j + 1] = r;
     });
     return ok;
+}
+
+// v / n with 1 / n at hand: the product and one correction, which leaves it within the rounding of a division (n from about 1e-162 to
+// 1e154, as norms are).
+__device__ __forceinline__ double quotient(double v, double n, double inverse)
+{
+    const double q = v * inverse;
+    return fma(fma(-n, q, v), inverse, q);
 }
 
 // The end of a sweep on the device: fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X|| into the sweep's record, and
@@ -386,178 +402,6 @@ struct SweepEnd {
     bool first;
 };
 
-// The whole update of a short factor (R <= 16, at most 16 rows a wavefront) in one workgroup, a chain of six exchanges: the Gram
-// matrices come with a wavefront each, the first wavefront multiplies and factorises them (factorise16), a wavefront solves
-// 16 rows and keeps them in registers, the Gram matrix of the new rows comes from the matrix cores and its sum over the
-// wavefronts, and the rows are scaled and written once.  100 x 80 x 60 at R = 10: 11.1 us a mode in als_update (factorisation 2.4,
-// Gram sums 2.9, rows read again 0.8, column sums 1.3) -> 6.7 (loads 0.8, product and scaling 0.9,
-// factorisation 1.1, solves 1.6, Gram matrix 0.6, scaling and sums 1.3).
-template <int WAVES>
-__global__ void __launch_bounds__(64 * WAVES)
-als_update_short(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, double* lambda,
-                 double* inner, int* flag, SweepEnd end)
-{
-    static_assert(WAVES >= MTTKRP_MAX_NDIM, "a wavefront for every Gram matrix");
-    __shared__ double Gs[MTTKRP_MAX_NDIM][256], Lf[16 * 17], dinv[16], nrm[16], scale[16], weight[16], model[4];
-    __shared__ double Ys[16 * WAVES * 17], red[WAVES][256], cols[WAVES][16];
-    __shared__ int bad;
-    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3, trow = 16 * wave + (lane >> 2);
-    const int64_t RR = (int64_t)R * R;
-    // (every lane loads, from the last row or column where its own does not exist: behind branches each load is waited for)
-    const int stop = flag[0];
-    double m[4], g[4];
-    const int64_t row = trow < I ? trow : I - 1;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        m[q] = M[row * R + min(4 * q + part, R - 1)];
-    const double* const Gm = G + (wave < ndim ? wave : 0) * RR;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        g[q] = Gm[min(4 * q + kq, R - 1) * R + min(n16, R - 1)];
-    if (wave < ndim) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            Gs[wave][16 * (4 * q + kq) + n16] = g[q];
-    }
-    if (__syncthreads_or(stop) != 0) {
-        if (end.record && tid == 0)
-            end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
-        return;
-    }
-    if (wave == 0) {
-        double a[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            a[i] = 1.0;
-        for (int t = 0; t < ndim; ++t)
-            if (t != k) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    a[i] *= Gs[t][16 * i + n16];
-            }
-        double d = 1.0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            d = i == n16 ? a[i] : d;
-        const double sc = unit_scale(d);
-        steps<16>([&](auto J) {
-            constexpr int i = decltype(J)::value;
-            a[i] = a[i] * row_value<i>(sc) * sc;
-        });
-        const bool ok = factorise16(a, dinv, R);
-        if (lane == 0)
-            bad = ok ? 0 : 1;
-        const double rd = dinv[n16 < R ? n16 : 0];
-        if (kq == 0) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                Lf[n16 * 17 + i] = i > n16 && i < R ? a[i] * rd : 0.0;
-            scale[n16] = sc;
-        }
-    }
-    __syncthreads();
-    if (bad) {
-        if (tid == 0) {
-            flag[0] = kFailed;
-            if (end.record)
-                end_sweep(end.scalars, flag, end.record, 0.0, 0.0, end.tol, end.first);
-        }
-        return;
-    }
-    double y[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const bool mine = trow < I && 4 * q + part < R;
-        m[q] = mine ? m[q] : 0.0;
-        y[q] = mine ? m[q] * scale[4 * q + part] : 0.0;
-    }
-    solve_forward<16>(y, Lf, R, part);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        y[q] = 4 * q + part < R ? y[q] * dinv[4 * q + part] : 0.0;
-    solve_backward<16>(y, Lf, R, part);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        y[q] *= scale[4 * q + part];
-        Ys[trow * 17 + 4 * q + part] = y[q];
-    }
-    // Y^T Y of this wavefront's 16 rows: both operands of a step are row 4 s + kq, column n16 (from other lanes of the wavefront)
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        const double v = Ys[(16 * wave + 4 * s + kq) * 17 + n16];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        red[wave][16 * (4 * q + kq) + n16] = acc[q];
-    __syncthreads();
-    double sum = 0.0;
-    if (tid < 256) {
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            sum += red[w][tid];
-        if ((tid >> 4) == (tid & 15)) {
-            const double n = sqrt(sum);
-            nrm[tid & 15] = n > 0.0 ? n : 1.0;       // a zero column is left alone
-            weight[tid & 15] = n;
-            if ((tid & 15) < R)
-                lambda[tid & 15] = n;
-        }
-    }
-    __syncthreads();
-    double model2 = 0.0;                             // this thread's share of ||X^||^2 (the sweep's last update)
-    if (tid < 256 && (tid >> 4) < R && (tid & 15) < R) {
-        const double gk = sum / (nrm[tid >> 4] * nrm[tid & 15]);
-        G[k * RR + (tid >> 4) * R + (tid & 15)] = gk;
-        if (end.record) {
-            model2 = weight[tid >> 4] * weight[tid & 15];
-            for (int t = 0; t < ndim; ++t)
-                model2 *= t == k ? gk : Gs[t][tid];
-        }
-    }
-    if (end.record && tid < 256) {
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1)
-            model2 += __shfl_xor(model2, d);
-        if (lane == 0)
-            model[wave] = model2;
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double v = y[q] / nrm[4 * q + part];
-        if (trow < I && 4 * q + part < R)
-            A[trow * R + 4 * q + part] = v;
-        double t = m[q] * v;
-        t += __shfl_xor(t, 4);
-        t += __shfl_xor(t, 8);
-        t += __shfl_xor(t, 16);
-        t += __shfl_xor(t, 32);
-        if (lane < 4)
-            cols[wave][4 * q + part] = t;
-    }
-    __syncthreads();
-    if (tid < R) {
-        double v = 0.0;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            v += cols[w][tid];
-        inner[tid] = v;
-        cols[0][tid] = v * weight[tid];
-    }
-    if (end.record) {
-        __syncthreads();
-        if (tid == 0) {
-            double v = 0.0;
-            for (int j = 0; j < R; ++j)
-                v += cols[0][j];
-            end_sweep(end.scalars, flag, end.record, v, (model[0] + model[1]) + (model[2] + model[3]), end.tol, end.first);
-        }
-    }
-}
-
 // y[t] += (y[t] of lane a of each 16 lanes) * f[a] for a = 0 .. 15 in order (FORWARD) or 15 .. 0: the substitution with a unit triangular 16 x 16
 // block, for 16 rows of which a lane has column lane % 16 of four.  One block of instructions: four rows take turns, so that a
 // register is read by DPP three instructions after it was written; the waits in front and behind are those of matrix
@@ -585,7 +429,6 @@ template <bool FORWARD> __device__ __forceinline__ void substitute16(double (&y)
 // What als_update keeps in LDS: V = L D L^T (then -L), one step's rows of L D, tiles of 16 rows of the factor.  Rows of four doubles
 // more than the columns: both operand layouts of the matrix cores then meet each bank twice.
 constexpr int update_ld(int nb) { return 16 * nb + 4; }
-constexpr int update_waves(int nb) { return nb <= 2 ? 16 : 8; }
 constexpr int update_sums(int nb) { return nb == 1 ? 7 * 256 : (nb == 2 ? 9 * 256 : 0); }       // blocks of the Gram matrix from several wavefronts
 constexpr int update_lds_doubles(int nb, int tiles) { return 16 * nb * update_ld(nb) + 16 * (nb - 1) * 20 + update_sums(nb) + tiles * 16 * update_ld(nb); }
 // tiles of a factor that fit the 160 KB beside V and 6 KB of smaller arrays
@@ -601,14 +444,14 @@ constexpr int update_most_tiles(int nb) { return (154 * 1024 / 8 - update_lds_do
 //   record follow in the same launch.  Otherwise every workgroup leaves its Gram matrix in gram_ws and als_normalise does the rest.
 // Bound by the chain of the pivots, by latency and by instruction fetches.  A row a quad of lanes, V in the threads' registers, four columns
 // a barrier and all of it unrolled (67 KB of code at R = 49 to 64, where the cache holds 64) took, against this: 293 rows at R = 62 59 us
-// and 12 in the second launch -> 26 and 10; 62 rows 59 and 12 -> 21; 96 rows at R = 48 40 and 12 -> 18; 32 rows at R = 24 22 -> 13; 145071 rows at R = 10
-// 91 and 40 -> 26 and 11.  36 drawn CP-ALS calls run 0.886 times as long in the mean.
-template <int NB, bool WHOLE>
-__global__ void __launch_bounds__(64 * update_waves(NB))
+// and 12 in the second launch -> 26 and 10; 62 rows 59 and 12 -> 20; 96 rows at R = 48 40 and 12 -> 17; 32 rows at R = 24 22 -> 12; 145071 rows at R = 10
+// 91 and 40 -> 26 and 11; 100 rows at R = 10, in a kernel for up to 16 columns, 7.7 -> 6.6.
+template <int NB, int WAVES, bool WHOLE>
+__global__ void __launch_bounds__(64 * WAVES)
 als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, double* A, int64_t I, int64_t n_tiles,
            double* gram_ws, double* lambda, double* inner, int* flag, SweepEnd end)
 {
-    constexpr int WAVES = update_waves(NB), THREADS = 64 * WAVES, LD = update_ld(NB), RP = 16 * NB, TILE = 16 * LD;
+    constexpr int THREADS = 64 * WAVES, LD = update_ld(NB), RP = 16 * NB, TILE = 16 * LD;
     constexpr int PAIRS = NB * (NB + 1) / 2;                                 // blocks (p, q), p >= q, of a symmetric matrix
     constexpr int KS = NB == 1 ? 8 : (NB == 2 ? 4 : 1);                      // wavefronts that share a block of the Gram matrix
     constexpr int UNITS = PAIRS * KS, PER = (UNITS + WAVES - 1) / WAVES;
@@ -617,7 +460,7 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     double* const W = P + RP * LD;               // [NB - 1][16][20]
     double* const Sums = W + 16 * (NB - 1) * 20;
     double* const T = Sums + update_sums(NB);    // tiles
-    __shared__ double dinv[RP], nrm[RP], weight[RP], scale[RP], red[WAVES];
+    __shared__ double dinv[RP], nrm[RP], inverse[RP], weight[RP], scale[RP], red[2 * WAVES];
     __shared__ int bad;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, kq = lane >> 4;
@@ -637,9 +480,16 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
     };
     // (every lane loads, from the last row or column where its own does not exist: behind branches each load is waited for)
     const int stop = flag[0];
+    // this thread's entries (r, c) of the blocks on and below the diagonal
+    constexpr int NV = (PAIRS * 256 + THREADS - 1) / THREADS;
+    auto own_entry = [&](int i, auto take) {
+        const int b = (tid >> 8) + i * (THREADS / 256);
+        if (b < PAIRS)
+            take(16 * block_row(b) + ((tid >> 4) & 15), 16 * block_col(b) + (tid & 15), block_row(b) != block_col(b));
+    };
+    double v[NV];                    // of V before it is scaled
     {
-        constexpr int NV = (PAIRS * 256 + THREADS - 1) / THREADS;
-        double v[NV], d = 1.0;
+        double d = 1.0;
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             v[i] = 1.0;
@@ -679,12 +529,8 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
             bad = 0;
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int b = (tid >> 8) + i * (THREADS / 256);
-            const int r = 16 * block_row(b) + ((tid >> 4) & 15), c = 16 * block_col(b) + (tid & 15);
-            if (b < PAIRS)
-                P[r * LD + c] = r < R && c < R ? v[i] * scale[r] * scale[c] : (r == c ? 1.0 : 0.0);
-        }
+        for (int i = 0; i < NV; ++i)
+            own_entry(i, [&](int r, int c, bool) { P[r * LD + c] = r < R && c < R ? v[i] * scale[r] * scale[c] : (r == c ? 1.0 : 0.0); });
     }
     double m[NB][4];                 // the first tile's rows: on their way while V is factorised
     load_rows((int64_t)blockIdx.x * WAVES + wave, m);
@@ -761,28 +607,61 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
         sc[u] = scale[16 * u + n16];
         dv[u] = 16 * u + n16 < R ? dinv[16 * u + n16] : 0.0;
     }
-    double4_t acc[PER];
+    double4_t acc[2][PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i)
-        acc[i] = {0.0, 0.0, 0.0, 0.0};
+        acc[0][i] = acc[1][i] = {0.0, 0.0, 0.0, 0.0};
     // this wavefront's blocks of Y^T Y over the tiles in LDS
     auto gram_of = [&](int tiles) {
+        int p[PER], q[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int unit = wave + i * WAVES;
-            if (unit < UNITS) {
-                const int b = unit / KS, p = 16 * block_row(b), q = 16 * block_col(b);
-                for (int t = unit % KS; t < tiles; t += KS) {
-                    double x[4], z[4];
+            const int b = min(wave + i * WAVES, UNITS - 1) / KS;
+            p[i] = 16 * block_row(b) + n16;
+            q[i] = 16 * block_col(b) + n16;
+        }
+        if (wave >= UNITS)
+            return;
+        const int mine = wave + WAVES < UNITS ? PER : 1;         // blocks of this wavefront
+        auto operands = [&](int t, double (&x)[PER][4], double (&z)[PER][4]) {
+            const double* const Y = T + min(t, tiles - 1) * TILE;
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        x[s] = T[t * TILE + (4 * s + kq) * LD + p + n16];
-                        z[s] = T[t * TILE + (4 * s + kq) * LD + q + n16];
-                    }
+            for (int i = 0; i < PER; ++i)
 #pragma unroll
-                    for (int s = 0; s < 4; ++s)
-                        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s], z[s], acc[i], 0, 0, 0);
+                for (int s = 0; s < 4; ++s) {
+                    x[i][s] = Y[(4 * s + kq) * LD + p[i]];
+                    z[i][s] = Y[(4 * s + kq) * LD + q[i]];
                 }
+        };
+        if constexpr (!WHOLE && NB % 2 == 0) {                   // (short of registers: a tile and a block after the other)
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (i < mine)
+                    for (int t = wave % KS; t < tiles; t += KS)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            const double* const row = T + t * TILE + (4 * s + kq) * LD;
+                            acc[0][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[p[i]], row[q[i]], acc[0][i], 0, 0, 0);
+                        }
+        } else {
+            double x[PER][4], z[PER][4];
+            auto add = [&](const double (&x)[PER][4], const double (&z)[PER][4], double4_t (&to)[PER]) {
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    if (i < mine)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            to[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i][s], z[i][s], to[i], 0, 0, 0);
+            };
+            // (every other tile goes into sums of its own: shorter chains of roundings)
+            operands(wave % KS, x, z);
+            for (int t = wave % KS; t < tiles; t += 2 * KS) {
+                double x1[PER][4], z1[PER][4];
+                operands(t + KS, x1, z1);                        // (under the matrix instructions)
+                add(x, z, acc[0]);
+                operands(t + 2 * KS, x, z);
+                if (t + KS < tiles)
+                    add(x1, z1, acc[1]);
             }
         }
     };
@@ -881,20 +760,23 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
         __syncthreads();
         gram_of((int)n_tiles);
     }
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        acc[0][i] += acc[1][i];
     const bool owner = wave % KS == 0;
     if (KS > 1) {          // a block's sums in the order of their wavefronts
         double* const mine = Sums + (wave / KS * (KS - 1) + wave % KS - 1) * 256 + lane;
         if (!owner && wave < UNITS) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                mine[64 * q] = acc[0][q];
+                mine[64 * q] = acc[0][0][q];
         }
         __syncthreads();
         if (owner && wave < UNITS) {
             for (int i = 0; i < KS - 1; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    acc[0][q] += Sums[(wave / KS * (KS - 1) + i) * 256 + 64 * q + lane];
+                    acc[0][0][q] += Sums[(wave / KS * (KS - 1) + i) * 256 + 64 * q + lane];
         }
     }
     // entry q of this lane's part of a block, (r, c), of the blocks whose sums this wavefront has
@@ -908,7 +790,7 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
                 for (int e = 0; e < 4; ++e) {
                     const int r = 16 * p + 4 * e + kq, c = 16 * q + n16;
                     if (r < R && c < R)
-                        take(r, c, acc[i][e], p != q);
+                        take(r, c, acc[0][i][e], p != q);
                 }
             }
         }
@@ -925,66 +807,71 @@ als_update(double* G, int ndim, int k, int R, const double* __restrict__ M, doub
         });
         return;
     }
-    entries([&](int r, int c, double v, bool) {
-        if (r == c) {
-            const double n = sqrt(v);
-            nrm[r] = n > 0.0 ? n : 1.0;       // a zero column is left alone
-            weight[r] = n;
-            lambda[r] = n;
-        }
-    });
+    entries([&](int r, int c, double v, bool) { P[r * LD + c] = v; });       // (V is no longer needed)
     __syncthreads();
-    double model2 = 0.0;                     // this thread's share of ||X^||^2 (a sweep's last update)
-    entries([&](int r, int c, double v, bool off) {
-        const double gk = v / (nrm[r] * nrm[c]);
-        G[k * RR + r * R + c] = gk;
-        if (off)
-            G[k * RR + c * R + r] = gk;
-        if (end.record) {
-            double t = weight[r] * weight[c] * gk;
-            for (int o = 0; o < ndim; ++o)
-                if (o != k)
-                    t *= G[o * RR + r * R + c];
-            model2 += off ? 2.0 * t : t;
-        }
-    });
+    if (tid < R) {
+        const double l = sqrt(P[tid * LD + tid]), n = l > 0.0 ? l : 1.0;       // a zero column is left alone
+        nrm[tid] = n;
+        inverse[tid] = 1.0 / n;
+        weight[tid] = l;
+        lambda[tid] = l;
+    }
+    __syncthreads();
+    double model2 = 0.0, with_m = 0.0;       // this thread's shares of ||X^||^2 and <X, X^> (a sweep's last update)
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+        own_entry(i, [&](int r, int c, bool off) {
+            if (r < R && c < R) {
+                const double gk = quotient(quotient(P[r * LD + c], nrm[r], inverse[r]), nrm[c], inverse[c]);
+                G[k * RR + r * R + c] = gk;
+                if (off)
+                    G[k * RR + c * R + r] = gk;
+                model2 += (off ? 2.0 : 1.0) * weight[r] * weight[c] * gk * v[i];
+            }
+        });
     constexpr int J = NB == 3 ? 64 : RP;     // threads of a row
     const int j = tid % J;
-    double s = 0.0;
-    if (j < R)
-        for (int i = tid / J; i < (int)I; i += THREADS / J) {
-            const double v = T[(i >> 4) * TILE + (i & 15) * LD + j] / nrm[j];
-            A[(int64_t)i * R + j] = v;
-            if (end.record)
-                s += M[(int64_t)i * R + j] * v;
+    if (j < R) {
+        const double n = nrm[j], in = inverse[j];
+        constexpr int STEP = THREADS / J;
+        for (int i = tid / J; i < (int)I; i += 4 * STEP) {
+            double y[4], f[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int r = min(i + u * STEP, (int)I - 1);
+                y[u] = T[(r >> 4) * TILE + (r & 15) * LD + j];
+                if (end.record)
+                    f[u] = M[(int64_t)r * R + j];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i + u * STEP < (int)I) {
+                    const double a = quotient(y[u], n, in);
+                    A[(int64_t)(i + u * STEP) * R + j] = a;
+                    with_m += f[u] * a;
+                }
         }
+        with_m *= weight[j];
+    }
     if (!end.record)
         return;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1)
+    for (int d = 1; d < 64; d <<= 1) {
         model2 += __shfl_xor(model2, d);
-    if (lane == 0)
-        red[wave] = model2;
-    double* const cols = KS > 1 ? Sums : P;
-    __syncthreads();                         // (the blocks' sums have been added)
-    cols[tid] = s;
-    __syncthreads();
-    double v = 0.0;
-    if (tid < R) {
-        for (int q = tid; q < THREADS; q += J)
-            v += cols[q];
-        v *= weight[tid];
+        with_m += __shfl_xor(with_m, d);
     }
-    __syncthreads();
-    if (tid < R)
-        cols[tid] = v;
+    if (lane == 0) {
+        red[2 * wave] = model2;
+        red[2 * wave + 1] = with_m;
+    }
     __syncthreads();
     if (tid == 0) {
         double fit = 0.0, m2 = 0.0;
-        for (int q = 0; q < R; ++q)
-            fit += cols[q];
-        for (int q = 0; q < WAVES; ++q)
-            m2 += red[q];
+#pragma unroll
+        for (int q = 0; q < WAVES; ++q) {
+            m2 += red[2 * q];
+            fit += red[2 * q + 1];
+        }
         end_sweep(end.scalars, flag, end.record, fit, m2, end.tol, end.first);
     }
 }
@@ -998,7 +885,7 @@ __global__ void __launch_bounds__(512)
 als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, const double* __restrict__ M, int64_t I,
               int64_t rows_per_block, double* Gk, double* lambda, double* inner, const int* flag)
 {
-    __shared__ double red[512], nrm[RP];
+    __shared__ double red[512], nrm[RP], inverse[RP];
     if (flag[0])
         return;
     const int tid = (int)threadIdx.x, j = tid % RP, lane = tid & 63, wave = tid >> 6;
@@ -1011,6 +898,7 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
             v += red[q];
         const double n = sqrt(v);
         nrm[tid] = n > 0.0 ? n : 1.0;       // a zero column is left alone
+        inverse[tid] = 1.0 / nrm[tid];
         if (blockIdx.x == 0 && tid < R)
             lambda[tid] = n;
     }
@@ -1023,7 +911,8 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
             double v = 0.0;
             for (int q = 0; q < 8; ++q)
                 v += red[64 * q + lane];
-            Gk[e] = v / (nrm[e / R] * nrm[e % R]);
+            const int r = e / R, c = e - r * R;
+            Gk[e] = quotient(quotient(v, nrm[r], inverse[r]), nrm[c], inverse[c]);
         }
         __syncthreads();
     }
@@ -1043,7 +932,7 @@ als_normalise(const double* __restrict__ gram_ws, int n_gram, int R, double* A, 
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (i + u * STEP < r1) {
-                    const double v = a[u] / nrm[j];
+                    const double v = quotient(a[u], nrm[j], inverse[j]);
                     A[(i + u * STEP) * R + j] = v;
                     s += m[u] * v;
                 }
@@ -1566,24 +1455,14 @@ void gram_big(const double* A, int64_t I, int R, double* G, hipStream_t st)
 int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I, double* lambda, SweepEnd& end, hipStream_t st)
 {
     double* const Gk = b.G + (int64_t)k * R * R;
-    if (R <= 16 && I <= 256) {
-        const SweepEnd now = k == ndim - 1 ? end : SweepEnd{nullptr, nullptr, 0.0, false};
-        if (I <= 128)
-            hipLaunchKernelGGL((als_update_short<8>), dim3(1), dim3(512), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag, now);
-        else
-            hipLaunchKernelGGL((als_update_short<16>), dim3(1), dim3(1024), 0, st, b.G, ndim, k, R, b.M, A, I, lambda, b.inner, b.flag, now);
-        if (k == ndim - 1)
-            end.record = nullptr;
-        return 1;
-    }
     const SweepEnd now = k == ndim - 1 ? end : SweepEnd{nullptr, nullptr, 0.0, false};
-    auto go = [&](auto nb, auto rp) {
-        constexpr int NB = decltype(nb)::value, RP = decltype(rp)::value, WAVES = update_waves(NB);
+    auto go = [&](auto nb, auto waves, auto rp) {
+        constexpr int NB = decltype(nb)::value, WAVES = decltype(waves)::value, RP = decltype(rp)::value;
         const int64_t tiles = ceil_div(I, 16);
         if (tiles <= update_most_tiles(NB)) {
             const int lds = update_lds_doubles(NB, (int)tiles) * (int)sizeof(double);
-            (void)hipFuncSetAttribute((const void*)als_update<NB, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-            hipLaunchKernelGGL((als_update<NB, true>), dim3(1), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I, tiles,
+            (void)hipFuncSetAttribute((const void*)als_update<NB, WAVES, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipLaunchKernelGGL((als_update<NB, WAVES, true>), dim3(1), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I, tiles,
                                b.gram_ws, lambda, b.inner, b.flag, now);
             if (k == ndim - 1)
                 end.record = nullptr;
@@ -1595,8 +1474,8 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
         const int64_t rows = ceil_div(I, want < kScaleBlocks ? want : kScaleBlocks);
         const int n_scale = (int)ceil_div(I, rows);
         const int lds = update_lds_doubles(NB, WAVES) * (int)sizeof(double);
-        (void)hipFuncSetAttribute((const void*)als_update<NB, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        hipLaunchKernelGGL((als_update<NB, false>), dim3((unsigned)n_gram), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I,
+        (void)hipFuncSetAttribute((const void*)als_update<NB, WAVES, false>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipLaunchKernelGGL((als_update<NB, WAVES, false>), dim3((unsigned)n_gram), dim3(64 * WAVES), lds, st, b.G, ndim, k, R, b.M, A, I,
                            tiles, b.gram_ws, lambda, b.inner, b.flag, SweepEnd{nullptr, nullptr, 0.0, false});
         hipLaunchKernelGGL((als_normalise<RP>), dim3((unsigned)n_scale), dim3(512), 0, st, b.gram_ws, n_gram, R, A, b.M, I,
                            rows, Gk, lambda, k == ndim - 1 ? b.inner : nullptr, b.flag);
@@ -1604,12 +1483,13 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
     };
     using std::integral_constant;
     if (R <= 16)
-        return go(integral_constant<int, 1>(), integral_constant<int, 16>());
+        return I <= 128 ? go(integral_constant<int, 1>(), integral_constant<int, 8>(), integral_constant<int, 16>())
+                        : go(integral_constant<int, 1>(), integral_constant<int, 16>(), integral_constant<int, 16>());
     if (R <= 32)
-        return go(integral_constant<int, 2>(), integral_constant<int, 32>());
+        return go(integral_constant<int, 2>(), integral_constant<int, 16>(), integral_constant<int, 32>());
     if (R <= 48)
-        return go(integral_constant<int, 3>(), integral_constant<int, 64>());
-    return go(integral_constant<int, 4>(), integral_constant<int, 64>());
+        return go(integral_constant<int, 3>(), integral_constant<int, 8>(), integral_constant<int, 64>());
+    return go(integral_constant<int, 4>(), integral_constant<int, 8>(), integral_constant<int, 64>());
 }
 
 // Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns from rank 320 on, below it four, since a
