@@ -263,34 +263,6 @@ __device__ __forceinline__ double reciprocal(double d)
     return r;
 }
 
-// The value of lane 4 * (lane / 4) + p in all four lanes of the quad.
-__device__ __forceinline__ double quad_value(double v, int p)
-{
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    switch (p) {      // p is a constant wherever this is called, after unrolling
-    case 0: lo = __builtin_amdgcn_mov_dpp(lo, 0x00, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x00, 0xf, 0xf, true); break;
-    case 1: lo = __builtin_amdgcn_mov_dpp(lo, 0x55, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x55, 0xf, 0xf, true); break;
-    case 2: lo = __builtin_amdgcn_mov_dpp(lo, 0xaa, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0xaa, 0xf, 0xf, true); break;
-    default: lo = __builtin_amdgcn_mov_dpp(lo, 0xff, 0xf, 0xf, true); hi = __builtin_amdgcn_mov_dpp(hi, 0xff, 0xf, 0xf, true); break;
-    }
-    return __hiloint2double(hi, lo);
-}
-
-// Triangular solves of 16 rows by one wavefront: the four lanes of a quad share a row, lane `part` holds its
-// unknowns 4 q + part.  An unknown that is final goes to the quad by DPP and every lane subtracts its
-// multiples of it (independent FMAs; L from LDS in the layout of factorise(), zeros where it has no entry).
-template <int RP> __device__ __forceinline__ void solve_forward(double (&y)[RP / 4], const double* Lf, int R, int part)
-{
-#pragma unroll
-    for (int a = 0; a < RP; ++a)
-        if (a < R) {
-            const double ya = quad_value(y[a >> 2], a & 3);
-#pragma unroll
-            for (int q = a >> 2; q < RP / 4; ++q)
-                y[q] -= Lf[a * (RP + 1) + 4 * q + part] * ya;
-        }
-}
-
 // The value of lane n of each 16 lanes in all of them, and acc += that value of a times b in one instruction (the compiler makes
 // a copy, a wait and a move of it; the two wait states are those between a register's write and its use by DPP).
 template <int n> __device__ __forceinline__ double row_value(double v) { return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + n, 0xf, 0xf, true); }
@@ -1033,8 +1005,8 @@ __global__ void __launch_bounds__(512) gram_tiled(const double* __restrict__ A, 
 // columns that follow on the matrix cores, the next diagonal block first, which the first wavefront then factorises
 // while the others go on.  At the end the tile's rows and columns are multiplied and subtracted from the tile: no workgroup waits for
 // another, and a step is one launch.  The chain of the columns bounds it (16 columns
-// take 3 us: 1.5 for their reciprocals and row operations, the rest for the exchanges): 24 us a launch, eight at R = 500 (one a 32 columns, a
-// column a barrier: sixteen of 14.4 us).
+// take 2.6 us: 1.2 for their reciprocals and row operations, the rest for the exchanges): 22.3 us a launch, eight at R = 500 (25.3 with the reciprocals
+// behind the row operations and a row a quad of lanes in the solves).
 // The block column of V is only read; the tiles on the diagonal write their rows of -L (which is what the solves add) and the same
 // above the diagonal, transposed, so that both solves read whole lines; workgroup (0, 0) the block's own rows and dinv = 1 / D.
 constexpr int kPB = 64;
@@ -1045,38 +1017,39 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
     extern __shared__ double P[];               // [3 kPB][LD]: L D of the diagonal block, of the tile's rows and of its columns
     __shared__ double Lg[2][16 * 17], dinv[kPB];
     __shared__ int bad;
-    constexpr int LD = kPB + 1;
+    constexpr int LD = kPB + 1, WAVES = 8;
     if (blockIdx.x > blockIdx.y)
         return;
     const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n16 = lane & 15, kq = lane >> 4, part = lane & 3;
+    const int n16 = lane & 15, kq = lane >> 4;
     const int nb = R - j0 < kPB ? R - j0 : kPB, j1 = j0 + nb;
     const int ng = (nb + 15) / 16;
     const bool trailing = j1 < R;               // then nb == 64
     auto v_row = [&](int r) { return r < kPB ? j0 + r : j1 + kPB * (int)(r < 2 * kPB ? blockIdx.y : blockIdx.x) + (r & (kPB - 1)); };
     {
         // (every lane loads, from the last row or column where its own does not exist: behind branches each load would be waited for)
-        double x[24];
+        double x[192 / WAVES];
         const int c = lane, cl = c < nb ? c : nb - 1;
 #pragma unroll
-        for (int i = 0; i < 24; ++i) {
-            const int vi = v_row(wave + 8 * i);
+        for (int i = 0; i < 192 / WAVES; ++i) {
+            const int vi = v_row(wave + WAVES * i);
             x[i] = V[(int64_t)(vi < R ? vi : R - 1) * R + j0 + cl];
         }
 #pragma unroll
-        for (int i = 0; i < 24; ++i) {
-            const int r = wave + 8 * i;
+        for (int i = 0; i < 192 / WAVES; ++i) {
+            const int r = wave + WAVES * i;
             P[r * LD + c] = c < nb && v_row(r) < R && (r >= kPB || (r >= c && r < nb)) ? x[i] : 0.0;
         }
     }
-    // this wavefront's 16 x 16 pieces of the tile: row wave / 4 + 2 t, column wave % 4 (none above the diagonal)
-    double4_t v[2];
-    int vr[2];
+    // this wavefront's 16 x 16 pieces of the tile: row wave / 4 + WAVES / 4 t, column wave % 4 (none above the diagonal)
+    constexpr int NT = 16 / WAVES;
+    double4_t v[NT];
+    int vr[NT];
     const int vc = j1 + kPB * (int)blockIdx.x + 16 * (wave & 3);
-    bool has[2];
+    bool has[NT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        vr[t] = j1 + kPB * (int)blockIdx.y + 16 * ((wave >> 2) + 2 * t);
+    for (int t = 0; t < NT; ++t) {
+        vr[t] = j1 + kPB * (int)blockIdx.y + 16 * ((wave >> 2) + WAVES / 4 * t);
         has[t] = trailing && vr[t] >= vc && vr[t] < R;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1088,15 +1061,18 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
         return;
     // rows [r0, r0 + 16) of P solved against the diagonal block of columns 16 g ..
     auto solve = [&](int r0, int g) {
-        double y[4];
-        double* const row = P + (r0 + (lane >> 2)) * LD + 16 * g + part;
+        double y[4], f[16];
+        double* const at = P + (r0 + kq) * LD + 16 * g + n16;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            y[q] = row[4 * q];
-        solve_forward<16>(y, Lg[g & 1], 16, part);
+            y[q] = at[4 * q * LD];
+#pragma unroll
+        for (int a = 0; a < 16; ++a)
+            f[a] = Lg[g & 1][a * 17 + n16];
+        substitute16<true>(y, f);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            row[4 * q] = y[q];
+            at[4 * q * LD] = y[q];
     };
     // piece (rows r0 .., columns 16 u ..) of P minus the product of its rows' and the column rows' solved columns 16 g ..
     auto update = [&](int r0, int u, int g) {
@@ -1124,7 +1100,7 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
         if (kq == 0) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                Lg[g & 1][n16 * 17 + i] = i > n16 ? a[i] * rd : 0.0;
+                Lg[g & 1][n16 * 17 + i] = i > n16 ? -a[i] * rd : 0.0;
                 if (i > n16)
                     P[(16 * g + i) * LD + 16 * g + n16] = a[i];
             }
@@ -1144,10 +1120,10 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
             int n = 0;
             for (int t = g + 1; t < ng; ++t)
                 for (int u = g; u <= t; ++u)
-                    if (n++ % 7 == wave - 1)
+                    if (n++ % (WAVES - 1) == wave - 1)
                         update(16 * t, u, g - 1);
             if (trailing)
-                for (int t = wave; t < 9; t += 7) {
+                for (int t = wave; t < 9; t += WAVES - 1) {
                     solve(kPB + 16 * (t - 1), g - 1);
                     for (int u = g; u < 4; ++u)
                         update(kPB + 16 * (t - 1), u, g - 1);
@@ -1164,7 +1140,7 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
         return;
     }
     if (blockIdx.x == 0 && blockIdx.y == 0) {
-        for (int r = wave; r < nb; r += 8)
+        for (int r = wave; r < nb; r += WAVES)
             if (lane != r && lane < nb)
                 L[(int64_t)(j0 + r) * ldL + j0 + lane] = lane < r ? -P[r * LD + lane] * dinv[lane] : -P[lane * LD + r] * dinv[r];
         if (tid < nb)
@@ -1174,7 +1150,7 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
         return;
     if (blockIdx.x == blockIdx.y) {
         const int row0 = v_row(2 * kPB);
-        for (int r = wave; r < kPB; r += 8) {
+        for (int r = wave; r < kPB; r += WAVES) {
             if (row0 + r < R)
                 L[(int64_t)(row0 + r) * ldL + j0 + lane] = -P[(2 * kPB + r) * LD + lane] * dinv[lane];
             if (row0 + lane < R)
@@ -1183,9 +1159,9 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
     }
     const double* const wb = P + (2 * kPB + 16 * (wave & 3) + n16) * LD + kq;
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < NT; ++t)
         if (has[t]) {
-            const double* const wa = P + (kPB + 16 * ((wave >> 2) + 2 * t) + n16) * LD + kq;
+            const double* const wa = P + (kPB + 16 * ((wave >> 2) + WAVES / 4 * t) + n16) * LD + kq;
 #pragma unroll
             for (int k = 0; k < kPB; k += 4)
                 v[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-wa[k], wb[k] * dinv[k + kq], v[t], 0, 0, 0);
