@@ -1330,6 +1330,159 @@ solve_rows_blocked(const double* __restrict__ L, int ldL, const double* __restri
             A[(r0 + r) * R + c] = get(r, c) * S[c];
 }
 
+// The same for ranks up to 32 WAVES: a wavefront keeps the 16 rows' unknowns of two blocks of 16 (wave and wave + WAVES) in the accumulators of the
+// matrix cores.  A block that is final goes to the others through LDS; the wavefront that has the next one updates and solves it
+// (substitute16) before its other block, so a step of the chain is four matrix instructions, a substitution and a barrier.  -L is symmetric
+// as it lies in memory, so both sweeps read the same lines, two steps ahead.
+// Bound by that chain, 2 R / 16 steps (0.7 us each with four wavefronts, 1.4 with sixteen), and by the matrix instructions of few compute
+// units.  With the unknowns in LDS and blocks of 32, solve_rows_blocked, against this: 129 rows at R = 500 106 -> 100 us, 300 rows at
+// R = 200 37 -> 30, 240 rows at R = 82 17.8 -> 15.4, 4736 at R = 87 21.9 -> 19.2.
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
+solve_rows(const double* __restrict__ L, int ldL, const double* __restrict__ dinv, const double* __restrict__ S, int R,
+           const double* __restrict__ M, double* A, int64_t I, const int* flag)
+{
+    extern __shared__ double diag[];             // [block][16][17]: row a of the diagonal blocks of -L
+    __shared__ double Yb[2][16 * 20];            // a final block, rows of four doubles more than the columns
+    if (flag[0])
+        return;
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int n16 = lane & 15, kq = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * 16;
+    const int nb = (R + 15) / 16;
+    // rows 16 b + 4 s + kq of -L, columns of this wavefront's blocks (from bases in scalar registers)
+    const uint32_t lane_off = (uint32_t)(kq * ldL + n16) * (uint32_t)sizeof(double);
+    auto load = [&](int b, double (&l)[2][4]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const char* const src = (const char*)(L + (16 * b + 4 * s) * ldL + 16 * min(wave + WAVES * i, nb - 1));
+                l[i][s] = *(const double*)(src + lane_off);
+            }
+    };
+    double y[2][4], l[3][2][4];
+    load(0, l[0]);
+    load(min(1, nb - 1), l[1]);
+    for (int t = (int)threadIdx.x; t < 256 * nb; t += 64 * WAVES) {
+        const int b = t >> 8, r = (t >> 4) & 15, c = t & 15;
+        diag[(b * 16 + r) * 17 + c] = r != c ? L[(int64_t)(16 * b + r) * ldL + 16 * b + c] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 16 * (wave + WAVES * i) + n16;
+        const double sc = c < R ? S[c] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t r = r0 + 4 * q + kq;
+            const double m = M[(r < I ? r : I - 1) * R + min(c, R - 1)];
+            y[i][q] = r < I && c < R ? m * sc : 0.0;
+        }
+    }
+    auto sweep = [&](auto forward) {
+        constexpr bool F = decltype(forward)::value;
+        double f[16];
+        auto entries = [&](int b) {                  // of block b's own part of -L
+#pragma unroll
+            for (int a = 0; a < 16; ++a) {
+                const double t = diag[(b * 16 + a) * 17 + n16];
+                f[a] = (F ? n16 > a : n16 < a) ? t : 0.0;
+            }
+        };
+        // block i of this wavefront is final but for itself: solve it and pass it on
+        auto finish = [&](auto I_) {
+            constexpr int i = decltype(I_)::value;
+            const int b = wave + WAVES * i;
+            if (WAVES == 16)                         // (no registers for them before)
+                entries(b);
+            substitute16<F>(y[i], f);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                Yb[b & 1][(4 * q + kq) * 20 + n16] = y[i][q];
+        };
+        auto with = [&](int i, auto take) {      // (the block as a constant)
+            if (i == 0)
+                take(std::integral_constant<int, 0>());
+            else
+                take(std::integral_constant<int, 1>());
+        };
+        auto step = [&](int b, const double (&now)[2][4], double (&ahead)[2][4]) {
+            __syncthreads();
+            double a[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                a[s] = Yb[b & 1][n16 * 20 + 4 * s + kq];
+            load(F ? min(b + 2, nb - 1) : max(b - 2, 0), ahead);     // (always: behind a branch all loads would be waited for)
+            const int next = F ? b + 1 : b - 1;
+            const int mine = next >= 0 && next < nb && next % WAVES == wave ? next / WAVES : -1;     // which of its blocks comes next
+            auto update = [&](auto I_) {
+                constexpr int i = decltype(I_)::value;
+                double4_t c = {y[i][0], y[i][1], y[i][2], y[i][3]};
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], now[i][s], c, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    y[i][q] = c[q];
+            };
+            if (mine >= 0) {
+                __builtin_amdgcn_s_setprio(3);       // (the others wait for this)
+                with(mine, update);
+                with(mine, finish);
+                __builtin_amdgcn_s_setprio(0);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int u = wave + WAVES * i;
+                if (i != mine && u < nb && (F ? u > b : u < b))
+                    with(i, update);
+            }
+            const int soon = F ? b + 2 : b - 2;
+            if (WAVES < 16 && soon >= 0 && soon < nb && soon % WAVES == wave)
+                entries(soon);
+        };
+        const int first = F ? 0 : nb - 1, second = F ? min(1, nb - 1) : max(nb - 2, 0);
+        if (first % WAVES == wave) {
+            entries(first);
+            with(first / WAVES, finish);
+        }
+        if (WAVES < 16 && second != first && second % WAVES == wave)
+            entries(second);
+        for (int n = 0; n < nb; n += 3) {
+            step(F ? n : nb - 1 - n, l[0], l[2]);
+            if (n + 1 < nb)
+                step(F ? n + 1 : nb - 2 - n, l[1], l[0]);
+            if (n + 2 < nb)
+                step(F ? n + 2 : nb - 3 - n, l[2], l[1]);
+        }
+    };
+    __syncthreads();                             // (the diagonal blocks)
+    sweep(std::true_type());
+    __syncthreads();
+    load(nb - 1, l[0]);
+    load(max(nb - 2, 0), l[1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 16 * (wave + WAVES * i) + n16;
+        const double d = c < R ? dinv[c] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            y[i][q] *= d;
+    }
+    sweep(std::false_type());
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 16 * (wave + WAVES * i) + n16;
+        const double sc = c < R ? S[c] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t r = r0 + 4 * q + kq;
+            if (r < I && c < R)
+                A[r * R + c] = y[i][q] * sc;
+        }
+    }
+}
+
 // Columns of A (n entries) divided by their norms = the roots of the diagonal of the Gram matrix S, and the
 // normalised Gram matrix.  One thread per entry of A, then of S.
 __global__ void __launch_bounds__(256)
@@ -1468,17 +1621,25 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
     return go(integral_constant<int, 4>(), integral_constant<int, 8>(), integral_constant<int, 64>());
 }
 
-// Rows of A = M V^{-1} above rank 64.  Few rows: sixteen wavefronts share a workgroup's columns from rank 320 on, below it four, since a
-// block has no more than a few pieces for each and the barriers of sixteen cost more (a sweep over 16 x 495 x 217: R = 66 352 against
-// 342 us, 128 400 and 383, 256 675 and 647, 384 958 and 957, 512 1264 and 1316).  Many rows: four, so
-// that several workgroups fit a compute unit.  Above rank 1024 the slab does not fit the 160 KB of LDS.
+// Rows of A = M V^{-1} above rank 64.  Up to rank 512 the unknowns stay in registers; not where eight and sixteen wavefronts, one workgroup a
+// compute unit, would take a second round that two to four of the other kernel's four wavefronts do not need (20000 rows at R = 130 101
+// against 69 us, 300 297 and 201; 500, where its slab leaves one of them too, 531 and 607).  Beyond, few rows: sixteen wavefronts share a
+// workgroup's columns; many rows: four.  Above rank 1024 the slab does not fit the 160 KB of LDS.
 void solve_big(const double* L, int ldL, const double* dinv, const double* S, int R, const double* M, double* A, int64_t I, const int* flag, hipStream_t st)
 {
     const unsigned grid = (unsigned)ceil_div(I, 16);
     const size_t lds = (size_t)16 * (ceil_div(R, kNB) * kNB + 1) * sizeof(double);
-    if (R > 1024) {
+    if (R <= 128 || (R <= 512 && (grid <= 256 || R > 448))) {
+        const int diag = (int)ceil_div(R, 16) * 16 * 17 * (int)sizeof(double);
+        auto go = [&](auto waves) {
+            constexpr int W = decltype(waves)::value;
+            (void)hipFuncSetAttribute((const void*)solve_rows<W>, hipFuncAttributeMaxDynamicSharedMemorySize, diag);
+            hipLaunchKernelGGL((solve_rows<W>), dim3(grid), dim3(64 * W), diag, st, L, ldL, dinv, S, R, M, A, I, flag);
+        };
+        R <= 128 ? go(std::integral_constant<int, 4>()) : R <= 256 ? go(std::integral_constant<int, 8>()) : go(std::integral_constant<int, 16>());
+    } else if (R > 1024) {
         hipLaunchKernelGGL((solve_rows_blocked<16, false>), dim3(grid), dim3(1024), 0, st, L, ldL, dinv, S, R, M, A, I, flag);
-    } else if (grid <= 512 && R > 320) {
+    } else if (grid <= 512) {
         (void)hipFuncSetAttribute((const void*)solve_rows_blocked<16, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL((solve_rows_blocked<16, true>), dim3(grid), dim3(1024), lds, st, L, ldL, dinv, S, R, M, A, I, flag);
     } else {
