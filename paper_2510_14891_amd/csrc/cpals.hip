@@ -1174,6 +1174,139 @@ factorise_panel(double* V, int R, int j0, double* L, int ldL, double* dinv_out, 
         }
 }
 
+// The whole factorisation up to rank 128 in one workgroup: V = S (Hadamard product of the Gram matrices of all modes but `skip`) S lies in LDS, 16
+// columns at a time as in als_update: the first wavefront factorises the diagonal block, one wavefront for 16 rows solves those below
+// against it, the others take the products off the pieces to the right while the first goes on with the next block.  Leaves what
+// hadamard_grams and factorise_panel leave: -L, symmetric with zeros in rows and columns from R on, dinv = 1 / D and the scales S.
+// Bound by the chain of the blocks, 2.5 us each.
+constexpr int kLdsRank = 128;
+constexpr int lds_factor_bytes(int nb) { return (16 * nb * (16 * nb + 4) + 16 * (nb - 1) * 20) * (int)sizeof(double); }
+__global__ void __launch_bounds__(1024)
+factorise_lds(const double* __restrict__ G, int ndim, int R, int skip, double* L, int ldL, double* dinv_out, double* S, int* flag)
+{
+    extern __shared__ double P[];                // [16 nb][16 nb + 4], then one step's rows of L D, [nb - 1][16][20]
+    __shared__ double dinv[kLdsRank], scale[kLdsRank];
+    __shared__ int bad;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kq = lane >> 4, nb = (R + 15) / 16, LD = 16 * nb + 4;
+    const int64_t RR = (int64_t)R * R;
+    double* const W = P + 16 * nb * LD;
+    if (failed_before(flag))
+        return;
+    if (tid < kLdsRank) {
+        double d = 1.0;
+        for (int m = 0; m < ndim; ++m)
+            if (m != skip)
+                d *= G[m * RR + (int64_t)min(tid, R - 1) * (R + 1)];
+        scale[tid] = tid < R ? unit_scale(d) : 1.0;
+    }
+    if (tid == 0)
+        bad = 0;
+    __syncthreads();
+    // a wavefront takes rows r0 + 16 u, up to the end of their diagonal block
+    for (int r0 = wave; r0 < 16 * nb; r0 += 64) {
+        double v[4][2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            v[u][0] = v[u][1] = 1.0;
+        for (int m = 0; m < ndim; ++m) {
+            if (m == skip)
+                continue;
+            double x[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    x[u][h] = G[m * RR + (int64_t)min(r0 + 16 * u, R - 1) * R + min(lane + 64 * h, R - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    v[u][h] *= x[u][h];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = r0 + 16 * u, c = lane + 64 * h;
+                if (r < 16 * nb && c < (r | 15) + 1)
+                    P[r * LD + c] = r < R && c < R ? v[u][h] * scale[r] * scale[c] : (r == c ? 1.0 : 0.0);
+            }
+    }
+    __syncthreads();
+    // piece (t, u) of V minus the product of what the columns of step g - 1 have become: (-L)(t, g - 1) times (L D)(u, g - 1)^T
+    auto update_piece = [&](int t, int u, int g) {
+        double4_t acc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            acc[q] = P[(16 * t + 4 * q + kq) * LD + 16 * u + n16];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(16 * t + n16) * LD + 16 * (g - 1) + 4 * s + kq], W[((u - 1) * 16 + n16) * 20 + 4 * s + kq], acc, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            P[(16 * t + 4 * q + kq) * LD + 16 * u + n16] = acc[q];
+    };
+    for (int g = 0; g < nb; ++g) {
+        if (wave == 0) {
+            if (g > 0)
+                update_piece(g, g, g);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            double a[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                a[i] = P[(16 * g + (i > n16 ? i : n16)) * LD + 16 * g + (i > n16 ? n16 : i)];
+            if (!factorise16(a, dinv + 16 * g) && lane == 0)
+                bad = 1;
+            const double rd = dinv[16 * g + n16];
+            if (kq == 0) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    P[(16 * g + i) * LD + 16 * g + n16] = i > n16 ? -a[i] * rd : 0.0;
+            }
+        } else if (g > 0) {
+            int n = 1;
+            for (int t = g + 1; t < nb; ++t)
+                for (int u = g; u <= t; ++u) {
+                    if (n == wave)
+                        update_piece(t, u, g);
+                    n = n == 15 ? 1 : n + 1;
+                }
+        }
+        __syncthreads();
+        if (wave < nb - 1 - g) {
+            const int t = g + 1 + wave;
+            double y[4], f[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                y[q] = P[(16 * t + 4 * q + kq) * LD + 16 * g + n16];
+#pragma unroll
+            for (int a = 0; a < 16; ++a)
+                f[a] = P[(16 * g + n16) * LD + 16 * g + a];
+            substitute16<true>(y, f);
+            const double rd = dinv[16 * g + n16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                W[((t - 1) * 16 + 4 * q + kq) * 20 + n16] = y[q];
+                P[(16 * t + 4 * q + kq) * LD + 16 * g + n16] = -y[q] * rd;
+            }
+        }
+        __syncthreads();
+    }
+    if (bad) {
+        if (tid == 0)
+            flag[0] = kFailed;
+        return;
+    }
+    for (int r = wave; r < ldL; r += 16)
+        for (int c = lane; c < ldL; c += 64)
+            L[(int64_t)r * ldL + c] = r < R && c < R && r != c ? P[max(r, c) * LD + min(r, c)] : 0.0;
+    if (tid < R) {
+        dinv_out[tid] = dinv[tid];
+        S[tid] = scale[tid];
+    }
+}
+
 // Rows of A = M V^{-1} = M S (L D L^T)^{-1} S.  A workgroup owns 16 rows and takes them through the whole forward and
 // backward solve, a block of 32 unknowns at a time.  Four wavefronts solve four rows each against the diagonal block (16
 // lanes hold a row's unknowns, and one that is final goes to them by DPP) while the others wait: an fp64 MFMA keeps its SIMD for 64
@@ -1619,6 +1752,25 @@ int update_small(const Buffers& b, int ndim, int k, int R, double* A, int64_t I,
     if (R <= 48)
         return go(integral_constant<int, 3>(), integral_constant<int, 8>(), integral_constant<int, 64>());
     return go(integral_constant<int, 4>(), integral_constant<int, 8>(), integral_constant<int, 64>());
+}
+
+// -L, 1 / D and the scales of V for the update of factor k above rank 64.  Up to rank 128 in one workgroup: 24 us at R = 82, 29 at 99 and 34 at 128,
+// where the product and two panels in launches of their own took 36, 37 and 49.
+void factor_big(const Buffers& b, int ndim, int k, int R, int ldL, hipStream_t st)
+{
+    double* const dinv = b.L + (size_t)ldL * ldL;
+    if (R <= kLdsRank) {
+        const int lds = lds_factor_bytes((int)ceil_div(R, 16));
+        (void)hipFuncSetAttribute((const void*)factorise_lds, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipLaunchKernelGGL(factorise_lds, dim3(1), dim3(1024), lds, st, b.G, ndim, R, k, b.L, ldL, dinv, dinv + R, b.flag);
+        return;
+    }
+    hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(ldL * ldL, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V, dinv + R, b.L, ldL);
+    (void)hipFuncSetAttribute((const void*)factorise_panel, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds);
+    for (int j0 = 0; j0 < R; j0 += kPB) {
+        const unsigned nt = R - j0 > kPB ? (unsigned)ceil_div(R - j0 - kPB, kPB) : 1u;
+        hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(512), kPanelLds, st, b.V, R, j0, b.L, ldL, dinv, b.flag);
+    }
 }
 
 // Rows of A = M V^{-1} above rank 64.  Up to rank 512 the unknowns stay in registers; not where eight and sixteen wavefronts, one workgroup a
@@ -2124,13 +2276,7 @@ int cpals_run(int ndim, const int64_t* dims, const double* X, double* const* fac
             n_inner = update_small(b, ndim, k, R, factors[k], I, lambda, end, st);
         } else {
             double* const dinv = b.L + (size_t)ldL * ldL;
-            hipLaunchKernelGGL(hadamard_grams, dim3((unsigned)ceil_div(ldL * ldL, 256)), dim3(256), 0, st, b.G, ndim, R, k, b.V,
-                               dinv + R, b.L, ldL);
-            (void)hipFuncSetAttribute((const void*)factorise_panel, hipFuncAttributeMaxDynamicSharedMemorySize, kPanelLds);
-            for (int j0 = 0; j0 < R; j0 += kPB) {
-                const unsigned nt = R - j0 > kPB ? (unsigned)ceil_div(R - j0 - kPB, kPB) : 1u;
-                hipLaunchKernelGGL(factorise_panel, dim3(nt, nt), dim3(512), kPanelLds, st, b.V, R, j0, b.L, ldL, dinv, b.flag);
-            }
+            factor_big(b, ndim, k, R, ldL, st);
             solve_big(b.L, ldL, dinv, dinv + R, R, b.M, factors[k], I, b.flag, st);
             gram_big(factors[k], I, R, b.V, st);
             const int64_t want = ceil_div(I * R + RR, 1024);
