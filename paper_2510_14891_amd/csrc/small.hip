@@ -11,10 +11,19 @@
 // adds them in a second launch (two launches instead of three).
 //
 // Columns are decoded by every lane for itself (a multiply-high per mode above the lowest): that hides
-// behind the loads, and short modes need no fused product matrices.  fp64, us a call, before and now: 64^3 at R = 16 15.7 /
+// behind the loads, and short modes need no fused product matrices.  fp64, us a call, general plan and this kernel: 64^3 at R = 16 15.7 /
 // 8.4 / 8.4 -> 8.3 / 5.1 / 5.0; 100 x 80 x 60 at R = 10, CP-ALS, 12 sweeps 1482 -> 1190; 4947 calls that take it 0.55 times as
 // long in the mean.  mttkrp.hip says where the line between the two paths lies.
+//
+// A wavefront has one or two batches of loads, so each wait counts: a remainder runs as a batch of its own length (the padding of a
+// full one cost loads and MFMAs: 64^3 5.4 -> 4.6 us), all column modes' loads are under way before the first product (8^5, third
+// mode 6.7 -> 3.7: a branch per mode had made each load wait for the one before), consecutive rows share a load (4.6 -> 4.2), the
+// weights come after the sweep, when their registers are free (64^3 at R = 32 7.8 -> 5.6, 128 x 128 x 64 at R = 64 12.9 -> 7.9 where
+// registers had been spilled), the wavefronts' sums are read eight at a time (100 x 80 x 60, first mode 5.6 -> 4.2 with the
+// remainders).
 #include "mttkrp_small.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -33,8 +42,14 @@ template <> struct Mfma<float> {
     static __device__ __forceinline__ int row(int lane, int q) { return 4 * (lane >> 4) + q; }
 };
 
-// steps (of four columns) whose loads are in flight together
-template <int RB, int JB> constexpr int kSteps = RB * JB <= 2 ? 8 : 4;
+// steps (of four columns) whose loads are in flight together: fewer where those of three or four column modes, the accumulators
+// and the weights would pass the 128 registers of a lane
+template <typename T, int RB, int JB, int NM> constexpr int steps_in_flight()
+{
+    constexpr int words = (int)sizeof(T) / 4, most = RB * JB <= 2 ? 8 : 4;
+    constexpr int held = words * 4 * RB * JB, step = words * (RB + (NM > 0 ? NM : 3) * JB);
+    return NM != 1 && held + most * step > 115 ? most / 2 : most;
+}
 
 // Output columns of a lane, as in the streaming kernel: JB consecutive ones, so that one wide load (two for more
 // than 16 bytes) fetches its entries of a factor row.  A group that would cross R is moved back to end at R and
@@ -45,14 +60,14 @@ template <typename T, int N> struct Lay {
     static constexpr int n1 = N - n0;
 };
 
-// NM: column modes (1 or 2), 0: any number.
+// NM: column modes (1 to 4: their loads are all under way before the first product is formed), 0: none or more.
 template <typename T, int RB, int JB, int NM, bool FIRST>
 __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const SmallArgs<T> p)
 {
     typedef Mfma<T> MF;
     typedef typename MF::acc_t acc_t;
     typedef Lay<T, JB> LC;
-    constexpr int U = kSteps<RB, JB>;
+    constexpr int U = steps_in_flight<T, RB, JB, NM>();
     extern __shared__ double red[];
     const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n_waves = (int)(blockDim.x >> 6);
@@ -79,64 +94,90 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
     const T* const xb = FIRST ? p.X : p.X + (int64_t)blockIdx.x * p.sx_batch;
     const int g0 = (int)blockIdx.z * p.cols_per_group, g1 = min(p.C, g0 + p.cols_per_group);   // this group's columns
 
+    // Rows of MFMA index i: RB consecutive ones (one load), block r holding the r-th.  Rows that would pass I_0 are moved back
+    // to end there; those that another index holds as well are dropped.
+    auto first_row = [&](int row0, int i) { return min(row0 + RB * i, p.I0 - RB); };
     acc_t acc[RB][JB];
     // acc = X(rows row0 .., columns [c0, c1)) * Khatri-Rao rows.  Lanes past c1 enter zeros for both operands (exact
-    // zeros whatever the tensor holds), rows past I_0 repeat the last one and are dropped by the caller.
+    // zeros whatever the tensor holds).
     auto sweep = [&](int row0, int c0, int c1) {
 #pragma unroll
         for (int r = 0; r < RB; ++r)
 #pragma unroll
             for (int jb = 0; jb < JB; ++jb)
                 acc[r][jb] = (acc_t)(0);
-        uint32_t row[RB];
+        const uint32_t row = (uint32_t)first_row(row0, il);
+        auto batch = [&](int c, auto count, bool masked) {
+            constexpr int N = decltype(count)::value;
+            T xs[N][RB], bs[N][JB];
+            uint32_t rem[N], off[N];
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-            row[r] = (uint32_t)min(row0 + 16 * r + il, p.I0 - 1);
-        auto batch = [&](int c, bool masked) {
-            T xs[U][RB], bs[U][JB];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                uint32_t rem = (uint32_t)(c + 4 * u + kk);
+            for (int u = 0; u < N; ++u) {
+                rem[u] = (uint32_t)(c + 4 * u + kk);
                 if (masked)
-                    rem = min(rem, (uint32_t)(c1 - 1));
-                uint32_t off = 0;
-                auto mode = [&](int m, bool last, bool first) {
-                    uint32_t i = rem;
-                    if (!last && p.dim[m] > 1) {
-                        const uint32_t q = __umulhi(rem, p.magic[m]) >> p.shift[m];
-                        i = rem - q * (uint32_t)p.dim[m];
-                        rem = q;
-                    } else if (!last) {
-                        i = 0;
-                    }
-                    off += i * (uint32_t)p.sx[m];
-                    T v[JB];
-                    load_cols(p.A[m], i * (uint32_t)p.ld[m], v);
+                    rem[u] = min(rem[u], (uint32_t)(c1 - 1));
+                off[u] = 0;
+            }
+            // index of mode m in step u's column, and its entries of the factor
+            auto mode = [&](int m, int u, bool last, T (&v)[JB]) {
+                uint32_t i = rem[u];
+                if (!last) {
+                    const uint32_t q = p.dim[m] > 1 ? __umulhi(i, p.magic[m]) >> p.shift[m] : i;
+                    i -= q * (uint32_t)p.dim[m];
+                    rem[u] = q;
+                }
+                off[u] += i * (uint32_t)p.sx[m];
+                load_cols(p.A[m], i * (uint32_t)p.ld[m], v);
+            };
+            auto tensor = [&](int u) {
+                const T* const x = xb + (off[u] + row);
 #pragma unroll
-                    for (int jb = 0; jb < JB; ++jb)
-                        bs[u][jb] = first ? v[jb] : bs[u][jb] * v[jb];
-                };
-                if constexpr (NM == 1) {
-                    mode(0, true, true);
-                } else if constexpr (NM == 2) {
-                    mode(0, false, true);
-                    mode(1, true, false);
-                } else {
+                for (int r = 0; r < RB; ++r)
+                    xs[u][r] = x[r];
+            };
+            if constexpr (NM > 0) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) {
+                        T v[JB];
+                        mode(m, u, m == NM - 1, v);
+#pragma unroll
+                        for (int jb = 0; jb < JB; ++jb)
+                            bs[u][jb] = m == 0 ? v[jb] : bs[u][jb] * v[jb];
+                    }
+                    tensor(u);
+                }
+            } else {
+                // a mode at a time, all its loads before the first product (no mode at all: columns of ones)
+#pragma unroll
+                for (int u = 0; u < N; ++u)
 #pragma unroll
                     for (int jb = 0; jb < JB; ++jb)
                         bs[u][jb] = (T)1;
+                if (p.n == 0)
 #pragma unroll
-                    for (int m = 0; m < kSmallModes; ++m)
-                        if (m < p.n)
-                            mode(m, m == p.n - 1, false);
+                    for (int u = 0; u < N; ++u)
+                        tensor(u);
+                for (int m = 0; m < p.n; ++m) {
+                    T v[N][JB];
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+                        mode(m, u, m == p.n - 1, v[u]);
+                    if (m == p.n - 1)
+#pragma unroll
+                        for (int u = 0; u < N; ++u)
+                            tensor(u);
+#pragma unroll
+                    for (int u = 0; u < N; ++u)
+#pragma unroll
+                        for (int jb = 0; jb < JB; ++jb)
+                            bs[u][jb] *= v[u][jb];
                 }
-#pragma unroll
-                for (int r = 0; r < RB; ++r)
-                    xs[u][r] = xb[off + row[r]];
             }
             if (masked) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
+                for (int u = 0; u < N; ++u) {
                     const bool ok = c + 4 * u + kk < c1;
 #pragma unroll
                     for (int r = 0; r < RB; ++r)
@@ -147,7 +188,7 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int r = 0; r < RB; ++r)
 #pragma unroll
@@ -156,9 +197,17 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
         };
         int c = c0;
         for (; c + 4 * U <= c1; c += 4 * U)
-            batch(c, false);
-        if (c < c1)
-            batch(c, true);
+            batch(c, std::integral_constant<int, U>(), false);
+        // the remainder in a batch of its own length: pieces of half a batch are the rule where a call is small
+        const int left = (c1 - c + 3) / 4, part = (U + 3) / 4;
+        if (left > 3 * part)
+            batch(c, std::integral_constant<int, U>(), true);
+        else if (left > 2 * part)
+            batch(c, std::integral_constant<int, U < 3 * part ? U : 3 * part>(), true);
+        else if (left > part)
+            batch(c, std::integral_constant<int, 2 * part>(), true);
+        else if (left > 0)
+            batch(c, std::integral_constant<int, part>(), true);
     };
     auto store = [&](int64_t row, int j, double v) {
         if (gridDim.z > 1) {       // the combine kernel applies weights and accumulation
@@ -173,6 +222,20 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
         *o = (T)v;
     };
 
+    // the wavefronts' values in their order, requested eight at a time: one after the other they cost an LDS latency each
+    auto add_up = [&](const double* a, int stride) {
+        double v = 0.0;
+        for (int w0 = 0; w0 < n_waves; w0 += 8) {
+            double x[8];
+#pragma unroll
+            for (int h = 0; h < 8; ++h)
+                x[h] = a[min(w0 + h, n_waves - 1) * stride];
+#pragma unroll
+            for (int h = 0; h < 8; ++h)
+                v += w0 + h < n_waves ? x[h] : 0.0;
+        }
+        return v;
+    };
     if constexpr (FIRST) {
         // one row tile; wavefront w holds the sum over piece w of the group's columns
         const int row0 = (int)blockIdx.x * 16;
@@ -180,18 +243,15 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
         sweep(row0, c0, min(g1, c0 + p.cols_per_range));
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
-            if (jb > 0)
-                __syncthreads();
+            double* const tile = red + (jb & 1) * n_waves * 256;     // two in turn: one barrier a block of columns
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                red[wave * 256 + MF::row(lane, q) * 16 + il] = (double)acc[0][jb][q];
+                tile[wave * 256 + MF::row(lane, q) * 16 + il] = (double)acc[0][jb][q];
             __syncthreads();
             for (int t = (int)threadIdx.x; t < 256; t += (int)blockDim.x) {
                 // (entry t & 15 belongs to lane t & 15 of the layout above: this thread's own il)
                 const int r = row0 + (t >> 4);
-                double v = 0.0;
-                for (int w = 0; w < n_waves; ++w)
-                    v += red[w * 256 + t];
+                const double v = add_up(tile + t, 256);
                 if (r < p.I0 && owned(jb))
                     store(r, column(jb), v);
             }
@@ -204,19 +264,19 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
             v[jb] = 0.0;
         for (int u = wave; u < p.n_tiles * p.n_ranges; u += n_waves) {
             const int rng = u / p.n_tiles, row0 = (u - rng * p.n_tiles) * 16 * RB;
-            T w[RB][4][JB];          // under way before the sweep
+            const int c0 = g0 + rng * p.cols_per_range;
+            sweep(row0, c0, min(g1, c0 + p.cols_per_range));
+            T w[RB][4][JB];
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    load_cols(p.A0, (uint32_t)min(row0 + 16 * r + MF::row(lane, q), p.I0 - 1) * (uint32_t)p.ld0, w[r][q]);
-            const int c0 = g0 + rng * p.cols_per_range;
-            sweep(row0, c0, min(g1, c0 + p.cols_per_range));
+                    load_cols(p.A0, (uint32_t)(first_row(row0, MF::row(lane, q)) + r) * (uint32_t)p.ld0, w[r][q]);
 #pragma unroll
             for (int r = 0; r < RB; ++r)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const bool in = row0 + 16 * r + MF::row(lane, q) < p.I0;
+                    const bool in = first_row(row0, MF::row(lane, q)) + r >= row0 + RB * MF::row(lane, q);
 #pragma unroll
                     for (int jb = 0; jb < JB; ++jb) {
                         const double t = (double)acc[r][jb][q] * (double)w[r][q][jb];
@@ -233,16 +293,8 @@ __global__ void __launch_bounds__(64 * kSmallWaves) mttkrp_small_kernel(const Sm
                 red[wave * (16 * JB) + 16 * jb + il] = t;
         }
         __syncthreads();
-        if (wave == 0 && kk == 0) {
-#pragma unroll
-            for (int jb = 0; jb < JB; ++jb) {
-                double t = 0.0;
-                for (int w = 0; w < n_waves; ++w)
-                    t += red[w * (16 * JB) + 16 * jb + il];
-                if (owned(jb))
-                    store((int64_t)blockIdx.x, column(jb), t);
-            }
-        }
+        if (wave == 0 && kk < JB && owned(kk))      // (lane group kk takes block kk)
+            store((int64_t)blockIdx.x, column(kk), add_up(red + lane, 16 * JB));
     }
 }
 
@@ -250,13 +302,14 @@ template <typename T, int RB, int JB, bool FIRST>
 void launch(const SmallPlan& pl, const SmallArgs<T>& a, hipStream_t st)
 {
     const dim3 grid((unsigned)pl.blocks, (unsigned)pl.n_jchunk, (unsigned)pl.n_groups), block(64 * pl.waves);
-    const size_t lds = (size_t)pl.waves * (FIRST ? 256 : 16 * JB) * sizeof(double);
-    if (a.n == 1)
-        hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 1, FIRST>), grid, block, lds, st, a);
-    else if (a.n == 2)
-        hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 2, FIRST>), grid, block, lds, st, a);
-    else
-        hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 0, FIRST>), grid, block, lds, st, a);
+    const size_t lds = (size_t)pl.waves * (FIRST ? (JB > 1 ? 512 : 256) : 16 * JB) * sizeof(double);
+    switch (a.n) {
+    case 1: hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 1, FIRST>), grid, block, lds, st, a); break;
+    case 2: hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 2, FIRST>), grid, block, lds, st, a); break;
+    case 3: hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 3, FIRST>), grid, block, lds, st, a); break;
+    case 4: hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 4, FIRST>), grid, block, lds, st, a); break;
+    default: hipLaunchKernelGGL((mttkrp_small_kernel<T, RB, JB, 0, FIRST>), grid, block, lds, st, a); break;
+    }
 }
 
 }  // namespace
@@ -284,7 +337,7 @@ SmallPlan mttkrp_small_plan(int ndim, const int64_t* dims, int R, int k, int sby
         tiles = (dims[0] + 16 * pl.RB - 1) / (16 * pl.RB);
         pl.blocks = dims[k];
     }
-    const int batch = pl.RB * pl.JB <= 2 ? 8 : 4;      // steps whose loads are in flight together (kSteps)
+    const int batch = pl.RB * pl.JB <= 2 ? 8 : 4;      // steps whose loads are in flight together (mostly)
     int64_t steps = (C + 3) / 4;
     if (groups > 1) {
         const int64_t per_group = (steps + groups - 1) / groups;
