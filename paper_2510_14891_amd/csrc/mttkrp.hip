@@ -2353,24 +2353,35 @@ int make_general_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, c
     return MTTKRP_OK;
 }
 
-// One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times on the GPU in us, fitted
-// to one half of 5650 calls (fp64 and fp32, two to eight modes, 2^8 to 2^23 values, R = 2 to 1000, each with one to three
-// numbers of groups).  On the other half the median error is 10 and 9 %.  4900 further calls that the
-// rule below gives to the small kernel take 0.55 times as long in the mean (0.52 below 2^17 values, 0.57 at 2^18, 0.69 at
-// 2^20, 0.75 at 2^21); 1.6 % of them are more than 5 % slower, the worst 1.7 times.
-// The small kernel by its number of column modes (one, two, others), per workgroup:
+// One launch or few workgroups with a combine launch (small.hip) against the plan above: the two times on the GPU in us.  Up to
+// kSmallFitValues the small kernel's is fitted to 17400 timings of graph replays (3800 calls, fp64 and fp32, three to seven modes, 2^15 to
+// 2^23 values, R = 4 to 1000, each with up to six numbers of groups); on a half that was not fitted the median error is 7 %.  The general
+// plan's is an older fit, 8 % off in the median.  2334 further calls of 2^8 to 2^19.8 values (two to eight modes): 734 run otherwise than by
+// the older fit, 0.63 times as long in the mean, 2.6 % of them more than 5 % slower, the worst 1.33 times; their errors against extended
+// precision are 0.78 (fp64) and 0.56 times (fp32) the former.  Beyond, an older fit of the small kernel stays (5650 calls; it gives times 1.15 to
+// 1.47 times too long, from before its batches became as long as their remainders): the plans of many calls from 2^19.9 values on are pinned, the
+// chosen streaming plans among them.  The new fit would take more calls there too (2^20 to 2^21 values: 0.80 against 0.90 times the general
+// plan's time; to 2^22 0.89 against 0.97).
+// By the number of column modes (up to one, two, three, four, more; the older fit one, two, others), per workgroup:
+constexpr int64_t kSmallFitValues = (int64_t)7 << 17;
 struct SmallFit {
     double base, mfma, loads, alu, sweep;      // launch; matrix cores, load instructions, address arithmetic; a sweep's start and end
     double crowd, rounds;                      // the share of each workgroup beyond one a compute unit; beyond what is resident
     double combine, part;                      // the second launch and its MB
-    double cold, bytes, spill;                 // batches of loads from beyond L2; MB of X; spilled registers (fp64, four blocks of columns)
+    double cold, bytes, spill;                 // batches of loads from beyond L2; MB of X; four blocks of columns in fp64
 };
-const SmallFit small_fit[3] = {{2.00, 1.67, 1.93, 0.00, 1.65, 1.92, 0.73, 2.46, 0.70, 0.03, 0.059, 1.09},
-                               {2.00, 1.27, 0.00, 0.75, 1.84, 1.72, 1.13, 2.59, 1.06, 0.00, 0.107, 5.72},
-                               {2.73, 0.71, 4.60, 1.35, 2.87, 1.72, 1.11, 3.12, 0.57, 1.25, 0.149, 3.55}};
+const SmallFit small_fit[5] = {{2.69, 1.06, 0.00, 0.62, 0.83, 1.44, 0.78, 2.10, 2.24, 0.14, 0.056, 0.55},
+                               {2.81, 1.24, 1.85, 0.53, 0.58, 1.38, 0.80, 2.22, 1.25, 0.00, 0.059, 0.72},
+                               {3.36, 1.23, 7.59, 0.06, 0.16, 1.26, 0.93, 2.18, 1.05, 0.00, 0.062, 0.24},
+                               {3.45, 1.44, 5.60, 0.27, 0.00, 1.13, 1.27, 2.44, 1.04, 0.00, 0.133, 0.77},
+                               {4.13, 1.74, 5.69, 0.54, 0.00, 1.19, 0.90, 2.37, 0.73, 0.32, 0.054, 0.00}};
+const SmallFit small_fit_large[3] = {{2.00, 1.67, 1.93, 0.00, 1.65, 1.92, 0.73, 2.46, 0.70, 0.03, 0.059, 1.09},
+                                     {2.00, 1.27, 0.00, 0.75, 1.84, 1.72, 1.13, 2.59, 1.06, 0.00, 0.107, 5.72},
+                                     {2.73, 0.71, 4.60, 1.35, 2.87, 1.72, 1.11, 3.12, 0.57, 1.25, 0.149, 3.55}};
 double small_cost(const SmallPlan& sp, int sbytes, int n_modes, int64_t N, double part_bytes, bool first)
 {
-    const SmallFit& f = small_fit[n_modes == 1 ? 0 : (n_modes == 2 ? 1 : 2)];
+    const SmallFit& f = N <= kSmallFitValues ? small_fit[n_modes < 1 ? 0 : (n_modes < 5 ? n_modes - 1 : 4)]
+                                             : small_fit_large[n_modes == 1 ? 0 : (n_modes == 2 ? 1 : 2)];
     const int batch = sp.RB * sp.JB <= 2 ? 8 : 4;
     const double units = (double)sp.n_tiles * sp.n_ranges, per = (double)(sp.cols_per_range / 4), steps = units * per / 2200.0;
     const double sweeps = ceil(units / sp.waves), mb = 1e-6 * (double)N * sbytes;
@@ -2401,9 +2412,8 @@ double general_cost(const Plan& pl, int ndim)
            0.0406e-6 * (double)pl.N * pl.sbytes + 1.15e-3 * items + 0.837e-6 * (double)pl.ws_bytes + 0.197 * tiles;
 }
 
-// The fit of 2600 other calls timed with their host work, with fewer terms, has to agree: the first estimate takes calls back that this
-// one misjudges.  Calls that only the first would take stay where they are (0.7 times as long below 2^20 values, but another
-// order of the sums; above 0.84 times and 24 % of them more than 5 % slower).
+// Above kSmallFitValues a fit of 2600 other calls timed with their host work, with fewer terms, has to agree: the older fit takes calls back
+// that this one misjudges (of those that only it would take 24 % were more than 5 % slower).
 double small_cost_with_host(const SmallPlan& sp, int sbytes, int n_modes, int64_t N)
 {
     const double steps = (double)sp.n_tiles * sp.n_ranges * (sp.cols_per_range / 4);       // of one workgroup
@@ -2569,8 +2579,8 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         return rc;
     const int n_modes = k == 0 ? ndim - 1 : ndim - 2;
     SmallPlan best;
-    // At 0.8 the calls that get slower are few (half of the fit's data: 1.8 % more than 5 % slower, at 0.9 3.8 %, for 0.765 instead
-    // of 0.775 times as long in the mean over all calls); beyond 2^22 values most would.
+    // At 0.8 the calls that get slower are few: of 1901 that were not fitted 1.7 % of those taken are more than 5 % slower than the general
+    // plan, at 0.9 3.0 %, at 1.0 6.3 %, and all are 0.681, 0.679 and 0.682 times as long in the mean; beyond 2^22 values 4 %.
     if (tn.small_route == 0 && N > ((int64_t)1 << 22))
         return rc;
     double best_cost = tn.small_route == 1 ? 1e300 : 0.8 * general_cost(pl, ndim);
@@ -2587,8 +2597,8 @@ int choose_plan(int ndim, const int64_t* dims, int R, int k, int sbytes, const T
         if ((sbytes == 8 || sp.cols_per_range <= 4 * pl.steps_per_item || tn.small_route == 1) &&
             (bytes <= 16777216.0 || bytes <= (double)pl.ws_bytes)) {
             const double cost = small_cost(sp, sbytes, n_modes, N, bytes, k == 0);
-            if (cost < best_cost &&
-                (tn.small_route == 1 || small_cost_with_host(sp, sbytes, n_modes, N) < 0.8 * general_cost_with_host(pl))) {
+            if (cost < best_cost && (tn.small_route == 1 || N <= kSmallFitValues ||
+                                     small_cost_with_host(sp, sbytes, n_modes, N) < 0.8 * general_cost_with_host(pl))) {
                 best = sp;
                 best_cost = cost;
                 take = true;
