@@ -13,7 +13,8 @@
  *       A_k = M V^{-1}                                      (V = L L^T, two triangular solves)
  *       lambda_j = ||A_k(:, j)||_2,  A_k(:, j) /= lambda_j  (a zero column is left alone)
  *   after the last mode:
- *       fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X||,
+ *       fit = 1 - sqrt(max(||X||^2 + ||X^||^2 - 2 <X, X^>, 0)) / ||X||
+ *       (a difference below 8 eps ||X||^2, the rounding of its terms, counts as 0),
  *       <X, X^> = sum_j lambda_j sum_i M(i, j) A_{d-1}(i, j),
  *       ||X^||^2 = lambda^T (Hadamard product of all Gram matrices) lambda
  *   stop when |fit - previous fit| < tol, or after max_iters sweeps.

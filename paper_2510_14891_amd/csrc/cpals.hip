@@ -356,7 +356,9 @@ __device__ void end_sweep(double* scalars, int* flag, SweepRecord* record, doubl
     }
     const double norm2 = scalars[0], norm = sqrt(norm2);
     double resid2 = norm2 + model2 - 2.0 * inner;
-    if (resid2 < 0.0)
+    // What is left below the rounding of the three terms is none: an exact model's fit is 1 in every sweep, not 1 or 1 - 2e-8 by how the
+    // last sums were rounded (which of the two depends on the order of the MTTKRP's sums).
+    if (resid2 < 8.0 * 0x1p-52 * norm2)
         resid2 = 0.0;
     const double fit = norm > 0.0 ? 1.0 - sqrt(resid2) / norm : 1.0;
     const bool settled = !first && fabs(fit - scalars[1]) < tol;
